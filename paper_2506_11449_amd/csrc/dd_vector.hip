@@ -63,138 +63,363 @@ __global__ __launch_bounds__(kProdThreads) void masked_gather_kernel(
     if (q < D) S::store(dst + t * size_t(D) + q, acc);
 }
 
-// ---- tiled variant: the source tile of TT tokens sits in LDS, every shifted read comes from there ----
+// ---- tiled variant: the source tile of a few tokens sits in LDS, every shifted read comes from there ----
 //
-// Layout: tile[c][TT + 4] fp32 (column-major, tokens minor).  A lane owns one destination column and TT
-// tokens: per diagonal it computes its source column once and fetches its TT tokens with TT/4 16-byte
-// reads at fixed offsets; the 4-float pad makes neighbouring columns start 16 bytes apart modulo the
-// 256-byte bank row, so the eight lanes served per clock never share a bank.  The weight of the
-// (column, diagonal) pair is read once and used for all TT tokens.
+// Layout: a tile holds NT 16-byte groups of tokens per source column (a group: four fp32 or eight bf16 tokens), columns
+// one after the other STRIDE bytes apart.  A lane owns one destination column and all tokens of the tile: per diagonal it
+// works out its source column once and fetches its tokens with NT 16-byte reads.  STRIDE is an odd multiple of 16 bytes,
+// so that the lanes of a read, which sit on neighbouring columns whatever the offset, fall on different banks.  Behind the
+// last column lies one of zeros: what a slot without a diagonal reads, so that an infinite or undefined input reaches the
+// results of its own diagonals only.
+//
+// What bounds it: one source element out of LDS per multiply-add -- 128 bytes per clock and CU, 32 fp32 or 64 bf16
+// multiply-adds.  bf16 multiply-adds are taken in pairs of diagonals by v_dot2_f32_bf16 (one v_perm per pair of tokens to
+// bring two diagonals' elements together), which is one vector instruction per multiply-add and the same 64 per clock.
+// Measured: 768 x 768, 77 diagonals, fp32, 3152 tokens 23 / 21 us (forward / backward-input; 9.5 us at the LDS rate), with
+// four waves per workgroup, which left the reads' latency open, 43 / 44 us; 307 diagonals 61 / 57 us (38 us);
+// 320 -> 1000, 100 diagonals, bf16, 5005 tokens 26 / 25 us, converted to fp32 in LDS 70 / 44 us.
 typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2p __attribute__((ext_vector_type(2)));
 
-template <class S, int TT, bool MASKED>
-__global__ __launch_bounds__(kProdThreads) void product_tiled_kernel(
-    int64_t T, int D, int L, int K, const typename S::storage *__restrict__ src, const int *__restrict__ offsets,
-    const typename S::storage *__restrict__ values, typename S::storage *__restrict__ dst)
+constexpr int kMaxWaves = 16;     // waves per workgroup of the product kernel
+constexpr int kLoadAhead = 4;     // groups of a tile a thread has on their way at once
+constexpr int kListLen = 256;     // diagonals looked at per pass; their list is private to a wave
+constexpr size_t kLdsPerCu = 160 * 1024;
+
+template <class S> struct Group;  // how a 16-byte group of tokens of one column is loaded and used
+template <> struct Group<F32> {
+    static constexpr int kTokens = 4;
+    using regs = f32x4v;
+    using weight = float;
+};
+template <> struct Group<BF16> {
+    static constexpr int kTokens = 8;
+    using regs = u32x4v;
+    using weight = unsigned;
+};
+
+constexpr int tile_stride(int nt) { return nt == 1 ? 16 : nt * 16 + 16; }  // nt is 1 or even
+
+// A group of a tile is named by (group of rows << 16 | column).  Its rows as they come from memory, and as the 16 bytes of
+// the group.  `base`: the tile's first row in a row-major matrix with `ld` columns (uniform over the wave: a lane only adds
+// an offset).  Of the tile's TT rows the first `rows` exist; the others are read from the last of these and replaced by
+// zeros in the group.
+template <class E> struct Loaded { E v[16 / sizeof(E)]; };
+template <class E>
+__device__ __forceinline__ void load_group(Loaded<E> &g, const E *base, unsigned name, int rows, int ld)
 {
-    constexpr int STRIDE = TT + 4;
-    extern __shared__ __align__(16) float smem[];
+    constexpr unsigned G = 16 / sizeof(E), kSize = sizeof(E);
+    const unsigned pitch = unsigned(ld) * kSize, in_row = (name & 0xffffu) * kSize;
+    const unsigned first = (name >> 16) * G * pitch + in_row, last = unsigned(rows - 1) * pitch + in_row;
+#pragma unroll
+    for (unsigned i = 0; i < G; ++i)
+        g.v[i] = *reinterpret_cast<const E *>(reinterpret_cast<const char *>(base) + min(first + i * pitch, last));
+}
+__device__ __forceinline__ unsigned group_name(unsigned e, unsigned cols)  // the e-th group, column by column
+{
+    const unsigned q = e / cols;
+    return q << 16 | (e - q * cols);
+}
+__device__ __forceinline__ unsigned group_place(unsigned name, int stride) { return (name & 0xffffu) * unsigned(stride) + (name >> 16) * 16u; }
+template <int TT>
+__device__ __forceinline__ u32x4v pack_group(const Loaded<float> &g, unsigned name, int rows)
+{
+    const int row0 = int(name >> 16) * 4;
+    u32x4v r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = rows == TT || row0 + i < rows ? __float_as_uint(g.v[i]) : 0u;
+    return r;
+}
+template <int TT>
+__device__ __forceinline__ u32x4v pack_group(const Loaded<uint16_t> &g, unsigned name, int rows)
+{
+    const int row0 = int(name >> 16) * 8;
+    u32x4v r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        r[i] = unsigned(g.v[2 * i]) | (unsigned(g.v[2 * i + 1]) << 16);
+        if (rows != TT) r[i] = row0 + 2 * i + 1 < rows ? r[i] : (row0 + 2 * i < rows ? r[i] & 0xffffu : 0u);
+    }
+    return r;
+}
+
+__device__ __forceinline__ float dot2(unsigned a, unsigned b, float c)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2p, a), __builtin_bit_cast(bf16x2p, b), c, false);
+}
+
+// Diagonals two at a time: acc[t] += x0[t] * w0 + x1[t] * w1 for the tokens of group q of the columns at p0 and p1.
+__device__ __forceinline__ void multiply_pair(float *acc, const unsigned char *p0, const unsigned char *p1, float w0, float w1)
+{
+    const f32x4v x0 = *reinterpret_cast<const f32x4v *>(p0), x1 = *reinterpret_cast<const f32x4v *>(p1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = fmaf(x1[i], w1, fmaf(x0[i], w0, acc[i]));
+}
+__device__ __forceinline__ void multiply_pair(float *acc, const unsigned char *p0, const unsigned char *p1, unsigned w0, unsigned w1)
+{
+    const u32x4v x0 = *reinterpret_cast<const u32x4v *>(p0), x1 = *reinterpret_cast<const u32x4v *>(p1);
+    const unsigned w = w0 | (w1 << 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc[2 * i] = dot2(__builtin_amdgcn_perm(x1[i], x0[i], 0x05040100u), w, acc[2 * i]);
+        acc[2 * i + 1] = dot2(__builtin_amdgcn_perm(x1[i], x0[i], 0x07060302u), w, acc[2 * i + 1]);
+    }
+}
+
+// A workgroup holds one tile of tokens (blockIdx.x) and one group of destination column blocks (blockIdx.y; 64
+// columns, one wave each); `k_parts` neighbouring waves share a column block and take a part of the diagonals each, whose
+// sums are added through LDS in order -- for calls with so few tokens that the chip would otherwise stand idle.  Every
+// wave lists the diagonals of its part that meet its columns (all of them for the plain gather; for the masked gather
+// onto a longer side most miss a given block), and walks the list eight at a time, the weights of the next eight on
+// their way while the current eight are multiplied.
+template <class S, int NT, bool MASKED>
+__global__ __launch_bounds__(64 * kMaxWaves) void product_tiled_kernel(
+    int64_t T, int D, int L, int K, int k_parts, const typename S::storage *__restrict__ src,
+    const int *__restrict__ offsets, const typename S::storage *__restrict__ values, typename S::storage *__restrict__ dst)
+{
+    constexpr int G = Group<S>::kTokens, TT = NT * G, STRIDE = tile_stride(NT), KB = 8;
+    using weight = typename Group<S>::weight;
+    extern __shared__ __align__(16) unsigned char tile[];
     const int src_cols = MASKED ? L : D, dst_cols = MASKED ? D : L;
-    float *tile = smem;
-    int *s_off = reinterpret_cast<int *>(smem + size_t(src_cols) * STRIDE);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned *list = reinterpret_cast<unsigned *>(tile + size_t(src_cols + 1) * STRIDE) + wave * kListLen;
     const int64_t t0 = int64_t(blockIdx.x) * TT;
 
-    for (int k = tid; k < K; k += kProdThreads) s_off[k] = canonical_offset(offsets[k], D);
-#pragma unroll 4
-    for (int t = 0; t < TT; ++t) {
-        const int64_t tg = t0 + t;
-        const typename S::storage *row = src + tg * src_cols;
-        const typename S::storage *safe = tg < T ? row : src;  // rows past the end read row 0 and store zeros
-        for (int c = tid; c < src_cols; c += kProdThreads) {
-            const float x = S::load(safe + c);
-            tile[c * STRIDE + t] = tg < T ? x : 0.f;
+    const int rows = int(min(T - t0, int64_t(TT)));  // tokens past the last one repeat it; their results are not stored
+    const unsigned n_groups = unsigned(src_cols) * NT;
+    for (unsigned e0 = tid; e0 < n_groups; e0 += kLoadAhead * threads) {
+        Loaded<typename S::storage> g[kLoadAhead];
+        unsigned at[kLoadAhead];
+#pragma unroll
+        for (int i = 0; i < kLoadAhead; ++i) {  // the last round repeats its first piece
+            const unsigned name = group_name(e0 + i * threads < n_groups ? e0 + i * threads : e0, unsigned(src_cols));
+            load_group(g[i], src + t0 * src_cols, name, rows, src_cols);
+            at[i] = group_place(name, STRIDE);
         }
+#pragma unroll
+        for (int i = 0; i < kLoadAhead; ++i)
+            *reinterpret_cast<u32x4v *>(tile + at[i]) = pack_group<TT>(g[i], 0, TT);
     }
+    if (tid < NT) *reinterpret_cast<u32x4v *>(tile + size_t(src_cols) * STRIDE + tid * 16) = u32x4v{0u, 0u, 0u, 0u};
     __syncthreads();
 
-    for (int jb = wave * 64; jb < dst_cols; jb += 4 * 64) {
-        const int j = jb + lane;
-        const bool active = j < dst_cols;
-        float acc[TT];
+    const int blocks_per_group = (threads >> 6) / k_parts;
+    const int part = wave % k_parts, local_block = wave / k_parts;
+    const int k_lo = int(int64_t(part) * K / k_parts), k_hi = int(int64_t(part + 1) * K / k_parts);
+    const int j0 = (int(blockIdx.y) * blocks_per_group + local_block) * 64, j = j0 + lane;
+    const bool active = j < dst_cols;
+    float acc[TT];
 #pragma unroll
-        for (int t = 0; t < TT; ++t) acc[t] = 0.f;
-        // Diagonals are taken eight at a time; the weights of the next eight are requested from memory
-        // (L2) before the current eight are multiplied, which hides that latency at two waves per SIMD.
-        constexpr int KB = 8;
-        float w_cur[KB], w_nxt[KB];
+    for (int t = 0; t < TT; ++t) acc[t] = 0.f;
+    for (int k0 = k_lo; k0 < k_hi && j0 < dst_cols; k0 += kListLen) {
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < kListLen / 64; ++r) {
+            const int k = k0 + r * 64 + lane;
+            bool meets = k < k_hi;
+            int o = 0;
+            if (meets) o = canonical_offset(offsets[k], D);
+            if (MASKED) {  // source columns j0 - o ... j0 - o + 63 (mod D): does one of them exist?
+                int a = j0 - o;
+                a += a < 0 ? D : 0;
+                meets = meets && (a < L || a + 63 >= D);
+            }
+            const unsigned long long b = __ballot(meets);
+            const int rank = __builtin_amdgcn_mbcnt_hi(unsigned(b >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(b), 0u));
+            if (meets) list[n + rank] = (unsigned(r * 64 + lane) << 16) | unsigned(o);
+            n += __popcll(b);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        weight w_cur[KB], w_nxt[KB];
         int c_cur[KB], c_nxt[KB];
-        auto fetch = [&](int k0, float (&w)[KB], int (&cc)[KB]) {
-            // lane u of this vector holds the offset of diagonal k0 + u; broadcast by lane index below
-            const int off_vec = s_off[min(k0 + (lane & (KB - 1)), K - 1)];
+        auto fetch = [&](int i0, weight (&w)[KB], int (&at)[KB]) {
+            const unsigned entries = list[min(i0 + (lane & (KB - 1)), n - 1)];  // lane u: entry i0 + u
 #pragma unroll
             for (int u = 0; u < KB; ++u) {
-                const int k = k0 + u;
-                const int o = __builtin_amdgcn_readlane(off_vec, u);
-                int c;
-                bool valid = active && k < K;
-                unsigned widx;  // K * L < 2^32: both are below 65536
+                const unsigned e = unsigned(__builtin_amdgcn_readlane(int(entries), u));
+                const int o = int(e & 0xffffu);
+                const bool there = i0 + u < n;
+                const typename S::storage *row = values + size_t(unsigned(k0) + (e >> 16)) * L;
                 if (MASKED) {
-                    c = j - o;
-                    if (c < 0) c += D;
-                    valid = valid && c < L;
-                    widx = unsigned(k) * unsigned(L) + unsigned(c);
+                    const unsigned d = unsigned(j - o), c = min(d, d + unsigned(D));
+                    const bool valid = c < (there ? unsigned(L) : 0u);
+                    const weight v = row[min(c, unsigned(L - 1))];
+                    w[u] = valid ? v : weight(0);
+                    at[u] = int(valid ? c : unsigned(L)) * STRIDE;
                 } else {
-                    c = j + o;
-                    if (c >= D) c -= D;
-                    widx = unsigned(k) * unsigned(L) + unsigned(j);
+                    const unsigned jj = unsigned(min(j, L - 1)), s = jj + unsigned(o), c = min(s, s - unsigned(D));
+                    const weight v = row[jj];
+                    w[u] = there ? v : weight(0);
+                    at[u] = int(there ? c : unsigned(D)) * STRIDE;
                 }
-                // the load itself is unconditional (entry 0 stands in) so that eight of them stay in flight
-                const float wv = S::load(values + (valid ? widx : 0u));
-                w[u] = valid ? wv : 0.f;
-                cc[u] = valid ? c : 0;
             }
         };
-        fetch(0, w_cur, c_cur);
-        for (int k0 = 0; k0 < K; k0 += KB) {
-            fetch(k0 + KB, w_nxt, c_nxt);
+        if (n > 0) fetch(0, w_cur, c_cur);
+        for (int i0 = 0; i0 < n; i0 += KB) {
+            if (i0 + KB < n) fetch(i0 + KB, w_nxt, c_nxt);
 #pragma unroll
-            for (int u = 0; u < KB; ++u) {
-                const float *col = tile + c_cur[u] * STRIDE;
+            for (int u = 0; u < KB; u += 2) {
 #pragma unroll
-                for (int q = 0; q < TT / 4; ++q) {
-                    const f32x4v x = *reinterpret_cast<const f32x4v *>(col + 4 * q);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[4 * q + i] = fmaf(x[i], w_cur[u], acc[4 * q + i]);
-                }
+                for (int q = 0; q < NT; ++q)
+                    multiply_pair(acc + q * G, tile + c_cur[u] + q * 16, tile + c_cur[u + 1] + q * 16, w_cur[u], w_cur[u + 1]);
+                if (TT == 32) __builtin_amdgcn_sched_barrier(0);  // else more reads are hoisted than there are registers
             }
 #pragma unroll
             for (int u = 0; u < KB; ++u) { w_cur[u] = w_nxt[u]; c_cur[u] = c_nxt[u]; }
         }
-        if (active) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (k_parts > 1) {  // the tile is not needed any more
+        __syncthreads();
+        float *sums = reinterpret_cast<float *>(tile);  // [block][part - 1][token][lane]
+        if (part > 0)
 #pragma unroll
-            for (int t = 0; t < TT; ++t)
-                if (t0 + t < T) S::store(dst + (t0 + t) * dst_cols + j, acc[t]);
+            for (int t = 0; t < TT; ++t) sums[((local_block * (k_parts - 1) + part - 1) * TT + t) * 64 + lane] = acc[t];
+        __syncthreads();
+        if (part > 0) return;
+        for (int g = 0; g < k_parts - 1; ++g)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) acc[t] += sums[((local_block * (k_parts - 1) + g) * TT + t) * 64 + lane];
+    }
+    typename S::storage *out = dst + t0 * dst_cols;
+    if (active) {
+        if (t0 + TT <= T) {
+#pragma unroll
+            for (int t = 0; t < TT; ++t, out += dst_cols) S::store(out + j, acc[t]);
+        } else {
+            const int rows = int(T - t0);
+#pragma unroll
+            for (int t = 0; t < TT; ++t, out += dst_cols)
+                if (t < rows) S::store(out + j, acc[t]);
         }
     }
 }
 
-template <class S, int TT>
-static hipError_t launch_tiled(const ProductArgs &a, hipStream_t stream, size_t lds)
+// Plans weigh some dozens of candidates, 3-5 us of host time: each thread remembers the last few (a plan is a pure function
+// of the sizes in its key, a value of a few dozen bytes).
+template <class Plan>
+struct PlanMemo {
+    struct Entry {
+        int64_t T = -1;
+        int D, L, K, flags;
+        Plan plan;
+    };
+    Entry entries[32];
+    template <class Make>
+    const Plan &get(int64_t T, int D, int L, int K, int flags, Make make)
+    {
+        const uint64_t h = (uint64_t(T) * 0x9e3779b97f4a7c15ull) ^ (uint64_t(uint32_t(D)) * 0xc2b2ae3d27d4eb4full) ^
+                           (uint64_t(uint32_t(L)) * 0x165667b19e3779f9ull) ^ (uint64_t(uint32_t(K * 4 + flags)) * 0x27d4eb2f165667c5ull);
+        Entry &e = entries[h >> 59];
+        if (e.T != T || e.D != D || e.L != L || e.K != K || e.flags != flags) {
+            e.plan = make();
+            e.T = T;
+            e.D = D;
+            e.L = L;
+            e.K = K;
+            e.flags = flags;
+        }
+        return e.plan;
+    }
+};
+
+struct TiledPlan {
+    int nt, k_parts, waves, grid_y;  // nt = 0: no tile fits LDS
+    unsigned grid_x;
+    size_t lds;
+};
+
+// Tile, parts and workgroup size by the time they should take (in clocks of a CU): the work is spread over the CUs in
+// whole workgroups; a wave can be no faster than its own chain of instructions; every workgroup stages its tile anew.
+static TiledPlan make_tiled_plan(int64_t T, int D, int L, int K, bool bf16, bool masked)
+{
+    TiledPlan best = {};
+    const int src_cols = masked ? L : D, dst_cols = masked ? D : L;
+    const int n_blocks = (dst_cols + 63) / 64;
+    const double met = masked ? K * (L + 63.0 < D ? (L + 63.0) / D : 1.0) : K;  // diagonals that meet a column block
+    double best_cost = 1e300;
+    static const int nts[] = {4, 2, 1};
+    for (int nt : nts) {
+        const int tt = nt * (bf16 ? 8 : 4);
+        const int64_t tiles = (T + tt - 1) / tt;
+        if (tiles >= (int64_t(1) << 31)) continue;
+        for (int parts = 1; parts <= 8; parts *= 2) {
+            if (parts > 1 && K / parts < 16) break;
+            for (int waves = parts; waves <= kMaxWaves; waves *= 2) {
+                const int per_group = waves / parts;
+                if (per_group > 1 && per_group / 2 >= n_blocks) break;
+                const int w = per_group > n_blocks ? n_blocks * parts : waves;
+                const int groups = (n_blocks + w / parts - 1) / (w / parts);
+                size_t lds = size_t(src_cols + 1) * tile_stride(nt) + size_t(w) * kListLen * 4;
+                const size_t sums = size_t(w) * tt * 256;
+                if (parts > 1 && sums > lds) lds = sums;
+                if (lds > kLdsPerCu || groups > 65535) continue;
+                const double wgs = double(tiles) * groups;
+                int resident = int(kLdsPerCu / lds);
+                if (resident * w > 16) resident = 16 / w > 0 ? 16 / w : 1;
+                const double diags = met / parts + 8;
+                const double issue = tt * 4 + 48, lds_clk = nt * 8 * 1.1;
+                const double per_cu = double(int64_t((wgs + 255) / 256));  // the busiest CU
+                const double rounds = double(int64_t((wgs + 256.0 * resident - 1) / (256.0 * resident)));
+                // the fewer waves a CU has, the less of their waiting is hidden
+                const double hidden = 1.0 + 4.0 / (per_cu < resident ? per_cu * w : resident * w);
+                const double busy = per_cu * w * diags * (issue / 4 > lds_clk ? issue / 4 : lds_clk) * hidden;
+                const double chain = rounds * diags * (issue + 40);
+                const double stage = rounds * 1500 + per_cu * (double(src_cols) * tt * (bf16 ? 2 : 4) / 24);
+                const double cost = (busy > chain ? busy : chain) + stage + (parts > 1 ? rounds * 500 : 0);
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    best.nt = nt;
+                    best.k_parts = parts;
+                    best.waves = w;
+                    best.grid_x = unsigned(tiles);
+                    best.grid_y = groups;
+                    best.lds = lds;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+static TiledPlan plan_tiled(int64_t T, int D, int L, int K, bool bf16, bool masked)
+{
+    static thread_local PlanMemo<TiledPlan> memo;
+    return memo.get(T, D, L, K, bf16 | masked << 1, [&] { return make_tiled_plan(T, D, L, K, bf16, masked); });
+}
+
+template <class S, int NT, bool MASKED>
+static hipError_t launch_tiled(const ProductArgs &a, const TiledPlan &pl, hipStream_t stream)
 {
     using st = typename S::storage;
-    const unsigned grid = unsigned((a.T + TT - 1) / TT);
-    const st *src = static_cast<const st *>(a.src), *values = static_cast<const st *>(a.values);
-    st *dst = static_cast<st *>(a.dst);
-    if (a.masked) {
-        static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&product_tiled_kernel<S, TT, true>), 160 * 1024, lds_allowed)) return e;
-        hipLaunchKernelGGL((product_tiled_kernel<S, TT, true>), dim3(grid), dim3(kProdThreads), lds, stream, a.T, a.D,
-                           a.L, a.K, src, a.offsets, values, dst);
-    } else {
-        static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&product_tiled_kernel<S, TT, false>), 160 * 1024, lds_allowed)) return e;
-        hipLaunchKernelGGL((product_tiled_kernel<S, TT, false>), dim3(grid), dim3(kProdThreads), lds, stream, a.T, a.D,
-                           a.L, a.K, src, a.offsets, values, dst);
-    }
+    static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&product_tiled_kernel<S, NT, MASKED>), int(kLdsPerCu), lds_allowed)) return e;
+    hipLaunchKernelGGL((product_tiled_kernel<S, NT, MASKED>), dim3(pl.grid_x, pl.grid_y), dim3(64 * pl.waves), pl.lds, stream,
+                       a.T, a.D, a.L, a.K, pl.k_parts, static_cast<const st *>(a.src), a.offsets,
+                       static_cast<const st *>(a.values), static_cast<st *>(a.dst));
     return hipGetLastError();
+}
+
+template <class S, int NT>
+static hipError_t launch_tiled(const ProductArgs &a, const TiledPlan &pl, hipStream_t stream)
+{
+    return a.masked ? launch_tiled<S, NT, true>(a, pl, stream) : launch_tiled<S, NT, false>(a, pl, stream);
 }
 
 template <class S>
 static hipError_t launch_product_t(const ProductArgs &a, hipStream_t stream)
 {
     using st = typename S::storage;
+    const TiledPlan pl = plan_tiled(a.T, a.D, a.L, a.K, a.bf16, a.masked);
+    if (pl.nt == 4) return launch_tiled<S, 4>(a, pl, stream);
+    if (pl.nt == 2) return launch_tiled<S, 2>(a, pl, stream);
+    if (pl.nt == 1) return launch_tiled<S, 1>(a, pl, stream);
+    // sources too wide for a tile in LDS.  grid.y carries the token index; split calls so that it stays within the
+    // 65535 limit
     const int cols = a.masked ? a.D : a.L;
-    // the tiled kernel needs the source tile (and the K offsets) in LDS and a 32-bit workgroup count
-    const size_t src_cols = a.masked ? a.L : a.D;
-    const size_t lds_limit = 160 * 1024;
-    auto lds_for = [&](int tt) { return (src_cols * size_t(tt + 4) + size_t(a.K)) * 4; };
-    if (a.T / 4 < (int64_t(1) << 31) - 1) {
-        if (lds_for(16) <= lds_limit) return launch_tiled<S, 16>(a, stream, lds_for(16));
-        if (lds_for(8) <= lds_limit) return launch_tiled<S, 8>(a, stream, lds_for(8));
-        if (lds_for(4) <= lds_limit) return launch_tiled<S, 4>(a, stream, lds_for(4));
-    }
-    // grid.y carries the token index; split calls so that it stays within the 65535 limit
     const int64_t max_rows = 65535;
     for (int64_t t0 = 0; t0 < a.T; t0 += max_rows) {
         const int64_t rows = a.T - t0 < max_rows ? a.T - t0 : max_rows;
