@@ -97,11 +97,6 @@ hipError_t launch_select_prepare(int D, int L, int K, bool expanding, const floa
                                  hipStream_t stream);
 size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16);
 hipError_t launch_weight_grad_vector(const WeightGradArgs &a, hipStream_t stream);
-// bf16 dot-product kernel of the vector family (feature counts multiples of 8, long side <= 2304)
-bool weight_grad_dot2_supported(int64_t T, int D, int L, int K);
-size_t weight_grad_dot2_ws_bytes(int64_t T, int D, int L, int K);
-int weight_grad_dot2_chunks(int64_t T, int D, int L, int K);
-hipError_t launch_weight_grad_dot2_partials(const WeightGradArgs &a, hipStream_t stream);
 
 // matrix-core family (bf16 only, both feature counts multiples of 192 or both multiples of 128)
 bool weight_grad_matrix_supported(int64_t T, int D, int L, bool bf16);

@@ -448,6 +448,8 @@ hipError_t launch_product_vector(const ProductArgs &a, hipStream_t stream)
 constexpr int kWgThreads = 256;
 constexpr int kWgTokensPerSplit = 1024;
 constexpr int kWgMaxSplits = 64;
+constexpr int kWgMaxWaves = 16;
+constexpr int kWgXcds = 8;
 
 static int weight_grad_splits(int64_t T)
 {
@@ -455,14 +457,6 @@ static int weight_grad_splits(int64_t T)
     if (s < 1) s = 1;
     if (s > kWgMaxSplits) s = kWgMaxSplits;
     return int(s);
-}
-
-size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16)
-{
-    // whichever kernel runs (the choice also depends on pointer alignment, unknown here) must fit
-    const size_t plain = size_t(weight_grad_splits(T)) * size_t(K) * size_t(L) * sizeof(float);
-    const size_t dot2 = bf16 && weight_grad_dot2_supported(T, D, L, K) ? weight_grad_dot2_ws_bytes(T, D, L, K) : 0;
-    return plain > dot2 ? plain : dot2;
 }
 
 // partial[s][k][p] = sum over the tokens of split s of A[t, p] * B[t, (p + o_k) mod D]
@@ -485,46 +479,301 @@ __global__ __launch_bounds__(kWgThreads) void weight_grad_partial_kernel(
     partial[(size_t(s) * K + k) * L + p] = acc;
 }
 
-// dV[i] = partial[0][i] + partial[1][i] + ... in that order
+__device__ __forceinline__ float multiply_group(f32x4v a, f32x4v b, float acc)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = fmaf(a[i], b[i], acc);
+    return acc;
+}
+__device__ __forceinline__ float multiply_group(u32x4v a, u32x4v b, float acc)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = dot2(a[i], b[i], acc);
+    return acc;
+}
+
+// The same with a tile of tokens in LDS, laid out as in product_tiled_kernel: all D columns of the long side and, behind
+// them, the short-side columns of this workgroup's positions.  A wave owns 64 positions and a block of KN diagonals: one
+// accumulator and one LDS address per lane and diagonal, fixed for the whole kernel, and one 16-byte read per diagonal and
+// group of tokens.  The waves of a workgroup share the tile (`waves_k` blocks of diagonals times the position blocks);
+// several workgroups per CU hide each other's staging.  A workgroup takes one chunk of the tokens; the chunks are added
+// afterwards in order, or, if there is only one, `partial` is the result.
+// Bound, as the products, by one LDS element per multiply-add (two bytes of bf16: v_dot2_f32_bf16 takes two tokens).
+// Measured: 768 x 768, 77 diagonals, fp32, 3152 tokens 30 us (one thread per gradient entry, straight from memory: 212 us),
+// 307 diagonals 69 us; 320 -> 1000, 100 diagonals, bf16, 5005 tokens 27 us (four waves per workgroup on a tile of their
+// own: 38 us).
+template <class S, int NT, int KN>
+__global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
+    int64_t T, int D, int L, int K, int chunks, int per_chunk, int waves_k, int groups_k, int k_blocks,
+    const typename S::storage *__restrict__ A, const typename S::storage *__restrict__ B,
+    const int *__restrict__ offsets, float *__restrict__ partial)
+{
+    constexpr int G = Group<S>::kTokens, TT = NT * G, STRIDE = tile_stride(NT);
+    using regs = typename Group<S>::regs;
+    using E = typename S::storage;
+    extern __shared__ __align__(16) unsigned char tile[];
+    // where the chunks divide evenly among the XCDs, a chunk's workgroups run on one, whose L2 then holds its rows
+    int chunk, sub;
+    if (chunks % kWgXcds == 0) {
+        const int local = blockIdx.x / kWgXcds;
+        chunk = local / per_chunk * kWgXcds + blockIdx.x % kWgXcds;
+        sub = local % per_chunk;
+    } else {
+        chunk = blockIdx.x / per_chunk;
+        sub = blockIdx.x % per_chunk;
+    }
+    const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int waves_p = (threads >> 6) / waves_k;
+    const int p_first = sub / groups_k * waves_p * 64;  // first position of the workgroup
+    const int p_cols = min(waves_p * 64, L - p_first);
+    const int p_local = wave / waves_k * 64 + lane, p = p_first + p_local;
+    const int kb = sub % groups_k * waves_k + wave % waves_k;
+    const int k_lo = int(int64_t(kb) * K / k_blocks), k_hi = kb < k_blocks ? int(int64_t(kb + 1) * K / k_blocks) : k_lo;
+    const int nk = k_hi - k_lo;  // <= KN
+    const bool works = nk > 0 && p - lane < L;
+    // tokens are dealt in whole groups
+    const int64_t groups = (T + G - 1) / G;
+    const int64_t t_begin = groups * chunk / chunks * G, t_end = min(groups * (chunk + 1) / chunks * G, T);
+
+    int at[KN];
+    float acc[KN];
+#pragma unroll
+    for (int u = 0; u < KN; ++u) {
+        acc[u] = 0.f;
+        int q = 0;
+        if (works && u < nk) {
+            q = min(p, L - 1) + canonical_offset(offsets[k_lo + u], D);
+            q -= q >= D ? D : 0;
+        }
+        at[u] = q * STRIDE;
+    }
+    const int a_at = (D + min(p_local, p_cols - 1)) * STRIDE;
+    const int buffer = (D + waves_p * 64) * STRIDE;
+    // A thread's share of a tile: groups tid, tid + threads, ... of the long side, kAheadB of them on their way into
+    // registers while the tile before is multiplied (wider layers: the rest afterwards), and kAheadA of the short side.
+    constexpr int kAheadB = kLoadAhead * 4 / G, kAheadA = kLoadAhead * 2 / G;
+    const unsigned n_b = unsigned(D) * NT, n_a = unsigned(p_cols) * NT;
+    unsigned name_b[kAheadB], name_a[kAheadA];  // past the end: the last group once more
+#pragma unroll
+    for (int i = 0; i < kAheadB; ++i) name_b[i] = group_name(min(unsigned(tid + i * threads), n_b - 1), unsigned(D));
+#pragma unroll
+    for (int i = 0; i < kAheadA; ++i) name_a[i] = group_name(min(unsigned(tid + i * threads), n_a - 1), unsigned(p_cols));
+    Loaded<E> gb[kAheadB], ga[kAheadA];
+    auto request = [&](int64_t t0) {
+        const int rows = int(min(t_end - t0, int64_t(TT)));
+#pragma unroll
+        for (int i = 0; i < kAheadB; ++i) {
+            if (unsigned(i * threads) >= n_b) break;
+            asm volatile("" : "+v"(name_b[i]));  // what follows from it is worked out anew: registers are short
+            load_group(gb[i], B + t0 * D, name_b[i], rows, D);
+        }
+#pragma unroll
+        for (int i = 0; i < kAheadA; ++i) {
+            if (unsigned(i * threads) >= n_a) break;
+            asm volatile("" : "+v"(name_a[i]));
+            load_group(ga[i], A + t0 * L + p_first, name_a[i], rows, L);
+        }
+    };
+    auto place = [&](int64_t t0, unsigned char *to) {
+        const int rows = int(min(t_end - t0, int64_t(TT)));
+#pragma unroll
+        for (int i = 0; i < kAheadB; ++i) {
+            if (unsigned(i * threads) >= n_b) break;
+            asm volatile("" : "+v"(name_b[i]));
+            *reinterpret_cast<u32x4v *>(to + group_place(name_b[i], STRIDE)) = pack_group<TT>(gb[i], name_b[i], rows);
+        }
+#pragma unroll
+        for (int i = 0; i < kAheadA; ++i) {
+            if (unsigned(i * threads) >= n_a) break;
+            asm volatile("" : "+v"(name_a[i]));
+            *reinterpret_cast<u32x4v *>(to + D * STRIDE + group_place(name_a[i], STRIDE)) = pack_group<TT>(ga[i], name_a[i], rows);
+        }
+        for (unsigned e = tid + kAheadB * threads; e < n_b; e += threads) {  // wide layers: the rest of the tile
+            const unsigned name = group_name(e, unsigned(D));
+            Loaded<E> g;
+            load_group(g, B + t0 * D, name, rows, D);
+            *reinterpret_cast<u32x4v *>(to + group_place(name, STRIDE)) = pack_group<TT>(g, name, rows);
+        }
+    };
+    if (t_begin < t_end) {
+        request(t_begin);
+        place(t_begin, tile);
+    }
+    __syncthreads();
+    int cur = 0;
+    for (int64_t t0 = t_begin; t0 < t_end; t0 += TT) {
+        const bool more = t0 + TT < t_end;
+        if (more) request(t0 + TT);  // in flight while this tile is multiplied
+        if (works) {
+            const unsigned char *base = tile + cur;
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                const regs a = *reinterpret_cast<const regs *>(base + a_at + q * 16);
+#pragma unroll
+                for (int u = 0; u < KN; ++u) {  // slots without a diagonal read column 0 and are dropped
+                    acc[u] = multiply_group(a, *reinterpret_cast<const regs *>(base + at[u] + q * 16), acc[u]);
+                    if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // else more reads are hoisted than there are registers
+                }
+            }
+        }
+        cur = buffer - cur;
+        if (more) place(t0 + TT, tile + cur);
+        __syncthreads();
+    }
+    if (works && p < L) {
+        float *out = partial + (size_t(chunk) * K + k_lo) * L + p;
+#pragma unroll
+        for (int u = 0; u < KN; ++u)
+            if (u < nk) out[size_t(u) * L] = acc[u];
+    }
+}
+
+// dV[i] = sum over the chunks of partial[chunk][i]: the chunks are cut into four runs that four waves add up side by side,
+// each in order with eight loads in flight; the four sums are then added in order.
 __global__ __launch_bounds__(256) void weight_grad_reduce_kernel(size_t n, int splits, const float *__restrict__ partial,
                                                                 float *__restrict__ dV)
 {
-    const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n) return;
+    __shared__ float run_s[3][64];
+    const int run = threadIdx.x >> 6, g = threadIdx.x & 63;
+    const size_t i = size_t(blockIdx.x) * 64 + g;
+    const int per_run = (splits + 3) / 4;
+    const int s_begin = min(run * per_run, splits), s_end = min(s_begin + per_run, splits);
     float acc = 0.f;
-    for (int s = 0; s < splits; ++s) acc += partial[size_t(s) * n + i];
-    dV[i] = acc;
+    if (i < n) {
+        const float *src = partial + size_t(s_begin) * n + i;
+        int s = s_begin;
+        for (; s + 8 <= s_end; s += 8, src += 8 * n) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[u * n];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += v[u];
+        }
+        for (; s < s_end; ++s, src += n) acc += *src;
+    }
+    if (run > 0) run_s[run - 1][g] = acc;
+    __syncthreads();
+    if (run == 0 && i < n) dV[i] = ((acc + run_s[0][g]) + run_s[1][g]) + run_s[2][g];
+}
+
+struct WgTiledPlan {
+    int nt, kn;              // nt = 0: no tile fits LDS
+    int waves_p, waves_k, groups_k, k_blocks, per_chunk, chunks;
+    size_t lds;
+};
+
+// Block of diagonals, tile and chunks by the time they should take, as in make_tiled_plan.
+static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
+{
+    WgTiledPlan best = {};
+    const int p_blocks = (L + 63) / 64, group = bf16 ? 8 : 4;
+    const size_t one = size_t(K) * L * sizeof(float);
+    size_t budget = one * weight_grad_splits(T);  // partial sums: what the untiled kernel would make, or 16 MiB
+    if (budget < (size_t(16) << 20)) budget = size_t(16) << 20;
+    double best_cost = 1e300;
+    static const int kns[] = {8, 16, 24}, nts[] = {1, 2, 4};
+    for (int kn : kns) {
+        const int k_blocks = (K + kn - 1) / kn;
+        const int groups_k = (k_blocks + kWgMaxWaves - 1) / kWgMaxWaves, waves_k = (k_blocks + groups_k - 1) / groups_k;
+        for (int waves_p = 1; waves_p * waves_k <= kWgMaxWaves && waves_p <= p_blocks; ++waves_p) {
+            const int waves = waves_p * waves_k, threads = waves * 64;
+            const int per_chunk = (p_blocks + waves_p - 1) / waves_p * groups_k;
+            const int64_t cols = D + waves_p * 64;
+            for (int nt : nts) {
+                const int tt = nt * group;
+                const size_t lds = 2 * size_t(cols) * tile_stride(nt);
+                if (lds > kLdsPerCu || nt > (bf16 ? 1 : 2) * waves_k) continue;
+                const int64_t tiles = (T + tt - 1) / tt;
+                int64_t chunks = 256 / per_chunk;  // one workgroup per CU: more cost more staging than they hide
+                if (chunks > tiles) chunks = tiles;
+                if (chunks > int64_t(budget / one)) chunks = int64_t(budget / one);
+                if (chunks < 1) chunks = 1;
+                const double rounds = double((chunks * per_chunk + 255) / 256);
+                const double steps = double((tiles + chunks - 1) / chunks);
+                // per tile: LDS reads of all waves, or one wave's chain of instructions; the barrier and the next tile
+                const double lds_clk = waves * nt * (kn + 4) * 8, issue = nt * (kn * 16 + 8) * 1.3 * ((waves + 3) / 4);
+                const double staging = 1500 + 150.0 * cols * nt / threads + (cols * nt > (bf16 ? 2 : 4) * threads ? 2000 : 0);
+                const double cost = rounds * (steps * ((lds_clk > issue ? lds_clk : issue) + staging) + 3000) +
+                                    (chunks > 1 ? 8000 + 2.0 * chunks * one / 2000 : 0);
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    best.nt = nt;
+                    best.kn = kn;
+                    best.waves_p = waves_p;
+                    best.waves_k = waves_k;
+                    best.groups_k = groups_k;
+                    best.k_blocks = k_blocks;
+                    best.per_chunk = per_chunk;
+                    best.chunks = int(chunks);
+                    best.lds = lds;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+static WgTiledPlan plan_wg_tiled(int64_t T, int D, int L, int K, bool bf16)
+{
+    static thread_local PlanMemo<WgTiledPlan> memo;
+    return memo.get(T, D, L, K, bf16, [&] { return make_wg_tiled_plan(T, D, L, K, bf16); });
+}
+
+size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16)
+{
+    // never less than the untiled kernel's: what a caller with a fixed amount of scratch may run does not hang on the plan
+    const WgTiledPlan pl = plan_wg_tiled(T, D, L, K, bf16);
+    const int splits = weight_grad_splits(T);
+    return size_t(pl.chunks > splits ? pl.chunks : splits) * size_t(K) * size_t(L) * sizeof(float);
+}
+
+template <class S, int NT, int KN>
+static hipError_t launch_wg_tiled(const WeightGradArgs &a, const WgTiledPlan &pl, float *partial, hipStream_t stream)
+{
+    using st = typename S::storage;
+    static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&weight_grad_tiled_kernel<S, NT, KN>), int(kLdsPerCu), lds_allowed)) return e;
+    hipLaunchKernelGGL((weight_grad_tiled_kernel<S, NT, KN>), dim3(pl.chunks * pl.per_chunk), dim3(64 * pl.waves_p * pl.waves_k),
+                       pl.lds, stream, a.T, a.D, a.L, a.K, pl.chunks, pl.per_chunk, pl.waves_k, pl.groups_k, pl.k_blocks,
+                       static_cast<const st *>(a.A), static_cast<const st *>(a.B), a.offsets, partial);
+    return hipGetLastError();
+}
+
+template <class S, int NT>
+static hipError_t launch_wg_tiled(const WeightGradArgs &a, const WgTiledPlan &pl, float *partial, hipStream_t stream)
+{
+    return pl.kn == 24   ? launch_wg_tiled<S, NT, 24>(a, pl, partial, stream)
+           : pl.kn == 16 ? launch_wg_tiled<S, NT, 16>(a, pl, partial, stream)
+                         : launch_wg_tiled<S, NT, 8>(a, pl, partial, stream);
 }
 
 template <class S>
 static hipError_t launch_weight_grad_t(const WeightGradArgs &a, hipStream_t stream)
 {
     using st = typename S::storage;
-    const int splits = weight_grad_splits(a.T);
+    const WgTiledPlan pl = plan_wg_tiled(a.T, a.D, a.L, a.K, a.bf16);
+    const int splits = pl.nt ? pl.chunks : weight_grad_splits(a.T);
     const size_t n = size_t(a.K) * a.L;
-    float *partial = static_cast<float *>(a.ws);
-    // K can exceed the grid.y limit only beyond 65535 diagonals, which the ABI rejects
-    dim3 grid((a.L + kWgThreads - 1) / kWgThreads, a.K, splits);
-    hipLaunchKernelGGL(weight_grad_partial_kernel<S>, grid, dim3(kWgThreads), 0, stream, a.T, a.D, a.L, a.K, splits,
-                       static_cast<const st *>(a.A), static_cast<const st *>(a.B), a.offsets, partial);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, n, splits, partial,
+    float *partial = splits == 1 ? a.dValues : static_cast<float *>(a.ws);
+    hipError_t e;
+    if (pl.nt == 4) e = launch_wg_tiled<S, 4>(a, pl, partial, stream);
+    else if (pl.nt == 2) e = launch_wg_tiled<S, 2>(a, pl, partial, stream);
+    else if (pl.nt == 1) e = launch_wg_tiled<S, 1>(a, pl, partial, stream);
+    else {
+        // K can exceed the grid.y limit only beyond 65535 diagonals, which the ABI rejects
+        dim3 grid((a.L + kWgThreads - 1) / kWgThreads, a.K, splits);
+        hipLaunchKernelGGL(weight_grad_partial_kernel<S>, grid, dim3(kWgThreads), 0, stream, a.T, a.D, a.L, a.K, splits,
+                           static_cast<const st *>(a.A), static_cast<const st *>(a.B), a.offsets, partial);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess || splits == 1) return e;
+    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3(unsigned((n + 63) / 64)), dim3(256), 0, stream, n, splits, partial,
                        a.dValues);
     return hipGetLastError();
 }
 
 hipError_t launch_weight_grad_vector(const WeightGradArgs &a, hipStream_t stream)
 {
-    const bool aligned = reinterpret_cast<uintptr_t>(a.A) % 16 == 0 && reinterpret_cast<uintptr_t>(a.B) % 16 == 0;
-    if (a.bf16 && aligned && weight_grad_dot2_supported(a.T, a.D, a.L, a.K)) {
-        hipError_t e = launch_weight_grad_dot2_partials(a, stream);
-        if (e != hipSuccess) return e;
-        const size_t n = size_t(a.K) * a.L;
-        hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, n,
-                           weight_grad_dot2_chunks(a.T, a.D, a.L, a.K), static_cast<const float *>(a.ws), a.dValues);
-        return hipGetLastError();
-    }
     return a.bf16 ? launch_weight_grad_t<BF16>(a, stream) : launch_weight_grad_t<F32>(a, stream);
 }
 
