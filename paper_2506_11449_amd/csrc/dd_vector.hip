@@ -688,24 +688,28 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
                 if (chunks > tiles) chunks = tiles;
                 if (chunks > int64_t(budget / one)) chunks = int64_t(budget / one);
                 if (chunks < 1) chunks = 1;
-                const double rounds = double((chunks * per_chunk + 255) / 256);
-                const double steps = double((tiles + chunks - 1) / chunks);
                 // per tile: LDS reads of all waves, or one wave's chain of instructions; the barrier and the next tile
                 const double lds_clk = waves * nt * (kn + 4) * 8, issue = nt * (kn * 16 + 8) * 1.3 * ((waves + 3) / 4);
                 const double staging = 1500 + 150.0 * cols * nt / threads + (cols * nt > (bf16 ? 2 : 4) * threads ? 2000 : 0);
-                const double cost = rounds * (steps * ((lds_clk > issue ? lds_clk : issue) + staging) + 3000) +
-                                    (chunks > 1 ? 8000 + 2.0 * chunks * one / 2000 : 0);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best.nt = nt;
-                    best.kn = kn;
-                    best.waves_p = waves_p;
-                    best.waves_k = waves_k;
-                    best.groups_k = groups_k;
-                    best.k_blocks = k_blocks;
-                    best.per_chunk = per_chunk;
-                    best.chunks = int(chunks);
-                    best.lds = lds;
+                for (;;) {  // that many chunks, or one and no sum over them
+                    const double rounds = double((chunks * per_chunk + 255) / 256);
+                    const double steps = double((tiles + chunks - 1) / chunks);
+                    const double cost = rounds * (steps * ((lds_clk > issue ? lds_clk : issue) + staging) + 3000) +
+                                        (chunks > 1 ? 8000 + 2.0 * chunks * one / 2000 : 0);
+                    if (cost < best_cost) {
+                        best_cost = cost;
+                        best.nt = nt;
+                        best.kn = kn;
+                        best.waves_p = waves_p;
+                        best.waves_k = waves_k;
+                        best.groups_k = groups_k;
+                        best.k_blocks = k_blocks;
+                        best.per_chunk = per_chunk;
+                        best.chunks = int(chunks);
+                        best.lds = lds;
+                    }
+                    if (chunks == 1) break;
+                    chunks = 1;
                 }
             }
         }
