@@ -39,6 +39,7 @@ constexpr int kRowBytes = kBK * 2;
 constexpr int kXcds = 8;
 constexpr int kRing = 3;         // LDS stages of the token operand
 constexpr int kFusedRows = 3;    // operand rows per workgroup of select_materialize_kernel
+constexpr int kFusedThreads = 256, kFusedSlots = 4;  // its threads, and candidates per thread
 
 // position of 16-byte chunk `chunk` (0..7) inside its 128-byte row
 __device__ __forceinline__ int swizzle_key(int row) { return (row >> 1) & 7; }
@@ -178,10 +179,10 @@ __global__ __launch_bounds__(256) void materialize_kernel(int D, int L, int K, i
 // offsets out.  Rows [0, D) are rows of the masked-gather operand, rows [D, D + L) rows of the gather operand.
 // The selection never returns an offset twice, so no two diagonals meet in one entry and the operands come out
 // bit for bit as materialize_kernel builds them.
-// LDS: keys [D] | chosen offsets [K] | ROWS rows of D floats.
+// LDS: chosen offsets [K] | ROWS rows of D floats.
 // ---------------------------------------------------------------------------------------------
 template <int ROWS>
-__global__ __launch_bounds__(kSelectThreads) void select_materialize_kernel(int D, int L, int K,
+__global__ __launch_bounds__(kFusedThreads) void select_materialize_kernel(int D, int L, int K,
                                                                              const float *__restrict__ scores,
                                                                              const uint16_t *__restrict__ values,
                                                                              int *__restrict__ offsets_out,
@@ -189,16 +190,16 @@ __global__ __launch_bounds__(kSelectThreads) void select_materialize_kernel(int 
                                                                              uint16_t *__restrict__ Wf_gather)
 {
     extern __shared__ uint32_t lds_words[];
-    uint32_t *keys = lds_words;
-    int *chosen = reinterpret_cast<int *>(lds_words + D);
-    float *rows = reinterpret_cast<float *>(lds_words + D + K);
-    for (int i = threadIdx.x; i < ROWS * D; i += kSelectThreads) rows[i] = 0.f;
-    select_topk_block<true>(D, K, scores, keys, chosen);
+    __shared__ __attribute__((aligned(16))) SelectScratch<kFusedThreads, kFusedSlots> scratch;
+    int *chosen = reinterpret_cast<int *>(lds_words);
+    float *rows = reinterpret_cast<float *>(lds_words + K);
+    for (int i = threadIdx.x; i < ROWS * D; i += kFusedThreads) rows[i] = 0.f;
+    select_topk_block<kFusedThreads, kFusedSlots>(D, K, scores, scratch, chosen);
     __syncthreads();
     if (blockIdx.x == 0)
-        for (int k = threadIdx.x; k < K; k += kSelectThreads) offsets_out[k] = chosen[k];
+        for (int k = threadIdx.x; k < K; k += kFusedThreads) offsets_out[k] = chosen[k];
     const int r0 = blockIdx.x * ROWS;
-    for (int k = threadIdx.x; k < K; k += kSelectThreads) {
+    for (int k = threadIdx.x; k < K; k += kFusedThreads) {
         const int o = chosen[k];  // already in [0, D)
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_materialize_kernel(int 
         const int KD = long_major ? L : D;
         uint16_t *Wf = long_major ? Wf_masked : Wf_gather;
         const int out_row = long_major ? r : r - D;
-        for (int c8 = threadIdx.x; c8 < KD / 8; c8 += kSelectThreads) {
+        for (int c8 = threadIdx.x; c8 < KD / 8; c8 += kFusedThreads) {
             const float *src = rows + j * D + c8 * 8;  // 4-byte aligned only: K words lie before the rows
             const u32x4 v = pack_bf16x8(f32x4{src[0], src[1], src[2], src[3]}, f32x4{src[4], src[5], src[6], src[7]});
             *reinterpret_cast<u32x4 *>(Wf + fragment_index(out_row, c8 * 8, KD)) = v;
@@ -902,16 +903,16 @@ bool select_prepare_fused(int D, int L, int K)
 {
     // pays while a handful of resident workgroups per CU cover all rows at once; beyond that the repeated
     // selections cost more than the launch they save
-    return D <= 1024 && size_t(D + K + kFusedRows * D) * 4 <= 48 * 1024;
+    return D <= kFusedThreads * kFusedSlots && size_t(K + kFusedRows * D) * 4 <= 48 * 1024;
 }
 
 hipError_t launch_select_prepare(int D, int L, int K, bool expanding, const float *scores, const void *values,
                                  int32_t *offsets_out, void *forward_operand, void *backward_operand,
                                  hipStream_t stream)
 {
-    const size_t lds = size_t(D + K + kFusedRows * D) * 4;
+    const size_t lds = size_t(K + kFusedRows * D) * 4;
     hipLaunchKernelGGL(select_materialize_kernel<kFusedRows>, dim3((D + L + kFusedRows - 1) / kFusedRows),
-                       dim3(kSelectThreads), lds, stream, D, L, K, scores, static_cast<const uint16_t *>(values),
+                       dim3(kFusedThreads), lds, stream, D, L, K, scores, static_cast<const uint16_t *>(values),
                        offsets_out, static_cast<uint16_t *>(expanding ? forward_operand : backward_operand),
                        static_cast<uint16_t *>(expanding ? backward_operand : forward_operand));
     return hipGetLastError();

@@ -517,19 +517,19 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(int D, int L, int K, 
 // diagonal.  One workgroup: the D sums are formed in LDS (one addition per diagonal; an offset given twice gets both
 // dots -- a sum of two is the same in either order, only an offset given three times or more sees an unspecified order
 // of fp32 additions) and written out once.
-__global__ __launch_bounds__(256) void wgrad_dalpha_kernel(int D, int K, int per_k, const int *__restrict__ offsets,
+__global__ __launch_bounds__(1024) void wgrad_dalpha_kernel(int D, int K, int per_k, const int *__restrict__ offsets,
                                                            const float *__restrict__ dots, float *__restrict__ dalpha)
 {
     extern __shared__ float sums[];  // [D]
-    for (int i = threadIdx.x; i < D; i += 256) sums[i] = 0.f;
+    for (int i = threadIdx.x; i < D; i += 1024) sums[i] = 0.f;
     __syncthreads();
-    for (int j = threadIdx.x; j < K; j += 256) {
+    for (int j = threadIdx.x; j < K; j += 1024) {
         float sum = 0.f;
         for (int b = 0; b < per_k; ++b) sum += dots[size_t(j) * per_k + b];
         atomicAdd(&sums[canonical_offset(offsets[j], D)], sum);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < D; i += 256) dalpha[i] = sums[i];
+    for (int i = threadIdx.x; i < D; i += 1024) dalpha[i] = sums[i];
 }
 
 // ---- host side ----
@@ -636,7 +636,7 @@ hipError_t launch_weight_grad_matrix_scaled(const WeightGradArgs &a, const float
     hipLaunchKernelGGL(wgrad_reduce_kernel<true>, dim3(per_k, a.K), dim3(256), 0, stream, a.D, a.L, a.K, pl.splits,
                        a.offsets, partial, a.dValues, alpha, static_cast<const uint16_t *>(V), dots);
     if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL(wgrad_dalpha_kernel, dim3(1), dim3(256), size_t(a.D) * sizeof(float), stream, a.D, a.K, per_k,
+    hipLaunchKernelGGL(wgrad_dalpha_kernel, dim3(1), dim3(1024), size_t(a.D) * sizeof(float), stream, a.D, a.K, per_k,
                        a.offsets, dots, dalpha);
     return hipGetLastError();
 }

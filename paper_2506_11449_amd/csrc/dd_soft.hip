@@ -7,6 +7,8 @@
 
 namespace dd {
 
+constexpr int kScaleThreads = 256;  // kernels that run over the K x L values
+
 __global__ __launch_bounds__(kSoftThreads) void soft_topk_kernel(int D, float k_over_1, float inv_temp,
                                                                  const float *__restrict__ scores,
                                                                  float *__restrict__ alpha_tilde)
@@ -20,7 +22,7 @@ __global__ __launch_bounds__(kSoftThreads) void soft_topk_bwd_kernel(int D, floa
                                                                      const float *__restrict__ g,
                                                                      float *__restrict__ dscores)
 {
-    __shared__ float scratch[4];
+    __shared__ float scratch[kSoftThreads / 64];
     const float *a = scores + size_t(blockIdx.x) * D, *gb = g + size_t(blockIdx.x) * D;
     float *out = dscores + size_t(blockIdx.x) * D;
     float m = -INFINITY;
@@ -45,12 +47,12 @@ __global__ __launch_bounds__(kSoftThreads) void soft_topk_bwd_kernel(int D, floa
 
 // values_eff[k][p] = alpha_tilde[o_k] * V[k][p]
 template <class S>
-__global__ __launch_bounds__(kSoftThreads) void scale_values_kernel(int L, int D, const int *__restrict__ offsets,
+__global__ __launch_bounds__(kScaleThreads) void scale_values_kernel(int L, int D, const int *__restrict__ offsets,
                                                                     const float *__restrict__ alpha_tilde,
                                                                     const typename S::storage *__restrict__ V,
                                                                     typename S::storage *__restrict__ out)
 {
-    const int k = blockIdx.y, p = blockIdx.x * kSoftThreads + threadIdx.x;
+    const int k = blockIdx.y, p = blockIdx.x * kScaleThreads + threadIdx.x;
     if (p >= L) return;
     const float a = alpha_tilde[canonical_offset(offsets[k], D)];
     S::store(out + size_t(k) * L + p, a * S::load(V + size_t(k) * L + p));
@@ -58,32 +60,32 @@ __global__ __launch_bounds__(kSoftThreads) void scale_values_kernel(int L, int D
 
 // dV[k][p] = alpha_tilde[o_k] * dValues[k][p];  dots[k] = <dValues[k], V[k]>
 template <class S>
-__global__ __launch_bounds__(kSoftThreads) void scale_values_bwd_kernel(int L, int D, const int *__restrict__ offsets,
+__global__ __launch_bounds__(kScaleThreads) void scale_values_bwd_kernel(int L, int D, const int *__restrict__ offsets,
                                                                         const float *__restrict__ alpha_tilde,
                                                                         const typename S::storage *__restrict__ V,
                                                                         const float *__restrict__ dValues,
                                                                         float *__restrict__ dV,
                                                                         float *__restrict__ dots)
 {
-    __shared__ float scratch[4];
+    __shared__ float scratch[kScaleThreads / 64];
     const int k = blockIdx.x;
     const float a = alpha_tilde[canonical_offset(offsets[k], D)];
     float dot = 0.f;
-    for (int p = threadIdx.x; p < L; p += kSoftThreads) {
+    for (int p = threadIdx.x; p < L; p += kScaleThreads) {
         const float g = dValues[size_t(k) * L + p];
         dV[size_t(k) * L + p] = a * g;
         dot = fmaf(g, S::load(V + size_t(k) * L + p), dot);
     }
-    dot = block_reduce<false>(dot, scratch);
+    dot = block_reduce<false, kScaleThreads>(dot, scratch);
     if (threadIdx.x == 0) dots[k] = dot;
 }
 
 // dalpha_tilde[i] = sum over the diagonals k with offset i, in index order, of dots[k]
-__global__ __launch_bounds__(kSoftThreads) void scatter_alpha_grad_kernel(int D, int K, const int *__restrict__ offsets,
+__global__ __launch_bounds__(kScaleThreads) void scatter_alpha_grad_kernel(int D, int K, const int *__restrict__ offsets,
                                                                           const float *__restrict__ dots,
                                                                           float *__restrict__ dalpha)
 {
-    const int i = blockIdx.x * kSoftThreads + threadIdx.x;
+    const int i = blockIdx.x * kScaleThreads + threadIdx.x;
     if (i >= D) return;
     float acc = 0.f;
     for (int k = 0; k < K; ++k)
@@ -110,12 +112,12 @@ hipError_t launch_soft_topk_bwd(int batch, int D, int K, float temperature, cons
 hipError_t launch_scale_values(int K, int L, int D, bool bf16, const int *offsets, const float *alpha_tilde,
                                const void *V, void *out, hipStream_t stream)
 {
-    dim3 grid((L + kSoftThreads - 1) / kSoftThreads, K);
+    dim3 grid((L + kScaleThreads - 1) / kScaleThreads, K);
     if (bf16)
-        hipLaunchKernelGGL(scale_values_kernel<BF16>, grid, dim3(kSoftThreads), 0, stream, L, D, offsets, alpha_tilde,
+        hipLaunchKernelGGL(scale_values_kernel<BF16>, grid, dim3(kScaleThreads), 0, stream, L, D, offsets, alpha_tilde,
                            static_cast<const uint16_t *>(V), static_cast<uint16_t *>(out));
     else
-        hipLaunchKernelGGL(scale_values_kernel<F32>, grid, dim3(kSoftThreads), 0, stream, L, D, offsets, alpha_tilde,
+        hipLaunchKernelGGL(scale_values_kernel<F32>, grid, dim3(kScaleThreads), 0, stream, L, D, offsets, alpha_tilde,
                            static_cast<const float *>(V), static_cast<float *>(out));
     return hipGetLastError();
 }
@@ -125,14 +127,14 @@ hipError_t launch_scale_values_bwd(int K, int L, int D, bool bf16, const int *of
                                    hipStream_t stream)
 {
     if (bf16)
-        hipLaunchKernelGGL(scale_values_bwd_kernel<BF16>, dim3(K), dim3(kSoftThreads), 0, stream, L, D, offsets,
+        hipLaunchKernelGGL(scale_values_bwd_kernel<BF16>, dim3(K), dim3(kScaleThreads), 0, stream, L, D, offsets,
                            alpha_tilde, static_cast<const uint16_t *>(V), dValues, dV, dots);
     else
-        hipLaunchKernelGGL(scale_values_bwd_kernel<F32>, dim3(K), dim3(kSoftThreads), 0, stream, L, D, offsets,
+        hipLaunchKernelGGL(scale_values_bwd_kernel<F32>, dim3(K), dim3(kScaleThreads), 0, stream, L, D, offsets,
                            alpha_tilde, static_cast<const float *>(V), dValues, dV, dots);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(scatter_alpha_grad_kernel, dim3((D + kSoftThreads - 1) / kSoftThreads), dim3(kSoftThreads), 0,
+    hipLaunchKernelGGL(scatter_alpha_grad_kernel, dim3((D + kScaleThreads - 1) / kScaleThreads), dim3(kScaleThreads), 0,
                        stream, D, K, offsets, dots, dalpha);
     return hipGetLastError();
 }
