@@ -2,17 +2,20 @@
 // Method"): the diagonals of lowest magnitude leave, as many inactive candidates enter at random.  The random
 // scores are an input, so the result is a pure function of its arguments.
 //
-// The update is two hard TopK selections on score vectors over the D candidates, and runs on the selection
-// kernel of Sec. 3.2 (dd_select.hip) without leaving the device:
-//   1. scores_1[i] = magnitude of the active diagonal with offset i (a NaN magnitude counts as -1, below
-//      every true magnitude, which is a sum of absolute values), -inf where no diagonal is active;
-//      keep = TopK(scores_1, K - n_drop)                     the diagonals that stay
-//   2. scores_2[i] = +inf for i in keep, random[i] for i that was not active (finite by contract; NaN
-//      counts as -inf), NaN -- the lowest rank there is -- for the diagonals that have just left;
-//      new = TopK(scores_2, K)                               the K - n_drop kept ones and the n_drop grown ones
+// The update is two hard TopK selections (Sec. 3.2, dd_select_block.h) on keys over the D candidates, by one workgroup that
+// keeps them in registers:
+//   1. key of the magnitude of the active diagonal with offset i (a NaN magnitude counts as -1, below every true
+//      magnitude, which is a sum of absolute values), of -inf where no diagonal is active;
+//      keep = TopK(K - n_drop)                               the diagonals that stay
+//   2. key of +inf for i in keep, of random[i] for i that was not active (finite by contract; NaN counts as -inf), and of
+//      NaN -- the lowest rank there is -- for the diagonals that have just left;
+//      new = TopK(K)                                         the K - n_drop kept ones and the n_drop grown ones
 // Both selections order equal scores by lower index and NaN lowest, and emit ascending indices.
+// Bound by latency (one workgroup, two trips to memory, two selections): D = 3072, K = 307 12 us in one launch, where five
+// launches (table, selection, scores, selection, sources) took 33 us one after the other.
 #include "dd_common.h"
 #include "dd_launch.h"
+#include "dd_select_block.h"
 
 #include <float.h>
 #include <math.h>
@@ -39,44 +42,52 @@ __global__ __launch_bounds__(kHeurThreads) void diag_magnitude_kernel(int L, con
     if (threadIdx.x == 0) magnitudes[blockIdx.x] = part[0];
 }
 
-// scores_1 and the table offset -> position in `offsets` (-1: not active); one workgroup
-__global__ __launch_bounds__(1024) void heur_scatter_kernel(int D, int K, const int *__restrict__ offsets,
-                                                            const float *__restrict__ magnitudes,
-                                                            float *__restrict__ scores, int *__restrict__ slot)
+// One workgroup.  slot: table offset -> position in `offsets` (-1: not active), D entries in LDS or, for more candidates
+// than fit there, in the caller's scratch.
+template <int SLOTS, bool TABLE_IN_LDS>
+__global__ __launch_bounds__(kSelectThreads) void heur_update_kernel(int D, int K, int n_keep,
+                                                                     const int *__restrict__ offsets,
+                                                                     const float *__restrict__ magnitudes,
+                                                                     const float *__restrict__ random,
+                                                                     int *__restrict__ new_offsets,
+                                                                     int *__restrict__ source, int *__restrict__ table)
 {
-    for (int i = threadIdx.x; i < D; i += 1024) {
-        scores[i] = -INFINITY;
-        slot[i] = -1;
-    }
-    __syncthreads();  // one workgroup: its own global writes above are ordered before those below
-    for (int k = threadIdx.x; k < K; k += 1024) {
-        const int o = canonical_offset(offsets[k], D);
-        const float m = magnitudes[k];
-        scores[o] = m != m ? -1.f : m;
-        slot[o] = k;
-    }
-}
-
-// scores_2 from the table, the random scores and the kept offsets; one workgroup
-__global__ __launch_bounds__(1024) void heur_combine_kernel(int D, int n_keep, const int *__restrict__ slot,
-                                                            const float *__restrict__ random,
-                                                            const int *__restrict__ keep, float *__restrict__ scores)
-{
-    for (int i = threadIdx.x; i < D; i += 1024) {
-        const float r = random[i];
-        scores[i] = slot[i] >= 0 ? NAN : (r != r ? -INFINITY : r);
-    }
+    extern __shared__ int lds_table[];
+    __shared__ __attribute__((aligned(16))) SelectScratch<kSelectThreads, SLOTS> scratch;
+    int *slot = TABLE_IN_LDS ? lds_table : table;
+    const int tid = threadIdx.x;
+    float r[SLOTS];  // requested first: needed last
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) r[j] = random[min(j * kSelectThreads + tid, D - 1)];
+    for (int i = tid; i < D; i += kSelectThreads) slot[i] = -1;
+    __syncthreads();  // one workgroup: its own writes above are ordered before those below
+    for (int k = tid; k < K; k += kSelectThreads) slot[canonical_offset(offsets[k], D)] = k;
     __syncthreads();
-    for (int j = threadIdx.x; j < n_keep; j += 1024) scores[keep[j]] = INFINITY;
-}
-
-// source[j] = position in the old arrays of new diagonal j, -1 for a grown one
-__global__ __launch_bounds__(kHeurThreads) void heur_source_kernel(int K, const int *__restrict__ slot,
-                                                                   const int *__restrict__ new_offsets,
-                                                                   int *__restrict__ source)
-{
-    const int j = blockIdx.x * kHeurThreads + threadIdx.x;
-    if (j < K) source[j] = slot[new_offsets[j]];
+    int mine[SLOTS], place[SLOTS];
+    uint32_t key[SLOTS];
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+        mine[j] = slot[min(j * kSelectThreads + tid, D - 1)];
+        const float m = mine[j] >= 0 ? magnitudes[mine[j]] : -INFINITY;
+        key[j] = score_key(m != m ? -1.f : m);
+        place[j] = -1;
+    }
+    if (n_keep > 0) {
+        select_block<kSelectThreads, SLOTS>(D, n_keep, key, scratch, place);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+        const float grow = r[j] != r[j] ? -INFINITY : r[j];
+        key[j] = score_key(place[j] >= 0 ? INFINITY : (mine[j] >= 0 ? NAN : grow));
+    }
+    select_block<kSelectThreads, SLOTS>(D, K, key, scratch, place);
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j)
+        if (place[j] >= 0) {
+            new_offsets[place[j]] = j * kSelectThreads + tid;
+            source[place[j]] = mine[j];
+        }
 }
 
 hipError_t launch_diag_magnitude(int K, int L, bool bf16, const void *values, float *magnitudes, hipStream_t stream)
@@ -92,35 +103,33 @@ hipError_t launch_diag_magnitude(int K, int L, bool bf16, const void *values, fl
 
 size_t diagheur_ws_bytes(int D, int K)
 {
-    // scores [D] float, slot [D] int, keep [K] int; each part a multiple of 256 bytes
+    // two tables of D entries and one of K, each a multiple of 256 bytes (of which the kernel for layers too wide for LDS
+    // uses one table)
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     return 2 * up(size_t(D) * 4) + up(size_t(K) * 4);
+}
+
+template <int SLOTS, bool TABLE_IN_LDS>
+static hipError_t launch_heur(int D, int K, int n_keep, const int *offsets, const float *magnitudes, const float *random,
+                              int *new_offsets, int *source, void *ws, hipStream_t stream)
+{
+    const int lds = TABLE_IN_LDS ? SLOTS * kSelectThreads * int(sizeof(int)) : 0;
+    static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
+    if (lds)
+        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&heur_update_kernel<SLOTS, TABLE_IN_LDS>), lds, lds_allowed)) return e;
+    hipLaunchKernelGGL((heur_update_kernel<SLOTS, TABLE_IN_LDS>), dim3(1), dim3(kSelectThreads), lds, stream, D, K, n_keep, offsets,
+                       magnitudes, random, new_offsets, source, static_cast<int *>(ws));
+    return hipGetLastError();
 }
 
 hipError_t launch_diagheur_update(int D, int K, int n_drop, const int *offsets, const float *magnitudes,
                                   const float *random, int *new_offsets, int *source, void *ws, hipStream_t stream)
 {
-    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    unsigned char *base = static_cast<unsigned char *>(ws);
-    float *scores = reinterpret_cast<float *>(base);
-    int *slot = reinterpret_cast<int *>(base + up(size_t(D) * 4));
-    int *keep = reinterpret_cast<int *>(base + 2 * up(size_t(D) * 4));
-    const int n_keep = K - n_drop;
-    hipLaunchKernelGGL(heur_scatter_kernel, dim3(1), dim3(1024), 0, stream, D, K, offsets, magnitudes, scores, slot);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (n_keep > 0) {
-        e = launch_select(1, D, n_keep, scores, keep, stream);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(heur_combine_kernel, dim3(1), dim3(1024), 0, stream, D, n_keep, slot, random, keep, scores);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = launch_select(1, D, K, scores, new_offsets, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(heur_source_kernel, dim3((K + kHeurThreads - 1) / kHeurThreads), dim3(kHeurThreads), 0, stream,
-                       K, slot, new_offsets, source);
-    return hipGetLastError();
+    const int slots = (D + kSelectThreads - 1) / kSelectThreads, n_keep = K - n_drop;
+    if (slots <= 1) return launch_heur<1, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    if (slots <= 4) return launch_heur<4, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    if (slots <= 16) return launch_heur<16, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    return launch_heur<kSelectMaxSlots, false>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
 }
 
 }  // namespace dd
