@@ -117,20 +117,24 @@ def dd_workspace_bytes(op, layer, batch=0):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    """Address of a tensor (None: the null pointer), as ctypes takes it for a void pointer."""
+    return None if t is None else t.data_ptr()
+
+
+_current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """Handle of the given stream, or of the current stream of the current device."""
+    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
 def _dev(t, dtype, shape, name):
+    if t.dtype is dtype and t.shape == shape and t.is_cuda and t.is_contiguous():
+        return t
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous GPU tensor")
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name}: expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
-    return t
+    raise ValueError(f"{name}: expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
 
 class Workspace:
