@@ -815,6 +815,154 @@ __global__ __launch_bounds__(64 * NW) void mm_persistent_kernel(int T, int NC, i
 }
 
 // ---------------------------------------------------------------------------------------------
+// Step 2 for few tokens.  With a tile of 64 or more tokens x 256 columns a product of a few hundred tokens has
+// fewer workgroups than the chip has CUs, and each walks the whole contraction with the operand one k-slice ahead: its
+// time is a chain of memory latencies.  Here a workgroup owns 32*FB tokens x 32*FA columns and its KS waves take
+// one KS-th of the contraction each, four k-steps (64 contraction indices) at a time and two such groups ahead, with no
+// barrier until the waves' sums meet in LDS, where they are added in order.  The operand goes from memory straight into the
+// fragments' registers; token rows are requested as whole 128-byte lines (eight lanes each) and change lanes through a
+// piece of LDS private to the wave -- requested fragment by fragment every instruction would touch 32 lines.
+// The tiles are numbered token blocks innermost, one contiguous run per XCD: what the workgroups of a column tile share
+// is the operand, the larger input here.
+// ---------------------------------------------------------------------------------------------
+template <int FA, int FB, int KS>
+struct MmSmallTile {
+    static constexpr int BM = 32 * FB, BN = 32 * FA;
+    static constexpr int STRIDE = BN + 4;  // floats; an odd number of 16-byte pieces staggers the rows over the banks
+    static constexpr int LDS_BYTES = KS * BM * (STRIDE * 4 > kRowBytes ? STRIDE * 4 : kRowBytes);
+};
+
+template <int FA, int FB, int KS>
+__global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_cols, int c_cols, int tiles_m, int tiles_n,
+                                                           const uint16_t *__restrict__ A,
+                                                           const uint16_t *__restrict__ Wf, uint16_t *__restrict__ C)
+{
+    using Tl = MmSmallTile<FA, FB, KS>;
+    constexpr int BM = Tl::BM, BN = Tl::BN;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int n_tiles = tiles_m * tiles_n;
+    const int per_xcd = (n_tiles + kXcds - 1) / kXcds;
+    const int lin = int(blockIdx.x % kXcds) * per_xcd + int(blockIdx.x / kXcds);
+    if (lin >= n_tiles) return;
+    const int tn = lin / tiles_m, tm = lin - tn * tiles_m;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int groups = KD / 64;
+    const int g_begin = groups * wave / KS, g_end = groups * (wave + 1) / KS;
+
+    // token rows: request j of block b is rows b*32 + 8j ... + 7, lane = (row, 16-byte chunk); byte offsets in one matrix
+    unsigned x_row[FB][4];
+    int x_dst[4], x_frag[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int row = 8 * j + (lane >> 3);
+#pragma unroll
+        for (int b = 0; b < FB; ++b)  // rows past the end re-read the last token; their results are not stored
+            x_row[b][j] = (unsigned(min(tm * BM + b * 32 + row, T - 1)) * unsigned(a_cols) + (lane & 7) * 8) * 2u;
+        x_dst[j] = row * kRowBytes + swizzle(row, lane & 7) * 16;
+        x_frag[j] = l32 * kRowBytes + swizzle(l32, 2 * j + half) * 16;  // k-step j
+    }
+    unsigned char *x_buf = smem + wave * (FB * 32 * kRowBytes);
+    const uint16_t *w_src = Wf + (size_t(tn * FA) * (KD / 16) + size_t(g_begin) * 4) * 512;
+    const size_t w_row = size_t(KD / 16) * 512;  // from one 32-column block to the next
+    // the cursor of the token rows inside the stack of matrices
+    int x_in = g_begin * 64 % a_cols;
+    const uint16_t *x_src = A + size_t(g_begin * 64 / a_cols) * T * a_cols + x_in;
+    const size_t x_jump = size_t(T - 1) * a_cols;
+
+    f32x16 acc[FA][FB];
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+    bf16x8 w0[4][FA], w1[4][FA];
+    u32x4 x0[FB][4], x1[FB][4];
+#define DD_SMALL_LOAD_X(x_)                                                                             \
+    {                                                                                                   \
+        _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
+                x_[b][j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(x_src) + x_row[b][j]); \
+        x_src += 64;                                                                                    \
+        x_in += 64;                                                                                     \
+        if (x_in == a_cols) {                                                                           \
+            x_in = 0;                                                                                   \
+            x_src += x_jump;                                                                            \
+        }                                                                                               \
+    }
+#define DD_SMALL_LOAD_W(w_)                                                                             \
+    {                                                                                                   \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+            _Pragma("unroll") for (int a = 0; a < FA; ++a)                                              \
+                w_[ks][a] = *reinterpret_cast<const bf16x8 *>(w_src + a * w_row + ks * 512 + lane * 8); \
+        w_src += 4 * 512;                                                                               \
+    }
+    // a wave's LDS accesses are served in order: the rows are read as fragments behind their own writes and before the
+    // writes of the next group
+#define DD_SMALL_GROUP(w_, x_, more_)                                                                   \
+    {                                                                                                   \
+        _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
+                *reinterpret_cast<u32x4 *>(x_buf + b * 32 * kRowBytes + x_dst[j]) = x_[b][j];           \
+        if (more_) DD_SMALL_LOAD_X(x_)                                                                  \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                              \
+            bf16x8 xf[FB];                                                                              \
+            _Pragma("unroll") for (int b = 0; b < FB; ++b)                                              \
+                xf[b] = *reinterpret_cast<const bf16x8 *>(x_buf + b * 32 * kRowBytes + x_frag[ks]);     \
+            _Pragma("unroll") for (int a = 0; a < FA; ++a)                                              \
+                _Pragma("unroll") for (int b = 0; b < FB; ++b)                                          \
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_[ks][a], xf[b], acc[a][b], 0, 0, 0); \
+        }                                                                                               \
+        if (more_) DD_SMALL_LOAD_W(w_)                                                                  \
+    }
+    int g = g_begin;
+    if (g < g_end) {
+        DD_SMALL_LOAD_X(x0)
+        DD_SMALL_LOAD_W(w0)
+    }
+    if (g + 1 < g_end) {
+        DD_SMALL_LOAD_X(x1)
+        DD_SMALL_LOAD_W(w1)
+    }
+    for (; g + 1 < g_end; g += 2) {
+        DD_SMALL_GROUP(w0, x0, g + 2 < g_end)
+        DD_SMALL_GROUP(w1, x1, g + 3 < g_end)
+    }
+    if (g < g_end) DD_SMALL_GROUP(w0, x0, false)
+#undef DD_SMALL_GROUP
+#undef DD_SMALL_LOAD_W
+#undef DD_SMALL_LOAD_X
+    __syncthreads();  // the sums take the place of the rows
+
+    // Accumulator i of lane l is output column 8*(i/4) + 4*(l/32) + i%4 of token l%32 inside its 32x32 tile.
+    float *sums = reinterpret_cast<float *>(smem);  // [KS][BM][STRIDE]
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+                *reinterpret_cast<f32x4 *>(sums + (wave * BM + b * 32 + l32) * Tl::STRIDE + a * 32 + 8 * q + 4 * half) = v;
+            }
+    __syncthreads();
+    const int matrix = tn * BN / c_cols, first_col = tn * BN - matrix * c_cols;  // c_cols is a multiple of BN
+    for (int idx = tid; idx < BM * BN / 8; idx += 64 * KS) {
+        const int row = idx / (BN / 8), ch = idx % (BN / 8), t = tm * BM + row;
+        const float *src = sums + row * Tl::STRIDE + ch * 8;
+        f32x4 lo = *reinterpret_cast<const f32x4 *>(src), hi = *reinterpret_cast<const f32x4 *>(src + 4);
+#pragma unroll
+        for (int k = 1; k < KS; ++k) {
+            lo += *reinterpret_cast<const f32x4 *>(src + k * BM * Tl::STRIDE);
+            hi += *reinterpret_cast<const f32x4 *>(src + k * BM * Tl::STRIDE + 4);
+        }
+        if (t < T) *reinterpret_cast<u32x4 *>(C + (size_t(matrix) * T + t) * c_cols + first_col + ch * 8) = pack_bf16x8(lo, hi);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
 bool product_matrix_supported(int64_t T, int D, int L, bool bf16)
@@ -938,6 +1086,20 @@ static hipError_t launch_mm_persistent(int T, int NC, int KD, int a_cols, int c_
     return hipGetLastError();
 }
 
+template <int FA, int FB, int KS>
+static hipError_t launch_mm_small(int T, int NC, int KD, int a_cols, int c_cols, const uint16_t *A, const uint16_t *Wf,
+                                  uint16_t *C, hipStream_t stream)
+{
+    using Tl = MmSmallTile<FA, FB, KS>;
+    static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_small_kernel<FA, FB, KS>), Tl::LDS_BYTES, lds_allowed)) return e;
+    const int tiles_m = (T + Tl::BM - 1) / Tl::BM, tiles_n = NC / Tl::BN;
+    const int per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds;
+    hipLaunchKernelGGL((mm_small_kernel<FA, FB, KS>), dim3(per_xcd * kXcds), dim3(64 * KS), Tl::LDS_BYTES, stream, T, KD,
+                       a_cols, c_cols, tiles_m, tiles_n, A, Wf, C);
+    return hipGetLastError();
+}
+
 constexpr int kMmWaves = 8;  // two waves per SIMD: one wave's waits hide behind the other's MFMAs
 
 // Largest tile whose workgroup count fills the 256 CUs in the fewest, fullest rounds.
@@ -955,6 +1117,40 @@ static int pick_tile(int64_t T, int NC)
         if (cost < best_cost) { best_cost = cost; best = bm[i]; }
     }
     return best;
+}
+
+// Few tokens: which tile of mm_small_kernel, if any (columns * 100 + tokens, 0: the kernels of 256 columns).  Times in us
+// fitted to T = 1 ... 6304 over 128^2 ... 4096^2 (kernel alone): a workgroup's fixed part and its time per 64 contraction
+// indices and wave, which grows as the chip fills; against the 64-token tile, the cheapest of the others, which walks the
+// whole contraction in one chain.  768 -> 3072 (3072 -> 768) at 197 tokens 7.8 -> 5.4 us (21.1 -> 5.8), 768^2 at 1279
+// tokens 7.9 -> 5.7, 4096^2 at 197 tokens 30.5 -> 16; the lines cross at 1300-2000 tokens for 768^2, at 400-800 for 3072
+// and more columns.
+// A group of layers takes these tiles where one of its layers by itself would (set_cols columns), so that a layer's result
+// has the same bits either way: its contraction is cut into the same four parts.
+static int pick_small(int64_t T, int NC, int KD, int a_cols, int set_cols)
+{
+    if (T * a_cols * 2 >= (int64_t(1) << 32)) return 0;  // 32-bit offsets into a matrix of token rows
+    static const struct {
+        int cols, tokens;
+        double fixed, per_group, load;
+    } tiles[] = {{32, 32, 2.8, 0.233, 0.4}, {64, 32, 3.25, 0.317, 0.3}, {64, 64, 3.65, 0.52, 0.85}, {128, 64, 4.7, 0.97, 0.45}};
+    const double groups = KD / 64, share = groups > 4 ? groups / 4 : 1;
+    const double limit = 0.9 * (3.0 + groups * (0.40 + 0.012 * (set_cols < 4096 ? set_cols : 4096) / 256 * (KD < 768 ? KD / 768.0 : 1.0)));
+    double best_cost = 1e300;
+    int best = 0;
+    bool pays = false;
+    for (const auto &t : tiles) {
+        const auto cost = [&](int cols) {
+            const double wgs = double((T + t.tokens - 1) / t.tokens) * (cols / t.cols);
+            return t.fixed + double(int64_t((wgs + 255) / 256)) * share * t.per_group * (1 + t.load * (wgs < 256 ? wgs / 256 : 1.0));
+        };
+        pays = pays || cost(set_cols) < limit;
+        if (cost(NC) < best_cost) {
+            best_cost = cost(NC);
+            best = t.cols * 100 + t.tokens;
+        }
+    }
+    return pays ? best : 0;
 }
 
 hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
@@ -978,6 +1174,12 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
     const uint16_t *A = static_cast<const uint16_t *>(a.src);
     uint16_t *C = static_cast<uint16_t *>(a.dst);
     const int T = int(a.T);
+    switch (pick_small(a.T, NC, KD, a_cols, c_cols)) {
+    case 3232: return launch_mm_small<1, 1, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+    case 6432: return launch_mm_small<2, 1, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+    case 6464: return launch_mm_small<2, 2, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+    case 12864: return launch_mm_small<4, 2, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+    }
     const int64_t tiles160 = ((a.T + 159) / 160) * ((NC + 255) / 256);
     if (NC % 256 == 0) {
         // more tiles than CUs: one workgroup per CU walks its tiles with the pipeline kept running
