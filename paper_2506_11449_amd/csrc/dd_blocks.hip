@@ -19,6 +19,7 @@
 // Which blocks are crossed is worked out by every workgroup from the offsets (a bitmap of the D candidates in LDS).
 #include "dd_common.h"
 #include "dd_launch.h"
+#include "dd_blocks.h"
 #include "dd_ring.h"
 
 namespace dd {
@@ -37,7 +38,6 @@ constexpr int kBlkSteps = kBlkSlice / 16;
 constexpr int kBlkRing = 3;            // LDS stages: one being multiplied, two on their way
 constexpr int kBlkAhead = kBlkRing - 1;
 constexpr int kBlkWBytes = kBlkFA * kBlkSteps * 1024;   // operand blocks of one slice
-constexpr int kBlkMaxD = 8192;
 constexpr int kBlkMaxSlices = kBlkMaxD / kBlkSlice;
 
 __device__ __align__(16) const unsigned int blk_zero_piece[4] = {0u, 0u, 0u, 0u};
@@ -62,24 +62,6 @@ struct BlkTile {
 // 64-byte rows, four to a 256-byte line of LDS banks: the 16-byte pieces of row r are permuted by XOR with
 // (r / 4) mod 4, so that 16 consecutive rows asked for the same piece fall on 16 different bank groups
 __device__ __forceinline__ int blk_swizzle_key(int row) { return (row >> 2) & 3; }
-
-// Is any of the 47 offsets lo, lo+1, ..., lo+46 (mod D) active?  bits: one bit per candidate, D a multiple of 128.
-__device__ __forceinline__ bool blk_crossed(const unsigned *bits, int D, int lo)
-{
-    lo = lo % D;
-    if (lo < 0) lo += D;
-    const int words = D >> 5;
-    int w = lo >> 5;
-    const int s = lo & 31;
-    const unsigned w0 = bits[w];
-    w = w + 1 == words ? 0 : w + 1;
-    const unsigned w1 = bits[w];
-    w = w + 1 == words ? 0 : w + 1;
-    const unsigned w2 = bits[w];
-    unsigned long long window = (((unsigned long long)w1 << 32) | w0) >> s;  // 64 - s >= 33 bits
-    if (s) window |= (unsigned long long)w2 << (64 - s);
-    return (window & ((1ull << 47) - 1)) != 0;
-}
 
 // C [T x NC] = A [T x KD] . W, W fragment-major; long_cols: the output columns are the long side of the layer
 // (masked gather), else the short side (gather).
@@ -132,8 +114,7 @@ __global__ __launch_bounds__(64 * NW, 3) void mm_blocks_kernel(int T, int NC, in
 #pragma unroll
                     for (int ks = 0; ks < kBlkSteps; ++ks) {
                         const int j0 = tn * kBlkBN + a * 32, i0 = g * kBlkSlice + ks * 16;
-                        const int lo = long_cols ? j0 - i0 - 15 : i0 - j0 - 31;
-                        if (blk_crossed(bits, D, lo)) mask |= 1u << (a * kBlkSteps + ks);
+                        if (blk_crossed(bits, D, blk_first_offset(j0, i0, long_cols))) mask |= 1u << (a * kBlkSteps + ks);
                     }
             }
             const unsigned long long any = __ballot(mask != 0);
@@ -288,6 +269,7 @@ static hipError_t launch_blocks(const ProductArgs &a, hipStream_t stream)
 hipError_t launch_product_blocks(const ProductArgs &a, hipStream_t stream)
 {
     if (a.src_sets != 1 || a.dst_sets != 1 || !a.prepared || !a.offsets) return hipErrorInvalidValue;
+    if (product_blocks_small(a)) return launch_product_blocks_small(a, stream);
     return launch_blocks<1, 4>(a, stream);
 }
 

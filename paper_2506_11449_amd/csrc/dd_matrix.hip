@@ -22,6 +22,7 @@
 //   with four consecutive output columns of one token, so the tile is transposed back through
 //   LDS once and stored with full-width row segments.
 #include "dd_common.h"
+#include "dd_blocks.h"
 #include "dd_launch.h"
 #include "dd_select_block.h"
 
@@ -824,6 +825,8 @@ __global__ __launch_bounds__(64 * NW) void mm_persistent_kernel(int T, int NC, i
 // piece of LDS private to the wave -- requested fragment by fragment every instruction would touch 32 lines.
 // The tiles are numbered token blocks innermost, one contiguous run per XCD: what the workgroups of a column tile share
 // is the operand, the larger input here.
+// BLOCKS: only the 32 x 16 blocks of the operand that a diagonal crosses are fetched and multiplied, and only the groups
+// that hold one are visited (dd_blocks.hip does the same for many tokens); the waves share the groups that are left.
 // ---------------------------------------------------------------------------------------------
 template <int FA, int FB, int KS>
 struct MmSmallTile {
@@ -832,10 +835,16 @@ struct MmSmallTile {
     static constexpr int LDS_BYTES = KS * BM * (STRIDE * 4 > kRowBytes ? STRIDE * 4 : kRowBytes);
 };
 
-template <int FA, int FB, int KS>
+struct BlockArgs {
+    const int *offsets;
+    int D, K;
+    bool long_cols;  // the output columns are the long side
+};
+
+template <int FA, int FB, int KS, bool BLOCKS>
 __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_cols, int c_cols, int tiles_m, int tiles_n,
                                                            const uint16_t *__restrict__ A,
-                                                           const uint16_t *__restrict__ Wf, uint16_t *__restrict__ C)
+                                                           const uint16_t *__restrict__ Wf, uint16_t *__restrict__ C, BlockArgs blocks)
 {
     using Tl = MmSmallTile<FA, FB, KS>;
     constexpr int BM = Tl::BM, BN = Tl::BN;
@@ -848,7 +857,39 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     const int groups = KD / 64;
-    const int g_begin = groups * wave / KS, g_end = groups * (wave + 1) / KS;
+    int n_groups = groups;
+    __shared__ unsigned bits[BLOCKS ? kBlkMaxD / 32 : 1], list[BLOCKS ? kBlkMaxD / 64 : 1], n_listed;
+    if constexpr (BLOCKS) {
+        for (int i = tid; i < blocks.D / 32; i += 64 * KS) bits[i] = 0u;
+        __syncthreads();
+        for (int k = tid; k < blocks.K; k += 64 * KS) {
+            const int o = canonical_offset(blocks.offsets[k], blocks.D);
+            atomicOr(&bits[o >> 5], 1u << (o & 31));
+        }
+        __syncthreads();
+        if (wave == 0) {  // list the groups that hold a crossed block, in order, with the blocks (a, k-step) that are
+            unsigned base = 0;
+            for (int g0 = 0; g0 < groups; g0 += 64) {
+                const int g = g0 + lane;
+                unsigned mask = 0;
+                if (g < groups)
+#pragma unroll
+                    for (int a = 0; a < FA; ++a)
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks)
+                            if (blk_crossed(bits, blocks.D, blk_first_offset(tn * BN + a * 32, g * 64 + ks * 16, blocks.long_cols)))
+                                mask |= 1u << (a * 4 + ks);
+                const unsigned long long any = __ballot(mask != 0);
+                const int rank = __builtin_amdgcn_mbcnt_hi(unsigned(any >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(any), 0u));
+                if (mask) list[base + rank] = unsigned(g) | (mask << 16);
+                base += unsigned(__popcll(any));
+            }
+            if (lane == 0) n_listed = base;
+        }
+        __syncthreads();
+        n_groups = __builtin_amdgcn_readfirstlane(int(n_listed));
+    }
+    const int g_begin = n_groups * wave / KS, g_end = n_groups * (wave + 1) / KS;
 
     // token rows: request j of block b is rows b*32 + 8j ... + 7, lane = (row, 16-byte chunk); byte offsets in one matrix
     unsigned x_row[FB][4];
@@ -863,9 +904,10 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
         x_frag[j] = l32 * kRowBytes + swizzle(l32, 2 * j + half) * 16;  // k-step j
     }
     unsigned char *x_buf = smem + wave * (FB * 32 * kRowBytes);
-    const uint16_t *w_src = Wf + (size_t(tn * FA) * (KD / 16) + size_t(g_begin) * 4) * 512;
+    const uint16_t *w_first = Wf + size_t(tn * FA) * (KD / 16) * 512, *w_src = w_first + size_t(g_begin) * 4 * 512;
     const size_t w_row = size_t(KD / 16) * 512;  // from one 32-column block to the next
     // the cursor of the token rows inside the stack of matrices
+    // (BLOCKS: one matrix, and the listed group says where)
     int x_in = g_begin * 64 % a_cols;
     const uint16_t *x_src = A + size_t(g_begin * 64 / a_cols) * T * a_cols + x_in;
     const size_t x_jump = size_t(T - 1) * a_cols;
@@ -880,6 +922,14 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
 
     bf16x8 w0[4][FA], w1[4][FA];
     u32x4 x0[FB][4], x1[FB][4];
+    unsigned m0 = 0xffffu, m1 = 0xffffu;  // the blocks of the two groups that count
+#define DD_SMALL_MASK(m_, n_) /* before the two loads of listed group n_ */                             \
+    if constexpr (BLOCKS) {                                                                             \
+        const unsigned entry = unsigned(__builtin_amdgcn_readfirstlane(int(list[n_])));                 \
+        m_ = entry >> 16;                                                                               \
+        x_src = A + size_t(entry & 0xffffu) * 64;                                                       \
+        w_src = w_first + size_t(entry & 0xffffu) * 4 * 512;                                            \
+    }
 #define DD_SMALL_LOAD_X(x_)                                                                             \
     {                                                                                                   \
         _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
@@ -892,48 +942,58 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
             x_src += x_jump;                                                                            \
         }                                                                                               \
     }
-#define DD_SMALL_LOAD_W(w_)                                                                             \
+#define DD_SMALL_LOAD_W(w_, m_)                                                                         \
     {                                                                                                   \
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
             _Pragma("unroll") for (int a = 0; a < FA; ++a)                                              \
-                w_[ks][a] = *reinterpret_cast<const bf16x8 *>(w_src + a * w_row + ks * 512 + lane * 8); \
+                if (!BLOCKS || (m_ >> (a * 4 + ks) & 1u))                                               \
+                    w_[ks][a] = *reinterpret_cast<const bf16x8 *>(w_src + a * w_row + ks * 512 + lane * 8); \
         w_src += 4 * 512;                                                                               \
     }
     // a wave's LDS accesses are served in order: the rows are read as fragments behind their own writes and before the
     // writes of the next group
-#define DD_SMALL_GROUP(w_, x_, more_)                                                                   \
+#define DD_SMALL_GROUP(w_, x_, m_, next_)                                                               \
     {                                                                                                   \
+        const unsigned now = m_;                                                                        \
         _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
             _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
                 *reinterpret_cast<u32x4 *>(x_buf + b * 32 * kRowBytes + x_dst[j]) = x_[b][j];           \
-        if (more_) DD_SMALL_LOAD_X(x_)                                                                  \
+        if ((next_) < g_end) {                                                                          \
+            DD_SMALL_MASK(m_, next_)                                                                    \
+            DD_SMALL_LOAD_X(x_)                                                                         \
+        }                                                                                               \
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                              \
             bf16x8 xf[FB];                                                                              \
             _Pragma("unroll") for (int b = 0; b < FB; ++b)                                              \
                 xf[b] = *reinterpret_cast<const bf16x8 *>(x_buf + b * 32 * kRowBytes + x_frag[ks]);     \
             _Pragma("unroll") for (int a = 0; a < FA; ++a)                                              \
-                _Pragma("unroll") for (int b = 0; b < FB; ++b)                                          \
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_[ks][a], xf[b], acc[a][b], 0, 0, 0); \
+                if (!BLOCKS || (now >> (a * 4 + ks) & 1u)) {                                            \
+                    _Pragma("unroll") for (int b = 0; b < FB; ++b)                                      \
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_[ks][a], xf[b], acc[a][b], 0, 0, 0); \
+                }                                                                                       \
         }                                                                                               \
-        if (more_) DD_SMALL_LOAD_W(w_)                                                                  \
+        if ((next_) < g_end) DD_SMALL_LOAD_W(w_, m_)                                                    \
     }
     int g = g_begin;
     if (g < g_end) {
+        DD_SMALL_MASK(m0, g)
         DD_SMALL_LOAD_X(x0)
-        DD_SMALL_LOAD_W(w0)
+        DD_SMALL_LOAD_W(w0, m0)
     }
     if (g + 1 < g_end) {
+        DD_SMALL_MASK(m1, g + 1)
         DD_SMALL_LOAD_X(x1)
-        DD_SMALL_LOAD_W(w1)
+        DD_SMALL_LOAD_W(w1, m1)
     }
     for (; g + 1 < g_end; g += 2) {
-        DD_SMALL_GROUP(w0, x0, g + 2 < g_end)
-        DD_SMALL_GROUP(w1, x1, g + 3 < g_end)
+        DD_SMALL_GROUP(w0, x0, m0, g + 2)
+        DD_SMALL_GROUP(w1, x1, m1, g + 3)
     }
-    if (g < g_end) DD_SMALL_GROUP(w0, x0, false)
+    if (g < g_end) DD_SMALL_GROUP(w0, x0, m0, g_end)
 #undef DD_SMALL_GROUP
 #undef DD_SMALL_LOAD_W
 #undef DD_SMALL_LOAD_X
+#undef DD_SMALL_MASK
     __syncthreads();  // the sums take the place of the rows
 
     // Accumulator i of lane l is output column 8*(i/4) + 4*(l/32) + i%4 of token l%32 inside its 32x32 tile.
@@ -1086,17 +1146,17 @@ static hipError_t launch_mm_persistent(int T, int NC, int KD, int a_cols, int c_
     return hipGetLastError();
 }
 
-template <int FA, int FB, int KS>
+template <int FA, int FB, int KS, bool BLOCKS = false>
 static hipError_t launch_mm_small(int T, int NC, int KD, int a_cols, int c_cols, const uint16_t *A, const uint16_t *Wf,
-                                  uint16_t *C, hipStream_t stream)
+                                  uint16_t *C, hipStream_t stream, BlockArgs blocks = {})
 {
     using Tl = MmSmallTile<FA, FB, KS>;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_small_kernel<FA, FB, KS>), Tl::LDS_BYTES, lds_allowed)) return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_small_kernel<FA, FB, KS, BLOCKS>), Tl::LDS_BYTES, lds_allowed)) return e;
     const int tiles_m = (T + Tl::BM - 1) / Tl::BM, tiles_n = NC / Tl::BN;
     const int per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL((mm_small_kernel<FA, FB, KS>), dim3(per_xcd * kXcds), dim3(64 * KS), Tl::LDS_BYTES, stream, T, KD,
-                       a_cols, c_cols, tiles_m, tiles_n, A, Wf, C);
+    hipLaunchKernelGGL((mm_small_kernel<FA, FB, KS, BLOCKS>), dim3(per_xcd * kXcds), dim3(64 * KS), Tl::LDS_BYTES, stream, T, KD,
+                       a_cols, c_cols, tiles_m, tiles_n, A, Wf, C, blocks);
     return hipGetLastError();
 }
 
@@ -1193,6 +1253,27 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
         }
     }
     return launch_mm<128, 128, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+}
+
+// Few tokens, as the number of 64 x 64 (and of 32 x 32) result tiles has it.  Up to 512 of them the chip holds all tiles at
+// once, two per CU, while the 128 x 128 tiles of dd_blocks.hip leave most CUs idle; measured over 512 ... 4096 features, one
+// and five runs, 10 and 40 % of the diagonals: 768^2 at 400 tokens 8.4-15.1 -> 5.1-6.6 us, 3072 -> 768 at 800 tokens 13.8-35
+// -> 6.9-11.6 us, 4096^2 at 197 tokens 16-44 -> 7.3-12.6 us; equal at about 700 tiles, behind from 900 on.
+static int64_t block_tiles(const ProductArgs &a, int tile) { return (a.T + tile - 1) / tile * ((a.masked ? a.D : a.L) / tile); }
+
+bool product_blocks_small(const ProductArgs &a)
+{
+    return block_tiles(a, 64) <= 512 && a.T * (a.masked ? a.L : a.D) * 2 < (int64_t(1) << 32);
+}
+
+hipError_t launch_product_blocks_small(const ProductArgs &a, hipStream_t stream)
+{
+    const int NC = a.masked ? a.D : a.L, KD = a.masked ? a.L : a.D, T = int(a.T);
+    const uint16_t *A = static_cast<const uint16_t *>(a.src), *Wf = static_cast<const uint16_t *>(a.ws);
+    uint16_t *C = static_cast<uint16_t *>(a.dst);
+    const BlockArgs b = {a.offsets, a.D, a.K, a.masked};
+    if (block_tiles(a, 32) <= 512) return launch_mm_small<1, 1, 4, true>(T, NC, KD, KD, NC, A, Wf, C, stream, b);
+    return launch_mm_small<2, 2, 4, true>(T, NC, KD, KD, NC, A, Wf, C, stream, b);
 }
 
 }  // namespace dd

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2506_11449_amd as dd
+from paper_2506_11449_amd import synth
 from oracle import dd_oracle as orc
 from tests.parity_util import TOL, random_case, rel_err, to_dev, to_host
 
@@ -42,3 +43,28 @@ def test_groups_of_layers_with_few_tokens(M, N, K, S, T):
     for s, (o, v, _, _) in enumerate(cases):
         assert rel_err(Y[s], orc.fwd(X, o, v, N)) <= TOL["bf16"]
     assert rel_err(dX, sum(orc.bwd_input(c[3], c[0], c[1], M) for c in cases)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("M,N,K,runs,T", [(128, 128, 1, 1, 1), (128, 384, 40, 2, 33), (384, 128, 60, 1, 200), (768, 768, 77, 1, 400),
+                                          (768, 768, 300, 5, 1279), (4096, 128, 400, 3, 65), (128, 8192, 900, 8, 130),
+                                          (2304, 640, 1, 1, 257)])
+def test_block_skipping_with_few_tokens(M, N, K, runs, T):
+    offsets, values, X, dY = random_case(M, N, K, T, "bf16", seed=M + N + K,
+                                         offsets=synth.draw_offsets_clustered(max(M, N), K, runs, seed=K))
+    off, V, x, dy = torch.from_numpy(offsets).cuda(), to_dev(values, "bf16"), to_dev(X, "bf16"), to_dev(dY, "bf16")
+    prepared = dd.dd_prepare(off, V, M, N)
+    Y = to_host(dd.dd_fwd(x, off, None, N, prepared=prepared, algo=dd.DD_ALGO_BLOCKS))
+    dX = to_host(dd.dd_bwd_input(dy, off, None, M, prepared=prepared, algo=dd.DD_ALGO_BLOCKS))
+    assert rel_err(Y, orc.fwd(X, offsets, values, N)) <= TOL["bf16"]
+    assert rel_err(dX, orc.bwd_input(dY, offsets, values, M)) <= TOL["bf16"]
+    # blocks that no diagonal crosses are not multiplied, so what stands in their rows does not matter
+    x[0, 0] = float("inf")
+    crossed = np.zeros((M, N), dtype=bool)
+    p = np.arange(min(M, N))
+    for o in offsets:
+        q = (p + o) % max(M, N)
+        rows, cols = (p, q) if M <= N else (q, p)
+        crossed[rows, cols] = True
+    touched = np.repeat(crossed[:16].reshape(16, N // 32, 32).any(axis=(0, 2)), 32)  # 32-column blocks of contraction indices 0-15
+    Y = to_host(dd.dd_fwd(x, off, None, N, prepared=prepared, algo=dd.DD_ALGO_BLOCKS))
+    assert np.isfinite(Y[0][~touched]).all() and np.isfinite(Y[1:]).all()
