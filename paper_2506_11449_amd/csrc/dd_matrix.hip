@@ -1181,36 +1181,30 @@ static int pick_tile(int64_t T, int NC)
 
 // Few tokens: which tile of mm_small_kernel, if any (columns * 100 + tokens, 0: the kernels of 256 columns).  Times in us
 // fitted to T = 1 ... 6304 over 128^2 ... 4096^2 (kernel alone): a workgroup's fixed part and its time per 64 contraction
-// indices and wave, which grows as the chip fills; against the 64-token tile, the cheapest of the others, which walks the
-// whole contraction in one chain.  768 -> 3072 (3072 -> 768) at 197 tokens 7.8 -> 5.4 us (21.1 -> 5.8), 768^2 at 1279
-// tokens 7.9 -> 5.7, 4096^2 at 197 tokens 30.5 -> 16; the lines cross at 1300-2000 tokens for 768^2, at 400-800 for 3072
-// and more columns.
-// A group of layers takes these tiles where one of its layers by itself would (set_cols columns), so that a layer's result
-// has the same bits either way: its contraction is cut into the same four parts.
-static int pick_small(int64_t T, int NC, int KD, int a_cols, int set_cols)
+// indices and wave, which grows as the chip fills, and by what the workgroups of a CU take from each other beyond that;
+// against the 64-token tile, the cheapest of the others, which walks the whole contraction in one chain.  768 -> 3072
+// (3072 -> 768) at 197 tokens 7.8 -> 5.4 us (21.1 -> 5.8), 768^2 at 1279 tokens 7.9 -> 5.7, 4096^2 at 197 tokens 30.5 -> 16;
+// the lines cross at about 1500 tokens for 768^2, at 400-800 for 3072 and more columns.
+static int pick_small(int64_t T, int NC, int KD, int a_cols)
 {
     if (T * a_cols * 2 >= (int64_t(1) << 32)) return 0;  // 32-bit offsets into a matrix of token rows
     static const struct {
         int cols, tokens;
-        double fixed, per_group, load;
-    } tiles[] = {{32, 32, 2.8, 0.233, 0.4}, {64, 32, 3.25, 0.317, 0.3}, {64, 64, 3.65, 0.52, 0.85}, {128, 64, 4.7, 0.97, 0.45}};
+        double fixed, per_group, load, crowded;
+    } tiles[] = {{32, 32, 2.8, 0.233, 0.4, 0.35}, {64, 32, 3.25, 0.317, 0.45, 0.62}, {64, 64, 3.65, 0.52, 0.85, 1.0}, {128, 64, 5.4, 1.12, 0.5, 1.8}};
     const double groups = KD / 64, share = groups > 4 ? groups / 4 : 1;
-    const double limit = 0.9 * (3.0 + groups * (0.40 + 0.012 * (set_cols < 4096 ? set_cols : 4096) / 256 * (KD < 768 ? KD / 768.0 : 1.0)));
-    double best_cost = 1e300;
+    double best_cost = 0.9 * (3.0 + groups * (0.40 + 0.012 * (NC < 4096 ? NC : 4096) / 256 * (KD < 768 ? KD / 768.0 : 1.0)));
     int best = 0;
-    bool pays = false;
     for (const auto &t : tiles) {
-        const auto cost = [&](int cols) {
-            const double wgs = double((T + t.tokens - 1) / t.tokens) * (cols / t.cols);
-            return t.fixed + double(int64_t((wgs + 255) / 256)) * share * t.per_group * (1 + t.load * (wgs < 256 ? wgs / 256 : 1.0));
-        };
-        pays = pays || cost(set_cols) < limit;
-        if (cost(NC) < best_cost) {
-            best_cost = cost(NC);
+        const double per_cu = double((T + t.tokens - 1) / t.tokens) * (NC / t.cols) / 256;
+        const double group = per_cu <= 1 ? t.per_group * (1 + t.load * per_cu) : t.crowded * 0.5 * (per_cu + double(int64_t(per_cu + 0.999)));
+        const double cost = t.fixed + share * group;
+        if (cost < best_cost) {
+            best_cost = cost;
             best = t.cols * 100 + t.tokens;
         }
     }
-    return pays ? best : 0;
+    return best;
 }
 
 hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
@@ -1234,7 +1228,7 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
     const uint16_t *A = static_cast<const uint16_t *>(a.src);
     uint16_t *C = static_cast<uint16_t *>(a.dst);
     const int T = int(a.T);
-    switch (pick_small(a.T, NC, KD, a_cols, c_cols)) {
+    switch (pick_small(a.T, NC, KD, a_cols)) {
     case 3232: return launch_mm_small<1, 1, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
     case 6432: return launch_mm_small<2, 1, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
     case 6464: return launch_mm_small<2, 2, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
