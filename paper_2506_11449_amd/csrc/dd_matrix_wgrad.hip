@@ -105,11 +105,20 @@ __global__ __launch_bounds__(kWgT, kWgPerCu) void wgrad_mm_kernel(int T, int D, 
     // column tile of the long-side matrix (the bulk of the bytes) are neighbours, and only the short-side
     // matrix is fetched once per half (measured on 768 <-> 3072 at 50432 tokens: 476 MB from memory per launch
     // against 684 MB with the long side first; 388 MB is each byte once).
+    // Fewer chunks than XCDs: the tiles of all chunks in order, one contiguous run per XCD.
     const int tiles = tiles_p * tiles_q;
     const int xcd = blockIdx.x % kWgXcds, local = blockIdx.x / kWgXcds;
-    const int split = (local / tiles) * kWgXcds + xcd;
-    if (split >= splits) return;
-    const int tile = local % tiles;
+    int split, tile;
+    if (splits >= kWgXcds) {
+        split = (local / tiles) * kWgXcds + xcd;
+        if (split >= splits) return;
+        tile = local % tiles;
+    } else {
+        const int run = (tiles * splits + kWgXcds - 1) / kWgXcds, lin = xcd * run + local;
+        if (lin >= tiles * splits) return;
+        split = lin / tiles;
+        tile = lin - split * tiles;
+    }
     // The two workgroups of a CU (an XCD's workgroup i and i + 32) take turns at the higher wave priority, k-step by
     // k-step.  Left alone the one dispatched first stays ahead and the two halves of the XCD drift apart by more
     // tokens than the L2 holds, so that what they share is fetched twice (768 <-> 3072 at 50432 tokens: 476 MB per
@@ -537,13 +546,30 @@ __global__ __launch_bounds__(1024) void wgrad_dalpha_kernel(int D, int K, int pe
 struct WgradPlan {
     int tp, tq;            // tile
     int tiles_p, tiles_q;
-    int splits;            // token chunks (a multiple of the XCD count unless T is tiny)
+    int splits;            // token chunks
+    int most;              // the most chunks a call of this size may take: what the scratch is sized for
     int slices;            // T in units of 32 tokens
     int skew;              // slices moved from each chunk of the second half of the workgroups to one of the first
     int grid;
 };
 
-static WgradPlan plan_wgrad(int64_t T, int D, int L)
+// Chunks of tokens, by the time they should take in us: a workgroup's k-steps of sixteen tokens (0.18-0.245 alone on its CU,
+// 0.45 with a second one beside it), its epilogue, which follows the share of the diagonals that are kept, and the partial
+// sums on their way out and back in.  Measured over 256^2 ... 4096^2, 64-25216 tokens, 10 and 40 % of the diagonals
+// (gradient and sum, graph replay), against two workgroups per CU whatever the size: 768^2 at 1279 tokens 16.1-27.6 ->
+// 13.3-21 us, 4096 -> 2560 at 788 tokens 54-99 -> 32-53 us, 4096^2 at 1279 tokens 88-172 -> 51-81 us, 1024 -> 4096 at 25216
+// tokens 178-205 -> 173-187 us; 768^2 at 12608 tokens and 768 -> 3072 from 12608 on stay within 2 %.
+static double wgrad_cost(int64_t slices, int tiles, int chunks, double tile_share, int D, int L, int K)
+{
+    const double wgs = double(tiles) * chunks, steps = double((slices + chunks - 1) / chunks) * (kSliceTokens / kTS);
+    const bool paired = wgs > 256;
+    const double rounds = wgs <= 512 ? 1.0 : wgs / 512 + 0.25;
+    const double step = tile_share * (paired ? 0.45 : 0.18 + 0.065 * wgs / 256);
+    const double epilogue = (3.0 + 16.0 * K / D) * (paired ? 1.5 : 1.0);
+    return rounds * (steps * step + epilogue) + 8.0 * chunks * K * L / 3.3e6;
+}
+
+static WgradPlan plan_wgrad(int64_t T, int D, int L, int K)
 {
     WgradPlan pl;
     // 192 x 192 tiles keep the four waves square (96 x 96) and divide the ViT-Base widths; otherwise 128 x 256,
@@ -554,16 +580,26 @@ static WgradPlan plan_wgrad(int64_t T, int D, int L)
     pl.tiles_p = L / pl.tp;
     pl.tiles_q = D / pl.tq;
     const int tiles = pl.tiles_p * pl.tiles_q;
-    // chunks per XCD: as many as fill its 32 CUs in one round
+    // at most as many chunks per XCD as fill its 32 CUs with two workgroups each; fewer than one per XCD, or whole XCDs' worth
     int per_xcd = kCusPerXcd * kWgPerCu / tiles;
     if (per_xcd < 1) per_xcd = 1;
-    int64_t splits = int64_t(per_xcd) * kWgXcds;
+    int64_t most = int64_t(per_xcd) * kWgXcds;
     const int64_t slices = (T + kSliceTokens - 1) / kSliceTokens;
-    if (splits > slices) splits = slices;
+    if (most > slices) most = slices;
     pl.slices = int(slices);
-    pl.splits = int(splits);
-    const int rounds = (pl.splits + kWgXcds - 1) / kWgXcds;
-    pl.grid = rounds * tiles * kWgXcds;
+    pl.most = int(most);
+    pl.splits = pl.most;
+    const double tile_share = double(pl.tp) * pl.tq / (192 * 192);
+    double best_cost = wgrad_cost(slices, tiles, pl.most, tile_share, D, L, K);
+    for (int chunks = 1; chunks < pl.most; chunks += chunks < kWgXcds ? 1 : kWgXcds) {
+        const double cost = wgrad_cost(slices, tiles, chunks, tile_share, D, L, K);
+        if (cost < 0.97 * best_cost) {
+            best_cost = cost;
+            pl.splits = chunks;
+        }
+    }
+    pl.grid = pl.splits >= kWgXcds ? (pl.splits + kWgXcds - 1) / kWgXcds * tiles * kWgXcds
+                                   : (tiles * pl.splits + kWgXcds - 1) / kWgXcds * kWgXcds;
     // When the grid is exactly the two workgroups per CU that fit, the second 256 get their first tokens about
     // 1.5 us after the first 256 (the burst of first requests is served in order) and would finish their main
     // loops as much later, alone on their CUs next to the first ones' epilogues.  Giving them two slices (four
@@ -571,8 +607,7 @@ static WgradPlan plan_wgrad(int64_t T, int D, int L)
     // layer: between 0.2 and 0.7 us of 22, box by box).  The split is a fixed function of the shape, so results stay reproducible.
     // (Workgroup b works on chunk (b / 8 / tiles) * 8 + b % 8: with an even number of chunks per XCD the first 256
     // workgroups are exactly the first half of the chunks.)
-    pl.skew = (pl.grid == 256 * kWgPerCu && per_xcd % 2 == 0 && splits == int64_t(per_xcd) * kWgXcds &&
-               slices / splits >= 8) ? 2 : 0;
+    pl.skew = (pl.grid == 256 * kWgPerCu && pl.splits % (2 * kWgXcds) == 0 && slices / pl.splits >= 8) ? 2 : 0;
     return pl;
 }
 
@@ -584,8 +619,8 @@ bool weight_grad_matrix_supported(int64_t T, int D, int L, bool bf16)
 
 size_t weight_grad_matrix_ws_bytes(int64_t T, int D, int L, int K)
 {
-    const WgradPlan pl = plan_wgrad(T, D, L);
-    return size_t(pl.splits) * K * L * sizeof(float);
+    const WgradPlan pl = plan_wgrad(T, D, L, K);
+    return size_t(pl.most) * K * L * sizeof(float);
 }
 
 template <int TP, int TQ>
@@ -610,7 +645,7 @@ static hipError_t launch_wgrad_mm_any(const WeightGradArgs &a, const WgradPlan &
 
 hipError_t launch_weight_grad_matrix(const WeightGradArgs &a, hipStream_t stream)
 {
-    const WgradPlan pl = plan_wgrad(a.T, a.D, a.L);
+    const WgradPlan pl = plan_wgrad(a.T, a.D, a.L, a.K);
     float *partial = static_cast<float *>(a.ws);
     if (hipError_t e = launch_wgrad_mm_any(a, pl, partial, stream)) return e;
     hipLaunchKernelGGL(wgrad_reduce_kernel<false>, dim3((a.L + 255) / 256, a.K), dim3(256), 0, stream, a.D, a.L, a.K,
@@ -628,7 +663,7 @@ size_t weight_grad_scaled_tail_bytes(int L, int K)
 hipError_t launch_weight_grad_matrix_scaled(const WeightGradArgs &a, const float *alpha, const void *V, float *dalpha,
                                             void *tail, hipStream_t stream)
 {
-    const WgradPlan pl = plan_wgrad(a.T, a.D, a.L);
+    const WgradPlan pl = plan_wgrad(a.T, a.D, a.L, a.K);
     float *partial = static_cast<float *>(a.ws);
     float *dots = static_cast<float *>(tail);
     const int per_k = (a.L + 255) / 256;
