@@ -16,14 +16,8 @@ struct F32 {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(uint32_t(b) << 16); }
 
-// Round to nearest even; NaN stays NaN (quiet).
-__device__ __forceinline__ uint16_t f32_to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return uint16_t(u >> 16);
-}
+// Round to nearest even, the hardware's conversion; NaN stays NaN (quiet).
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f)); }
 
 struct BF16 {
     using storage = uint16_t;
@@ -31,10 +25,11 @@ struct BF16 {
     static __device__ __forceinline__ void store(storage *p, float v) { *p = f32_to_bf16(v); }
 };
 
-// off mod D into [0, D) for any int32 off.
+// off mod D into [0, D) for any int32 off.  (The division, some thirty instructions, is for offsets outside the range.)
 __device__ __forceinline__ int canonical_offset(int off, int D)
 {
-    int r = off % D;
+    if (unsigned(off) < unsigned(D)) return off;
+    const int r = off % D;
     return r < 0 ? r + D : r;
 }
 

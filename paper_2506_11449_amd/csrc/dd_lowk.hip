@@ -81,9 +81,12 @@ static LkPlan plan_lowk(int D, int dst_cols, int K)
     return pl;
 }
 
+// (one conversion instruction for the pair; rounded by hand, a pair cost fourteen)
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 {
-    return uint32_t(f32_to_bf16(a)) | (uint32_t(f32_to_bf16(b)) << 16);
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
 // gather (MASKED = false):  dst[t, p] = sum_k src[t, (p + o_k) mod D] * v_k[p]            src [T x D], dst [T x L]
