@@ -1183,7 +1183,8 @@ static int pick_tile(int64_t T, int NC)
 // fitted to T = 1 ... 6304 over 128^2 ... 4096^2 (kernel alone): a workgroup's fixed part and its time per 64 contraction
 // indices and wave, which grows as the chip fills, and by what the workgroups of a CU take from each other beyond that;
 // against the 64-token tile, the cheapest of the others, which walks the whole contraction in one chain.  768 -> 3072
-// (3072 -> 768) at 197 tokens 7.8 -> 5.4 us (21.1 -> 5.8), 768^2 at 1279 tokens 7.9 -> 5.7, 4096^2 at 197 tokens 30.5 -> 16;
+// (3072 -> 768) at 197 tokens 7.8 -> 5.4 us (21.1 -> 5.8), 1024^2 at 197 and 800 tokens 9.2 -> 3.8 and 9.5 -> 6.2, 768^2
+// at 1279 tokens 7.9 -> 5.7, 4096^2 at 197 tokens 30.5 -> 16;
 // the lines cross at about 1500 tokens for 768^2, at 400-800 for 3072 and more columns.
 static int pick_small(int64_t T, int NC, int KD, int a_cols)
 {
