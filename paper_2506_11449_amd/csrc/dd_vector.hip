@@ -450,6 +450,7 @@ constexpr int kWgTokensPerSplit = 1024;
 constexpr int kWgMaxSplits = 64;
 constexpr int kWgMaxWaves = 16;
 constexpr int kWgXcds = 8;
+constexpr int kWgCus = 256;
 
 static int weight_grad_splits(int64_t T)
 {
@@ -662,14 +663,25 @@ struct WgTiledPlan {
     size_t lds;
 };
 
+// The most chunks a plan may take: what the scratch is sized for.  Never fewer for more tokens, so that scratch sized for
+// the largest batch serves every smaller one, whatever their plans; never fewer than the untiled kernel makes; and no more
+// than 16 MiB of partial sums unless that kernel needs more (768 x 768, 77 diagonals: 15.1 MB from 256 tokens on).
+static int wg_most_chunks(int64_t T, int L, int K, bool bf16)
+{
+    const int64_t one = int64_t(K) * L * int64_t(sizeof(float)), splits = weight_grad_splits(T), group = bf16 ? 8 : 4;
+    int64_t most = (int64_t(16) << 20) / one;
+    if (most > kWgCus) most = kWgCus;
+    if (most > (T + group - 1) / group) most = (T + group - 1) / group;
+    return int(most > splits ? most : splits);
+}
+
 // Block of diagonals, tile and chunks by the time they should take, as in make_tiled_plan.
 static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
 {
     WgTiledPlan best = {};
     const int p_blocks = (L + 63) / 64, group = bf16 ? 8 : 4;
     const size_t one = size_t(K) * L * sizeof(float);
-    size_t budget = one * weight_grad_splits(T);  // partial sums: what the untiled kernel would make, or 16 MiB
-    if (budget < (size_t(16) << 20)) budget = size_t(16) << 20;
+    const int most = wg_most_chunks(T, L, K, bf16);
     double best_cost = 1e300;
     static const int kns[] = {8, 16, 24}, nts[] = {1, 2, 4};
     for (int kn : kns) {
@@ -684,9 +696,9 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
                 const size_t lds = 2 * size_t(cols) * tile_stride(nt);
                 if (lds > kLdsPerCu || nt > (bf16 ? 1 : 2) * waves_k) continue;
                 const int64_t tiles = (T + tt - 1) / tt;
-                int64_t chunks = 256 / per_chunk;  // one workgroup per CU: more cost more staging than they hide
+                int64_t chunks = kWgCus / per_chunk;  // one workgroup per CU: more cost more staging than they hide
                 if (chunks > tiles) chunks = tiles;
-                if (chunks > int64_t(budget / one)) chunks = int64_t(budget / one);
+                if (chunks > most) chunks = most;
                 if (chunks < 1) chunks = 1;
                 // per tile: LDS reads of all waves, or one wave's chain of instructions; the barrier and the next tile
                 const double lds_clk = waves * nt * (kn + 4) * 8, issue = nt * (kn * 16 + 8) * 1.3 * ((waves + 3) / 4);
@@ -723,12 +735,9 @@ static WgTiledPlan plan_wg_tiled(int64_t T, int D, int L, int K, bool bf16)
     return memo.get(T, D, L, K, bf16, [&] { return make_wg_tiled_plan(T, D, L, K, bf16); });
 }
 
-size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16)
+size_t weight_grad_vector_ws_bytes(int64_t T, int L, int K, bool bf16)
 {
-    // never less than the untiled kernel's: what a caller with a fixed amount of scratch may run does not hang on the plan
-    const WgTiledPlan pl = plan_wg_tiled(T, D, L, K, bf16);
-    const int splits = weight_grad_splits(T);
-    return size_t(pl.chunks > splits ? pl.chunks : splits) * size_t(K) * size_t(L) * sizeof(float);
+    return size_t(wg_most_chunks(T, L, K, bf16)) * size_t(K) * size_t(L) * sizeof(float);
 }
 
 template <class S, int NT, int KN>

@@ -1,0 +1,31 @@
+"""Scratch sizes as a caller plans with them (host only): scratch sized for the largest batch serves every smaller one."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_11449_amd as dd
+
+AUTO, VECTOR, MATRIX = dd.DD_ALGO_AUTO, dd.DD_ALGO_VECTOR, dd.DD_ALGO_MATRIX
+BF16, F32 = torch.bfloat16, torch.float32
+
+LAYERS = [(512, 512, 51, BF16, AUTO), (320, 1000, 100, BF16, AUTO), (1000, 320, 100, BF16, VECTOR), (768, 768, 77, F32, AUTO),
+          (300, 200, 20, F32, AUTO), (64, 64, 8, F32, AUTO), (768, 768, 77, BF16, AUTO), (768, 768, 77, BF16, MATRIX),
+          (768, 768, 4, BF16, AUTO), (1024, 4096, 819, BF16, AUTO), (2000, 2000, 2000, F32, AUTO), (1536, 1528, 700, BF16, AUTO),
+          (333, 1001, 700, BF16, AUTO), (24, 10300, 12, F32, AUTO)]
+
+
+@pytest.mark.parametrize("M,N,K,dtype,algo", LAYERS)
+@pytest.mark.parametrize("op", [dd.DD_OP_FWD, dd.DD_OP_BWD_INPUT, dd.DD_OP_BWD_WEIGHT, dd.DD_OP_BWD, dd.DD_OP_BWD_WEIGHT_SCALED])
+def test_more_tokens_never_need_less(op, M, N, K, dtype, algo):
+    tokens = sorted(set(range(1, 1500)) | {int(t) for t in np.geomspace(1500, 300000, 800)})
+    sizes = [dd.dd_workspace_bytes(op, dd.make_layer(T, M, N, K, dtype, algo)) for T in tokens]
+    drops = [(a, b) for a, b, x, y in zip(tokens, tokens[1:], sizes, sizes[1:]) if y < x]
+    assert drops == []
+
+
+@pytest.mark.parametrize("M,N,K,dtype", [(97, 1001, 300, BF16), (96, 1000, 300, BF16), (700, 700, 700, F32), (3001, 900, 1500, BF16)])
+def test_vector_scratch_stays_within_sixteen_megabytes_or_one_chunk_per_thousand_tokens(M, N, K, dtype):
+    one = 4 * K * min(M, N)
+    for T in (1, 7, 64, 500, 1024, 1025, 5000, 65536, 200000):
+        need = dd.dd_workspace_bytes(dd.DD_OP_BWD_WEIGHT, dd.make_layer(T, M, N, K, dtype, VECTOR))
+        assert one <= need <= max(16 << 20, one * min(64, -(-T // 1024)))
