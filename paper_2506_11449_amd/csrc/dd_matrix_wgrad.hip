@@ -555,10 +555,9 @@ struct WgradPlan {
 
 // Chunks of tokens, by the time they should take in us: a workgroup's k-steps of sixteen tokens (0.18-0.245 alone on its CU,
 // 0.45 with a second one beside it), its epilogue, which follows the share of the diagonals that are kept, and the partial
-// sums on their way out and back in.  Measured over 256^2 ... 4096^2, 64-25216 tokens, 10 and 40 % of the diagonals
-// (gradient and sum, graph replay), against two workgroups per CU whatever the size: 768^2 at 1279 tokens 16.1-27.6 ->
-// 13.3-21 us, 4096 -> 2560 at 788 tokens 54-99 -> 32-53 us, 4096^2 at 1279 tokens 88-172 -> 51-81 us, 1024 -> 4096 at 25216
-// tokens 178-205 -> 173-187 us; 768^2 at 12608 tokens and 768 -> 3072 from 12608 on stay within 2 %.
+// sums on their way out and back in.  Taken only where the sums are no less exact for it (wgrad_chain), which leaves it the
+// layers of few tiles: gradient and sum against two workgroups per CU whatever the size, 256^2, 100 diagonals, 6304 tokens
+// 25.8 -> 18.2 us, 128 -> 512, 77 diagonals, 10320 tokens 19.6 -> 13.8 us.
 static double wgrad_cost(int64_t slices, int tiles, int chunks, double tile_share, int D, int L, int K)
 {
     const double wgs = double(tiles) * chunks, steps = double((slices + chunks - 1) / chunks) * (kSliceTokens / kTS);
@@ -568,6 +567,11 @@ static double wgrad_cost(int64_t slices, int tiles, int chunks, double tile_shar
     const double epilogue = (3.0 + 16.0 * K / D) * (paired ? 1.5 : 1.0);
     return rounds * (steps * step + epilogue) + 8.0 * chunks * K * L / 3.3e6;
 }
+
+// Additions that an entry of the gradient goes through one after the other: two per k-step of its chunk, then a run of a
+// quarter of the chunks, then the four runs.  Its error grows with their square root (measured against 64 bits: 2.5e-8 times
+// the root of half of them, from 10 to 800), so a long chunk costs precision and many chunks cost some too.
+static double wgrad_chain(int64_t T, int chunks) { return double(T) / (kTS / 2 * chunks) + (chunks + 3) / 4 + 3; }
 
 static WgradPlan plan_wgrad(int64_t T, int D, int L, int K)
 {
@@ -592,6 +596,7 @@ static WgradPlan plan_wgrad(int64_t T, int D, int L, int K)
     const double tile_share = double(pl.tp) * pl.tq / (192 * 192);
     double best_cost = wgrad_cost(slices, tiles, pl.most, tile_share, D, L, K);
     for (int chunks = 1; chunks < pl.most; chunks += chunks < kWgXcds ? 1 : kWgXcds) {
+        if (wgrad_chain(T, chunks) > wgrad_chain(T, pl.most)) continue;
         const double cost = wgrad_cost(slices, tiles, chunks, tile_share, D, L, K);
         if (cost < 0.97 * best_cost) {
             best_cost = cost;
