@@ -92,7 +92,7 @@ bool wants_matrix_wgrad(const dd_layer *l, const Shape &s)
 // the two families cut the tokens into different numbers of chunks: the size covers whichever of them runs.
 size_t weight_grad_ws_bytes(const dd_layer *l, const Shape &s)
 {
-    size_t vector = dd::weight_grad_vector_ws_bytes(l->tokens, s.L, l->K, l->dtype == DD_BF16);
+    size_t vector = dd::weight_grad_vector_ws_bytes(l->tokens, s.D, s.L, l->K, l->dtype == DD_BF16);
     if (wants_lowk_wgrad(l, s)) {
         const size_t lowk = dd::weight_grad_lowk_ws_bytes(l->tokens, s.D, s.L, l->K);
         vector = lowk > vector ? lowk : vector;
@@ -327,7 +327,7 @@ dd_status dd_bwd_weight(const dd_layer *layer, const void *X, const void *dY, co
     // the family that runs must fit the scratch that was checked (the families cut the tokens differently)
     const size_t runs_in = lowk     ? dd::weight_grad_lowk_ws_bytes(layer->tokens, s.D, s.L, layer->K)
                            : matrix ? dd::weight_grad_matrix_ws_bytes(layer->tokens, s.D, s.L, layer->K)
-                                    : dd::weight_grad_vector_ws_bytes(layer->tokens, s.L, layer->K,
+                                    : dd::weight_grad_vector_ws_bytes(layer->tokens, s.D, s.L, layer->K,
                                                                       layer->dtype == DD_BF16);
     if (ws_bytes < runs_in) return DD_ERR_WORKSPACE;
     dd::WeightGradArgs a;

@@ -98,7 +98,7 @@ bool select_prepare_fused(int D, int L, int K);
 hipError_t launch_select_prepare(int D, int L, int K, bool expanding, const float *scores, const void *values,
                                  int32_t *offsets_out, void *forward_operand, void *backward_operand,
                                  hipStream_t stream);
-size_t weight_grad_vector_ws_bytes(int64_t T, int L, int K, bool bf16);
+size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16);
 hipError_t launch_weight_grad_vector(const WeightGradArgs &a, hipStream_t stream);
 
 // matrix-core family (bf16 only, both feature counts multiples of 192 or both multiples of 128)

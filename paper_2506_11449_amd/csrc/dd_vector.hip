@@ -630,7 +630,7 @@ __global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
 }
 
 // dV[i] = sum over the chunks of partial[chunk][i]: the chunks are cut into four runs that four waves add up side by side,
-// each in order with eight loads in flight; the four sums are then added in order.
+// each in a fixed order with eight loads in flight; the four sums are then added in order.
 __global__ __launch_bounds__(256) void weight_grad_reduce_kernel(size_t n, int splits, const float *__restrict__ partial,
                                                                 float *__restrict__ dV)
 {
@@ -647,8 +647,8 @@ __global__ __launch_bounds__(256) void weight_grad_reduce_kernel(size_t n, int s
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = src[u * n];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
+            // in pairs: added one after the other, 256 chunks cost more precision than the chains that they cut short
+            acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
         for (; s < s_end; ++s, src += n) acc += *src;
     }
@@ -663,16 +663,27 @@ struct WgTiledPlan {
     size_t lds;
 };
 
-// The most chunks a plan may take: what the scratch is sized for.  Never fewer for more tokens, so that scratch sized for
-// the largest batch serves every smaller one, whatever their plans; never fewer than the untiled kernel makes; and no more
-// than 16 MiB of partial sums unless that kernel needs more (768 x 768, 77 diagonals: 15.1 MB from 256 tokens on).
-static int wg_most_chunks(int64_t T, int L, int K, bool bf16)
+// The fewest chunks a plan may take, so that no sum is a longer chain of additions than the kernels before these made it: at
+// most 1024 tokens one after the other (or 64 chunks), and bf16 layers of whole 16-byte rows in at least eight chunks.
+// (The error grows with the root of the chain: one chunk of 25216 tokens, 1000^2, 600 diagonals, fp32, 1.0e-6 against 64 bits.)
+static int wg_fewest_chunks(int64_t T, int D, int L, bool bf16)
 {
-    const int64_t one = int64_t(K) * L * int64_t(sizeof(float)), splits = weight_grad_splits(T), group = bf16 ? 8 : 4;
+    const int splits = weight_grad_splits(T);
+    if (!bf16 || D % 8 || L % 8 || D > 2304) return splits;
+    const int eighths = T < 8 * 16 ? int((T + 15) / 16) : 8;
+    return eighths > splits ? eighths : splits;
+}
+
+// The most chunks a plan may take: what the scratch is sized for.  Never fewer for more tokens, so that scratch sized for
+// the largest batch serves every smaller one, whatever their plans; and no more
+// than 16 MiB of partial sums unless the fewest need more (768 x 768, 77 diagonals: 15.1 MB from 256 tokens on).
+static int wg_most_chunks(int64_t T, int D, int L, int K, bool bf16)
+{
+    const int64_t one = int64_t(K) * L * int64_t(sizeof(float)), fewest = wg_fewest_chunks(T, D, L, bf16), group = bf16 ? 8 : 4;
     int64_t most = (int64_t(16) << 20) / one;
     if (most > kWgCus) most = kWgCus;
     if (most > (T + group - 1) / group) most = (T + group - 1) / group;
-    return int(most > splits ? most : splits);
+    return int(most > fewest ? most : fewest);
 }
 
 // Block of diagonals, tile and chunks by the time they should take, as in make_tiled_plan.
@@ -681,7 +692,7 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
     WgTiledPlan best = {};
     const int p_blocks = (L + 63) / 64, group = bf16 ? 8 : 4;
     const size_t one = size_t(K) * L * sizeof(float);
-    const int most = wg_most_chunks(T, L, K, bf16);
+    const int fewest = wg_fewest_chunks(T, D, L, bf16), most = wg_most_chunks(T, D, L, K, bf16);
     double best_cost = 1e300;
     static const int kns[] = {8, 16, 24}, nts[] = {1, 2, 4};
     for (int kn : kns) {
@@ -699,11 +710,11 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
                 int64_t chunks = kWgCus / per_chunk;  // one workgroup per CU: more cost more staging than they hide
                 if (chunks > tiles) chunks = tiles;
                 if (chunks > most) chunks = most;
-                if (chunks < 1) chunks = 1;
+                if (chunks < fewest) chunks = fewest;
                 // per tile: LDS reads of all waves, or one wave's chain of instructions; the barrier and the next tile
                 const double lds_clk = waves * nt * (kn + 4) * 8, issue = nt * (kn * 16 + 8) * 1.3 * ((waves + 3) / 4);
                 const double staging = 1500 + 150.0 * cols * nt / threads + (cols * nt > (bf16 ? 2 : 4) * threads ? 2000 : 0);
-                for (;;) {  // that many chunks, or one and no sum over them
+                for (;;) {  // that many chunks, or as few as may be (one: no sum over them)
                     const double rounds = double((chunks * per_chunk + 255) / 256);
                     const double steps = double((tiles + chunks - 1) / chunks);
                     const double cost = rounds * (steps * ((lds_clk > issue ? lds_clk : issue) + staging) + 3000) +
@@ -720,8 +731,8 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
                         best.chunks = int(chunks);
                         best.lds = lds;
                     }
-                    if (chunks == 1) break;
-                    chunks = 1;
+                    if (chunks == fewest) break;
+                    chunks = fewest;
                 }
             }
         }
@@ -735,9 +746,9 @@ static WgTiledPlan plan_wg_tiled(int64_t T, int D, int L, int K, bool bf16)
     return memo.get(T, D, L, K, bf16, [&] { return make_wg_tiled_plan(T, D, L, K, bf16); });
 }
 
-size_t weight_grad_vector_ws_bytes(int64_t T, int L, int K, bool bf16)
+size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16)
 {
-    return size_t(wg_most_chunks(T, L, K, bf16)) * size_t(K) * size_t(L) * sizeof(float);
+    return size_t(wg_most_chunks(T, D, L, K, bf16)) * size_t(K) * size_t(L) * sizeof(float);
 }
 
 template <class S, int NT, int KN>

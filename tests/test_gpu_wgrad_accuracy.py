@@ -35,3 +35,17 @@ def test_matrix_cores(M, N, K, T):
     chunks = dd.dd_workspace_bytes(dd.DD_OP_BWD_WEIGHT, l) // (4 * K * min(M, N))
     additions = T / 8 / chunks + -(-chunks // 4) + 3
     assert _error(M, N, K, T, torch.bfloat16, dd.DD_ALGO_MATRIX) <= 1.2 * 2.5e-8 * (additions / 2) ** 0.5
+
+
+@pytest.mark.parametrize("M,N,K,T,dtype", [(1000, 1000, 600, 25216, torch.float32), (2000, 2000, 1000, 8192, torch.float32),
+                                           (40, 3000, 3000, 9000, torch.float32), (1024, 1000, 500, 1024, torch.float32),
+                                           (1536, 1528, 700, 12608, torch.bfloat16), (333, 1001, 700, 40000, torch.bfloat16),
+                                           (2000, 2000, 1000, 8192, torch.bfloat16), (56, 1960, 196, 4651, torch.bfloat16)])
+def test_vector_kernels(M, N, K, T, dtype):
+    """At most 1024 tokens one after the other, in bf16 two tokens an addition and layers of whole 16-byte rows in at least
+    eight chunks; the chunks are added in four runs, by eights.  A fifth on top for the mantissas that occur."""
+    chunks = -(-T // 1024)
+    if dtype == torch.bfloat16 and M % 8 == 0 and N % 8 == 0:
+        chunks = max(chunks, 8)
+    additions = T / chunks / (2 if dtype == torch.bfloat16 else 1) + chunks / 32 + 14
+    assert _error(M, N, K, T, dtype, dd.DD_ALGO_VECTOR) <= 1.2 * 2.5e-8 * (additions / 2) ** 0.5
