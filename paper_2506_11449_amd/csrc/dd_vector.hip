@@ -460,8 +460,31 @@ static int weight_grad_splits(int64_t T)
     return int(s);
 }
 
-// partial[s][k][p] = sum over the tokens of split s of A[t, p] * B[t, (p + o_k) mod D]
-template <class S>
+// x[t] * y[t] over N tokens, rows `la` and `lb` elements apart, a sum for every four (fewer additions one after the other, and
+// smaller ones); of the N rows the first `rows` count, the others are not read.
+template <class S, int N>
+__device__ __forceinline__ float multiply_rows(const typename S::storage *x, const typename S::storage *y, int la, int lb, int rows)
+{
+    float a[N], b[N], sum[N / 4] = {};
+    static_assert(N == 4 || N == 16, "one sum or four");
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int row = min(i, rows - 1);
+        a[i] = S::load(x + size_t(row) * la);
+        b[i] = S::load(y + size_t(row) * lb);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) sum[i >> 2] = i < rows ? fmaf(a[i], b[i], sum[i >> 2]) : sum[i >> 2];
+    return N == 4 ? sum[0] : (sum[0] + sum[1]) + (sum[N / 4 - 2] + sum[N / 4 - 1]);
+}
+
+// partial[s][k][p] = sum over the tokens of split s of A[t, p] * B[t, (p + o_k) mod D], a thread per entry, straight from
+// memory, AHEAD tokens on their way at once.  For so few tokens that a tile in LDS is not worth laying out, AHEAD = 16: bound
+// by the latency of its loads, beyond some 10^7 products by their number.  For long sides too wide for a tile, 4: one of
+// 12000, 300 wide, 50 diagonals, 3000 tokens, fp32, 88 us (251 one by one, bf16 90 and 260).  Rows of more than 64 KB, 1:
+// the diagonals share the rows in L2, and the faster the threads go the further they drift apart there (9800^2, 30 diagonals,
+// fp32, 3000 tokens 611 us, by fours 1026).
+template <class S, int AHEAD>
 __global__ __launch_bounds__(kWgThreads) void weight_grad_partial_kernel(
     int64_t T, int D, int L, int K, int splits, const typename S::storage *__restrict__ A,
     const typename S::storage *__restrict__ B, const int *__restrict__ offsets, float *__restrict__ partial)
@@ -471,12 +494,20 @@ __global__ __launch_bounds__(kWgThreads) void weight_grad_partial_kernel(
     const int s = blockIdx.z;
     if (p >= L) return;
     const int64_t per = (T + splits - 1) / splits;
-    const int64_t t0 = s * per, t1 = min(t0 + per, T);
+    const int64_t t0 = min(s * per, T), t1 = min(t0 + per, T);
     int q = p + canonical_offset(offsets[k], D);
     if (q >= D) q -= D;
+    const typename S::storage *x = A + t0 * L + p, *y = B + t0 * D + q;
     float acc = 0.f;
-    for (int64_t t = t0; t < t1; ++t)
-        acc = fmaf(S::load(A + t * L + p), S::load(B + t * D + q), acc);
+    if constexpr (AHEAD == 1) {
+        for (int64_t t = t0; t < t1; ++t, x += L, y += D) acc = fmaf(S::load(x), S::load(y), acc);
+    } else {
+        int64_t left = t1 - t0;
+        for (; left >= AHEAD; left -= AHEAD, x += size_t(AHEAD) * L, y += size_t(AHEAD) * D)
+            acc += multiply_rows<S, AHEAD>(x, y, L, D, AHEAD);
+        if (left > 4) acc += multiply_rows<S, AHEAD>(x, y, L, D, int(left));
+        else if (left > 0) acc += multiply_rows<S, 4>(x, y, L, D, int(left));
+    }
     partial[(size_t(s) * K + k) * L + p] = acc;
 }
 
@@ -740,8 +771,16 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
     return best;
 }
 
+// Few tokens: straight from memory.  The tiled kernel lays out the whole long side before its first multiply-add; where the
+// lines cross (fp32 and bf16, 64^2 ... 4000 x 3000, 3 ... 100 % of the diagonals) T lies between 200 and 300 for small layers and
+// T * K * L between 3e7 and 2e8 for large ones.  At 16 tokens, tiled -> this (one thread per entry without the loads in
+// flight, and a second launch for the sum): 64^2, 8 diagonals, fp32 5.6 -> 1.8 us (4.7), 768 -> 3072, 307 diagonals
+// 11.7 -> 3.0 us (5.8); at 160 tokens 21.2 -> 13.1 us (20.7).
+static bool wg_few_tokens(int64_t T, int L, int K) { return T <= 192 && T * K * L <= 30000000; }
+
 static WgTiledPlan plan_wg_tiled(int64_t T, int D, int L, int K, bool bf16)
 {
+    if (wg_few_tokens(T, L, K)) return {};
     static thread_local PlanMemo<WgTiledPlan> memo;
     return memo.get(T, D, L, K, bf16, [&] { return make_wg_tiled_plan(T, D, L, K, bf16); });
 }
@@ -786,8 +825,12 @@ static hipError_t launch_weight_grad_t(const WeightGradArgs &a, hipStream_t stre
     else {
         // K can exceed the grid.y limit only beyond 65535 diagonals, which the ABI rejects
         dim3 grid((a.L + kWgThreads - 1) / kWgThreads, a.K, splits);
-        hipLaunchKernelGGL(weight_grad_partial_kernel<S>, grid, dim3(kWgThreads), 0, stream, a.T, a.D, a.L, a.K, splits,
-                           static_cast<const st *>(a.A), static_cast<const st *>(a.B), a.offsets, partial);
+        const bool wide_rows = (size_t(a.D) + a.L) * sizeof(st) > 64 * 1024;
+        hipLaunchKernelGGL((wg_few_tokens(a.T, a.L, a.K) ? weight_grad_partial_kernel<S, 16>
+                            : wide_rows                  ? weight_grad_partial_kernel<S, 1>
+                                                         : weight_grad_partial_kernel<S, 4>),
+                           grid, dim3(kWgThreads), 0, stream, a.T, a.D, a.L, a.K, splits, static_cast<const st *>(a.A),
+                           static_cast<const st *>(a.B), a.offsets, partial);
         e = hipGetLastError();
     }
     if (e != hipSuccess || splits == 1) return e;
