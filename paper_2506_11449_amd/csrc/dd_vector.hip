@@ -84,6 +84,7 @@ typedef __bf16 bf16x2p __attribute__((ext_vector_type(2)));
 
 constexpr int kMaxWaves = 16;     // waves per workgroup of the product kernel
 constexpr int kLoadAhead = 4;     // groups of a tile a thread has on their way at once
+constexpr int kWideSource = 4500; // columns beyond which a tile may not pay
 constexpr int kListLen = 256;     // diagonals looked at per pass; their list is private to a wave
 constexpr size_t kLdsPerCu = 160 * 1024;
 
@@ -337,6 +338,7 @@ struct TiledPlan {
 static TiledPlan make_tiled_plan(int64_t T, int D, int L, int K, bool bf16, bool masked)
 {
     TiledPlan best = {};
+    double best_rounds = 0;
     const int src_cols = masked ? L : D, dst_cols = masked ? D : L;
     const int n_blocks = (dst_cols + 63) / 64;
     const double met = masked ? K * (L + 63.0 < D ? (L + 63.0) / D : 1.0) : K;  // diagonals that meet a column block
@@ -372,6 +374,7 @@ static TiledPlan make_tiled_plan(int64_t T, int D, int L, int K, bool bf16, bool
                 const double cost = (busy > chain ? busy : chain) + stage + (parts > 1 ? rounds * 500 : 0);
                 if (cost < best_cost) {
                     best_cost = cost;
+                    best_rounds = rounds;
                     best.nt = nt;
                     best.k_parts = parts;
                     best.waves = w;
@@ -381,6 +384,20 @@ static TiledPlan make_tiled_plan(int64_t T, int D, int L, int K, bool bf16, bool
                 }
             }
         }
+    }
+    // Wide sources leave room for one group per column and few waves: laying the tile out can take longer than reading every
+    // operand from L1 and L2.  Times in us, fitted to sources of 6000 ... 9800 columns onto 300 ... 9800, 20 ... 500
+    // diagonals, 1 ... 4000 tokens, fp32 and bf16: 9800 -> 300, 30 diagonals, 200 tokens 25 tiled, 3.5 untiled; 9800^2, 3000
+    // tokens 1254 and 313 (gather), 1297 and 632 (masked); 6000^2, 200 diagonals, 4000 tokens 769 and 1180, 898 and 2706.
+    // Narrower sources are ahead in LDS at every size where that counts (4500^2: 230 and 569).
+    if (best.nt && src_cols > kWideSource) {
+        const double tiled = 1.5 + best_cost / 2400 * (masked ? 1.3 : 1.15) +
+                             best_rounds * (bf16 ? 0.69 : 0.43) * src_cols * best.nt / (256.0 * best.waves);
+        const double share = masked && L + 63.0 < D ? (L + 63.0) / D : 1.0;
+        const double chain = masked ? 1.5 + 0.172 * K * share : 1.8 + 0.051 * K;
+        double work = double(T) * dst_cols * (masked ? (K * share + 9) / 1.85e6 : (K + 11) / 4.2e6);
+        if (double(K) * L * (bf16 ? 2 : 4) > 8e6) work *= 1.35;  // the weights do not stay in L2
+        if ((chain > work ? chain : work) < tiled) best.nt = 0;
     }
     return best;
 }
