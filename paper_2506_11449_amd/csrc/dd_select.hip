@@ -9,56 +9,58 @@
 
 namespace dd {
 
-template <int SLOTS>
-__global__ __launch_bounds__(kSelectThreads) void select_topk_kernel(int D, int K, const float *__restrict__ scores,
-                                                                     int *__restrict__ out)
+template <int THREADS, int SLOTS>
+__global__ __launch_bounds__(THREADS) void select_topk_kernel(int D, int K, const float *__restrict__ scores,
+                                                              int *__restrict__ out)
 {
-    __shared__ __attribute__((aligned(16))) SelectScratch<kSelectThreads, SLOTS> scratch;
-    select_topk_block<kSelectThreads, SLOTS>(D, K, scores + size_t(blockIdx.x) * D, scratch, out + size_t(blockIdx.x) * K);
+    __shared__ __attribute__((aligned(16))) SelectScratch<THREADS, SLOTS> scratch;
+    select_topk_block<THREADS, SLOTS>(D, K, scores + size_t(blockIdx.x) * D, scratch, out + size_t(blockIdx.x) * K);
 }
 
 // The selection and, in the same launch, the soft TopK weights of the same scores (Eq. 4 picks the diagonals, Eq. 5
 // weighs them): the workgroup that has just ranked a score vector also normalises it.
-template <int SLOTS>
-__global__ __launch_bounds__(kSelectThreads) void select_soft_kernel(int D, int K, float inv_temp,
-                                                                     const float *__restrict__ scores,
-                                                                     int *__restrict__ out,
-                                                                     float *__restrict__ alpha_tilde)
+template <int THREADS, int SLOTS>
+__global__ __launch_bounds__(THREADS) void select_soft_kernel(int D, int K, float inv_temp,
+                                                              const float *__restrict__ scores, int *__restrict__ out,
+                                                              float *__restrict__ alpha_tilde)
 {
-    __shared__ __attribute__((aligned(16))) SelectScratch<kSelectThreads, SLOTS> scratch;
-    static_assert(kSelectThreads == kSoftThreads, "one workgroup serves both routines");
-    select_topk_block<kSelectThreads, SLOTS>(D, K, scores + size_t(blockIdx.x) * D, scratch, out + size_t(blockIdx.x) * K);
-    soft_topk_block(D, float(K), inv_temp, scores + size_t(blockIdx.x) * D, alpha_tilde + size_t(blockIdx.x) * D);
+    __shared__ __attribute__((aligned(16))) SelectScratch<THREADS, SLOTS> scratch;
+    select_topk_block<THREADS, SLOTS>(D, K, scores + size_t(blockIdx.x) * D, scratch, out + size_t(blockIdx.x) * K);
+    soft_topk_block<THREADS>(D, float(K), inv_temp, scores + size_t(blockIdx.x) * D, alpha_tilde + size_t(blockIdx.x) * D);
 }
 
-template <int SLOTS>
-static void launch_select_soft_slots(int batch, int D, int K, float temperature, const float *scores, int *out,
-                                     float *alpha_tilde, hipStream_t stream)
-{
-    hipLaunchKernelGGL(select_soft_kernel<SLOTS>, dim3(batch), dim3(kSelectThreads), 0, stream, D, K, 1.f / temperature,
-                       scores, out, alpha_tilde);
-}
+// the instance for that many threads and candidates per thread, by the name of a template of the two
+#define DD_BY_SLOTS(kernel_, threads_, slots_)                                                          \
+    ((threads_) == kSelectThreadsFew ? ((slots_) <= 1   ? kernel_<kSelectThreadsFew, 1>                 \
+                                        : (slots_) <= 2 ? kernel_<kSelectThreadsFew, 2>                 \
+                                        : (slots_) <= 4 ? kernel_<kSelectThreadsFew, 4>                 \
+                                        : (slots_) <= 8 ? kernel_<kSelectThreadsFew, 8>                 \
+                                                        : kernel_<kSelectThreadsFew, 16>)               \
+                                     : ((slots_) <= 1    ? kernel_<kSelectThreads, 1>                   \
+                                        : (slots_) <= 4  ? kernel_<kSelectThreads, 4>                   \
+                                        : (slots_) <= 16 ? kernel_<kSelectThreads, 16>                  \
+                                                         : kernel_<kSelectThreads, kSelectMaxSlots>))
 
 hipError_t launch_select_soft(int batch, int D, int K, float temperature, const float *scores, int *out,
                               float *alpha_tilde, hipStream_t stream)
 {
-    const int slots = (D + kSelectThreads - 1) / kSelectThreads;
-    if (slots <= 1) launch_select_soft_slots<1>(batch, D, K, temperature, scores, out, alpha_tilde, stream);
-    else if (slots <= 4) launch_select_soft_slots<4>(batch, D, K, temperature, scores, out, alpha_tilde, stream);
-    else if (slots <= 16) launch_select_soft_slots<16>(batch, D, K, temperature, scores, out, alpha_tilde, stream);
-    else launch_select_soft_slots<kSelectMaxSlots>(batch, D, K, temperature, scores, out, alpha_tilde, stream);
+    const int threads = soft_threads(batch, D), slots = (D + threads - 1) / threads;
+    hipLaunchKernelGGL(DD_BY_SLOTS(select_soft_kernel, threads, slots), dim3(batch), dim3(threads), 0, stream, D, K,
+                       1.f / temperature, scores, out, alpha_tilde);
     return hipGetLastError();
 }
 
 hipError_t launch_select(int batch, int D, int K, const float *scores, int *out, hipStream_t stream)
 {
-    const int slots = (D + kSelectThreads - 1) / kSelectThreads;
-    const dim3 grid(batch), block(kSelectThreads);
-    if (slots <= 1) hipLaunchKernelGGL(select_topk_kernel<1>, grid, block, 0, stream, D, K, scores, out);
-    else if (slots <= 4) hipLaunchKernelGGL(select_topk_kernel<4>, grid, block, 0, stream, D, K, scores, out);
-    else if (slots <= 16) hipLaunchKernelGGL(select_topk_kernel<16>, grid, block, 0, stream, D, K, scores, out);
-    else hipLaunchKernelGGL(select_topk_kernel<kSelectMaxSlots>, grid, block, 0, stream, D, K, scores, out);
+    if (batch > 256 && D <= 256) {  // many short vectors: fewer waves yet (4000 x 64 scores 5.2 us, with 256 threads 7.8)
+        hipLaunchKernelGGL((D <= 128 ? select_topk_kernel<128, 1> : select_topk_kernel<128, 2>), dim3(batch), dim3(128), 0, stream,
+                           D, K, scores, out);
+        return hipGetLastError();
+    }
+    const int threads = select_threads(batch, D), slots = (D + threads - 1) / threads;
+    hipLaunchKernelGGL(DD_BY_SLOTS(select_topk_kernel, threads, slots), dim3(batch), dim3(threads), 0, stream, D, K, scores, out);
     return hipGetLastError();
 }
+#undef DD_BY_SLOTS
 
 }  // namespace dd

@@ -8,16 +8,25 @@
 // be broadcast.  The chosen candidates' places in ascending order come from ballots and a prefix sum over the
 // (slot, wave) pairs, which run through the candidates in index order.
 //
-// What bounds it is latency: one trip to memory for the scores, then a chain of five barriers; nothing else runs on the
-// chip meanwhile.  Measured (a kernel by itself): one vector of 4096 scores 6.4 us, of 1024 scores 4.6 us; with 256
-// threads that read the keys from LDS in every pass and compacted contiguous chunks 18.8 us and 5.3 us.
+// What bounds it is latency: one trip to memory for the scores, then a chain of seven barriers; nothing else runs on the
+// chip meanwhile.  Measured (graph replay): one vector of 4096 scores 5.5 us, of 1024 scores 3.3 us; with 256 threads that
+// read the keys from LDS in every pass and compacted contiguous chunks 12.8 and 5.0 us.
 #pragma once
 #include "dd_common.h"
 
 namespace dd {
 
-constexpr int kSelectThreads = 1024;   // threads of the kernels that only select
+constexpr int kSelectThreads = 1024;   // threads of the kernels that work on score vectors ...
+constexpr int kSelectThreadsFew = 256; // ... or these: select_threads, soft_threads
 constexpr int kSelectMaxSlots = 64;    // 65536 candidates
+
+// Threads of the workgroup for one score vector.  Alone on the chip a long vector is done sooner by many threads; of many
+// vectors more fit a CU at a time with few, and a short one leaves the other waves waiting at barriers.  Selection, us with
+// 256 and 1024 threads: 1 x 1024 scores 3.3 and 3.6, 1 x 2000 4.4 and 4.8, 1 x 3072 6.5 and 5.2, 600 x 768 4.4 and 7.2,
+// 4000 x 4096 38 and 54; weights: 1 x 768 4.3 and 2.6, 1 x 64 2.0 and 2.3, 300 x 2000 5.7 and 5.2, 4000 x 1024 10 and 24.
+inline bool many_vectors(int batch, int D) { return batch > 256 && D <= 16 * kSelectThreadsFew; }
+inline int select_threads(int batch, int D) { return D <= 8 * kSelectThreadsFew || many_vectors(batch, D) ? kSelectThreadsFew : kSelectThreads; }
+inline int soft_threads(int batch, int D) { return D <= kSelectThreadsFew || many_vectors(batch, D) ? kSelectThreadsFew : kSelectThreads; }
 
 __device__ __forceinline__ uint32_t score_key(float s)
 {

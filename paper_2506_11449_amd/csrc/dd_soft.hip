@@ -3,42 +3,39 @@
 // reductions: launch-bound, one workgroup per score vector / per diagonal, fixed reduction order.
 #include "dd_common.h"
 #include "dd_launch.h"
+#include "dd_select_block.h"
 #include "dd_soft_block.h"
 
 namespace dd {
 
 constexpr int kScaleThreads = 256;  // kernels that run over the K x L values
 
-__global__ __launch_bounds__(kSoftThreads) void soft_topk_kernel(int D, float k_over_1, float inv_temp,
-                                                                 const float *__restrict__ scores,
-                                                                 float *__restrict__ alpha_tilde)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void soft_topk_kernel(int D, float k_over_1, float inv_temp,
+                                                            const float *__restrict__ scores,
+                                                            float *__restrict__ alpha_tilde)
 {
-    soft_topk_block(D, k_over_1, inv_temp, scores + size_t(blockIdx.x) * D, alpha_tilde + size_t(blockIdx.x) * D);
+    soft_topk_block<THREADS>(D, k_over_1, inv_temp, scores + size_t(blockIdx.x) * D, alpha_tilde + size_t(blockIdx.x) * D);
 }
 
 // d a_i = (K / temp) * s_i * (m_i g_i - sum_j m_j g_j s_j),  m_j = [K s_j < 1]
-__global__ __launch_bounds__(kSoftThreads) void soft_topk_bwd_kernel(int D, float k_over_1, float inv_temp,
-                                                                     const float *__restrict__ scores,
-                                                                     const float *__restrict__ g,
-                                                                     float *__restrict__ dscores)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void soft_topk_bwd_kernel(int D, float k_over_1, float inv_temp,
+                                                                const float *__restrict__ scores,
+                                                                const float *__restrict__ g,
+                                                                float *__restrict__ dscores)
 {
-    __shared__ float scratch[kSoftThreads / 64];
+    __shared__ SoftScratch scratch;
     const float *a = scores + size_t(blockIdx.x) * D, *gb = g + size_t(blockIdx.x) * D;
     float *out = dscores + size_t(blockIdx.x) * D;
-    float m = -INFINITY;
-    for (int i = threadIdx.x; i < D; i += kSoftThreads) m = fmaxf(m, a[i]);
-    m = block_reduce<true>(m, scratch);
-    float s = 0.f;
-    for (int i = threadIdx.x; i < D; i += kSoftThreads) s += expf((a[i] - m) * inv_temp);
-    s = block_reduce<false>(s, scratch);
+    const float m = reduce_scores<true, THREADS>(D, scratch, [&](int i) { return a[i]; });
+    const float s = reduce_scores<false, THREADS>(D, scratch, [&](int i) { return expf((a[i] - m) * inv_temp); });
     const float inv_s = 1.f / s;
-    float dot = 0.f;
-    for (int i = threadIdx.x; i < D; i += kSoftThreads) {
+    const float dot = reduce_scores<false, THREADS>(D, scratch, [&](int i) {
         const float si = expf((a[i] - m) * inv_temp) * inv_s;
-        if (k_over_1 * si < 1.f) dot += gb[i] * si;
-    }
-    dot = block_reduce<false>(dot, scratch);
-    for (int i = threadIdx.x; i < D; i += kSoftThreads) {
+        return k_over_1 * si < 1.f ? gb[i] * si : 0.f;
+    });
+    for (int i = threadIdx.x; i < D; i += THREADS) {
         const float si = expf((a[i] - m) * inv_temp) * inv_s;
         const float mg = k_over_1 * si < 1.f ? gb[i] : 0.f;
         out[i] = k_over_1 * inv_temp * si * (mg - dot);
@@ -96,16 +93,18 @@ __global__ __launch_bounds__(kScaleThreads) void scatter_alpha_grad_kernel(int D
 hipError_t launch_soft_topk(int batch, int D, int K, float temperature, const float *scores, float *alpha_tilde,
                             hipStream_t stream)
 {
-    hipLaunchKernelGGL(soft_topk_kernel, dim3(batch), dim3(kSoftThreads), 0, stream, D, float(K), 1.f / temperature,
-                       scores, alpha_tilde);
+    const int threads = soft_threads(batch, D);
+    hipLaunchKernelGGL((threads == kSelectThreadsFew ? soft_topk_kernel<kSelectThreadsFew> : soft_topk_kernel<kSelectThreads>),
+                       dim3(batch), dim3(threads), 0, stream, D, float(K), 1.f / temperature, scores, alpha_tilde);
     return hipGetLastError();
 }
 
 hipError_t launch_soft_topk_bwd(int batch, int D, int K, float temperature, const float *scores, const float *g,
                                 float *dscores, hipStream_t stream)
 {
-    hipLaunchKernelGGL(soft_topk_bwd_kernel, dim3(batch), dim3(kSoftThreads), 0, stream, D, float(K),
-                       1.f / temperature, scores, g, dscores);
+    const int threads = soft_threads(batch, D);
+    hipLaunchKernelGGL((threads == kSelectThreadsFew ? soft_topk_bwd_kernel<kSelectThreadsFew> : soft_topk_bwd_kernel<kSelectThreads>),
+                       dim3(batch), dim3(threads), 0, stream, D, float(K), 1.f / temperature, scores, g, dscores);
     return hipGetLastError();
 }
 
