@@ -950,14 +950,16 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
                     w_[ks][a] = *reinterpret_cast<const bf16x8 *>(w_src + a * w_row + ks * 512 + lane * 8); \
         w_src += 4 * 512;                                                                               \
     }
-    // a wave's LDS accesses are served in order: the rows are read as fragments behind their own writes and before the
-    // writes of the next group
+    // The rows change lanes inside the wave, whose LDS accesses are served in order: the fences keep the compiler from moving
+    // a fragment's read before the writes of its group or behind those of the next (they wait for nothing).
 #define DD_SMALL_GROUP(w_, x_, m_, next_)                                                               \
     {                                                                                                   \
         const unsigned now = m_;                                                                        \
         _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
             _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
                 *reinterpret_cast<u32x4 *>(x_buf + b * 32 * kRowBytes + x_dst[j]) = x_[b][j];           \
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                          \
+        __builtin_amdgcn_wave_barrier();                                                                \
         if ((next_) < g_end) {                                                                          \
             DD_SMALL_MASK(m_, next_)                                                                    \
             DD_SMALL_LOAD_X(x_)                                                                         \
@@ -973,6 +975,8 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
                 }                                                                                       \
         }                                                                                               \
         if ((next_) < g_end) DD_SMALL_LOAD_W(w_, m_)                                                    \
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                          \
+        __builtin_amdgcn_wave_barrier();                                                                \
     }
     int g = g_begin;
     if (g < g_end) {
