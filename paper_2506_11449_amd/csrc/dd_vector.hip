@@ -684,7 +684,7 @@ __global__ __launch_bounds__(256) void weight_grad_reduce_kernel(size_t n, int s
 {
     __shared__ float run_s[3][64];
     const int run = threadIdx.x >> 6, g = threadIdx.x & 63;
-    const size_t i = size_t(blockIdx.x) * 64 + g;
+    const size_t i = (size_t(blockIdx.y) * gridDim.x + blockIdx.x) * 64 + g;
     const int per_run = (splits + 3) / 4;
     const int s_begin = min(run * per_run, splits), s_end = min(s_begin + per_run, splits);
     float acc = 0.f;
@@ -851,8 +851,10 @@ static hipError_t launch_weight_grad_t(const WeightGradArgs &a, hipStream_t stre
         e = hipGetLastError();
     }
     if (e != hipSuccess || splits == 1) return e;
-    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3(unsigned((n + 63) / 64)), dim3(256), 0, stream, n, splits, partial,
-                       a.dValues);
+    // two dimensions: one holds 2^32 threads, a gradient up to 2^32 entries with four threads each
+    const size_t blocks = (n + 63) / 64, across = blocks < (size_t(1) << 20) ? blocks : size_t(1) << 20;
+    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3(unsigned(across), unsigned((blocks + across - 1) / across)), dim3(256), 0,
+                       stream, n, splits, partial, a.dValues);
     return hipGetLastError();
 }
 

@@ -27,3 +27,20 @@ def test_few_tokens_and_wide_layers(M, N, K, T, dtype):
     rows, cols = (p + 0 * q, q) if M <= N else (q, p + 0 * q)
     touched = torch.from_numpy((rows == 0) | (cols == N - 1)).cuda()
     assert torch.equal(got[~touched], dV[~touched]) and not torch.isfinite(got[touched]).any()
+
+
+def test_more_than_a_thousand_million_values():
+    """K * L beyond 2^30: every entry of the sum over the chunks has a workgroup (4.4 GB of gradient, 8.7 GB of scratch)."""
+    D, T = 33000, 1025
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    offsets = torch.randperm(D, device="cuda", generator=gen).to(torch.int32)
+    X, dY = (torch.randn((T, D), device="cuda", generator=gen) for _ in range(2))
+    dV = torch.full((D, D), float("nan"), device="cuda")
+    dd.dd_bwd_weight(X, dY, offsets, dValues=dV, ws=dd.Workspace())
+    k, p = (torch.randint(0, D, (4000,), device="cuda", generator=gen) for _ in range(2))
+    k[:2], p[:2] = torch.tensor([0, D - 1]), torch.tensor([0, D - 1])
+    q = (p + offsets[k].long()) % D
+    ref = (X[:, p].double() * dY[:, q].double()).sum(0)
+    assert float((dV[k, p].double() - ref).norm() / ref.norm()) <= 1e-6
+    assert not torch.isnan(dV.sum(1)).any()
