@@ -414,10 +414,19 @@ static hipError_t launch_tiled(const ProductArgs &a, const TiledPlan &pl, hipStr
     using st = typename S::storage;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&product_tiled_kernel<S, NT, MASKED>), int(kLdsPerCu), lds_allowed)) return e;
-    hipLaunchKernelGGL((product_tiled_kernel<S, NT, MASKED>), dim3(pl.grid_x, pl.grid_y), dim3(64 * pl.waves), pl.lds, stream,
-                       a.T, a.D, a.L, a.K, pl.k_parts, static_cast<const st *>(a.src), a.offsets,
-                       static_cast<const st *>(a.values), static_cast<st *>(a.dst));
-    return hipGetLastError();
+    // a grid holds fewer than 2^32 threads along x: beyond that many tiles, one launch after the other
+    constexpr int TT = NT * Group<S>::kTokens;
+    const unsigned most = unsigned(((uint64_t(1) << 32) - 1) / (64 * unsigned(pl.waves)));
+    for (unsigned done = 0; done < pl.grid_x; done += most) {
+        const unsigned tiles = pl.grid_x - done < most ? pl.grid_x - done : most;
+        const int64_t t0 = int64_t(done) * TT;
+        const st *src = static_cast<const st *>(a.src) + t0 * (MASKED ? a.L : a.D);
+        st *dst = static_cast<st *>(a.dst) + t0 * (MASKED ? a.D : a.L);
+        hipLaunchKernelGGL((product_tiled_kernel<S, NT, MASKED>), dim3(tiles, pl.grid_y), dim3(64 * pl.waves), pl.lds, stream,
+                           a.T - t0, a.D, a.L, a.K, pl.k_parts, src, a.offsets, static_cast<const st *>(a.values), dst);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 template <class S, int NT>

@@ -22,3 +22,18 @@ def test_wide_sources(M, N, K, T, dtype):
     dX = dd.dd_bwd_input(dy, off, V, M, algo=dd.DD_ALGO_VECTOR)[rows]
     assert rel_err(to_host(Y), orc.fwd(X[rows], offsets, values, N)) <= TOL[dtype]
     assert rel_err(to_host(dX), orc.bwd_input(dY[rows], offsets, values, M)) <= TOL[dtype]
+
+
+def test_more_tiles_than_one_grid_holds():
+    """1.08e9 tokens of a 2 -> 1 layer (13 GB): the tokens behind the 2^32nd thread are worked too."""
+    T = (1 << 30) + 5000000
+    X = torch.ones((T, 2), device="cuda")
+    X[:, 1] = 3.0
+    X[T - 1, 0], X[(1 << 30) + 1, 1] = 7.0, -2.0
+    offsets, values = torch.tensor([1], dtype=torch.int32, device="cuda"), torch.tensor([[0.5]], device="cuda")
+    Y = torch.full((T, 1), float("nan"), device="cuda")
+    dd.dd_fwd(X, offsets, values, 1, Y=Y, algo=dd.DD_ALGO_VECTOR)
+    assert (Y[:(1 << 30) + 1] == 1.5).all() and Y[(1 << 30) + 1, 0] == -1.0 and (Y[(1 << 30) + 2:] == 1.5).all()
+    dX = X
+    dd.dd_bwd_input(Y, offsets, values, 2, dX=dX, algo=dd.DD_ALGO_VECTOR)
+    assert (dX[:, 0] == 0).all() and dX[(1 << 30) + 1, 1] == -0.5 and dX[T - 1, 1] == 0.75
