@@ -40,6 +40,10 @@
  *     DD_ERR_HIP: the launch itself failed.
  *   - tokens == 0 is legal: fwd / bwd_input return DD_OK without a launch; bwd_weight
  *     writes zeros.
+ *   - Two calls with the same arguments give the same bits.  Calls of other sizes may take other kernels, whose fp32 sums
+ *     run in another order: a token's row may differ in rounding between batches of few and of many tokens, and a
+ *     layer's result between dd_fwd and dd_fwd_shared.  Scratch sizes never fall as tokens grow, so scratch sized for
+ *     the largest batch serves every smaller one.
  */
 #ifndef DYNADIAG_H
 #define DYNADIAG_H

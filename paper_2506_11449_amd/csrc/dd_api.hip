@@ -48,9 +48,10 @@ size_t select_ws_bytes(int32_t, int32_t, int32_t) { return 0; }
 bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // Does the shape allow the matrix-core kernels?  Then every request but DD_ALGO_VECTOR may run them.  The dense
-// contraction costs the same whatever K is and the general vector kernels cost in proportion to K, but measured over
-// K = 1 ... D/8 (`bench.py --k-sweep`) the matrix cores are ahead of those at every density, so between the two there
-// is no density threshold; the kernels for a handful of diagonals (wants_lowk) are asked first.
+// contraction costs the same whatever K is and the general vector kernels cost in proportion to K; measured over
+// K = 17 ... D/8 (`bench.py --k-sweep`) the matrix cores are ahead or level on 768^2 and 1024^2 (24 against 26 us and 61 against
+// 63 at K = 21), and behind only on 768 <-> 3072 below some 40 diagonals (products at K = 21 104-114 against 81-95 us).  No
+// density threshold is drawn between the two; the kernels for a handful of diagonals (wants_lowk) are asked first.
 bool wants_matrix(const dd_layer *l, const Shape &s)
 {
     if (l->algo == DD_ALGO_VECTOR) return false;

@@ -9,8 +9,8 @@
 //     first columns, so that a cyclically shifted read never wraps (and, for the masked gather, with zeros where the
 //     source has no column);
 //   * a lane owns the column pairs 2*lane + 128*i + {0, 1}, i < NI: for a fixed i the 64 lanes of a wave read 128
-//     consecutive floats whatever the shift, which is free of bank conflicts at any offset, and store 256
-//     consecutive bytes;
+//     consecutive floats whatever the shift -- every bank twice, at any offset (the counters call half of the LDS clocks
+//     conflicts) -- and store 256 consecutive bytes;
 //   * the K x 2*NI weights a lane needs stay in registers for all rows of the tile, the K shifts in scalar registers.
 #include "dd_common.h"
 #include "dd_launch.h"

@@ -72,12 +72,14 @@ __global__ __launch_bounds__(kProdThreads) void masked_gather_kernel(
 // last column lies one of zeros: what a slot without a diagonal reads, so that an infinite or undefined input reaches the
 // results of its own diagonals only.
 //
-// What bounds it: one source element out of LDS per multiply-add -- 128 bytes per clock and CU, 32 fp32 or 64 bf16
-// multiply-adds.  bf16 multiply-adds are taken in pairs of diagonals by v_dot2_f32_bf16 (one v_perm per pair of tokens to
-// bring two diagonals' elements together), which is one vector instruction per multiply-add and the same 64 per clock.
-// Measured: 768 x 768, 77 diagonals, fp32, 3152 tokens 23 / 21 us (forward / backward-input; 9.5 us at the LDS rate), with
-// four waves per workgroup, which left the reads' latency open, 43 / 44 us; 307 diagonals 61 / 57 us (38 us);
-// 320 -> 1000, 100 diagonals, bf16, 5005 tokens 26 / 25 us, converted to fp32 in LDS 70 / 44 us.
+// What bounds it: the vector instructions.  A wave of 16 fp32 tokens spends 38 (gather) or 42 (masked) of them per diagonal,
+// 16 of which are multiply-adds; the rest are the wrap, the bounds and the byte address of every lane's column, and the
+// staging.  On 768 x 768, 77 diagonals, 3152 tokens they take 92-96 % of the waves' life, the reads out of LDS 42 % (whole
+// groups; LDS alone delivers 174-248 bytes per clock and CU).  bf16 multiply-adds are taken in pairs of diagonals by
+// v_dot2_f32_bf16 (one v_perm per pair of tokens to bring two diagonals' elements together): one vector instruction per
+// multiply-add.  Measured, that layer in fp32: 21 / 20 us (forward / backward-input; 5.6 us for the multiply-adds at the 67
+// TFLOP/s of plain fp32), with four waves per workgroup, which left the reads' latency open, 43 / 44 us; 307 diagonals 61 /
+// 57 us; 320 -> 1000, 100 diagonals, bf16, 5005 tokens 23 / 23 us, converted to fp32 in LDS 70 / 44 us.
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2p __attribute__((ext_vector_type(2)));
@@ -299,8 +301,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void product_tiled_kernel(
     }
 }
 
-// Plans weigh some dozens of candidates, 3-5 us of host time: each thread remembers the last few (a plan is a pure function
-// of the sizes in its key, a value of a few dozen bytes).
+// Plans weigh some dozens of candidates, about half a microsecond of host time: each thread remembers the last few (a plan is a
+// pure function of the sizes in its key, a value of a few dozen bytes).
 template <class Plan>
 struct PlanMemo {
     struct Entry {
@@ -554,11 +556,13 @@ __device__ __forceinline__ float multiply_group(u32x4v a, u32x4v b, float acc)
 // them, the short-side columns of this workgroup's positions.  A wave owns 64 positions and a block of KN diagonals: one
 // accumulator and one LDS address per lane and diagonal, fixed for the whole kernel, and one 16-byte read per diagonal and
 // group of tokens.  The waves of a workgroup share the tile (`waves_k` blocks of diagonals times the position blocks);
-// several workgroups per CU hide each other's staging.  A workgroup takes one chunk of the tokens; the chunks are added
-// afterwards in order, or, if there is only one, `partial` is the result.
-// Bound, as the products, by one LDS element per multiply-add (two bytes of bf16: v_dot2_f32_bf16 takes two tokens).
+// one workgroup per CU, with the next tile on its way into registers while the current one is multiplied and two tiles in
+// LDS.  A workgroup takes one chunk of the tokens; the chunks are added afterwards in order, or, if there is only one,
+// `partial` is the result.
+// Bound by neither unit alone: vector instructions take 49 % of the waves' life in fp32 and 66 % in bf16 (v_dot2_f32_bf16 takes
+// two tokens), LDS reads 25 %; the rest is the staging of the next tile and the barrier between tiles.
 // Measured: 768 x 768, 77 diagonals, fp32, 3152 tokens 30 us (one thread per gradient entry, straight from memory: 212 us),
-// 307 diagonals 69 us; 320 -> 1000, 100 diagonals, bf16, 5005 tokens 27 us (four waves per workgroup on a tile of their
+// 307 diagonals 69 us; 320 -> 1000, 100 diagonals, bf16, 5005 tokens 23 us (four waves per workgroup on a tile of their
 // own: 38 us).
 template <class S, int NT, int KN>
 __global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
