@@ -78,6 +78,18 @@ bool wants_lowk_wgrad(const dd_layer *l, const Shape &s)
     return dd::weight_grad_lowk_supported(l->tokens, s.D, s.L, l->K, l->dtype == DD_BF16);
 }
 
+// Both gradients of an expanding layer with a handful of diagonals in one kernel (they read dY at the same shifted places).  It
+// is ahead of two such kernels wherever they run (1024^2, 4 diagonals, 25216 tokens 59 -> 41 us), and of the two products that
+// DD_ALGO_AUTO would take one by one up to 8 diagonals (us, one kernel and the two calls, 25216 tokens: 512^2, 8 diagonals 40 and
+// 47, 768^2, 6 43 and 58, 1024^2, 8 55 and 79; 3000 tokens: 512^2, 8 18 and 20) but on narrow layers with many tokens (256^2, 6
+// 29 and 26, 128^2, 4 33 and 18), where the sum over the workgroups weighs.
+bool wants_lowk_bwd(const dd_layer *l, const Shape &s)
+{
+    if (!s.expanding || !dd::lowk_bwd_supported(l->tokens, s.D, s.L, l->K, l->dtype == DD_BF16)) return false;
+    if (wants_lowk(l, s, false) && wants_lowk_wgrad(l, s)) return true;
+    return l->algo == DD_ALGO_AUTO && (s.L >= 512 || l->tokens <= 4096);
+}
+
 // the block dd_prepare fills: the operand of the forward product, then the one of the backward-input product
 size_t prepared_bytes(const Shape &s) { return 2 * dd::product_matrix_ws_bytes(s.D, s.L); }
 
@@ -359,6 +371,11 @@ dd_status dd_bwd(const dd_layer *layer, const void *X, const void *dY, const int
     const bool have_prepared = layer->algo == DD_ALGO_PREPARED;
     if (have_prepared && !prepared) return DD_ERR_INVALID_ARG;
     if (dd_status st = check_ws(ws, ws_bytes, bwd_ws_bytes(layer))) return st;
+    if (layer->tokens > 0 && X && dY && offsets && values && dX && dValues && aligned16(X) && aligned16(dY) && aligned16(dX) &&
+        wants_lowk_bwd(layer, s) && ws_bytes >= dd::weight_grad_lowk_ws_bytes(layer->tokens, s.D, s.L, layer->K)) {
+        const dd::WeightGradArgs a = {layer->tokens, s.D, s.L, layer->K, true, X, dY, offsets, dValues, ws};
+        return dd::launch_lowk_bwd(a, values, dX, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? DD_OK : DD_ERR_HIP;
+    }
     // The input gradient first: the weight gradient, issued right behind it, then finds in the memory-side cache
     // whatever of dY that cache could keep.  Both take their scratch from the same block, one after the other.
     if (dd_status st = dd_bwd_input(layer, dY, offsets, values, dX, have_prepared ? const_cast<void *>(prepared) : ws,

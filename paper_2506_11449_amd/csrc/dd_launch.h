@@ -68,6 +68,10 @@ hipError_t launch_product_lowk(const ProductArgs &a, hipStream_t stream);
 bool weight_grad_lowk_supported(int64_t T, int D, int L, int K, bool bf16);
 size_t weight_grad_lowk_ws_bytes(int64_t T, int D, int L, int K);
 hipError_t launch_weight_grad_lowk(const WeightGradArgs &a, hipStream_t stream);
+// Both gradients of an expanding (or square) layer from one reading of dY: a as for launch_weight_grad_lowk (A = X, B = dY), and
+// dX[t, p] = sum_k dY[t, (p + o_k) mod D] * values[k][p].  Bit for bit what the two launches give.
+bool lowk_bwd_supported(int64_t T, int D, int L, int K, bool bf16);
+hipError_t launch_lowk_bwd(const WeightGradArgs &a, const void *values, void *dX, hipStream_t stream);
 
 // matrix-core family (bf16 only, feature counts multiples of 128)
 bool product_matrix_supported(int64_t T, int D, int L, bool bf16);

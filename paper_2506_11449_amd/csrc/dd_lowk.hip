@@ -8,10 +8,11 @@
 //   * a tile of token rows is converted to fp32 once and laid out row-major in LDS, each row followed by a copy of its
 //     first columns, so that a cyclically shifted read never wraps (and, for the masked gather, with zeros where the
 //     source has no column);
-//   * a lane owns the column pairs 2*lane + 128*i + {0, 1}, i < NI: for a fixed i the 64 lanes of a wave read 128
-//     consecutive floats whatever the shift -- every bank twice, at any offset (the counters call half of the LDS clocks
-//     conflicts) -- and store 256 consecutive bytes;
-//   * the K x 2*NI weights a lane needs stay in registers for all rows of the tile, the K shifts in scalar registers.
+//   * a lane owns two columns of each of NI runs of 128 (LkColumns): the 64 lanes of a wave read 128 consecutive floats
+//     whatever the shift and store 256 consecutive bytes;
+//   * the K x 2*NI weights a lane needs stay in registers for all rows of the tile, the K shifts in scalar registers;
+//   * the backward pass of an expanding layer reads dY at the same shifted places for both gradients, so one kernel takes both:
+//     dY from memory and out of LDS once (1024^2, 4 diagonals, 25216 tokens: 41 us, floor 31; two kernels 59).
 #include "dd_common.h"
 #include "dd_launch.h"
 
@@ -33,6 +34,9 @@ constexpr int lowk_unroll(int K) { return K <= 8 ? K : (K <= 12 ? 12 : 16); }
 // most waves of a workgroup: the 2 * ni * kc weights and kc read positions of a lane must fit the registers that many
 // waves leave each other
 constexpr int lowk_max_waves(int ni, int kc) { return (2 * ni + 1) * kc <= 40 ? 16 : 8; }
+// the same where a lane keeps 2 * ni * kc sums beside the weights (both gradients at once)
+constexpr int lowk_bwd_max_waves(int ni, int kc) { return (4 * ni + 1) * kc <= 40 ? 16 : 8; }
+constexpr int kLkBwdMaxK = 8;
 
 struct LkPlan {
     int ni;         // column pairs per lane: a slab is 128 * ni columns
@@ -89,6 +93,35 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
+// Which two columns of each 128 a lane owns.  Neighbouring ones, 2 * lane and 2 * lane + 1, are moved from and to memory as
+// they are, four bytes a lane, but two lanes of a read out of LDS then meet in every bank.  The columns lane and lane + 64
+// are read without conflicts; in memory an even lane moves the pair lane / 2 of the 64 pairs and an odd lane the pair
+// 32 + lane / 2, and neighbouring lanes trade halves.
+template <bool SPLIT>
+struct LkColumns {
+    static constexpr int kSecond = SPLIT ? 64 : 1;
+    static __device__ __forceinline__ int first(int lane) { return SPLIT ? lane : 2 * lane; }
+    static __device__ __forceinline__ int pair(int lane) { return SPLIT ? (lane >> 1) + 32 * (lane & 1) : lane; }
+    static __device__ __forceinline__ uint32_t of_neighbour(uint32_t v) { return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0xb1, 0xf, 0xf, true)); }
+    // the pair that this lane moves, from its own columns
+    static __device__ __forceinline__ uint32_t pack(float a, float b, bool odd)
+    {
+        const uint32_t own = pack_bf16x2(a, b);
+        return SPLIT ? __builtin_amdgcn_perm(of_neighbour(own), own, odd ? 0x03020706u : 0x05040100u) : own;
+    }
+    // its own columns, from the pair that it moved
+    static __device__ __forceinline__ void unpack(uint32_t pair, bool odd, float &a, float &b)
+    {
+        const uint32_t other = SPLIT ? of_neighbour(pair) : pair;
+        a = __uint_as_float(SPLIT ? __builtin_amdgcn_perm(other, pair, odd ? 0x07060c0cu : 0x01000c0cu) : pair << 16);
+        b = __uint_as_float(SPLIT ? __builtin_amdgcn_perm(other, pair, odd ? 0x03020c0cu : 0x05040c0cu) : pair & 0xffff0000u);
+    }
+};
+// Diagonals from which on the reads weigh more than the halves that change lanes and the stores whose lanes are not in order.
+// 25216 tokens, us per product, neighbouring and split columns: 1024^2, 2 diagonals 20.5 and 21.2, 4 25.4 and 23.5, 8 37 and
+// 28.5; 1024 -> 2048, 1 34 and 37, 8 70 and 54; 768 -> 3072 (two pairs a lane), 3 49 and 55, 4 68 and 60.
+constexpr int lowk_split_from(int ni) { return ni == 1 ? 3 : 4; }
+
 // gather (MASKED = false):  dst[t, p] = sum_k src[t, (p + o_k) mod D] * v_k[p]            src [T x D], dst [T x L]
 // masked gather:            dst[t, q] = sum_{k: c < L} src[t, c] * v_k[c], c = (q - o_k) mod D   src [T x L], dst [T x D]
 // blockIdx.y: group of wg_slabs slabs, one per wave (times rowgroups waves that share the slab's rows);
@@ -97,14 +130,16 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 // for c < src_cols and 0 beyond; columns D .. wlds repeat columns 0 .. wlds - D.  Rows past the last token are zero.
 // While the waves work on a tile, the next one is on its way from memory into registers.
 template <int NI, int KC, bool MASKED>
-__global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_product_kernel(
+__global__ __launch_bounds__(64 * lowk_max_waves(NI, KC), NI == 1 ? 4 : 1) void lowk_product_kernel(
     int64_t T, int D, int L, int K, int wg_slabs, int rowgroups, int wlds, int rows, const uint16_t *__restrict__ src,
     const int *__restrict__ offsets, const uint16_t *__restrict__ values, uint16_t *__restrict__ dst)
 {
+    using Cols = LkColumns<(KC >= lowk_split_from(NI))>;
     extern __shared__ __align__(16) float lk_lds[];
     __shared__ int s_off[kLkMaxK];
     const int src_cols = MASKED ? L : D, dst_cols = MASKED ? D : L;
     const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
+    const bool odd = lane & 1;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     if (tid < KC) s_off[tid] = tid < K ? canonical_offset(offsets[tid], D) : 0;
@@ -161,12 +196,12 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_product_kern
         const int o = s_off[k];
         int s = MASKED ? j0 - o : j0 + o;   // logical column the slab's first destination column reads
         s = s < 0 ? s + D : (s >= D ? s - D : s);
-        start[k] = s + 2 * lane;
+        start[k] = s + Cols::first(lane);
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const int j = j0 + 2 * lane + 128 * i + e;
+                const int j = j0 + Cols::first(lane) + 128 * i + Cols::kSecond * e;
                 int c = j;
                 if (MASKED) {
                     c = j - o;
@@ -209,9 +244,10 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_product_kern
 #pragma unroll
                     for (int i = 0; i < NI; ++i) {
                         xv[k][i][0] = x[128 * i];
-                        xv[k][i][1] = x[128 * i + 1];
+                        xv[k][i][1] = x[128 * i + Cols::kSecond];
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);  // (short of registers the compiler waits for every read before the next)
 #pragma unroll
                 for (int k = 0; k < KB; ++k) {
                     if (kb + k >= KC) break;
@@ -224,7 +260,7 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_product_kern
             }
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                res[q][i] = pack_bf16x2(a0[i], a1[i]);
+                res[q][i] = Cols::pack(a0[i], a1[i], odd);
                 // Rounded here: left to the compiler the one instruction moves down to the store, the sums of all rows stay
                 // alive in its place, and kernels of four diagonals and more spill (768 -> 3072, 8 diagonals, 25216 tokens
                 // 449 us against 99, rounded by hand 105; 4096^2 711 against 128).
@@ -250,7 +286,7 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_product_kern
         for (int q = 0; q < RW; ++q) {
             const int r = first_row + q * rowgroups;
             if (r >= rows || t0 + r >= T) break;
-            uint32_t *out = reinterpret_cast<uint32_t *>(dst + (t0 + r) * dst_cols + j0) + lane;
+            uint32_t *out = reinterpret_cast<uint32_t *>(dst + (t0 + r) * dst_cols + j0) + Cols::pair(lane);
 #pragma unroll
             for (int i = 0; i < NI; ++i) out[64 * i] = res[q][i];
         }
@@ -260,21 +296,25 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_product_kern
 
 // ---- weight gradient:  dV[k][p] = sum_t A[t, p] * B[t, (p + o_k) mod D],  A [T x L] the short side, B [T x D] ----
 // The same tile image as the gather (rows of B in fp32, each followed by a copy of its first columns); a lane owns the
-// positions p = j0 + 2*lane + 128*i + {0, 1} and keeps one accumulator per position and diagonal for all tokens of its
-// workgroup.  Its own columns of A come straight from memory, four bytes per lane and row, one tile ahead.
+// positions and keeps one accumulator per position and diagonal for all tokens of its workgroup.  Its own columns of A come straight from memory, four bytes per lane and row, one tile ahead.
+// WITH_DX: also dX[t, p] = sum_k B[t, (p + o_k) mod D] * values[k][p], with the sums of lowk_product_kernel.
 // partial[chunk][k][p], chunk = blockIdx.x * rowgroups + (which of the waves that share a slab); lowk_reduce_kernel
 // adds the chunks in index order.
 constexpr int kLkMaxChunks = 512;
 constexpr size_t kLkPartialBytes = size_t(16) << 20;  // partial sums of all chunks, at most (or 64 chunks' worth)
 
-template <int NI, int KC>
-__global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel(
+template <int NI, int KC, bool WITH_DX>
+__global__ __launch_bounds__(64 * (WITH_DX ? lowk_bwd_max_waves(NI, KC) : lowk_max_waves(NI, KC))) void lowk_wgrad_kernel(
     int64_t T, int D, int L, int K, int wg_slabs, int rowgroups, int wlds, int rows, const uint16_t *__restrict__ A,
-    const uint16_t *__restrict__ B, const int *__restrict__ offsets, float *__restrict__ partial)
+    const uint16_t *__restrict__ B, const int *__restrict__ offsets, float *__restrict__ partial,
+    const uint16_t *__restrict__ values, uint16_t *__restrict__ dX)
 {
+    // (both gradients at once take as many vector instructions per read again: the reads weigh more from 7 diagonals on only)
+    using Cols = LkColumns<(KC >= (WITH_DX ? 7 : lowk_split_from(NI)))>;
     extern __shared__ __align__(16) float lk_lds[];
     __shared__ int s_off[kLkMaxK];
     const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
+    const bool odd = lane & 1;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     if (tid < KC) s_off[tid] = tid < K ? canonical_offset(offsets[tid], D) : 0;
@@ -310,7 +350,7 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel
         for (int q = 0; q < RW; ++q) {
             const int r = first_row + q * rowgroups;
             const bool there = r < rows && t0 + r < T;
-            const uint32_t *a = reinterpret_cast<const uint32_t *>(A + (there ? (t0 + r) * L + j0 : 0)) + lane;
+            const uint32_t *a = reinterpret_cast<const uint32_t *>(A + (there ? (t0 + r) * L + j0 : 0)) + Cols::pair(lane);
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const uint32_t v = a[64 * i];
@@ -343,10 +383,20 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel
     for (int k = 0; k < KC; ++k) {
         int s = j0 + s_off[k];
         s = s >= D ? s - D : s;
-        start[k] = s + 2 * lane;
+        start[k] = s + Cols::first(lane);
 #pragma unroll
         for (int i = 0; i < NI; ++i) acc[k][i][0] = acc[k][i][1] = 0.f;
     }
+    float w[WITH_DX ? KC : 1][NI][2];
+    if constexpr (WITH_DX)
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const uint16_t *v = values + (k < K ? size_t(k) * L : 0) + j0 + Cols::first(lane) + 128 * i;
+                w[k][i][0] = k < K ? bf16_to_f32(v[0]) : 0.f;
+                w[k][i][1] = k < K ? bf16_to_f32(v[Cols::kSecond]) : 0.f;
+            }
 
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         uint32_t cur_a[RW][NI];
@@ -356,19 +406,20 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel
             for (int i = 0; i < NI; ++i) cur_a[q][i] = next_a[q][i];
         const bool more = tile + gridDim.x < n_tiles;
         if (more) fetch((tile + gridDim.x) * rows);
+        uint32_t res[WITH_DX ? RW : 1][NI];
 #pragma unroll
         for (int q = 0; q < RW; ++q) {
             const int r = first_row + q * rowgroups;
             if (r >= rows) break;
             int row_at = r * wlds;
             asm volatile("" : "+s"(row_at));
-            float a0[NI], a1[NI];
+            float a0[NI], a1[NI], d0[NI], d1[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                a0[i] = __uint_as_float(cur_a[q][i] << 16);
-                a1[i] = __uint_as_float(cur_a[q][i] & 0xffff0000u);
+                Cols::unpack(cur_a[q][i], odd, a0[i], a1[i]);
+                d0[i] = d1[i] = 0.f;
             }
-            constexpr int KB = 8 / NI < KC ? 8 / NI : KC;
+            constexpr int kBatch = WITH_DX && KC > 6 ? 4 : 8, KB = kBatch / NI < KC ? kBatch / NI : KC;
 #pragma unroll
             for (int kb = 0; kb < KC; kb += KB) {
                 float xv[KB][NI][2];
@@ -379,9 +430,10 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel
 #pragma unroll
                     for (int i = 0; i < NI; ++i) {
                         xv[k][i][0] = x[128 * i];
-                        xv[k][i][1] = x[128 * i + 1];
+                        xv[k][i][1] = x[128 * i + Cols::kSecond];
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);  // (short of registers the compiler waits for every read before the next)
 #pragma unroll
                 for (int k = 0; k < KB; ++k) {
                     if (kb + k >= KC) break;
@@ -389,12 +441,31 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel
                     for (int i = 0; i < NI; ++i) {
                         acc[kb + k][i][0] = fmaf(a0[i], xv[k][i][0], acc[kb + k][i][0]);
                         acc[kb + k][i][1] = fmaf(a1[i], xv[k][i][1], acc[kb + k][i][1]);
+                        if constexpr (WITH_DX) {
+                            d0[i] = fmaf(xv[k][i][0], w[kb + k][i][0], d0[i]);
+                            d1[i] = fmaf(xv[k][i][1], w[kb + k][i][1], d1[i]);
+                        }
                     }
                 }
             }
+            if constexpr (WITH_DX)
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    res[q][i] = Cols::pack(d0[i], d1[i], odd);
+                    asm volatile("" : "+v"(res[q][i]));  // rounded here, as in lowk_product_kernel
+                }
         }
         __syncthreads();  // every wave is done with the tile in LDS
         if (more) park();
+        if constexpr (WITH_DX)
+#pragma unroll
+            for (int q = 0; q < RW; ++q) {
+                const int r = first_row + q * rowgroups;
+                if (r >= rows || tile * rows + r >= T) break;
+                uint32_t *out = reinterpret_cast<uint32_t *>(dX + (tile * rows + r) * L + j0) + Cols::pair(lane);
+#pragma unroll
+                for (int i = 0; i < NI; ++i) out[64 * i] = res[q][i];
+            }
         __syncthreads();  // the next tile is in LDS
     }
 
@@ -402,22 +473,28 @@ __global__ __launch_bounds__(64 * lowk_max_waves(NI, KC)) void lowk_wgrad_kernel
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
         if (k >= K) break;
-        float *out = partial + (size_t(chunk) * K + k) * L + j0 + 2 * lane;
+        float *out = partial + (size_t(chunk) * K + k) * L + j0 + Cols::first(lane);
 #pragma unroll
-        for (int i = 0; i < NI; ++i) *reinterpret_cast<float2 *>(out + 128 * i) = float2{acc[k][i][0], acc[k][i][1]};
+        for (int i = 0; i < NI; ++i) {
+            out[128 * i] = acc[k][i][0];
+            out[128 * i + Cols::kSecond] = acc[k][i][1];
+        }
     }
 }
 
-// dV[i..i+3] = partial[0][i..] + partial[1][i..] + ...: sixteen runs of consecutive chunks side by side, each summed in
-// index order with up to eight loads in flight, then the sixteen sums in run order.  n4 = K * L / 4.
-__global__ __launch_bounds__(1024) void lowk_reduce_kernel(int n4, int chunks, const float *__restrict__ partial,
-                                                           float *__restrict__ dV)
+// dV[i..i+3] = partial[0][i..] + partial[1][i..] + ...: sixty-four runs of consecutive chunks side by side, each summed in
+// index order with up to eight loads in flight, then the sums of the runs in order, by fours and those by sixteens.
+// n4 = K * L / 4.  Bound by latency; sixteen columns per workgroup, so that 4 diagonals of 1024 make 64 workgroups (64 columns
+// and sixteen runs, 16 workgroups: 6.7 us, now 3.9).
+constexpr int kLkRuns = 64, kLkRunCols = 16;
+__global__ __launch_bounds__(kLkRuns *kLkRunCols) void lowk_reduce_kernel(int n4, int chunks, const float *__restrict__ partial,
+                                                                          float *__restrict__ dV)
 {
-    __shared__ f32x4 run_s[15][64];
-    const int run = threadIdx.x >> 6, g = threadIdx.x & 63;
-    const int i4 = blockIdx.x * 64 + g;
+    __shared__ f32x4 run_s[kLkRuns][kLkRunCols];
+    const int run = threadIdx.x / kLkRunCols, g = threadIdx.x % kLkRunCols;
+    const int i4 = blockIdx.x * kLkRunCols + g;
     const bool active = i4 < n4;
-    const int per_run = (chunks + 15) / 16;
+    const int per_run = (chunks + kLkRuns - 1) / kLkRuns;
     const int s_begin = min(run * per_run, chunks), s_end = min(s_begin + per_run, chunks);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     if (active) {
@@ -436,11 +513,17 @@ __global__ __launch_bounds__(1024) void lowk_reduce_kernel(int n4, int chunks, c
             src += n4;
         }
     }
-    if (run > 0) run_s[run - 1][g] = acc;
+    run_s[run][g] = acc;
+    __syncthreads();
+    if (run < kLkRuns / 4) {
+        acc = ((run_s[4 * run][g] + run_s[4 * run + 1][g]) + run_s[4 * run + 2][g]) + run_s[4 * run + 3][g];
+    }
+    __syncthreads();
+    if (run < kLkRuns / 4) run_s[run][g] = acc;
     __syncthreads();
     if (run == 0 && active) {
 #pragma unroll
-        for (int r = 0; r < 15; ++r) acc += run_s[r][g];
+        for (int r = 1; r < kLkRuns / 4; ++r) acc += run_s[r][g];
         reinterpret_cast<f32x4 *>(dV)[i4] = acc;
     }
 }
@@ -550,13 +633,14 @@ size_t weight_grad_lowk_ws_bytes(int64_t T, int D, int L, int K)
     return size_t(lowk_wgrad_chunk_cap(pl, L, K)) * K * L * sizeof(float);
 }
 
+// Workgroups side by side over the tokens: what decides how the tokens are dealt, and with it the bits of the sums -- the same
+// for the weight gradient alone and for both gradients.
 template <int NI, int KC>
-static hipError_t launch_lowk_wgrad(const WeightGradArgs &a, const LkPlan &pl, hipStream_t stream)
+static hipError_t lowk_wgrad_workers(const LkPlan &pl, size_t lds_max, int L, int K, int64_t &workers)
 {
-    const void *kernel = reinterpret_cast<const void *>(&lowk_wgrad_kernel<NI, KC>);
+    const void *kernel = reinterpret_cast<const void *>(&lowk_wgrad_kernel<NI, KC, false>);
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
     if (hipError_t e = allow_dynamic_lds(kernel, kLkLdsMax, lds_allowed)) return e;
-    const size_t lds_max = size_t(pl.rows_max) * pl.wlds * sizeof(float);
     static std::atomic<uint64_t> resident[17];  // LDS bytes << 16 | workgroups
     const uint64_t seen = resident[pl.threads / 64].load(std::memory_order_relaxed);
     int per_cu = int(seen & 0xffff);
@@ -565,21 +649,35 @@ static hipError_t launch_lowk_wgrad(const WeightGradArgs &a, const LkPlan &pl, h
         if (per_cu < 1) return hipErrorInvalidValue;
         resident[pl.threads / 64].store(uint64_t(lds_max) << 16 | uint64_t(per_cu), std::memory_order_relaxed);
     }
-    int64_t workers = int64_t(kLkCUs) * per_cu / pl.groups;
-    const int64_t cap = lowk_wgrad_chunk_cap(pl, a.L, a.K) / pl.rowgroups;
+    workers = int64_t(kLkCUs) * per_cu / pl.groups;
+    const int64_t cap = lowk_wgrad_chunk_cap(pl, L, K) / pl.rowgroups;
     if (workers > cap) workers = cap;
     if (workers < 1) workers = 1;
+    return hipSuccess;
+}
+
+// With `values` and `dX` given, the input gradient of the layer from the same tiles (lowk_bwd_supported).
+template <int NI, int KC, bool WITH_DX>
+static hipError_t launch_lowk_wgrad(const WeightGradArgs &a, const LkPlan &pl, const uint16_t *values, uint16_t *dX, hipStream_t stream)
+{
+    const void *kernel = reinterpret_cast<const void *>(&lowk_wgrad_kernel<NI, KC, WITH_DX>);
+    static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
+    if (hipError_t e = allow_dynamic_lds(kernel, kLkLdsMax, lds_allowed)) return e;
+    const size_t lds_max = size_t(pl.rows_max) * pl.wlds * sizeof(float);
+    int64_t workers = 0;
+    if (hipError_t e = lowk_wgrad_workers<NI, KC>(pl, lds_max, a.L, a.K, workers)) return e;
     const int rows = lowk_rows(pl, a.T, workers);
     const int64_t n_tiles = (a.T + rows - 1) / rows;
     if (workers > n_tiles) workers = n_tiles;
     const dim3 grid{unsigned(workers), unsigned(pl.groups), 1u};
     float *partial = static_cast<float *>(a.ws);
-    hipLaunchKernelGGL((lowk_wgrad_kernel<NI, KC>), grid, dim3(pl.threads), lds_max, stream, a.T, a.D, a.L, a.K,
+    hipLaunchKernelGGL((lowk_wgrad_kernel<NI, KC, WITH_DX>), grid, dim3(pl.threads), lds_max, stream, a.T, a.D, a.L, a.K,
                        pl.wg_slabs, pl.rowgroups, pl.wlds, rows, static_cast<const uint16_t *>(a.A),
-                       static_cast<const uint16_t *>(a.B), a.offsets, partial);
+                       static_cast<const uint16_t *>(a.B), a.offsets, partial, values, dX);
     if (hipError_t e = hipGetLastError()) return e;
     const int n4 = a.K * a.L / 4, chunks = int(workers) * pl.rowgroups;
-    hipLaunchKernelGGL(lowk_reduce_kernel, dim3((n4 + 63) / 64), dim3(1024), 0, stream, n4, chunks, partial, a.dValues);
+    hipLaunchKernelGGL(lowk_reduce_kernel, dim3((n4 + kLkRunCols - 1) / kLkRunCols), dim3(kLkRuns * kLkRunCols), 0, stream, n4, chunks,
+                       partial, a.dValues);
     return hipGetLastError();
 }
 
@@ -587,16 +685,16 @@ template <int NI>
 static hipError_t launch_lowk_wgrad_k(const WeightGradArgs &a, const LkPlan &pl, hipStream_t stream)
 {
     switch (lowk_unroll(a.K)) {
-    case 1: return launch_lowk_wgrad<NI, 1>(a, pl, stream);
-    case 2: return launch_lowk_wgrad<NI, 2>(a, pl, stream);
-    case 3: return launch_lowk_wgrad<NI, 3>(a, pl, stream);
-    case 4: return launch_lowk_wgrad<NI, 4>(a, pl, stream);
-    case 5: return launch_lowk_wgrad<NI, 5>(a, pl, stream);
-    case 6: return launch_lowk_wgrad<NI, 6>(a, pl, stream);
-    case 7: return launch_lowk_wgrad<NI, 7>(a, pl, stream);
-    case 8: return launch_lowk_wgrad<NI, 8>(a, pl, stream);
-    case 12: return launch_lowk_wgrad<NI, 12>(a, pl, stream);
-    default: return launch_lowk_wgrad<NI, 16>(a, pl, stream);
+    case 1: return launch_lowk_wgrad<NI, 1, false>(a, pl, nullptr, nullptr, stream);
+    case 2: return launch_lowk_wgrad<NI, 2, false>(a, pl, nullptr, nullptr, stream);
+    case 3: return launch_lowk_wgrad<NI, 3, false>(a, pl, nullptr, nullptr, stream);
+    case 4: return launch_lowk_wgrad<NI, 4, false>(a, pl, nullptr, nullptr, stream);
+    case 5: return launch_lowk_wgrad<NI, 5, false>(a, pl, nullptr, nullptr, stream);
+    case 6: return launch_lowk_wgrad<NI, 6, false>(a, pl, nullptr, nullptr, stream);
+    case 7: return launch_lowk_wgrad<NI, 7, false>(a, pl, nullptr, nullptr, stream);
+    case 8: return launch_lowk_wgrad<NI, 8, false>(a, pl, nullptr, nullptr, stream);
+    case 12: return launch_lowk_wgrad<NI, 12, false>(a, pl, nullptr, nullptr, stream);
+    default: return launch_lowk_wgrad<NI, 16, false>(a, pl, nullptr, nullptr, stream);
     }
 }
 
@@ -608,6 +706,41 @@ hipError_t launch_weight_grad_lowk(const WeightGradArgs &a, hipStream_t stream)
     case 4: return launch_lowk_wgrad_k<4>(a, pl, stream);
     case 2: return launch_lowk_wgrad_k<2>(a, pl, stream);
     default: return launch_lowk_wgrad_k<1>(a, pl, stream);
+    }
+}
+
+template <int NI>
+static hipError_t launch_lowk_bwd_k(const WeightGradArgs &a, const LkPlan &pl, const uint16_t *v, uint16_t *dX, hipStream_t stream)
+{
+    switch (lowk_unroll(a.K)) {
+    case 1: return launch_lowk_wgrad<NI, 1, true>(a, pl, v, dX, stream);
+    case 2: return launch_lowk_wgrad<NI, 2, true>(a, pl, v, dX, stream);
+    case 3: return launch_lowk_wgrad<NI, 3, true>(a, pl, v, dX, stream);
+    case 4: return launch_lowk_wgrad<NI, 4, true>(a, pl, v, dX, stream);
+    case 5: return launch_lowk_wgrad<NI, 5, true>(a, pl, v, dX, stream);
+    case 6: return launch_lowk_wgrad<NI, 6, true>(a, pl, v, dX, stream);
+    case 7: return launch_lowk_wgrad<NI, 7, true>(a, pl, v, dX, stream);
+    default: return launch_lowk_wgrad<NI, 8, true>(a, pl, v, dX, stream);
+    }
+}
+
+bool lowk_bwd_supported(int64_t T, int D, int L, int K, bool bf16)
+{
+    if (!weight_grad_lowk_supported(T, D, L, K, bf16) || K > kLkBwdMaxK) return false;
+    const LkPlan pl = plan_lowk(D, L, K);
+    return pl.threads <= 64 * lowk_bwd_max_waves(pl.ni, K);
+}
+
+hipError_t launch_lowk_bwd(const WeightGradArgs &a, const void *values, void *dX, hipStream_t stream)
+{
+    const LkPlan pl = plan_lowk(a.D, a.L, a.K);
+    if (!lowk_bwd_supported(a.T, a.D, a.L, a.K, a.bf16)) return hipErrorInvalidValue;
+    const uint16_t *v = static_cast<const uint16_t *>(values);
+    uint16_t *out = static_cast<uint16_t *>(dX);
+    switch (pl.ni) {
+    case 4: return launch_lowk_bwd_k<4>(a, pl, v, out, stream);
+    case 2: return launch_lowk_bwd_k<2>(a, pl, v, out, stream);
+    default: return launch_lowk_bwd_k<1>(a, pl, v, out, stream);
     }
 }
 
