@@ -371,10 +371,28 @@ dd_status dd_bwd(const dd_layer *layer, const void *X, const void *dY, const int
     const bool have_prepared = layer->algo == DD_ALGO_PREPARED;
     if (have_prepared && !prepared) return DD_ERR_INVALID_ARG;
     if (dd_status st = check_ws(ws, ws_bytes, bwd_ws_bytes(layer))) return st;
-    if (layer->tokens > 0 && X && dY && offsets && values && dX && dValues && aligned16(X) && aligned16(dY) && aligned16(dX) &&
-        wants_lowk_bwd(layer, s) && ws_bytes >= dd::weight_grad_lowk_ws_bytes(layer->tokens, s.D, s.L, layer->K)) {
-        const dd::WeightGradArgs a = {layer->tokens, s.D, s.L, layer->K, true, X, dY, offsets, dValues, ws};
-        return dd::launch_lowk_bwd(a, values, dX, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? DD_OK : DD_ERR_HIP;
+    if (layer->tokens > 0 && !have_prepared && X && dY && offsets && values && dX && dValues) {  // both gradients in one kernel?
+        const bool aligned_input = aligned16(dY) && aligned16(dX), aligned_weight = aligned16(X) && aligned16(dY);
+        const dd::WeightGradArgs w = {layer->tokens, s.D, s.L, layer->K, layer->dtype == DD_BF16, s.expanding ? X : dY, s.expanding ? dY : X,
+                                      offsets, dValues, ws};
+        if (aligned_input && aligned_weight && wants_lowk_bwd(layer, s) &&
+            ws_bytes >= dd::weight_grad_lowk_ws_bytes(layer->tokens, s.D, s.L, layer->K))
+            return dd::launch_lowk_bwd(w, values, dX, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? DD_OK : DD_ERR_HIP;
+        dd::ProductArgs p;
+        p.T = layer->tokens;
+        p.D = s.D;
+        p.L = s.L;
+        p.K = layer->K;
+        p.bf16 = w.bf16;
+        p.masked = !s.expanding;
+        p.src = dY;
+        p.offsets = offsets;
+        p.values = values;
+        p.dst = dX;
+        const bool vector_input = !(aligned_input && (wants_matrix(layer, s) || wants_lowk(layer, s, p.masked)));
+        const bool vector_weight = !(aligned_weight && (wants_matrix_wgrad(layer, s) || wants_lowk_wgrad(layer, s)));
+        if (layer->algo != DD_ALGO_MATRIX && vector_input && vector_weight && dd::bwd_few_tokens(p))
+            return dd::launch_bwd_few_tokens(p, w, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? DD_OK : DD_ERR_HIP;
     }
     // The input gradient first: the weight gradient, issued right behind it, then finds in the memory-side cache
     // whatever of dY that cache could keep.  Both take their scratch from the same block, one after the other.

@@ -105,6 +105,10 @@ hipError_t launch_select_prepare(int D, int L, int K, bool expanding, const floa
 size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16);
 hipError_t launch_weight_grad_vector(const WeightGradArgs &a, hipStream_t stream);
 
+// Both gradients in one launch for few tokens, bit for bit the two vector launches: p the input gradient, w the weight gradient.
+bool bwd_few_tokens(const ProductArgs &p);
+hipError_t launch_bwd_few_tokens(const ProductArgs &p, const WeightGradArgs &w, hipStream_t stream);
+
 // matrix-core family (bf16 only, both feature counts multiples of 192 or both multiples of 128)
 bool weight_grad_matrix_supported(int64_t T, int D, int L, bool bf16);
 size_t weight_grad_matrix_ws_bytes(int64_t T, int D, int L, int K);

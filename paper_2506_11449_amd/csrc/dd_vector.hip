@@ -170,24 +170,23 @@ __device__ __forceinline__ void multiply_pair(float *acc, const unsigned char *p
     }
 }
 
-// A workgroup holds one tile of tokens (blockIdx.x) and one group of destination column blocks (blockIdx.y; 64
+// A workgroup holds one tile of tokens (tile_x) and one group of destination column blocks (tile_y; 64
 // columns, one wave each); `k_parts` neighbouring waves share a column block and take a part of the diagonals each, whose
 // sums are added through LDS in order -- for calls with so few tokens that the chip would otherwise stand idle.  Every
 // wave lists the diagonals of its part that meet its columns (all of them for the plain gather; for the masked gather
 // onto a longer side most miss a given block), and walks the list eight at a time, the weights of the next eight on
 // their way while the current eight are multiplied.
 template <class S, int NT, bool MASKED>
-__global__ __launch_bounds__(64 * kMaxWaves) void product_tiled_kernel(
-    int64_t T, int D, int L, int K, int k_parts, const typename S::storage *__restrict__ src,
-    const int *__restrict__ offsets, const typename S::storage *__restrict__ values, typename S::storage *__restrict__ dst)
+__device__ __forceinline__ void product_tiled(unsigned char *tile, unsigned tile_x, int tile_y, int64_t T, int D, int L, int K, int k_parts,
+                                              const typename S::storage *__restrict__ src, const int *__restrict__ offsets,
+                                              const typename S::storage *__restrict__ values, typename S::storage *__restrict__ dst)
 {
     constexpr int G = Group<S>::kTokens, TT = NT * G, STRIDE = tile_stride(NT), KB = 8;
     using weight = typename Group<S>::weight;
-    extern __shared__ __align__(16) unsigned char tile[];
     const int src_cols = MASKED ? L : D, dst_cols = MASKED ? D : L;
     const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     unsigned *list = reinterpret_cast<unsigned *>(tile + size_t(src_cols + 1) * STRIDE) + wave * kListLen;
-    const int64_t t0 = int64_t(blockIdx.x) * TT;
+    const int64_t t0 = int64_t(tile_x) * TT;
 
     const int rows = int(min(T - t0, int64_t(TT)));  // tokens past the last one repeat it; their results are not stored
     const unsigned n_groups = unsigned(src_cols) * NT;
@@ -210,7 +209,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void product_tiled_kernel(
     const int blocks_per_group = (threads >> 6) / k_parts;
     const int part = wave % k_parts, local_block = wave / k_parts;
     const int k_lo = int(int64_t(part) * K / k_parts), k_hi = int(int64_t(part + 1) * K / k_parts);
-    const int j0 = (int(blockIdx.y) * blocks_per_group + local_block) * 64, j = j0 + lane;
+    const int j0 = (tile_y * blocks_per_group + local_block) * 64, j = j0 + lane;
     const bool active = j < dst_cols;
     float acc[TT];
 #pragma unroll
@@ -299,6 +298,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void product_tiled_kernel(
                 if (t < rows) S::store(out + j, acc[t]);
         }
     }
+}
+
+template <class S, int NT, bool MASKED>
+__global__ __launch_bounds__(64 * kMaxWaves) void product_tiled_kernel(
+    int64_t T, int D, int L, int K, int k_parts, const typename S::storage *__restrict__ src,
+    const int *__restrict__ offsets, const typename S::storage *__restrict__ values, typename S::storage *__restrict__ dst)
+{
+    extern __shared__ __align__(16) unsigned char tile[];
+    product_tiled<S, NT, MASKED>(tile, blockIdx.x, int(blockIdx.y), T, D, L, K, k_parts, src, offsets, values, dst);
 }
 
 // Plans weigh some dozens of candidates, about half a microsecond of host time: each thread remembers the last few (a plan is a
@@ -513,13 +521,10 @@ __device__ __forceinline__ float multiply_rows(const typename S::storage *x, con
 // the diagonals share the rows in L2, and the faster the threads go the further they drift apart there (9800^2, 30 diagonals,
 // fp32, 3000 tokens 611 us, by fours 1026).
 template <class S, int AHEAD>
-__global__ __launch_bounds__(kWgThreads) void weight_grad_partial_kernel(
-    int64_t T, int D, int L, int K, int splits, const typename S::storage *__restrict__ A,
-    const typename S::storage *__restrict__ B, const int *__restrict__ offsets, float *__restrict__ partial)
+__device__ __forceinline__ void weight_grad_partial(int p, int k, int s, int64_t T, int D, int L, int K, int splits,
+                                                    const typename S::storage *__restrict__ A, const typename S::storage *__restrict__ B,
+                                                    const int *__restrict__ offsets, float *__restrict__ partial)
 {
-    const int p = blockIdx.x * kWgThreads + threadIdx.x;
-    const int k = blockIdx.y;
-    const int s = blockIdx.z;
     if (p >= L) return;
     const int64_t per = (T + splits - 1) / splits;
     const int64_t t0 = min(s * per, T), t1 = min(t0 + per, T);
@@ -537,6 +542,34 @@ __global__ __launch_bounds__(kWgThreads) void weight_grad_partial_kernel(
         else if (left > 0) acc += multiply_rows<S, 4>(x, y, L, D, int(left));
     }
     partial[(size_t(s) * K + k) * L + p] = acc;
+}
+
+template <class S, int AHEAD>
+__global__ __launch_bounds__(kWgThreads) void weight_grad_partial_kernel(
+    int64_t T, int D, int L, int K, int splits, const typename S::storage *__restrict__ A,
+    const typename S::storage *__restrict__ B, const int *__restrict__ offsets, float *__restrict__ partial)
+{
+    weight_grad_partial<S, AHEAD>(int(blockIdx.x * kWgThreads + threadIdx.x), blockIdx.y, blockIdx.z, T, D, L, K, splits, A, B, offsets, partial);
+}
+
+// Both gradients of a layer for few tokens in one launch, each with the arithmetic of its own kernel: workgroups below `products`
+// take a tile of dX (MASKED, k_parts, grid_y: as planned for the product), the others entries of dV, `across` workgroups along a
+// diagonal.  Each of the two is a chain of memory latencies that leaves most of the chip idle, so side by side they take little
+// more than one of them (us, two launches and one, fp32: 64^2, 25 diagonals, 16 tokens 6.9 and 5.1; 257 x 255, 12, 130 tokens 9.1
+// and 4.5; 768 -> 3072, 153, 16 tokens 9.1 and 6.7; 1023 x 1001, 409, 192 tokens, where either fills the chip, 40.5 and 40.0).
+template <class S, int NT, bool MASKED>
+__global__ __launch_bounds__(64 * kMaxWaves) void bwd_few_tokens_kernel(
+    int64_t T, int D, int L, int K, int k_parts, int grid_y, unsigned products, unsigned across, const typename S::storage *__restrict__ dY,
+    const typename S::storage *__restrict__ A, const typename S::storage *__restrict__ B, const int *__restrict__ offsets,
+    const typename S::storage *__restrict__ values, typename S::storage *__restrict__ dX, float *__restrict__ dV)
+{
+    extern __shared__ __align__(16) unsigned char tile[];
+    if (blockIdx.x < products) {
+        product_tiled<S, NT, MASKED>(tile, blockIdx.x / unsigned(grid_y), int(blockIdx.x % unsigned(grid_y)), T, D, L, K, k_parts, dY, offsets, values, dX);
+    } else {
+        const unsigned at = blockIdx.x - products;
+        weight_grad_partial<S, 16>(int(at % across * blockDim.x + threadIdx.x), int(at / across), 0, T, D, L, K, 1, A, B, offsets, dV);
+    }
 }
 
 __device__ __forceinline__ float multiply_group(f32x4v a, f32x4v b, float acc)
@@ -874,6 +907,39 @@ static hipError_t launch_weight_grad_t(const WeightGradArgs &a, hipStream_t stre
 hipError_t launch_weight_grad_vector(const WeightGradArgs &a, hipStream_t stream)
 {
     return a.bf16 ? launch_weight_grad_t<BF16>(a, stream) : launch_weight_grad_t<F32>(a, stream);
+}
+
+template <class S, int NT, bool MASKED>
+static hipError_t launch_bwd_few(const ProductArgs &p, const WeightGradArgs &w, const TiledPlan &pl, hipStream_t stream)
+{
+    using st = typename S::storage;
+    static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&bwd_few_tokens_kernel<S, NT, MASKED>), int(kLdsPerCu), lds_allowed)) return e;
+    const unsigned threads = 64u * unsigned(pl.waves), products = pl.grid_x * unsigned(pl.grid_y), across = (unsigned(p.L) + threads - 1) / threads;
+    hipLaunchKernelGGL((bwd_few_tokens_kernel<S, NT, MASKED>), dim3(products + across * unsigned(p.K)), dim3(threads), pl.lds, stream, p.T, p.D,
+                       p.L, p.K, pl.k_parts, pl.grid_y, products, across, static_cast<const st *>(p.src), static_cast<const st *>(w.A),
+                       static_cast<const st *>(w.B), p.offsets, static_cast<const st *>(p.values), static_cast<st *>(p.dst), w.dValues);
+    return hipGetLastError();
+}
+
+template <class S, bool MASKED>
+static hipError_t launch_bwd_few(const ProductArgs &p, const WeightGradArgs &w, const TiledPlan &pl, hipStream_t stream)
+{
+    return pl.nt == 4   ? launch_bwd_few<S, 4, MASKED>(p, w, pl, stream)
+           : pl.nt == 2 ? launch_bwd_few<S, 2, MASKED>(p, w, pl, stream)
+                        : launch_bwd_few<S, 1, MASKED>(p, w, pl, stream);
+}
+
+bool bwd_few_tokens(const ProductArgs &p)
+{
+    return p.T > 0 && wg_few_tokens(p.T, p.L, p.K) && plan_tiled(p.T, p.D, p.L, p.K, p.bf16, p.masked).nt != 0;
+}
+
+hipError_t launch_bwd_few_tokens(const ProductArgs &p, const WeightGradArgs &w, hipStream_t stream)
+{
+    const TiledPlan pl = plan_tiled(p.T, p.D, p.L, p.K, p.bf16, p.masked);
+    if (p.bf16) return p.masked ? launch_bwd_few<BF16, true>(p, w, pl, stream) : launch_bwd_few<BF16, false>(p, w, pl, stream);
+    return p.masked ? launch_bwd_few<F32, true>(p, w, pl, stream) : launch_bwd_few<F32, false>(p, w, pl, stream);
 }
 
 }  // namespace dd
