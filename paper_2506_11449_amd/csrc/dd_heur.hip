@@ -11,7 +11,7 @@
 //      NaN -- the lowest rank there is -- for the diagonals that have just left;
 //      new = TopK(K)                                         the K - n_drop kept ones and the n_drop grown ones
 // Both selections order equal scores by lower index and NaN lowest, and emit ascending indices.
-// Bound by latency (one workgroup, two trips to memory, two selections): D = 3072, K = 307 12 us in one launch, where five
+// Bound by latency (one workgroup, two trips to memory, two selections): D = 3072, K = 307 10.5 us in one launch, where five
 // launches (table, selection, scores, selection, sources) took 33 us one after the other.  Beyond 16384 candidates the 256
 // words that a thread holds do not fit its registers: 135-175 us at 16385 (the five launches 149-173), 218-288 us at 65536
 // (571-655), with 10 and 90 % of the candidates active.
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(kHeurThreads) void diag_magnitude_kernel(int L, con
 
 // One workgroup.  slot: table offset -> position in `offsets` (-1: not active), D entries in LDS or, for more candidates
 // than fit there, in the caller's scratch.
-template <int SLOTS, bool TABLE_IN_LDS>
-__global__ __launch_bounds__(kSelectThreads) void heur_update_kernel(int D, int K, int n_keep,
+template <int THREADS, int SLOTS, bool TABLE_IN_LDS>
+__global__ __launch_bounds__(THREADS) void heur_update_kernel(int D, int K, int n_keep,
                                                                      const int *__restrict__ offsets,
                                                                      const float *__restrict__ magnitudes,
                                                                      const float *__restrict__ random,
@@ -55,27 +55,27 @@ __global__ __launch_bounds__(kSelectThreads) void heur_update_kernel(int D, int 
                                                                      int *__restrict__ source, int *__restrict__ table)
 {
     extern __shared__ int lds_table[];
-    __shared__ __attribute__((aligned(16))) SelectScratch<kSelectThreads, SLOTS> scratch;
+    __shared__ __attribute__((aligned(16))) SelectScratch<THREADS, SLOTS> scratch;
     int *slot = TABLE_IN_LDS ? lds_table : table;
     const int tid = threadIdx.x;
     float r[SLOTS];  // requested first: needed last
 #pragma unroll
-    for (int j = 0; j < SLOTS; ++j) r[j] = random[min(j * kSelectThreads + tid, D - 1)];
-    for (int i = tid; i < D; i += kSelectThreads) slot[i] = -1;
+    for (int j = 0; j < SLOTS; ++j) r[j] = random[min(j * THREADS + tid, D - 1)];
+    for (int i = tid; i < D; i += THREADS) slot[i] = -1;
     __syncthreads();  // one workgroup: its own writes above are ordered before those below
-    for (int k = tid; k < K; k += kSelectThreads) slot[canonical_offset(offsets[k], D)] = k;
+    for (int k = tid; k < K; k += THREADS) slot[canonical_offset(offsets[k], D)] = k;
     __syncthreads();
     int mine[SLOTS], place[SLOTS];
     uint32_t key[SLOTS];
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
-        mine[j] = slot[min(j * kSelectThreads + tid, D - 1)];
+        mine[j] = slot[min(j * THREADS + tid, D - 1)];
         const float m = mine[j] >= 0 ? magnitudes[mine[j]] : -INFINITY;
         key[j] = score_key(m != m ? -1.f : m);
         place[j] = -1;
     }
     if (n_keep > 0) {
-        select_block<kSelectThreads, SLOTS>(D, n_keep, key, scratch, place);
+        select_block<THREADS, SLOTS, true>(D, n_keep, key, scratch, place);
         __syncthreads();
     }
 #pragma unroll
@@ -83,11 +83,11 @@ __global__ __launch_bounds__(kSelectThreads) void heur_update_kernel(int D, int 
         const float grow = r[j] != r[j] ? -INFINITY : r[j];
         key[j] = score_key(place[j] >= 0 ? INFINITY : (mine[j] >= 0 ? NAN : grow));
     }
-    select_block<kSelectThreads, SLOTS>(D, K, key, scratch, place);
+    select_block<THREADS, SLOTS>(D, K, key, scratch, place);
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j)
         if (place[j] >= 0) {
-            new_offsets[place[j]] = j * kSelectThreads + tid;
+            new_offsets[place[j]] = j * THREADS + tid;
             source[place[j]] = mine[j];
         }
 }
@@ -111,27 +111,36 @@ size_t diagheur_ws_bytes(int D, int K)
     return 2 * up(size_t(D) * 4) + up(size_t(K) * 4);
 }
 
-template <int SLOTS, bool TABLE_IN_LDS>
+template <int THREADS, int SLOTS, bool TABLE_IN_LDS>
 static hipError_t launch_heur(int D, int K, int n_keep, const int *offsets, const float *magnitudes, const float *random,
                               int *new_offsets, int *source, void *ws, hipStream_t stream)
 {
-    const int lds = TABLE_IN_LDS ? SLOTS * kSelectThreads * int(sizeof(int)) : 0;
+    const int lds = TABLE_IN_LDS ? SLOTS * THREADS * int(sizeof(int)) : 0;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
     if (lds)
-        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&heur_update_kernel<SLOTS, TABLE_IN_LDS>), lds, lds_allowed)) return e;
-    hipLaunchKernelGGL((heur_update_kernel<SLOTS, TABLE_IN_LDS>), dim3(1), dim3(kSelectThreads), lds, stream, D, K, n_keep, offsets,
+        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&heur_update_kernel<THREADS, SLOTS, TABLE_IN_LDS>), lds, lds_allowed)) return e;
+    hipLaunchKernelGGL((heur_update_kernel<THREADS, SLOTS, TABLE_IN_LDS>), dim3(1), dim3(THREADS), lds, stream, D, K, n_keep, offsets,
                        magnitudes, random, new_offsets, source, static_cast<int *>(ws));
     return hipGetLastError();
 }
 
+// Threads as for one score vector (select_threads: what a pass costs grows with the waves that meet at its barrier): 128
+// candidates 6.6 us with 1024 threads, 4.6 with 256, 768 7.1 and 6.5, 2048 10 and 9.4.
 hipError_t launch_diagheur_update(int D, int K, int n_drop, const int *offsets, const float *magnitudes,
                                   const float *random, int *new_offsets, int *source, void *ws, hipStream_t stream)
 {
-    const int slots = (D + kSelectThreads - 1) / kSelectThreads, n_keep = K - n_drop;
-    if (slots <= 1) return launch_heur<1, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
-    if (slots <= 4) return launch_heur<4, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
-    if (slots <= 16) return launch_heur<16, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
-    return launch_heur<kSelectMaxSlots, false>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    const int n_keep = K - n_drop;
+    if (select_threads(1, D) == kSelectThreadsFew) {
+        constexpr int kFew = kSelectThreadsFew;
+        const int slots = (D + kFew - 1) / kFew;
+        if (slots <= 1) return launch_heur<kFew, 1, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+        if (slots <= 4) return launch_heur<kFew, 4, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+        return launch_heur<kFew, 8, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    }
+    const int slots = (D + kSelectThreads - 1) / kSelectThreads;
+    if (slots <= 4) return launch_heur<kSelectThreads, 4, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    if (slots <= 16) return launch_heur<kSelectThreads, 16, true>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
+    return launch_heur<kSelectThreads, kSelectMaxSlots, false>(D, K, n_keep, offsets, magnitudes, random, new_offsets, source, ws, stream);
 }
 
 }  // namespace dd
