@@ -34,7 +34,10 @@
  *     takes them there at every density but the extreme one -- for a handful of diagonals (K <= 16 and, for a
  *     product whose output is W columns wide, K * W <= D * L / 96; for dd_bwd_weight K <= D / 192; Sec. 4.4's
  *     regime of >= 99 % sparsity) it takes vector kernels built for that case, whose time follows K down to
- *     the cost of reading the input and writing the output once -- and the vector kernels everywhere else,
+ *     the cost of reading the input and writing the output once -- and the vector kernels everywhere else, except that
+ *     from 256 tokens on bf16 layers with M and N multiples of 8 (256 <= max(M, N) <= 2048) go to the matrix cores where
+ *     that is faster: with the same results, inputs that are not finite and repeated offsets included.  The products need
+ *     scratch for it (dd_workspace_bytes); without it they take the vector kernels.  Those serve
  *     also for a matrix that is not 16-byte aligned (a view that starts at an odd element): such a call is legal under DD_ALGO_AUTO
  *     and several times slower; DD_ALGO_MATRIX / DD_ALGO_PREPARED report it as DD_ERR_UNSUPPORTED instead.
  *     DD_ERR_HIP: the launch itself failed.

@@ -78,6 +78,24 @@ bool wants_lowk_wgrad(const dd_layer *l, const Shape &s)
     return dd::weight_grad_lowk_supported(l->tokens, s.D, s.L, l->K, l->dtype == DD_BF16);
 }
 
+// Widths that are multiples of eight but not of 128: the matrix cores on an operand padded with zeros, where that is ahead of the
+// vector kernels and the caller's scratch has room for the operand (it may be the smaller scratch of the vector kernels).  Scratch
+// is asked for wherever it might be of use at that many tokens or more.
+constexpr int64_t kRaggedTokens = 256;  // the fewest for which the two launches were ever ahead (1496^2, 40 % of the diagonals)
+bool may_be_ragged(const dd_layer *l, const Shape &s)
+{
+    return l->algo == DD_ALGO_AUTO && l->tokens >= kRaggedTokens && !wants_matrix(l, s) &&
+           dd::product_ragged_supported(l->tokens, s.D, s.L, l->dtype == DD_BF16);
+}
+bool wants_ragged(const dd_layer *l, const Shape &s, bool masked)
+{
+    return may_be_ragged(l, s) && dd::product_ragged_pays(l->tokens, s.D, s.L, l->K, masked);
+}
+bool fits_ragged(const Shape &s, const void *ws, size_t ws_bytes)
+{
+    return ws && reinterpret_cast<uintptr_t>(ws) % kWsAlign == 0 && ws_bytes >= dd::product_ragged_ws_bytes(s.D, s.L);
+}
+
 // Both gradients of an expanding layer with a handful of diagonals in one kernel (they read dY at the same shifted places).  It
 // is ahead of two such kernels wherever they run (1024^2, 4 diagonals, 25216 tokens 59 -> 41 us), and of the two products that
 // DD_ALGO_AUTO would take one by one up to 8 diagonals (us, one kernel and the two calls, 25216 tokens: 512^2, 8 diagonals 40 and
@@ -100,6 +118,13 @@ bool wants_matrix_wgrad(const dd_layer *l, const Shape &s)
     return true;
 }
 
+// The weight gradient of widths that are multiples of eight only, as wants_ragged, in the scratch of the vector kernels.
+bool wants_ragged_wgrad(const dd_layer *l, const Shape &s)
+{
+    return l->algo == DD_ALGO_AUTO && !wants_matrix_wgrad(l, s) && dd::weight_grad_ragged_supported(l->tokens, s.D, s.L, l->dtype == DD_BF16) &&
+           dd::weight_grad_ragged_pays(l->tokens, s.D, s.L, l->K);
+}
+
 // Scratch of dd_bwd_weight.  A forced matrix-core call runs those kernels or fails, so it needs their partial
 // sums only.  Under DD_ALGO_AUTO the family is settled at the call, once the alignment of X and dY is known, and
 // the two families cut the tokens into different numbers of chunks: the size covers whichever of them runs.
@@ -116,6 +141,13 @@ size_t weight_grad_ws_bytes(const dd_layer *l, const Shape &s)
     return matrix > vector ? matrix : vector;
 }
 
+// scratch without which a product is refused
+size_t product_ws_bytes(const dd_layer *l, const Shape &s)
+{
+    if (!wants_matrix(l, s)) return 0;
+    return l->algo == DD_ALGO_PREPARED || l->algo == DD_ALGO_BLOCKS ? prepared_bytes(s) : dd::product_matrix_ws_bytes(s.D, s.L);
+}
+
 constexpr int kMaxSets = 8;
 
 // `sets` > 1: a group of equally shaped layers sharing their input, operands prepared by dd_prepare_shared
@@ -129,8 +161,7 @@ dd_status product(const dd_layer *l, const Shape &s, bool transposed, const void
     if (l->tokens > 0 && (!src || !dst)) return DD_ERR_INVALID_ARG;
     bool matrix = wants_matrix(l, s);
     if (prepared && !matrix) return DD_ERR_UNSUPPORTED;
-    const size_t need = dd_workspace_bytes(transposed ? DD_OP_BWD_INPUT : DD_OP_FWD, l, 0) * size_t(sets);
-    if (dd_status st = check_ws(ws, ws_bytes, need)) return st;
+    if (dd_status st = check_ws(ws, ws_bytes, product_ws_bytes(l, s) * size_t(sets))) return st;
     if (l->tokens == 0) return DD_OK;
     if (matrix && !(aligned16(src) && aligned16(dst))) matrix = false;  // 16-byte vector accesses
     if ((l->algo == DD_ALGO_MATRIX || prepared) && !matrix) return DD_ERR_UNSUPPORTED;
@@ -154,7 +185,9 @@ dd_status product(const dd_layer *l, const Shape &s, bool transposed, const void
         (transposed ? a.src_sets : a.dst_sets) = sets;
     }
     const bool lowk = !prepared && wants_lowk(l, s, a.masked) && aligned16(src) && aligned16(dst);
+    const bool ragged = wants_ragged(l, s, a.masked) && fits_ragged(s, ws, ws_bytes) && aligned16(src) && aligned16(dst);
     const hipError_t e = blocks   ? dd::launch_product_blocks(a, static_cast<hipStream_t>(stream))
+                         : ragged ? dd::launch_product_ragged(a, static_cast<hipStream_t>(stream))
                          : lowk   ? dd::launch_product_lowk(a, static_cast<hipStream_t>(stream))
                          : matrix ? dd::launch_product_matrix(a, static_cast<hipStream_t>(stream))
                                   : dd::launch_product_vector(a, static_cast<hipStream_t>(stream));
@@ -162,12 +195,12 @@ dd_status product(const dd_layer *l, const Shape &s, bool transposed, const void
 }
 
 // ---- the backward pass as one call (dd_bwd): the two products back to back, sharing one scratch ----
-size_t bwd_ws_bytes(const dd_layer *l)
+size_t bwd_ws_bytes(const dd_layer *l, const Shape &s, bool wanted)
 {
     dd_layer plain = *l;
     if (plain.algo == DD_ALGO_PREPARED) plain.algo = DD_ALGO_MATRIX;  // the prepared block is passed beside the scratch
-    const size_t a = l->algo == DD_ALGO_PREPARED ? 0 : dd_workspace_bytes(DD_OP_BWD_INPUT, &plain, 0);
-    const size_t b = dd_workspace_bytes(DD_OP_BWD_WEIGHT, &plain, 0);
+    const size_t a = l->algo == DD_ALGO_PREPARED ? 0 : wanted ? dd_workspace_bytes(DD_OP_BWD_INPUT, &plain, 0) : product_ws_bytes(&plain, s);
+    const size_t b = weight_grad_ws_bytes(&plain, s);
     return a > b ? a : b;
 }
 
@@ -194,15 +227,14 @@ size_t dd_workspace_bytes(int op, const dd_layer *layer, int32_t batch)
     switch (op) {
     case DD_OP_FWD:
     case DD_OP_BWD_INPUT:
-        if (layer->algo == DD_ALGO_PREPARED || layer->algo == DD_ALGO_BLOCKS)
-            return wants_matrix(layer, s) ? prepared_bytes(s) : 0;
-        return wants_matrix(layer, s) ? dd::product_matrix_ws_bytes(s.D, s.L) : 0;
+        if (may_be_ragged(layer, s)) return dd::product_ragged_ws_bytes(s.D, s.L);
+        return product_ws_bytes(layer, s);
     case DD_OP_PREPARE:
         return dd::product_matrix_supported(1, s.D, s.L, layer->dtype == DD_BF16) ? prepared_bytes(s) : 0;
     case DD_OP_BWD_WEIGHT:
         return weight_grad_ws_bytes(layer, s);
     case DD_OP_BWD:
-        return layer->algo == DD_ALGO_BLOCKS ? 0 : bwd_ws_bytes(layer);
+        return layer->algo == DD_ALGO_BLOCKS ? 0 : bwd_ws_bytes(layer, s, true);
     case DD_OP_BWD_WEIGHT_SCALED: {
         if (layer->algo == DD_ALGO_VECTOR || !wants_matrix_wgrad(layer, s)) return 0;
         const size_t partials = dd::weight_grad_matrix_ws_bytes(layer->tokens, s.D, s.L, layer->K);
@@ -332,11 +364,12 @@ dd_status dd_bwd_weight(const dd_layer *layer, const void *X, const void *dY, co
     if (dd_status st = check_layer(layer, &s)) return st;
     if (!offsets || !dValues) return DD_ERR_INVALID_ARG;
     if (layer->tokens > 0 && (!X || !dY)) return DD_ERR_INVALID_ARG;
-    if (dd_status st = check_ws(ws, ws_bytes, dd_workspace_bytes(DD_OP_BWD_WEIGHT, layer, 0))) return st;
+    if (dd_status st = check_ws(ws, ws_bytes, weight_grad_ws_bytes(layer, s))) return st;
     const bool aligned = aligned16(X) && aligned16(dY);  // 16-byte transfers
     const bool lowk = layer->tokens > 0 && aligned && wants_lowk_wgrad(layer, s);
     const bool matrix = !lowk && aligned && wants_matrix_wgrad(layer, s);
     if (layer->algo != DD_ALGO_AUTO && layer->algo != DD_ALGO_VECTOR && !matrix) return DD_ERR_UNSUPPORTED;
+    const bool ragged = !lowk && !matrix && aligned && aligned16(dValues) && layer->tokens > 0 && wants_ragged_wgrad(layer, s);
     // the family that runs must fit the scratch that was checked (the families cut the tokens differently)
     const size_t runs_in = lowk     ? dd::weight_grad_lowk_ws_bytes(layer->tokens, s.D, s.L, layer->K)
                            : matrix ? dd::weight_grad_matrix_ws_bytes(layer->tokens, s.D, s.L, layer->K)
@@ -356,6 +389,7 @@ dd_status dd_bwd_weight(const dd_layer *layer, const void *X, const void *dY, co
     a.dValues = dValues;
     a.ws = ws;
     const hipError_t e = lowk     ? dd::launch_weight_grad_lowk(a, static_cast<hipStream_t>(hip_stream))
+                         : ragged ? dd::launch_weight_grad_ragged(a, static_cast<hipStream_t>(hip_stream))
                          : matrix ? dd::launch_weight_grad_matrix(a, static_cast<hipStream_t>(hip_stream))
                                   : dd::launch_weight_grad_vector(a, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? DD_OK : DD_ERR_HIP;
@@ -370,7 +404,7 @@ dd_status dd_bwd(const dd_layer *layer, const void *X, const void *dY, const int
     if (layer->algo == DD_ALGO_BLOCKS) return DD_ERR_UNSUPPORTED;
     const bool have_prepared = layer->algo == DD_ALGO_PREPARED;
     if (have_prepared && !prepared) return DD_ERR_INVALID_ARG;
-    if (dd_status st = check_ws(ws, ws_bytes, bwd_ws_bytes(layer))) return st;
+    if (dd_status st = check_ws(ws, ws_bytes, bwd_ws_bytes(layer, s, false))) return st;
     if (layer->tokens > 0 && !have_prepared && X && dY && offsets && values && dX && dValues) {  // both gradients in one kernel?
         const bool aligned_input = aligned16(dY) && aligned16(dX), aligned_weight = aligned16(X) && aligned16(dY);
         const dd::WeightGradArgs w = {layer->tokens, s.D, s.L, layer->K, layer->dtype == DD_BF16, s.expanding ? X : dY, s.expanding ? dY : X,
@@ -391,7 +425,8 @@ dd_status dd_bwd(const dd_layer *layer, const void *X, const void *dY, const int
         p.dst = dX;
         const bool vector_input = !(aligned_input && (wants_matrix(layer, s) || wants_lowk(layer, s, p.masked)));
         const bool vector_weight = !(aligned_weight && (wants_matrix_wgrad(layer, s) || wants_lowk_wgrad(layer, s)));
-        if (layer->algo != DD_ALGO_MATRIX && vector_input && vector_weight && dd::bwd_few_tokens(p))
+        if (layer->algo != DD_ALGO_MATRIX && vector_input && vector_weight && !wants_ragged(layer, s, p.masked) && !wants_ragged_wgrad(layer, s) &&
+            dd::bwd_few_tokens(p))
             return dd::launch_bwd_few_tokens(p, w, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? DD_OK : DD_ERR_HIP;
     }
     // The input gradient first: the weight gradient, issued right behind it, then finds in the memory-side cache

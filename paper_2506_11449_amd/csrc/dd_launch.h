@@ -77,6 +77,14 @@ hipError_t launch_lowk_bwd(const WeightGradArgs &a, const void *values, void *dX
 bool product_matrix_supported(int64_t T, int D, int L, bool bf16);
 size_t product_matrix_ws_bytes(int D, int L);
 hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream);
+// The same for one product from offsets and values where the feature counts are multiples of eight only.  `ws` as large as
+// product_ragged_ws_bytes; inputs that are not finite reach the results of their own diagonals only, as in the vector kernels, and
+// repeated offsets cost no precision.
+bool product_ragged_supported(int64_t T, int D, int L, bool bf16);
+bool product_ragged_pays(int64_t T, int D, int L, int K, bool masked);
+size_t product_ragged_ws_bytes(int D, int L);
+double product_vector_us(int64_t T, int D, int L, int K, bool masked);  // what it is weighed against
+hipError_t launch_product_ragged(const ProductArgs &a, hipStream_t stream);
 // The same product on prepared operands, skipping the 32 x 16 operand blocks that no diagonal crosses (a.offsets says
 // which); one layer at a time (no groups), long side <= 8192.
 bool product_blocks_supported(int64_t T, int D, int L, bool bf16);
@@ -113,6 +121,11 @@ hipError_t launch_bwd_few_tokens(const ProductArgs &p, const WeightGradArgs &w, 
 bool weight_grad_matrix_supported(int64_t T, int D, int L, bool bf16);
 size_t weight_grad_matrix_ws_bytes(int64_t T, int D, int L, int K);
 hipError_t launch_weight_grad_matrix(const WeightGradArgs &a, hipStream_t stream);
+// The same where the feature counts are multiples of eight only (dValues 16-byte aligned), in the scratch of the vector kernels.
+bool weight_grad_ragged_supported(int64_t T, int D, int L, bool bf16);
+bool weight_grad_ragged_pays(int64_t T, int D, int L, int K);
+double weight_grad_vector_us(int64_t T, int D, int L, int K, int &chunks, int &most);
+hipError_t launch_weight_grad_ragged(const WeightGradArgs &a, hipStream_t stream);
 // The same with the adjoint of the scaling by the importance weights (Sec. 3.2 Eq. 4) as the epilogue of the ordered
 // sum over the token chunks: dV[k][p] = alpha[o_k] * dValues[k][p] (to a.dValues) and dalpha[i] = sum over the
 // diagonals with offset i of <dValues[k], V[k]>.  tail: scratch behind the partial sums, weight_grad_scaled_tail_bytes.

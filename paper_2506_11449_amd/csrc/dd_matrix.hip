@@ -90,27 +90,37 @@ struct OperandPlace {
 // inside a matrix of kd_total contraction indices; or, for layers that merely share a launch, set s has a whole
 // operand of its own block_step elements further on.  D, L, col_step and k_step are multiples of 32.
 // ---------------------------------------------------------------------------------------------
+constexpr int kRaggedMaxD = 2048;          // long side of layers whose widths are multiples of eight only (scratch: 16.8 MB at most)
 constexpr int kMatRows = 32;
 constexpr int kMatRange = 256;
 constexpr int kMatChunk = 512;             // diagonals looked at per pass
 constexpr int kMatStride = kMatRange + 8;  // floats per row in LDS: the 32 rows of a fragment start 8 banks apart
 
-__global__ __launch_bounds__(256) void materialize_kernel(int D, int L, int K, int masked_blocks,
+// RAGGED: D and L are multiples of eight and the operand is padded with zeros to kd_total contraction indices and whole blocks of
+// rows.  One operand of one layer; where an offset is given twice the rounded sums leave a rest, which goes to a second operand
+// `rest_at` elements behind the first, and *repeated says whether there is one.
+template <bool RAGGED = false, int THREADS = 256>
+__global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int K, int masked_blocks,
                                                           const int *__restrict__ offsets,
                                                           const uint16_t *__restrict__ values,
                                                           uint16_t *__restrict__ Wf_masked,
                                                           uint16_t *__restrict__ Wf_gather, OperandPlace place_masked,
                                                           OperandPlace place_gather,
-                                                          const float *__restrict__ alpha)
+                                                          const float *__restrict__ alpha, size_t rest_at = 0, int *__restrict__ repeated = nullptr)
 {
     __shared__ __attribute__((aligned(16))) float rows[kMatRows * kMatStride];
-    __shared__ int hit_k[kMatChunk], hit_first[kMatChunk], hit_offset[kMatChunk], n_hits;
-    const int ranges_masked = (L + kMatRange - 1) / kMatRange, ranges_gather = (D + kMatRange - 1) / kMatRange;
+    constexpr int kMatList = THREADS > kMatChunk ? THREADS : kMatChunk;
+    constexpr int kMatPer = kMatChunk / THREADS > 0 ? kMatChunk / THREADS : 1;  // offsets a thread looks at per pass
+    static_assert(kMatPer * THREADS <= kMatList, "the list holds what a pass finds");
+    __shared__ int hit_k[kMatList], hit_first[kMatList], hit_offset[kMatList], n_hits;
+    __shared__ unsigned seen[RAGGED ? kRaggedMaxD / 32 : 1], any_repeated;
+    const int ranges_masked = RAGGED ? (place_masked.kd_total + kMatRange - 1) / kMatRange : (L + kMatRange - 1) / kMatRange;
+    const int ranges_gather = RAGGED ? (place_gather.kd_total + kMatRange - 1) / kMatRange : (D + kMatRange - 1) / kMatRange;
     const bool long_major = int(blockIdx.x) < masked_blocks * ranges_masked;
     const int job = long_major ? blockIdx.x : blockIdx.x - masked_blocks * ranges_masked;
     const int ranges = long_major ? ranges_masked : ranges_gather;
     const int r0 = job / ranges * kMatRows;
-    const int KD = long_major ? L : D;
+    const int KD = RAGGED ? (long_major ? place_masked : place_gather).kd_total : long_major ? L : D;
     const int i0 = job % ranges * kMatRange;
     const int extent = min(kMatRange, KD - i0);
     const int set = blockIdx.y;
@@ -118,27 +128,33 @@ __global__ __launch_bounds__(256) void materialize_kernel(int D, int L, int K, i
     values += size_t(set) * K * L;
     const OperandPlace place = long_major ? place_masked : place_gather;
     uint16_t *Wf = (long_major ? Wf_masked : Wf_gather) + size_t(set) * place.block_step;
-    for (int c = threadIdx.x; c < kMatRows * kMatStride / 4; c += 256)
+    for (int c = threadIdx.x; c < kMatRows * kMatStride / 4; c += THREADS)
         reinterpret_cast<f32x4 *>(rows)[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (RAGGED) {
+        for (int i = threadIdx.x; i < (D + 31) / 32; i += THREADS) seen[i] = 0u;
+        if (threadIdx.x == 0) any_repeated = 0u;
+    }
     // A diagonal meets the block where the contraction indices of the 32 rows -- consecutive modulo D from `first`
     // on -- fall into this workgroup's range; most diagonals miss.  Up to kMatChunk diagonals at a time: every thread
     // looks at its share of the offsets (all loads first: one trip to memory) and lists the ones that meet the block;
     // then the (listed diagonal, row) pairs are dealt to all threads, rows innermost, so that a wave reads runs of
     // 32 consecutive values.
-    for (int k0 = 0; k0 < K; k0 += kMatChunk) {
+    for (int k0 = 0; k0 < K; k0 += kMatPer * THREADS) {
         if (threadIdx.x == 0) n_hits = 0;
-        int o[kMatChunk / 256];
+        int o[kMatPer];
 #pragma unroll
-        for (int j = 0; j < kMatChunk / 256; ++j) {
-            const int k = k0 + j * 256 + threadIdx.x;
+        for (int j = 0; j < kMatPer; ++j) {
+            const int k = k0 + j * THREADS + threadIdx.x;
             o[j] = k < K ? offsets[k] : 0;
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kMatChunk / 256; ++j) {
-            const int k = k0 + j * 256 + threadIdx.x;
+        for (int j = 0; j < kMatPer; ++j) {
+            const int k = k0 + j * THREADS + threadIdx.x;
             if (k >= K) continue;
             const int oc = canonical_offset(o[j], D);
+            if constexpr (RAGGED)
+                if (atomicOr(&seen[oc >> 5], 1u << (oc & 31)) >> (oc & 31) & 1u) any_repeated = 1u;
             int first = long_major ? r0 - oc : r0 + oc;  // contraction index of row r0
             first += first < 0 ? D : 0;
             first -= first >= D ? D : 0;
@@ -152,7 +168,7 @@ __global__ __launch_bounds__(256) void materialize_kernel(int D, int L, int K, i
         }
         __syncthreads();
         const int items = n_hits * kMatRows;
-        for (int item = threadIdx.x; item < items; item += 256) {
+        for (int item = threadIdx.x; item < items; item += THREADS) {
             const int h = item / kMatRows, rr = item % kMatRows;
             const int i = hit_first[h] + rr >= D ? hit_first[h] + rr - D : hit_first[h] + rr;
             const int p = long_major ? i : r0 + rr;  // position along the diagonal
@@ -166,10 +182,26 @@ __global__ __launch_bounds__(256) void materialize_kernel(int D, int L, int K, i
     // fragments (r0 / 32, i0 / 16 ...) lie one after the other: piece `pc` is lane pc % 64 of fragment pc / 64
     u32x4 *out = reinterpret_cast<u32x4 *>(Wf + fragment_index(r0 + set * place.col_step, i0 + set * place.k_step,
                                                                 place.kd_total));
-    for (int pc = threadIdx.x; pc < extent * 4; pc += 256) {
+    for (int pc = threadIdx.x; pc < extent * 4; pc += THREADS) {
         const int lane = pc & 63;
         const float *src = rows + (lane & 31) * kMatStride + (pc >> 6) * 16 + 8 * (lane >> 5);
         out[pc] = pack_bf16x8(*reinterpret_cast<const f32x4 *>(src), *reinterpret_cast<const f32x4 *>(src + 4));
+    }
+    if constexpr (RAGGED) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *repeated = int(any_repeated);
+        if (!any_repeated) return;
+        u32x4 *rest = reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(out) + rest_at);
+        for (int pc = threadIdx.x; pc < extent * 4; pc += THREADS) {
+            const int lane = pc & 63;
+            const float *src = rows + (lane & 31) * kMatStride + (pc >> 6) * 16 + 8 * (lane >> 5);
+            f32x4 v[2];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float rounded = bf16_to_f32(f32_to_bf16(src[i])), left = src[i] - rounded;
+                v[i >> 2][i & 3] = fabsf(rounded) < INFINITY ? left : 0.f;
+            }
+            rest[pc] = pack_bf16x8(v[0], v[1]);
+        }
     }
 }
 
@@ -240,6 +272,49 @@ __global__ __launch_bounds__(kFusedThreads) void select_materialize_kernel(int D
 // matrix i / a_cols, column i % a_cols; C = NC / c_cols matrices [T x c_cols] likewise.  a_cols is
 // a multiple of the k-slice, c_cols of eight; a plain product has a_cols = KD and c_cols = NC.
 // ---------------------------------------------------------------------------------------------
+// What a product of a layer whose widths are multiples of eight only needs beside its padded operand (RaggedArgs of the kernels
+// below; the others ignore it).  The dense contraction multiplies every input by the zeros between the diagonals, which an input
+// that is not finite must not survive: a workgroup that meets one takes its tile diagonal by diagonal instead.
+struct RaggedArgs {
+    const int *offsets;
+    const uint16_t *values;
+    int D, L, K;
+    bool masked;
+    size_t rest_at;       // elements from the operand to the one of the rests ...
+    const int *repeated;  // ... which counts if this is set
+};
+__device__ __align__(16) const unsigned int mm_zero_piece[4] = {0u, 0u, 0u, 0u};
+
+// Notes in bits 15 and 31 of `seen` whether one of eight numbers is infinite or undefined.  (Pinned: else the words of all pieces
+// stay in registers until one sum over them at the end.)
+__device__ __forceinline__ void note_not_finite(unsigned &seen, u32x4 v)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) seen |= (v[i] & 0x7fff7fffu) + 0x00800080u;
+    asm volatile("" : "+v"(seen));
+}
+
+// Result tile of tokens t0 ... t0 + BM - 1 and columns j0 ... j0 + BN - 1, from offsets and values: rare, and as slow as it looks.
+template <int BM, int BN>
+__device__ __forceinline__ void tile_by_diagonals(const RaggedArgs &r, const uint16_t *__restrict__ A, uint16_t *__restrict__ C, int T, int t0, int j0)
+{
+    const int src_cols = r.masked ? r.L : r.D, dst_cols = r.masked ? r.D : r.L;
+    for (int e = threadIdx.x; e < BM * BN; e += blockDim.x) {
+        const int t = t0 + e / BN, j = j0 + e % BN;
+        if (t >= T || j >= dst_cols) continue;
+        const uint16_t *row = A + size_t(t) * src_cols;
+        float acc = 0.f;
+        for (int k = 0; k < r.K; ++k) {
+            const int o = canonical_offset(r.offsets[k], r.D);
+            int c = r.masked ? j - o : j + o;
+            c += c < 0 ? r.D : 0;
+            c -= c >= r.D ? r.D : 0;
+            if (c < src_cols) acc = fmaf(bf16_to_f32(row[c]), bf16_to_f32(r.values[size_t(k) * r.L + (r.masked ? c : j)]), acc);
+        }
+        C[size_t(t) * dst_cols + j] = f32_to_bf16(acc);
+    }
+}
+
 template <int BM, int BN, int NW>
 struct MmTile {
     static constexpr int THREADS = 64 * NW;
@@ -290,11 +365,12 @@ __device__ __forceinline__ void store_tile(uint16_t *__restrict__ C, const unsig
         store_tile_piece<BM, BN>(C, tile, tile_stride, tm, first_matrix, first_col, T, c_cols, idx);
 }
 
-template <int BM, int BN, int NW>
+// RAGGED: one product whose widths a_cols and c_cols are multiples of eight; KD and NC are those of the operand, padded with zeros.
+template <int BM, int BN, int NW, bool RAGGED = false>
 __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int a_cols, int c_cols, int tiles_m,
                                                         int tiles_n, int group_n, const uint16_t *__restrict__ A,
                                                         const uint16_t *__restrict__ Wf,
-                                                        uint16_t *__restrict__ C)
+                                                        uint16_t *__restrict__ C, RaggedArgs ragged)
 {
     using Tl = MmTile<BM, BN, NW>;
     constexpr int kMmThreads = Tl::THREADS;
@@ -319,7 +395,7 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
 
     // token operand, global -> registers -> LDS: thread handles chunk (row = idx / 8, chunk = idx % 8)
     const uint16_t *x_src[Tl::X_CHUNKS];
-    int x_dst[Tl::X_CHUNKS];
+    int x_dst[Tl::X_CHUNKS], x_first[Tl::X_CHUNKS];
 #pragma unroll
     for (int n = 0; n < Tl::X_CHUNKS; ++n) {
         const int idx = min(tid + kMmThreads * n, BM * kChunksPerRow - 1);  // a last partial round repeats the final piece
@@ -327,6 +403,7 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
         int t = tm * BM + row;
         t = t < T ? t : T - 1;  // rows past the end re-read the last token; their results are not stored
         x_src[n] = A + size_t(t) * a_cols + ch * 8;
+        x_first[n] = ch * 8;
         x_dst[n] = row * kRowBytes + swizzle(row, ch) * 16;
     }
     // Where the next k-slice to request starts, relative to a row's first element: 64 columns further on, or in
@@ -339,11 +416,15 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
         ++x_slice;                                                                                      \
         x_off += kBK;                                                                                   \
         x_in += kBK;                                                                                    \
-        if (x_in == a_cols) {                                                                           \
+        if (!RAGGED && x_in == a_cols) {                                                                \
             x_in = 0;                                                                                   \
             x_off += x_jump;                                                                            \
         }                                                                                               \
     }
+    // piece n_ of the slice at x_in_ (elements from the start of the row) and x_off_; past the end of a ragged row: zeros
+#define DD_X_PIECE(n_, x_in_, x_off_)                                                                   \
+    (*reinterpret_cast<const u32x4 *>(!RAGGED || (x_in_) + x_first[n_] < a_cols ? x_src[n_] + (x_off_)   \
+                                                                              : reinterpret_cast<const uint16_t *>(mm_zero_piece)))
     // weight fragments of this wave: block row (tn*BN + wave*WN)/32 + a, 1 KB per k-step, 16 bytes per lane
     const uint16_t *w_src[Tl::FA];
 #pragma unroll
@@ -373,14 +454,16 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
 #define DD_LOAD_X(xg_) /* the slice under the cursor; the cursor moves on */                           \
     {                                                                                                   \
         _Pragma("unroll") for (int n = 0; n < Tl::X_CHUNKS; ++n)                                        \
-            xg_[n] = *reinterpret_cast<const u32x4 *>(x_src[n] + x_off);                                \
+            xg_[n] = DD_X_PIECE(n, x_in, x_off);                                                        \
         DD_X_ADVANCE                                                                                    \
     }
 #define DD_STORE_X(xg_, kt_)                                                                            \
     {                                                                                                   \
         unsigned char *dstb = smem + ((kt_) % kRing) * Tl::X_BYTES;                                     \
-        _Pragma("unroll") for (int n = 0; n < Tl::X_CHUNKS; ++n)                                        \
+        _Pragma("unroll") for (int n = 0; n < Tl::X_CHUNKS; ++n) {                                      \
+            if (RAGGED) note_not_finite(undefined, xg_[n]);                                                \
             *reinterpret_cast<u32x4 *>(dstb + x_dst[n]) = xg_[n];                                       \
+        }                                                                                               \
     }
 #define DD_LOAD_W(wf_, g_) /* g_ counts groups of four k-steps (64 contraction indices) */            \
     {                                                                                                   \
@@ -424,6 +507,7 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
         const int gmax = KD / 64 - 1;                                                                   \
         const size_t w_kk = size_t(((kt_) + 1) < gmax ? ((kt_) + 1) : gmax) * 4 * 512;                  \
         const size_t x_kk = x_off; /* slice kt_ + 4 */                                                 \
+        const int x_at = x_in;                                                                          \
         DD_X_ADVANCE                                                                                    \
         unsigned char *x_dstb = smem + ring_fill;                                                       \
         DD_STEP(wf_cur_, 0, xf0, xf1, ring_cur, 1,                                                      \
@@ -432,8 +516,9 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
                     wf_next_[2 * b + 1][a] = *reinterpret_cast<const bf16x8 *>(w_src[a] + w_kk + (2 * b + 1) * 512); } }) \
         DD_STEP(wf_cur_, 1, xf1, xf0, ring_cur, 2, )                                                    \
         DD_STEP(wf_cur_, 2, xf0, xf1, ring_cur, 3,                                                      \
-                if (b < Tl::X_CHUNKS) { *reinterpret_cast<u32x4 *>(x_dstb + x_dst[b]) = xg_[b];         \
-                                        xg_[b] = *reinterpret_cast<const u32x4 *>(x_src[b] + x_kk); })  \
+                if (b < Tl::X_CHUNKS) { if (RAGGED) note_not_finite(undefined, xg_[b]);                     \
+                                        *reinterpret_cast<u32x4 *>(x_dstb + x_dst[b]) = xg_[b];         \
+                                        xg_[b] = DD_X_PIECE(b, x_at, x_kk); })                          \
         DD_STEP(wf_cur_, 3, xf1, xf0, ring_next, 0, )                                                   \
         {                                                                                               \
             const int t = ring_cur;                                                                     \
@@ -445,6 +530,9 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
     }
     static_assert(Tl::X_CHUNKS <= Tl::FB && Tl::FB >= 2, "one extra piece of work per MFMA");
 
+    unsigned undefined = 0u;
+    const bool rests = RAGGED && *ragged.repeated;
+    for (int pass = 0;; ++pass) {
     // prologue: slices 0 and 1 in LDS, slices 2 and 3 in flight, weight fragments of slice 0 loaded
     DD_LOAD_X(xg0)
     DD_LOAD_X(xg1)
@@ -459,8 +547,21 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
         DD_SLICE(kt, wf0, wf1, xg0)
         DD_SLICE(kt + 1, wf1, wf0, xg1)
     }
+    if (!RAGGED) break;
+    if (pass == 0 && __syncthreads_or(undefined & 0x80008000u)) {
+        tile_by_diagonals<BM, BN>(ragged, A, C, T, tm * BM, tn * BN);
+        return;
+    }
+    if (!rests || pass == 1) break;
+#pragma unroll
+    for (int a = 0; a < Tl::FA; ++a) w_src[a] += ragged.rest_at;  // once more with what the rounding of the operand left
+    x_off = 0;
+    x_in = x_slice = 0;
+    ring_cur = 0, ring_next = Tl::X_BYTES, ring_fill = 2 * Tl::X_BYTES;
+    }
 #undef DD_LOAD_X
 #undef DD_X_ADVANCE
+#undef DD_X_PIECE
 #undef DD_STORE_X
 #undef DD_LOAD_W
 #undef DD_LOAD_XF
@@ -485,6 +586,15 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
                 *reinterpret_cast<bf16x4 *>(smem + t_local * Tl::C_STRIDE + j_local * 2) = h;
             }
     __syncthreads();
+    if constexpr (RAGGED) {
+        for (int idx = tid; idx < BM * (BN / 8); idx += kMmThreads) {
+            const int row = idx / (BN / 8), ch = idx % (BN / 8), t = tm * BM + row, col = tn * BN + ch * 8;
+            if (t < T && col < c_cols)
+                __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(smem + row * Tl::C_STRIDE + ch * 16),
+                                            reinterpret_cast<u32x4 *>(C + size_t(t) * c_cols + col));
+        }
+        return;
+    }
     store_tile<BM, BN, kMmThreads>(C, smem, Tl::C_STRIDE, tm, tn, T, c_cols, tid);
 }
 
@@ -841,10 +951,11 @@ struct BlockArgs {
     bool long_cols;  // the output columns are the long side
 };
 
-template <int FA, int FB, int KS, bool BLOCKS>
+template <int FA, int FB, int KS, bool BLOCKS, bool RAGGED = false>
 __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_cols, int c_cols, int tiles_m, int tiles_n,
                                                            const uint16_t *__restrict__ A,
-                                                           const uint16_t *__restrict__ Wf, uint16_t *__restrict__ C, BlockArgs blocks)
+                                                           const uint16_t *__restrict__ Wf, uint16_t *__restrict__ C, BlockArgs blocks,
+                                                           RaggedArgs ragged)
 {
     using Tl = MmSmallTile<FA, FB, KS>;
     constexpr int BM = Tl::BM, BN = Tl::BN;
@@ -856,7 +967,7 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
     const int tn = lin / tiles_m, tm = lin - tn * tiles_m;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int groups = KD / 64;
+    const int groups = RAGGED ? (a_cols + 63) / 64 : KD / 64;
     int n_groups = groups;
     __shared__ unsigned bits[BLOCKS ? kBlkMaxD / 32 : 1], list[BLOCKS ? kBlkMaxD / 64 : 1], n_listed;
     if constexpr (BLOCKS) {
@@ -908,8 +1019,8 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
     const size_t w_row = size_t(KD / 16) * 512;  // from one 32-column block to the next
     // the cursor of the token rows inside the stack of matrices
     // (BLOCKS: one matrix, and the listed group says where)
-    int x_in = g_begin * 64 % a_cols;
-    const uint16_t *x_src = A + size_t(g_begin * 64 / a_cols) * T * a_cols + x_in;
+    int x_in = RAGGED ? g_begin * 64 : g_begin * 64 % a_cols;
+    const uint16_t *x_src = RAGGED ? A + x_in : A + size_t(g_begin * 64 / a_cols) * T * a_cols + x_in;
     const size_t x_jump = size_t(T - 1) * a_cols;
 
     f32x16 acc[FA][FB];
@@ -934,10 +1045,11 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
     {                                                                                                   \
         _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
             _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
-                x_[b][j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(x_src) + x_row[b][j]); \
+                x_[b][j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(x_src) +      \
+                               (!RAGGED || x_in + (lane & 7) * 8 < a_cols ? x_row[b][j] : x_row[b][j] - (lane & 7) * 16u)); \
         x_src += 64;                                                                                    \
         x_in += 64;                                                                                     \
-        if (x_in == a_cols) {                                                                           \
+        if (!RAGGED && x_in == a_cols) {                                                                           \
             x_in = 0;                                                                                   \
             x_src += x_jump;                                                                            \
         }                                                                                               \
@@ -952,12 +1064,21 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
     }
     // The rows change lanes inside the wave, whose LDS accesses are served in order: the fences keep the compiler from moving
     // a fragment's read before the writes of its group or behind those of the next (they wait for nothing).
-#define DD_SMALL_GROUP(w_, x_, m_, next_)                                                               \
+    // (the last group of a ragged row: what lies past its end was read from the group's first piece, and is replaced by zeros)
+#define DD_SMALL_GROUP(w_, x_, m_, next_, g_)                                                           \
     {                                                                                                   \
         const unsigned now = m_;                                                                        \
+        if (RAGGED && (g_) * 64 + 64 > a_cols) {                                                        \
+            const bool past = (g_) * 64 + (lane & 7) * 8 >= a_cols;                                     \
+            _Pragma("unroll") for (int b = 0; b < FB; ++b)                                              \
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)                                           \
+                    if (past) x_[b][j] = u32x4{0u, 0u, 0u, 0u};                                         \
+        }                                                                                               \
         _Pragma("unroll") for (int b = 0; b < FB; ++b)                                                  \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                             \
+                if (RAGGED) note_not_finite(undefined, x_[b][j]);                                          \
                 *reinterpret_cast<u32x4 *>(x_buf + b * 32 * kRowBytes + x_dst[j]) = x_[b][j];           \
+            }                                                                                           \
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                          \
         __builtin_amdgcn_wave_barrier();                                                                \
         if ((next_) < g_end) {                                                                          \
@@ -978,6 +1099,9 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                          \
         __builtin_amdgcn_wave_barrier();                                                                \
     }
+    unsigned undefined = 0u;
+    const bool rests = RAGGED && *ragged.repeated;
+    for (int pass = 0;; ++pass) {
     int g = g_begin;
     if (g < g_end) {
         DD_SMALL_MASK(m0, g)
@@ -990,14 +1114,25 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
         DD_SMALL_LOAD_W(w1, m1)
     }
     for (; g + 1 < g_end; g += 2) {
-        DD_SMALL_GROUP(w0, x0, m0, g + 2)
-        DD_SMALL_GROUP(w1, x1, m1, g + 3)
+        DD_SMALL_GROUP(w0, x0, m0, g + 2, g)
+        DD_SMALL_GROUP(w1, x1, m1, g + 3, g + 1)
     }
-    if (g < g_end) DD_SMALL_GROUP(w0, x0, m0, g_end)
+    if (g < g_end) DD_SMALL_GROUP(w0, x0, m0, g_end, g)
+    if (!RAGGED || !rests || pass == 1) break;
+    w_src = w_first + ragged.rest_at + size_t(g_begin) * 4 * 512;  // once more with what the rounding of the operand left
+    x_in = g_begin * 64;
+    x_src = A + x_in;
+    }
 #undef DD_SMALL_GROUP
 #undef DD_SMALL_LOAD_W
 #undef DD_SMALL_LOAD_X
 #undef DD_SMALL_MASK
+    if constexpr (RAGGED) {
+        if (__syncthreads_or(undefined & 0x80008000u)) {
+            tile_by_diagonals<BM, BN>(ragged, A, C, T, tm * BM, tn * BN);
+            return;
+        }
+    }
     __syncthreads();  // the sums take the place of the rows
 
     // Accumulator i of lane l is output column 8*(i/4) + 4*(l/32) + i%4 of token l%32 inside its 32x32 tile.
@@ -1012,7 +1147,7 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
                 *reinterpret_cast<f32x4 *>(sums + (wave * BM + b * 32 + l32) * Tl::STRIDE + a * 32 + 8 * q + 4 * half) = v;
             }
     __syncthreads();
-    const int matrix = tn * BN / c_cols, first_col = tn * BN - matrix * c_cols;  // c_cols is a multiple of BN
+    const int matrix = RAGGED ? 0 : tn * BN / c_cols, first_col = tn * BN - matrix * c_cols;  // c_cols is a multiple of BN
     for (int idx = tid; idx < BM * BN / 8; idx += 64 * KS) {
         const int row = idx / (BN / 8), ch = idx % (BN / 8), t = tm * BM + row;
         const float *src = sums + row * Tl::STRIDE + ch * 8;
@@ -1022,7 +1157,7 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
             lo += *reinterpret_cast<const f32x4 *>(src + k * BM * Tl::STRIDE);
             hi += *reinterpret_cast<const f32x4 *>(src + k * BM * Tl::STRIDE + 4);
         }
-        if (t < T) *reinterpret_cast<u32x4 *>(C + (size_t(matrix) * T + t) * c_cols + first_col + ch * 8) = pack_bf16x8(lo, hi);
+        if (t < T && (!RAGGED || first_col + ch * 8 < c_cols)) *reinterpret_cast<u32x4 *>(C + (size_t(matrix) * T + t) * c_cols + first_col + ch * 8) = pack_bf16x8(lo, hi);
     }
 }
 
@@ -1059,17 +1194,17 @@ static int tile_group(int64_t tiles_m, int tiles_n, int BN, int KD)
     return best;
 }
 
-template <int BM, int BN, int NW>
+template <int BM, int BN, int NW, bool RAGGED = false>
 static hipError_t launch_mm(int T, int NC, int KD, int a_cols, int c_cols, const uint16_t *A, const uint16_t *Wf,
-                            uint16_t *C, hipStream_t stream)
+                            uint16_t *C, hipStream_t stream, RaggedArgs ragged = {})
 {
     using Tl = MmTile<BM, BN, NW>;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_kernel<BM, BN, NW>), Tl::LDS_BYTES, lds_allowed)) return e;
-    const int tiles_m = (T + BM - 1) / BM, tiles_n = NC / BN;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_kernel<BM, BN, NW, RAGGED>), Tl::LDS_BYTES, lds_allowed)) return e;
+    const int tiles_m = (T + BM - 1) / BM, tiles_n = (NC + BN - 1) / BN;
     const int per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL((mm_kernel<BM, BN, NW>), dim3(per_xcd * kXcds), dim3(Tl::THREADS), Tl::LDS_BYTES, stream, T, NC, KD,
-                       a_cols, c_cols, tiles_m, tiles_n, tiles_n, A, Wf, C);  // every tile is resident at once: plain order
+    hipLaunchKernelGGL((mm_kernel<BM, BN, NW, RAGGED>), dim3(per_xcd * kXcds), dim3(Tl::THREADS), Tl::LDS_BYTES, stream, T, NC, KD,
+                       a_cols, c_cols, tiles_m, tiles_n, tiles_n, A, Wf, C, ragged);  // every tile is resident at once: plain order
     return hipGetLastError();
 }
 
@@ -1089,11 +1224,11 @@ hipError_t launch_prepare_matrix(int D, int L, int K, int sets, bool expanding, 
     // of each other (the sets' contributions to the one input gradient add up in the contraction).
     const OperandPlace side_by_side = {expanding ? L : D, expanding ? D : L, 0, 0};
     const OperandPlace stacked = {sets * (expanding ? D : L), 0, expanding ? D : L, 0};
-    hipLaunchKernelGGL(materialize_kernel, materialize_grid(D, L, D, L, sets), dim3(256), 0, stream, D, L, K, D / kMatRows,
+    hipLaunchKernelGGL(materialize_kernel<false>, materialize_grid(D, L, D, L, sets), dim3(256), 0, stream, D, L, K, D / kMatRows,
                        offsets, static_cast<const uint16_t *>(values),
                        static_cast<uint16_t *>(expanding ? forward_operand : backward_operand),
                        static_cast<uint16_t *>(expanding ? backward_operand : forward_operand),
-                       expanding ? side_by_side : stacked, expanding ? stacked : side_by_side, alpha);
+                       expanding ? side_by_side : stacked, expanding ? stacked : side_by_side, alpha, size_t(0), static_cast<int *>(nullptr));
     return hipGetLastError();
 }
 
@@ -1105,9 +1240,9 @@ hipError_t launch_prepare_matrix_batched(int D, int L, int K, int layers, bool e
     const size_t operand = size_t(D) * L;
     const OperandPlace masked = {L, 0, 0, 2 * operand}, gather = {D, 0, 0, 2 * operand};
     uint16_t *first = static_cast<uint16_t *>(prepared);
-    hipLaunchKernelGGL(materialize_kernel, materialize_grid(D, L, D, L, layers), dim3(256), 0, stream, D, L, K, D / kMatRows,
+    hipLaunchKernelGGL(materialize_kernel<false>, materialize_grid(D, L, D, L, layers), dim3(256), 0, stream, D, L, K, D / kMatRows,
                        offsets, static_cast<const uint16_t *>(values), expanding ? first : first + operand,
-                       expanding ? first + operand : first, masked, gather, static_cast<const float *>(nullptr));
+                       expanding ? first + operand : first, masked, gather, static_cast<const float *>(nullptr), size_t(0), static_cast<int *>(nullptr));
     return hipGetLastError();
 }
 
@@ -1150,17 +1285,17 @@ static hipError_t launch_mm_persistent(int T, int NC, int KD, int a_cols, int c_
     return hipGetLastError();
 }
 
-template <int FA, int FB, int KS, bool BLOCKS = false>
+template <int FA, int FB, int KS, bool BLOCKS = false, bool RAGGED = false>
 static hipError_t launch_mm_small(int T, int NC, int KD, int a_cols, int c_cols, const uint16_t *A, const uint16_t *Wf,
-                                  uint16_t *C, hipStream_t stream, BlockArgs blocks = {})
+                                  uint16_t *C, hipStream_t stream, BlockArgs blocks = {}, RaggedArgs ragged = {})
 {
     using Tl = MmSmallTile<FA, FB, KS>;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_small_kernel<FA, FB, KS, BLOCKS>), Tl::LDS_BYTES, lds_allowed)) return e;
-    const int tiles_m = (T + Tl::BM - 1) / Tl::BM, tiles_n = NC / Tl::BN;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mm_small_kernel<FA, FB, KS, BLOCKS, RAGGED>), Tl::LDS_BYTES, lds_allowed)) return e;
+    const int tiles_m = (T + Tl::BM - 1) / Tl::BM, tiles_n = (NC + Tl::BN - 1) / Tl::BN;
     const int per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL((mm_small_kernel<FA, FB, KS, BLOCKS>), dim3(per_xcd * kXcds), dim3(64 * KS), Tl::LDS_BYTES, stream, T, KD,
-                       a_cols, c_cols, tiles_m, tiles_n, A, Wf, C, blocks);
+    hipLaunchKernelGGL((mm_small_kernel<FA, FB, KS, BLOCKS, RAGGED>), dim3(per_xcd * kXcds), dim3(64 * KS), Tl::LDS_BYTES, stream, T, KD,
+                       a_cols, c_cols, tiles_m, tiles_n, A, Wf, C, blocks, ragged);
     return hipGetLastError();
 }
 
@@ -1224,9 +1359,9 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
     if (!a.prepared) {
         if (a.src_sets != 1 || a.dst_sets != 1) return hipErrorInvalidValue;  // groups come prepared
         const OperandPlace place = {KD, 0, 0, 0};
-        hipLaunchKernelGGL(materialize_kernel, materialize_grid(a.D, a.L, a.masked ? NC : 0, a.masked ? 0 : NC, 1), dim3(256), 0, stream, a.D, a.L, a.K,
+        hipLaunchKernelGGL(materialize_kernel<false>, materialize_grid(a.D, a.L, a.masked ? NC : 0, a.masked ? 0 : NC, 1), dim3(256), 0, stream, a.D, a.L, a.K,
                            a.masked ? NC / kMatRows : 0, a.offsets, static_cast<const uint16_t *>(a.values), Wf, Wf, place, place,
-                           static_cast<const float *>(nullptr));
+                           static_cast<const float *>(nullptr), size_t(0), static_cast<int *>(nullptr));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1252,6 +1387,100 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
         }
     }
     return launch_mm<128, 128, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+}
+
+// ---- widths that are multiples of eight only ----
+static int padded256(int n) { return (n + 255) / 256 * 256; }
+static int padded(int n) { return (n + 127) / 128 * 128; }
+
+bool product_ragged_supported(int64_t T, int D, int L, bool bf16)
+{
+    return bf16 && T > 0 && T < (int64_t(1) << 31) && D % 8 == 0 && L % 8 == 0 && D >= 256 && D <= kRaggedMaxD;
+}
+
+// Tile of the product, and the time it should take in us.  The kernels for few tokens as pick_small has them; mm_kernel: every round of
+// workgroups costs a fill and a copy-out, and its k-slices are bound by the latency of their loads or, with several workgroups on a
+// CU, by what all of them move and multiply.  Fitted to 264^2 ... 1496^2, 320 -> 1000 and 200 -> 1400 at 50 ... 12608 tokens (within a
+// tenth beyond 2000 tokens).
+static double small_tile_cost(int64_t T, int NC, double groups, int &best)
+{
+    static const struct {
+        int cols, tokens;
+        double fixed, per_group, load, crowded;
+    } tiles[] = {{32, 32, 2.8, 0.233, 0.4, 0.35}, {64, 64, 3.65, 0.52, 0.85, 1.0}};
+    double best_cost = 1e300;
+    for (const auto &t : tiles) {
+        const double per_cu = double((T + t.tokens - 1) / t.tokens) * ((NC + t.cols - 1) / t.cols) / 256;
+        const double group = per_cu <= 1 ? t.per_group * (1 + t.load * per_cu) : t.crowded * 0.5 * (per_cu + double(int64_t(per_cu + 0.999)));
+        const double cost = t.fixed + (groups > 4 ? groups / 4 : 1) * group;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = t.cols * 100 + t.tokens;
+        }
+    }
+    return best_cost;
+}
+
+static int pick_ragged(int64_t T, int c_cols, int a_cols, double &us)
+{
+    int best = 0;
+    us = T * a_cols * 2 < (int64_t(1) << 32) ? 1.1 * small_tile_cost(T, c_cols, (a_cols + 63) / 64, best) : 1e300;
+    static const struct {
+        int bm, bn, per_cu;
+        double slice;
+    } tiles[] = {{64, 128, 3, 0.33}, {128, 128, 2, 0.6}, {64, 256, 2, 0.52}, {128, 256, 1, 1.0}, {160, 256, 1, 1.25}};
+    const double slices = padded(a_cols) / 64;
+    for (const auto &t : tiles) {
+        const double wgs = double((T + t.bm - 1) / t.bm) * ((c_cols + t.bn - 1) / t.bn), per_cu = double(int64_t((wgs + 255) / 256));
+        const double rounds = double(int64_t((per_cu + t.per_cu - 1) / t.per_cu));
+        const double busy = per_cu * t.slice, latency = rounds * 0.38, cost = 3.5 * rounds + slices * (busy > latency ? busy : latency);
+        if (cost < us) {
+            us = cost;
+            best = t.bm * 1000 + t.bn;
+        }
+    }
+    return best;
+}
+
+// Two launches, the operand and the product, against one of the vector kernels (times in us as predicted; measured 320 -> 1000, 100
+// diagonals, 5005 tokens 16 and 25, 200 tokens 10 and 9; 1000^2, 12608 tokens 48 and 101, with 20 diagonals 46 and 34; 1496^2, 598
+// diagonals, 12608 tokens 84 and 647; nine tenths of the predictions within a fifth, hence the margin).
+bool product_ragged_pays(int64_t T, int D, int L, int K, bool masked)
+{
+    double us;
+    pick_ragged(T, masked ? D : L, masked ? L : D, us);
+    us = 4.5 + 1.2 * us + 10.0 * K / D + 1.4e-6 * D * L;
+    return us < 0.9 * product_vector_us(T, D, L, K, masked);
+}
+
+// the operand and the one of the rests, padded, and the flag
+size_t product_ragged_ws_bytes(int D, int L) { return 2 * size_t(padded256(D)) * size_t(padded256(L)) * 2 + 256; }
+
+hipError_t launch_product_ragged(const ProductArgs &a, hipStream_t stream)
+{
+    const int c_cols = a.masked ? a.D : a.L, a_cols = a.masked ? a.L : a.D;
+    const int NC = padded256(c_cols), KD = padded(a_cols), T = int(a.T);
+    const size_t operand = size_t(NC) * KD;
+    uint16_t *Wf = static_cast<uint16_t *>(a.ws);
+    int *repeated = reinterpret_cast<int *>(Wf + 2 * operand);
+    const uint16_t *A = static_cast<const uint16_t *>(a.src), *values = static_cast<const uint16_t *>(a.values);
+    uint16_t *C = static_cast<uint16_t *>(a.dst);
+    const OperandPlace place = {KD, 0, 0, 0};
+    const int blocks = NC / kMatRows * ((KD + kMatRange - 1) / kMatRange);
+    hipLaunchKernelGGL((materialize_kernel<true, 1024>), dim3(blocks), dim3(1024), 0, stream, a.D, a.L, a.K, a.masked ? NC / kMatRows : 0, a.offsets,
+                       values, Wf, Wf, place, place, static_cast<const float *>(nullptr), operand, repeated);
+    if (hipError_t e = hipGetLastError()) return e;
+    const RaggedArgs r = {a.offsets, values, a.D, a.L, a.K, a.masked, operand, repeated};
+    double us;
+    switch (pick_ragged(a.T, c_cols, a_cols, us)) {
+    case 3232: return launch_mm_small<1, 1, 4, false, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, {}, r);
+    case 6464: return launch_mm_small<2, 2, 4, false, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, {}, r);
+    case 64128: return launch_mm<64, 128, 4, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, r);
+    case 128128: return launch_mm<128, 128, 4, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, r);
+    case 64256: return launch_mm<64, 256, 8, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, r);
+    case 128256: return launch_mm<128, 256, 8, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, r);
+    default: return launch_mm<160, 256, 8, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, r);
+    }
 }
 
 // Few tokens, as the number of 64 x 64 (and of 32 x 32) result tiles has it.  Up to 512 of them the chip holds all tiles at

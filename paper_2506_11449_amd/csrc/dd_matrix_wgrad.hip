@@ -81,7 +81,9 @@ __device__ __forceinline__ bf16x8 read_transposed(const unsigned char *p0, const
 }
 
 // partial[split][k][p] for the representatives k of this tile's active offsets
-template <int TP, int TQ>
+// RAGGED: L and D are multiples of eight only and the last tiles reach past them: columns that do not exist are read from the block
+// of zeros, and their entries of G are not kept (modulo D they would be taken for entries of other diagonals).
+template <int TP, int TQ, bool RAGGED = false>
 __global__ __launch_bounds__(kWgT, kWgPerCu) void wgrad_mm_kernel(int T, int D, int L, int K, int tiles_p,
                                                                   int tiles_q, int splits, int slices, int skew,
                                                                   const uint16_t *__restrict__ A,
@@ -156,6 +158,10 @@ __global__ __launch_bounds__(kWgT, kWgPerCu) void wgrad_mm_kernel(int T, int D, 
         src_col[i] = is_a ? A + p0 + col : B + q0 + col;
         src_row[i] = t_begin + row;
         src_ld[i] = is_a ? L : D;
+        if (RAGGED && (is_a ? p0 + col >= L : q0 + col >= D)) {
+            src_col[i] = reinterpret_cast<const uint16_t *>(wg_zero_piece);
+            src_ld[i] = 0;
+        }
     }
     const unsigned lds_stage0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * 1024);
     // Rows past the end of the chunk must add nothing: their pieces come from a block of zeros instead.  The
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(kWgT, kWgPerCu) void wgrad_mm_kernel(int T, int D, 
 #define DD_WG_ENTER(o_, k_)                                                                              \
     {                                                                                                   \
         int e = canonical_offset(o_, D) - window_base;                                                  \
-        e = e < 0 ? e + D : (e >= D ? e - D : e);                                                       \
+        e = RAGGED ? canonical_offset(e, D) : e < 0 ? e + D : (e >= D ? e - D : e);                     \
         if (e < Tl::Window - 1) atomicMin(&table[e], k_);                                               \
     }
 #pragma unroll
@@ -390,8 +396,9 @@ __global__ __launch_bounds__(kWgT, kWgPerCu) void wgrad_mm_kernel(int T, int D, 
 #define DD_WG_DIAG_STORE(v_, col_, t_, e_)                                                               \
     {                                                                                                   \
         const unsigned byte0 = (unsigned((e_) >> 6) * unsigned(L) + unsigned(p0 + wp * (TP / 2) + ((t_) / Tl::FB) * 32 + rmod)) * 4u; \
+        const int p_left = L - (p0 + wp * (TP / 2) + ((t_) / Tl::FB) * 32 + rmod), q_left = D - (q0 + wq * (TQ / 2) + ((t_) % Tl::FB) * 32); \
         _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                   \
-            if (col_[i] < 32u)                                                         \
+            if (col_[i] < 32u && (!RAGGED || (8 * i < p_left && int(col_[i]) < q_left)))                \
                 *reinterpret_cast<float *>(reinterpret_cast<char *>(out) + (byte0 + 32u * i)) = v_[i];  \
     }
 #pragma unroll
@@ -453,7 +460,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(int D, int L, int K, 
     __shared__ f32x4 run_s[3][64];
     const int k = blockIdx.y;
     const int run = threadIdx.x >> 6, g = threadIdx.x & 63;
-    const int p = blockIdx.x * 256 + g * 4;  // L is a multiple of 64
+    const int p = blockIdx.x * 256 + g * 4;  // L is a multiple of 8
     const int per_run = (splits + 3) / 4;
     const int s_begin = min(run * per_run, splits), s_end = min(s_begin + per_run, splits);
     const size_t stride = size_t(K) * L;
@@ -483,17 +490,22 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(int D, int L, int K, 
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4 *>(src + u * stride);
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
+            acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
             src += 8 * stride;
             s += 8;
         }
         for (; s + 8 <= s_end; s += 8) {  // eight loads in flight
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4 *>(src + u * stride);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
+            acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));  // in pairs: fewer additions one after the other
             src += 8 * stride;
+        }
+        if (s + 4 <= s_end) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4 *>(src + u * stride);
+            acc += (v[0] + v[1]) + (v[2] + v[3]);
+            src += 4 * stride;
+            s += 4;
         }
         for (; s < s_end; ++s) {
             acc += *reinterpret_cast<const f32x4 *>(src);
@@ -573,6 +585,13 @@ static double wgrad_cost(int64_t slices, int tiles, int chunks, double tile_shar
 // the root of half of them, from 10 to 800), so a long chunk costs precision and many chunks cost some too.
 static double wgrad_chain(int64_t T, int chunks) { return double(T) / (kTS / 2 * chunks) + (chunks + 3) / 4 + 3; }
 
+static void plan_grid(WgradPlan &pl)
+{
+    const int tiles = pl.tiles_p * pl.tiles_q;
+    pl.grid = pl.splits >= kWgXcds ? (pl.splits + kWgXcds - 1) / kWgXcds * tiles * kWgXcds
+                                   : (tiles * pl.splits + kWgXcds - 1) / kWgXcds * kWgXcds;
+}
+
 static WgradPlan plan_wgrad(int64_t T, int D, int L, int K)
 {
     WgradPlan pl;
@@ -603,8 +622,7 @@ static WgradPlan plan_wgrad(int64_t T, int D, int L, int K)
             pl.splits = chunks;
         }
     }
-    pl.grid = pl.splits >= kWgXcds ? (pl.splits + kWgXcds - 1) / kWgXcds * tiles * kWgXcds
-                                   : (tiles * pl.splits + kWgXcds - 1) / kWgXcds * kWgXcds;
+    plan_grid(pl);
     // When the grid is exactly the two workgroups per CU that fit, the second 256 get their first tokens about
     // 1.5 us after the first 256 (the burst of first requests is served in order) and would finish their main
     // loops as much later, alone on their CUs next to the first ones' epilogues.  Giving them two slices (four
@@ -628,14 +646,14 @@ size_t weight_grad_matrix_ws_bytes(int64_t T, int D, int L, int K)
     return size_t(pl.most) * K * L * sizeof(float);
 }
 
-template <int TP, int TQ>
+template <int TP, int TQ, bool RAGGED = false>
 static hipError_t launch_wgrad_mm(const WeightGradArgs &a, const WgradPlan &pl, float *partial, hipStream_t stream)
 {
     using Tl = WgTile<TP, TQ>;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_mm_kernel<TP, TQ>), Tl::LdsBytes, lds_allowed)) return e;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_mm_kernel<TP, TQ, RAGGED>), Tl::LdsBytes, lds_allowed)) return e;
     const int lds_bytes = Tl::LdsBytes;
-    hipLaunchKernelGGL((wgrad_mm_kernel<TP, TQ>), dim3(pl.grid), dim3(kWgT), lds_bytes, stream, int(a.T), a.D, a.L,
+    hipLaunchKernelGGL((wgrad_mm_kernel<TP, TQ, RAGGED>), dim3(pl.grid), dim3(kWgT), lds_bytes, stream, int(a.T), a.D, a.L,
                        a.K, pl.tiles_p, pl.tiles_q, pl.splits, pl.slices, pl.skew,
                        static_cast<const uint16_t *>(a.A), static_cast<const uint16_t *>(a.B), a.offsets, partial);
     return hipGetLastError();
@@ -653,6 +671,76 @@ hipError_t launch_weight_grad_matrix(const WeightGradArgs &a, hipStream_t stream
     const WgradPlan pl = plan_wgrad(a.T, a.D, a.L, a.K);
     float *partial = static_cast<float *>(a.ws);
     if (hipError_t e = launch_wgrad_mm_any(a, pl, partial, stream)) return e;
+    hipLaunchKernelGGL(wgrad_reduce_kernel<false>, dim3((a.L + 255) / 256, a.K), dim3(256), 0, stream, a.D, a.L, a.K,
+                       pl.splits, a.offsets, partial, a.dValues, static_cast<const float *>(nullptr),
+                       static_cast<const uint16_t *>(nullptr), static_cast<float *>(nullptr));
+    return hipGetLastError();
+}
+
+bool weight_grad_ragged_supported(int64_t T, int D, int L, bool bf16)
+{
+    // (a window of the largest tile wraps onto itself at most once)
+    return bf16 && T > 0 && T < (int64_t(1) << 31) && D % 8 == 0 && L % 8 == 0 && D >= 256 && D <= 8192;
+}
+
+// Widths that are multiples of eight only: the tile that covers L x D with the least work (the smallest one's twelve fragment reads per
+// eight MFMAs weighed in), and the cheapest number of chunks with which an entry's sum is no less exact than the vector kernels make
+// it -- squared errors against 64 bits, in units of half the square of 2.5e-8, measured over 264^2 ... 1496^2, 500 ... 12608 tokens:
+// 0.147 T / chunks + 0.055 chunks + 9.5 there, 0.125 T / chunks + chunks / 32 + 12.5 here.  us: what it should take with the sum.
+static WgradPlan plan_wgrad_ragged(int64_t T, int D, int L, int K, double &us, double &vector_us)
+{
+    WgradPlan pl;
+    static const int sizes[3][2] = {{192, 192}, {128, 256}, {128, 128}};
+    double least = 1e300;
+    for (const auto &t : sizes) {
+        const double work = double((L + t[0] - 1) / t[0] * t[0]) * ((D + t[1] - 1) / t[1] * t[1]) * (t[0] * t[1] < 32768 ? 1.2 : 1.0);
+        if (work < least) {
+            least = work;
+            pl.tp = t[0];
+            pl.tq = t[1];
+        }
+    }
+    pl.tiles_p = (L + pl.tp - 1) / pl.tp;
+    pl.tiles_q = (D + pl.tq - 1) / pl.tq;
+    const int64_t slices = (T + kSliceTokens - 1) / kSliceTokens;
+    pl.slices = int(slices);
+    pl.skew = 0;
+    pl.splits = 0;
+    int vector_chunks;
+    vector_us = weight_grad_vector_us(T, D, L, K, vector_chunks, pl.most);
+    if (pl.most > slices) pl.most = int(slices);
+    const double exact = 0.147 * T / vector_chunks + 0.055 * vector_chunks;
+    us = 1e300;
+    for (int step = 1; step <= pl.most + kWgXcds - 1; step += step < kWgXcds ? 1 : kWgXcds) {
+        const int chunks = step < pl.most ? step : pl.most;
+        if (0.125 * T / chunks + chunks / 32.0 + 3.0 > exact) continue;
+        const double cost = 7.9 + 0.82 * wgrad_cost(slices, pl.tiles_p * pl.tiles_q, chunks, double(pl.tp) * pl.tq / (192 * 192), D, L, K);
+        if (cost < us) {
+            us = cost;
+            pl.splits = chunks;
+        }
+    }
+    plan_grid(pl);
+    return pl;
+}
+
+// (measured 320 -> 1000, 100 diagonals, 6000 tokens 20 and 37 us, 500 tokens 13.6 and 13.1; 264^2, 5 diagonals, 3000 tokens 12.7 and
+// 12.3; 1000^2, 100 diagonals, 12608 tokens 45 and 134)
+bool weight_grad_ragged_pays(int64_t T, int D, int L, int K)
+{
+    double us, vector_us;
+    const WgradPlan pl = plan_wgrad_ragged(T, D, L, K, us, vector_us);
+    return pl.splits > 0 && us < 0.88 * vector_us;
+}
+
+hipError_t launch_weight_grad_ragged(const WeightGradArgs &a, hipStream_t stream)
+{
+    double us, vector_us;
+    const WgradPlan pl = plan_wgrad_ragged(a.T, a.D, a.L, a.K, us, vector_us);
+    float *partial = static_cast<float *>(a.ws);
+    if (hipError_t e = pl.tp == 192   ? launch_wgrad_mm<192, 192, true>(a, pl, partial, stream)
+                       : pl.tq == 256 ? launch_wgrad_mm<128, 256, true>(a, pl, partial, stream)
+                                      : launch_wgrad_mm<128, 128, true>(a, pl, partial, stream)) return e;
     hipLaunchKernelGGL(wgrad_reduce_kernel<false>, dim3((a.L + 255) / 256, a.K), dim3(256), 0, stream, a.D, a.L, a.K,
                        pl.splits, a.offsets, partial, a.dValues, static_cast<const float *>(nullptr),
                        static_cast<const uint16_t *>(nullptr), static_cast<float *>(nullptr));

@@ -341,6 +341,7 @@ struct TiledPlan {
     int nt, k_parts, waves, grid_y;  // nt = 0: no tile fits LDS
     unsigned grid_x;
     size_t lds;
+    double clocks;  // of a CU, as estimated
 };
 
 // Tile, parts and workgroup size by the time they should take (in clocks of a CU): the work is spread over the CUs in
@@ -391,6 +392,7 @@ static TiledPlan make_tiled_plan(int64_t T, int D, int L, int K, bool bf16, bool
                     best.grid_x = unsigned(tiles);
                     best.grid_y = groups;
                     best.lds = lds;
+                    best.clocks = cost;
                 }
             }
         }
@@ -755,6 +757,7 @@ struct WgTiledPlan {
     int nt, kn;              // nt = 0: no tile fits LDS
     int waves_p, waves_k, groups_k, k_blocks, per_chunk, chunks;
     size_t lds;
+    double clocks;  // of a CU, as estimated
 };
 
 // The fewest chunks a plan may take, so that no sum is a longer chain of additions than the kernels before these made it: at
@@ -824,6 +827,7 @@ static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
                         best.per_chunk = per_chunk;
                         best.chunks = int(chunks);
                         best.lds = lds;
+                        best.clocks = cost;
                     }
                     if (chunks == fewest) break;
                     chunks = fewest;
@@ -851,6 +855,23 @@ static WgTiledPlan plan_wg_tiled(int64_t T, int D, int L, int K, bool bf16)
 size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16)
 {
     return size_t(wg_most_chunks(T, D, L, K, bf16)) * size_t(K) * size_t(L) * sizeof(float);
+}
+
+// What the tiled kernels for bf16 should take, in us (estimates of the plans against measured times, 56 ... 1500 features, 50 ... 12608
+// tokens, 2 ... 40 % of the diagonals: nine tenths of them within a fifth), or 0 where no tile is taken; and into how many chunks the
+// weight gradient cuts the tokens, of how many it may.
+double product_vector_us(int64_t T, int D, int L, int K, bool masked)
+{
+    const TiledPlan pl = plan_tiled(T, D, L, K, true, masked);
+    return pl.nt ? 5.0 + pl.clocks / 2400 * (masked ? 1.23 : 1.13) : 0.0;
+}
+
+double weight_grad_vector_us(int64_t T, int D, int L, int K, int &chunks, int &most)
+{
+    const WgTiledPlan pl = plan_wg_tiled(T, D, L, K, true);
+    most = wg_most_chunks(T, D, L, K, true);
+    chunks = pl.nt ? pl.chunks : weight_grad_splits(T);
+    return pl.nt ? 2.6 + 1.35 * pl.clocks / 2400 : 0.0;
 }
 
 template <class S, int NT, int KN>
