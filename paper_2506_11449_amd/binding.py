@@ -5,11 +5,13 @@ used for device memory and for the current stream handle, nothing else.  There i
 if the shared library is missing or a call fails, an exception is raised.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch  # imported before the library so that both share one HIP runtime
 
-from .build import LIB_PATH
+from .build import FASTCALL_PATH, LIB_PATH
 
 DD_F32, DD_BF16 = 0, 1
 DD_ALGO_AUTO, DD_ALGO_VECTOR, DD_ALGO_MATRIX, DD_ALGO_PREPARED, DD_ALGO_BLOCKS = 0, 1, 2, 3, 4
@@ -34,15 +36,28 @@ class dd_layer(ctypes.Structure):
 
 
 _lib = None
+_fast = None  # csrc/fastcall.cpp: plain calls done whole; None from it: not one of those, nothing done
+
+_FAST_ENTRIES = ("dd_workspace_bytes", "dd_fwd", "dd_bwd_input", "dd_bwd", "dd_bwd_weight", "dd_select_diagonals", "dd_select_prepare",
+                 "dd_diag_magnitude", "dd_diagheur_update")
+
+
+def _load_fastcall(lib):
+    loader = importlib.machinery.ExtensionFileLoader(f"{__package__}._fastcall", FASTCALL_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(loader.name, FASTCALL_PATH, loader=loader))
+    loader.exec_module(module)
+    module.bind(_current_stream, _check, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _FAST_ENTRIES))
+    return module
 
 
 def load_library():
     """dlopen libdynadiag.so and declare the prototypes.  Raises if it has not been built."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise DynaDiagError(-1, f"{LIB_PATH} is not built; run `python -m paper_2506_11449_amd.build`")
+    for path in (LIB_PATH, FASTCALL_PATH):
+        if not os.path.exists(path):
+            raise DynaDiagError(-1, f"{path} is not built; run `python -m paper_2506_11449_amd.build`")
     lib = ctypes.CDLL(LIB_PATH)
     vp, sz, i32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32
     lp = ctypes.POINTER(dd_layer)
@@ -79,8 +94,14 @@ def load_library():
         getattr(lib, name).restype = ctypes.c_int
     lib.dd_status_string.argtypes = [ctypes.c_int]
     lib.dd_status_string.restype = ctypes.c_char_p
+    _fast = _load_fastcall(lib)
     _lib = lib
     return lib
+
+
+def _load_fast():
+    load_library()
+    return _fast
 
 
 def _check(status):
@@ -124,9 +145,13 @@ def _ptr(t):
 _current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
 
+def _current_stream():
+    return _current_raw_stream(_current_device())
+
+
 def _stream(stream):
     """Handle of the given stream, or of the current stream of the current device."""
-    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
+    return _current_stream() if stream is None else stream.cuda_stream
 
 
 def _dev(t, dtype, shape, name):
@@ -157,6 +182,13 @@ _default_ws = Workspace()
 def _ws_for(need, device, ws):
     buf, n = (ws or _default_ws).get(need, device)
     return _ptr(buf), n
+
+
+def _scratch(ws):
+    """The tensor behind a workspace, for _fast; an object that it refuses where only .get() can tell."""
+    if ws is None:
+        return _default_ws.buf
+    return ws.buf if type(ws) is Workspace else ()
 
 
 class Prepared:
@@ -204,6 +236,10 @@ def dd_prepare_batched(offsets, values, in_features, out_features, prepared=None
 def dd_select_prepare(scores, values, in_features, out_features, offsets_out=None, prepared=None, stream=None):
     """dd_select_diagonals on one score vector [D] and dd_prepare on its result, one call: (offsets [K], prepared)."""
     M, N, K = int(in_features), int(out_features), values.shape[0]
+    if prepared is not None and (prepared.in_features, prepared.out_features, prepared.K, prepared.dtype) == (M, N, K, values.dtype):
+        done = (_fast or _load_fast()).select_prepare(scores, values, M, N, offsets_out, prepared.buf, stream)
+        if done is not None:
+            return done, prepared
     D = max(M, N)
     _, ref, need = _plan(DD_OP_PREPARE, 0, M, N, K, values.dtype, DD_ALGO_PREPARED)
     _dev(scores, torch.float32, (D,), "scores")
@@ -283,6 +319,9 @@ def _product(fn, op, src, offsets, values, n_src, n_dst, M, N, dst, algo, ws, st
         if (prepared.in_features, prepared.out_features, prepared.dtype) != (M, N, src.dtype):
             raise ValueError("prepared block belongs to another layer")
         algo, K = (DD_ALGO_BLOCKS if algo == DD_ALGO_BLOCKS else DD_ALGO_PREPARED), prepared.K
+        done = _fast.product_prepared(op, src, offsets, dst, M, N, K, algo, prepared.buf, stream)
+        if done is not None:
+            return done
         if algo == DD_ALGO_BLOCKS:
             _dev(offsets, torch.int32, (K,), "offsets")
     else:
@@ -309,6 +348,11 @@ def dd_fwd(X, offsets, values, out_features, Y=None, algo=DD_ALGO_AUTO, ws=None,
 
     With prepared= (from dd_prepare) offsets and values are not read and may be None; with algo=DD_ALGO_BLOCKS
     as well, the offsets are read (the product then skips the operand blocks no diagonal crosses)."""
+    if prepared is None:
+        N = int(out_features)
+        done = (_fast or _load_fast()).product(DD_OP_FWD, X, offsets, values, Y, N, algo, _scratch(ws), stream)
+        if done is not None:
+            return done
     M, N = X.shape[1], int(out_features)
     return _product(load_library().dd_fwd, DD_OP_FWD, X, offsets, values, M, N, M, N, Y, algo, ws, stream, prepared,
                     ("X", "Y"))
@@ -316,6 +360,11 @@ def dd_fwd(X, offsets, values, out_features, Y=None, algo=DD_ALGO_AUTO, ws=None,
 
 def dd_bwd_input(dY, offsets, values, in_features, dX=None, algo=DD_ALGO_AUTO, ws=None, stream=None, prepared=None):
     """dX = dY . W_K^T.  dY [T x N] -> dX [T x M].  prepared= as for dd_fwd."""
+    if prepared is None:
+        M = int(in_features)
+        done = (_fast or _load_fast()).product(DD_OP_BWD_INPUT, dY, offsets, values, dX, M, algo, _scratch(ws), stream)
+        if done is not None:
+            return done
     M, N = int(in_features), dY.shape[1]
     return _product(load_library().dd_bwd_input, DD_OP_BWD_INPUT, dY, offsets, values, N, M, M, N, dX, algo, ws, stream,
                     prepared, ("dY", "dX"))
@@ -323,6 +372,9 @@ def dd_bwd_input(dY, offsets, values, in_features, dX=None, algo=DD_ALGO_AUTO, w
 
 def dd_bwd_weight(X, dY, offsets, dValues=None, algo=DD_ALGO_AUTO, ws=None, stream=None):
     """dValues [K x min(M,N)] fp32: the gradient of the values on the K diagonals."""
+    done = (_fast or _load_fast()).bwd_weight(X, dY, offsets, dValues, algo, _scratch(ws), stream)
+    if done is not None:
+        return done
     T, M = X.shape
     N = dY.shape[1]
     K = offsets.shape[0]
@@ -340,6 +392,10 @@ def dd_bwd_weight(X, dY, offsets, dValues=None, algo=DD_ALGO_AUTO, ws=None, stre
 
 def dd_bwd(X, dY, offsets, values, dX=None, dValues=None, algo=DD_ALGO_AUTO, ws=None, stream=None, prepared=None):
     """The backward pass as one call: (dX [T x M], dValues [K x min(M,N)] fp32).  prepared= as for dd_fwd."""
+    if prepared is None:
+        done = (_fast or _load_fast()).bwd(X, dY, offsets, values, None, dX, dValues, algo, _scratch(ws), stream)
+        if done is not None:
+            return done
     T, M = X.shape
     N = dY.shape[1]
     K = offsets.shape[0]
@@ -347,6 +403,9 @@ def dd_bwd(X, dY, offsets, values, dX=None, dValues=None, algo=DD_ALGO_AUTO, ws=
         if (prepared.in_features, prepared.out_features, prepared.dtype) != (M, N, X.dtype):
             raise ValueError("prepared block belongs to another layer")
         algo = DD_ALGO_PREPARED
+        done = (_fast or _load_fast()).bwd(X, dY, offsets, values, prepared.buf, dX, dValues, algo, _scratch(ws), stream)
+        if done is not None:
+            return done
     else:
         _dev(values, X.dtype, (K, min(M, N)), "values")
     _, ref, need = _plan(DD_OP_BWD, T, M, N, K, X.dtype, algo)
@@ -386,6 +445,10 @@ def dd_bwd_weight_static(X, dY, offsets, dValues, algo=DD_ALGO_AUTO, stream=None
 
 def dd_select_diagonals(scores, K, offsets_out=None, ws=None, stream=None):
     """Indices of the K largest scores of each row of scores [batch x D], ascending, int32 [batch x K]."""
+    if ws is None or type(ws) is Workspace:
+        done = (_fast or _load_fast()).select_diagonals(scores, K, offsets_out, stream)
+        if done is not None:
+            return done
     if scores.dim() != 2:
         raise ValueError("scores must be [batch x D]")
     B, D = scores.shape
@@ -513,6 +576,9 @@ def dd_scale_values_bwd(offsets, alpha_tilde, V, dValues, ws=None, stream=None):
 
 def dd_diag_magnitude(values, magnitudes=None, stream=None):
     """magnitudes[k] = sum_p |values[k][p]| (fp32) for values [K x L]."""
+    done = (_fast or _load_fast()).diag_magnitude(values, magnitudes, stream)
+    if done is not None:
+        return done
     K, L = values.shape
     _dev(values, values.dtype, (K, L), "values")
     if magnitudes is None:
@@ -527,6 +593,9 @@ def dd_diagheur_update(D, offsets, magnitudes, random, n_drop, new_offsets=None,
     """Drop the n_drop weakest active diagonals, grow the n_drop inactive candidates with the largest random score.
 
     Returns (new_offsets [K] ascending, source [K]: position in `offsets` or -1 for a grown diagonal)."""
+    done = (_fast or _load_fast()).diagheur_update(D, n_drop, offsets, magnitudes, random, new_offsets, source, _scratch(ws), stream)
+    if done is not None:
+        return done
     D, K = int(D), offsets.shape[0]
     _dev(offsets, torch.int32, (K,), "offsets")
     _dev(magnitudes, torch.float32, (K,), "magnitudes")
