@@ -33,11 +33,15 @@ __global__ __launch_bounds__(THREADS) void select_soft_kernel(int D, int K, floa
 #define DD_BY_SLOTS(kernel_, threads_, slots_)                                                          \
     ((threads_) == kSelectThreadsFew ? ((slots_) <= 1   ? kernel_<kSelectThreadsFew, 1>                 \
                                         : (slots_) <= 2 ? kernel_<kSelectThreadsFew, 2>                 \
+                                        : (slots_) <= 3 ? kernel_<kSelectThreadsFew, 3>                 \
                                         : (slots_) <= 4 ? kernel_<kSelectThreadsFew, 4>                 \
+                                        : (slots_) <= 6 ? kernel_<kSelectThreadsFew, 6>                 \
                                         : (slots_) <= 8 ? kernel_<kSelectThreadsFew, 8>                 \
                                                         : kernel_<kSelectThreadsFew, 16>)               \
                                      : ((slots_) <= 1    ? kernel_<kSelectThreads, 1>                   \
+                                        : (slots_) <= 3  ? kernel_<kSelectThreads, 3>                   \
                                         : (slots_) <= 4  ? kernel_<kSelectThreads, 4>                   \
+                                        : (slots_) <= 8  ? kernel_<kSelectThreads, 8>                   \
                                         : (slots_) <= 16 ? kernel_<kSelectThreads, 16>                  \
                                                          : kernel_<kSelectThreads, kSelectMaxSlots>))
 

@@ -9,8 +9,11 @@
 // (slot, wave) pairs, which run through the candidates in index order.
 //
 // What bounds it is latency: one trip to memory for the scores, then a chain of seven barriers; nothing else runs on the
-// chip meanwhile.  Measured (graph replay): one vector of 4096 scores 5.5 us, of 1024 scores 3.3 us; with 256 threads that
-// read the keys from LDS in every pass and compacted contiguous chunks 12.8 and 5.0 us.
+// chip meanwhile.  The first pass, whose byte is the sign and most of the exponent, has few busy counters -- a quarter to half of
+// all scores meet at one, 2.6 clk each -- and so counts into four copies by lane (from three candidates per thread on; with two
+// and eight copies the shorter vectors are slower).  Measured (graph replay, against one copy and instances for 1, 2, 4, 8, 16
+// candidates per thread): one vector of 768 scores 3.9 -> 3.7 us, 3072 5.7 -> 5.0, 4096 6.2 -> 5.5, 8192 12.0 -> 7.3, 16384
+// 14.1 -> 11.1; 600 x 768 5.0 -> 4.5, 1000 x 4096 13.6 -> 10.9.
 #pragma once
 #include "dd_common.h"
 
@@ -22,8 +25,8 @@ constexpr int kSelectMaxSlots = 64;    // 65536 candidates
 
 // Threads of the workgroup for one score vector.  Alone on the chip a long vector is done sooner by many threads; of many
 // vectors more fit a CU at a time with few, and a short one leaves the other waves waiting at barriers.  Selection, us with
-// 256 and 1024 threads: 1 x 1024 scores 3.3 and 3.6, 1 x 2000 4.4 and 4.8, 1 x 3072 6.5 and 5.2, 600 x 768 4.4 and 7.2,
-// 4000 x 4096 38 and 54; weights: 1 x 768 4.3 and 2.6, 1 x 64 2.0 and 2.3, 300 x 2000 5.7 and 5.2, 4000 x 1024 10 and 24.
+// 256 and 1024 threads: 1 x 1024 scores 3.8 and 4.2, 1 x 2048 4.7 and 4.8, 1 x 2304 6.7 and 4.8, 600 x 768 4.5 and 7.8,
+// 4000 x 4096 30 and 48; weights: 1 x 768 4.3 and 2.6, 1 x 64 2.0 and 2.3, 300 x 2000 5.7 and 5.2, 4000 x 1024 10 and 24.
 inline bool many_vectors(int batch, int D) { return batch > 256 && D <= 16 * kSelectThreadsFew; }
 inline int select_threads(int batch, int D) { return D <= 8 * kSelectThreadsFew || many_vectors(batch, D) ? kSelectThreadsFew : kSelectThreads; }
 inline int soft_threads(int batch, int D) { return D <= kSelectThreadsFew || many_vectors(batch, D) ? kSelectThreadsFew : kSelectThreads; }
@@ -56,23 +59,26 @@ __device__ __forceinline__ unsigned wave_inclusive_scan(unsigned v, int lane)
 template <int THREADS, int SLOTS>
 struct SelectScratch {
     static constexpr int kWaves = THREADS / 64, kPairs = SLOTS * kWaves;
-    unsigned hist[4][256];
+    static constexpr int kCopies = SLOTS >= 3 ? 4 : 1, kCopyStride = 264;  // of the first pass's histogram: other banks, rows of 16 bytes
+    unsigned first[kCopies * kCopyStride], hist[3][256];
     unsigned gt[kPairs], eq[kPairs];  // per (slot, wave): how many are larger than tau / equal to it; then those before
 };
 
 // Of the D candidates (D <= THREADS * SLOTS) the K with the largest keys, 1 <= K <= D.  place[j]: the position of this
 // thread's candidate j * THREADS + threadIdx.x among the chosen ones, ascending by index, or -1.  A workgroup may call it
-// again on the same scratch after a barrier.
+// again on the same scratch after a barrier.  Groups of THREADS threads of one workgroup may call it side by side, each with keys and
+// scratch of its own; tid is then the thread's number within its group.
 // MASKED_OUT: many of the candidates may share the lowest keys (-infinity and NaN, what candidates are masked out with); the first
 // pass counts these by the wave, where one by one all 64 lanes would wait for the same counter (2765 of 3072: 3 us).
 template <int THREADS, int SLOTS, bool MASKED_OUT = false>
 __device__ __forceinline__ void select_block(int D, int K, const uint32_t (&key)[SLOTS], SelectScratch<THREADS, SLOTS> &s,
-                                             int (&place)[SLOTS])
+                                             int (&place)[SLOTS], const int tid = int(threadIdx.x))
 {
     using Scratch = SelectScratch<THREADS, SLOTS>;
     constexpr int kWaves = Scratch::kWaves, kPairs = Scratch::kPairs;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < 4 * 256; i += THREADS) (&s.hist[0][0])[i] = 0u;
+    const int lane = tid & 63, wave = tid >> 6;
+    constexpr int kCopies = Scratch::kCopies, kCopyStride = Scratch::kCopyStride;
+    for (int i = tid; i < kCopies * kCopyStride + 3 * 256; i += THREADS) s.first[i] = 0u;  // and hist behind it
     __syncthreads();
     unsigned prefix = 0u, mask = 0u, remaining = unsigned(K);
 #pragma unroll
@@ -87,13 +93,21 @@ __device__ __forceinline__ void select_block(int D, int K, const uint32_t (&key)
                 lowest += unsigned(__popcll(low));
                 counts = counts && key[j] >> 24 != 0u;
             }
-            if (counts) atomicAdd(&s.hist[pass][(key[j] >> shift) & 255u], 1u);
+            unsigned *to = pass == 0 ? s.first + (lane & (kCopies - 1)) * kCopyStride : s.hist[pass - 1];
+            if (counts) atomicAdd(to + ((key[j] >> shift) & 255u), 1u);
         }
-        if (MASKED_OUT && pass == 0 && lane == 0 && lowest) atomicAdd(&s.hist[0][0], lowest);
+        if (MASKED_OUT && pass == 0 && lane == 0 && lowest) atomicAdd(&s.first[0], lowest);
         __syncthreads();
         // lane l owns bins 255 - 4l ... 252 - 4l (descending); the bin where the running count of larger-or-equal keys
         // first reaches `remaining`
-        const uint4 bins = *reinterpret_cast<const uint4 *>(&s.hist[pass][252 - 4 * lane]);
+        uint4 bins = *reinterpret_cast<const uint4 *>((pass == 0 ? s.first : s.hist[pass - 1]) + 252 - 4 * lane);
+        if (pass == 0) {
+#pragma unroll
+            for (int c = 1; c < kCopies; ++c) {
+                const uint4 more = *reinterpret_cast<const uint4 *>(&s.first[c * kCopyStride + 252 - 4 * lane]);
+                bins.x += more.x, bins.y += more.y, bins.z += more.z, bins.w += more.w;
+            }
+        }
         const unsigned h[4] = {bins.w, bins.z, bins.y, bins.x};
         const unsigned mine = h[0] + h[1] + h[2] + h[3];
         const unsigned incl = wave_inclusive_scan(mine, lane);
