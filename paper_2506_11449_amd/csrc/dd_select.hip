@@ -25,8 +25,18 @@ __global__ __launch_bounds__(THREADS) void select_soft_kernel(int D, int K, floa
                                                               float *__restrict__ alpha_tilde)
 {
     __shared__ __attribute__((aligned(16))) SelectScratch<THREADS, SLOTS> scratch;
-    select_topk_block<THREADS, SLOTS>(D, K, scores + size_t(blockIdx.x) * D, scratch, out + size_t(blockIdx.x) * K);
-    soft_topk_block<THREADS>(D, float(K), inv_temp, scores + size_t(blockIdx.x) * D, alpha_tilde + size_t(blockIdx.x) * D);
+    const float *row = scores + size_t(blockIdx.x) * D;
+    int *chosen = out + size_t(blockIdx.x) * K;
+    float *weights = alpha_tilde + size_t(blockIdx.x) * D;
+    if constexpr (SLOTS <= kSoftHeldSlots) {
+        float a[SLOTS];
+        hold<THREADS, SLOTS>(D, row, a);
+        select_held_block<THREADS, SLOTS>(D, K, a, scratch, chosen);
+        soft_topk_held<THREADS, SLOTS>(D, float(K), inv_temp, a, weights);
+    } else {
+        select_topk_block<THREADS, SLOTS>(D, K, row, scratch, chosen);
+        soft_topk_block(D, float(K), inv_temp, row, weights);
+    }
 }
 
 // the instance for that many threads and candidates per thread, by the name of a template of the two
@@ -38,8 +48,7 @@ __global__ __launch_bounds__(THREADS) void select_soft_kernel(int D, int K, floa
                                         : (slots_) <= 6 ? kernel_<kSelectThreadsFew, 6>                 \
                                         : (slots_) <= 8 ? kernel_<kSelectThreadsFew, 8>                 \
                                                         : kernel_<kSelectThreadsFew, 16>)               \
-                                     : ((slots_) <= 1    ? kernel_<kSelectThreads, 1>                   \
-                                        : (slots_) <= 3  ? kernel_<kSelectThreads, 3>                   \
+                                     : ((slots_) <= 3  ? kernel_<kSelectThreads, 3>                   \
                                         : (slots_) <= 4  ? kernel_<kSelectThreads, 4>                   \
                                         : (slots_) <= 8  ? kernel_<kSelectThreads, 8>                   \
                                         : (slots_) <= 16 ? kernel_<kSelectThreads, 16>                  \
@@ -48,7 +57,7 @@ __global__ __launch_bounds__(THREADS) void select_soft_kernel(int D, int K, floa
 hipError_t launch_select_soft(int batch, int D, int K, float temperature, const float *scores, int *out,
                               float *alpha_tilde, hipStream_t stream)
 {
-    const int threads = soft_threads(batch, D), slots = (D + threads - 1) / threads;
+    const int threads = select_threads(batch, D), slots = (D + threads - 1) / threads;
     hipLaunchKernelGGL(DD_BY_SLOTS(select_soft_kernel, threads, slots), dim3(batch), dim3(threads), 0, stream, D, K,
                        1.f / temperature, scores, out, alpha_tilde);
     return hipGetLastError();

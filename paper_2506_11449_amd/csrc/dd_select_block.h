@@ -20,16 +20,16 @@
 namespace dd {
 
 constexpr int kSelectThreads = 1024;   // threads of the kernels that work on score vectors ...
-constexpr int kSelectThreadsFew = 256; // ... or these: select_threads, soft_threads
+constexpr int kSelectThreadsFew = 256; // ... or these: select_threads
 constexpr int kSelectMaxSlots = 64;    // 65536 candidates
 
-// Threads of the workgroup for one score vector.  Alone on the chip a long vector is done sooner by many threads; of many
-// vectors more fit a CU at a time with few, and a short one leaves the other waves waiting at barriers.  Selection, us with
-// 256 and 1024 threads: 1 x 1024 scores 3.8 and 4.2, 1 x 2048 4.7 and 4.8, 1 x 2304 6.7 and 4.8, 600 x 768 4.5 and 7.8,
-// 4000 x 4096 30 and 48; weights: 1 x 768 4.3 and 2.6, 1 x 64 2.0 and 2.3, 300 x 2000 5.7 and 5.2, 4000 x 1024 10 and 24.
+// Threads of the workgroup for one score vector, for the selection and for the weights.  Alone on the chip a long vector is done
+// sooner by many threads; of many vectors more fit a CU at a time with few, and a short one leaves the other waves waiting at
+// barriers.  us with 256 and 1024 threads: selection of 1 x 1024 scores 3.8 and 4.2, 1 x 2048 4.7 and 4.8, 1 x 2304 6.7 and 4.8,
+// 600 x 768 4.5 and 7.8, 4000 x 4096 30 and 48; with the weights 1 x 768 4.4 and 5.3, 1 x 2000 6.0 and 6.4, 1 x 3072 9.2 and 6.6,
+// 1000 x 4096 18 and 21; weights alone 1 x 64 2.5 and 2.7, 1 x 2000 3.1 and 3.5, 1 x 4096 3.6 and 3.6.
 inline bool many_vectors(int batch, int D) { return batch > 256 && D <= 16 * kSelectThreadsFew; }
 inline int select_threads(int batch, int D) { return D <= 8 * kSelectThreadsFew || many_vectors(batch, D) ? kSelectThreadsFew : kSelectThreads; }
-inline int soft_threads(int batch, int D) { return D <= kSelectThreadsFew || many_vectors(batch, D) ? kSelectThreadsFew : kSelectThreads; }
 
 __device__ __forceinline__ uint32_t score_key(float s)
 {
@@ -170,23 +170,29 @@ __device__ __forceinline__ void select_block(int D, int K, const uint32_t (&key)
     }
 }
 
-// The same from a vector of scores in memory; the chosen indices go to `dst` (global or LDS), ascending.  Ends without a
-// barrier.
+// The same for scores that the threads hold (slot j of thread t: candidate j * THREADS + t, anything past the end); the chosen
+// indices go to `dst` (global or LDS), ascending.  Ends without a barrier.
 template <int THREADS, int SLOTS>
-__device__ __forceinline__ void select_topk_block(int D, int K, const float *__restrict__ row,
-                                                  SelectScratch<THREADS, SLOTS> &s, int *dst)
+__device__ __forceinline__ void select_held_block(int D, int K, const float (&a)[SLOTS], SelectScratch<THREADS, SLOTS> &s, int *dst)
 {
     uint32_t key[SLOTS];
     int place[SLOTS];
 #pragma unroll
-    for (int j = 0; j < SLOTS; ++j) {
-        const int i = j * THREADS + int(threadIdx.x);
-        key[j] = score_key(row[min(i, D - 1)]);
-    }
+    for (int j = 0; j < SLOTS; ++j) key[j] = score_key(a[j]);
     select_block<THREADS, SLOTS>(D, K, key, s, place);
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j)
         if (place[j] >= 0) dst[place[j]] = j * THREADS + int(threadIdx.x);
+}
+// The same from a vector of scores in memory.
+template <int THREADS, int SLOTS>
+__device__ __forceinline__ void select_topk_block(int D, int K, const float *__restrict__ row,
+                                                  SelectScratch<THREADS, SLOTS> &s, int *dst)
+{
+    float a[SLOTS];
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) a[j] = row[min(j * THREADS + int(threadIdx.x), D - 1)];
+    select_held_block<THREADS, SLOTS>(D, K, a, s, dst);
 }
 
 }  // namespace dd

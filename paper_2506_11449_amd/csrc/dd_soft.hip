@@ -10,35 +10,62 @@ namespace dd {
 
 constexpr int kScaleThreads = 256;  // kernels that run over the K x L values
 
-template <int THREADS>
+// SLOTS: candidates that a thread holds in registers, 0 (1024 threads): read from memory by each pass
+template <int THREADS, int SLOTS>
 __global__ __launch_bounds__(THREADS) void soft_topk_kernel(int D, float k_over_1, float inv_temp,
                                                             const float *__restrict__ scores,
                                                             float *__restrict__ alpha_tilde)
 {
-    soft_topk_block<THREADS>(D, k_over_1, inv_temp, scores + size_t(blockIdx.x) * D, alpha_tilde + size_t(blockIdx.x) * D);
+    const float *row = scores + size_t(blockIdx.x) * D;
+    float *out = alpha_tilde + size_t(blockIdx.x) * D;
+    if constexpr (SLOTS > 0) {
+        float a[SLOTS];
+        hold<THREADS, SLOTS>(D, row, a);
+        soft_topk_held<THREADS, SLOTS>(D, k_over_1, inv_temp, a, out);
+    } else {
+        soft_topk_block(D, k_over_1, inv_temp, row, out);
+    }
 }
 
 // d a_i = (K / temp) * s_i * (m_i g_i - sum_j m_j g_j s_j),  m_j = [K s_j < 1]
-template <int THREADS>
+template <int THREADS, int SLOTS>
 __global__ __launch_bounds__(THREADS) void soft_topk_bwd_kernel(int D, float k_over_1, float inv_temp,
                                                                 const float *__restrict__ scores,
                                                                 const float *__restrict__ g,
                                                                 float *__restrict__ dscores)
 {
-    __shared__ SoftScratch scratch;
     const float *a = scores + size_t(blockIdx.x) * D, *gb = g + size_t(blockIdx.x) * D;
     float *out = dscores + size_t(blockIdx.x) * D;
-    const float m = reduce_scores<true, THREADS>(D, scratch, [&](int i) { return a[i]; });
-    const float s = reduce_scores<false, THREADS>(D, scratch, [&](int i) { return expf((a[i] - m) * inv_temp); });
-    const float inv_s = 1.f / s;
-    const float dot = reduce_scores<false, THREADS>(D, scratch, [&](int i) {
-        const float si = expf((a[i] - m) * inv_temp) * inv_s;
-        return k_over_1 * si < 1.f ? gb[i] * si : 0.f;
-    });
-    for (int i = threadIdx.x; i < D; i += THREADS) {
-        const float si = expf((a[i] - m) * inv_temp) * inv_s;
-        const float mg = k_over_1 * si < 1.f ? gb[i] : 0.f;
-        out[i] = k_over_1 * inv_temp * si * (mg - dot);
+    if constexpr (SLOTS > 0) {
+        __shared__ HeldScratch held;
+        float x[SLOTS], g_held[SLOTS], s[SLOTS], part[SLOTS];
+        hold<THREADS, SLOTS>(D, a, x);
+        hold<THREADS, SLOTS>(D, gb, g_held);
+        const float inv_s = 1.f / exponentials_held<THREADS, SLOTS>(D, inv_temp, x, held, s);
+#pragma unroll
+        for (int j = 0; j < SLOTS; ++j) {
+            s[j] *= inv_s;
+            if (!(k_over_1 * s[j] < 1.f)) g_held[j] = 0.f;
+            part[j] = j * THREADS + int(threadIdx.x) < D && k_over_1 * s[j] < 1.f ? g_held[j] * s[j] : 0.f;
+        }
+        const float dot = sum_held<THREADS, SLOTS>(part, held.waves[2], held.parts[1]);
+#pragma unroll
+        for (int j = 0; j < SLOTS; ++j)
+            if (j * THREADS + int(threadIdx.x) < D) out[j * THREADS + threadIdx.x] = k_over_1 * inv_temp * s[j] * (g_held[j] - dot);
+    } else {
+        __shared__ SoftScratch scratch;
+        const float m = reduce_scores<true>(D, scratch, [&](int i) { return a[i]; });
+        const float s = reduce_scores<false>(D, scratch, [&](int i) { return expf((a[i] - m) * inv_temp); });
+        const float inv_s = 1.f / s;
+        const float dot = reduce_scores<false>(D, scratch, [&](int i) {
+            const float si = expf((a[i] - m) * inv_temp) * inv_s;
+            return k_over_1 * si < 1.f ? gb[i] * si : 0.f;
+        });
+        for (int i = threadIdx.x; i < D; i += THREADS) {
+            const float si = expf((a[i] - m) * inv_temp) * inv_s;
+            const float mg = k_over_1 * si < 1.f ? gb[i] : 0.f;
+            out[i] = k_over_1 * inv_temp * si * (mg - dot);
+        }
     }
 }
 
@@ -90,11 +117,21 @@ __global__ __launch_bounds__(kScaleThreads) void scatter_alpha_grad_kernel(int D
     dalpha[i] = acc;
 }
 
+// the instance for that many threads and candidates per thread
+#define DD_SOFT_BY_SLOTS(kernel_, threads_, slots_)                                                     \
+    ((threads_) == kSelectThreadsFew ? ((slots_) <= 1    ? kernel_<kSelectThreadsFew, 1>                \
+                                        : (slots_) <= 4  ? kernel_<kSelectThreadsFew, 4>                \
+                                        : (slots_) <= 8  ? kernel_<kSelectThreadsFew, 8>                \
+                                                         : kernel_<kSelectThreadsFew, 16>)              \
+                                     : ((slots_) <= 4  ? kernel_<kSelectThreads, 4>                   \
+                                        : (slots_) <= 16 ? kernel_<kSelectThreads, 16>                  \
+                                                         : kernel_<kSelectThreads, 0>))
+
 hipError_t launch_soft_topk(int batch, int D, int K, float temperature, const float *scores, float *alpha_tilde,
                             hipStream_t stream)
 {
-    const int threads = soft_threads(batch, D);
-    hipLaunchKernelGGL((threads == kSelectThreadsFew ? soft_topk_kernel<kSelectThreadsFew> : soft_topk_kernel<kSelectThreads>),
+    const int threads = select_threads(batch, D);
+    hipLaunchKernelGGL(DD_SOFT_BY_SLOTS(soft_topk_kernel, threads, (D + threads - 1) / threads),
                        dim3(batch), dim3(threads), 0, stream, D, float(K), 1.f / temperature, scores, alpha_tilde);
     return hipGetLastError();
 }
@@ -102,8 +139,8 @@ hipError_t launch_soft_topk(int batch, int D, int K, float temperature, const fl
 hipError_t launch_soft_topk_bwd(int batch, int D, int K, float temperature, const float *scores, const float *g,
                                 float *dscores, hipStream_t stream)
 {
-    const int threads = soft_threads(batch, D);
-    hipLaunchKernelGGL((threads == kSelectThreadsFew ? soft_topk_bwd_kernel<kSelectThreadsFew> : soft_topk_bwd_kernel<kSelectThreads>),
+    const int threads = select_threads(batch, D);
+    hipLaunchKernelGGL(DD_SOFT_BY_SLOTS(soft_topk_bwd_kernel, threads, (D + threads - 1) / threads),
                        dim3(batch), dim3(threads), 0, stream, D, float(K), 1.f / temperature, scores, g, dscores);
     return hipGetLastError();
 }
