@@ -25,7 +25,9 @@ namespace dd {
 
 constexpr int kHeurThreads = 256;
 
-// magnitudes[k] = sum_p |values[k][p]|: one workgroup per diagonal, fixed-order tree reduction
+// magnitudes[k] = sum_p |values[k][p]|: one workgroup per diagonal, fixed-order tree reduction (thread t's sum over p = t, t + 256, ...;
+// then t with t + 128, t + 64, ... t + 1).  Bound by latency: eight values are requested
+// at a time, and after one barrier a wave adds by lane shuffles (307 diagonals of 768 bf16 values 3.05 -> 2.94 us, 1638 of 4096 4.63 -> 4.54).
 template <typename Tr>
 __global__ __launch_bounds__(kHeurThreads) void diag_magnitude_kernel(int L, const typename Tr::storage *__restrict__ values,
                                                                       float *__restrict__ magnitudes)
@@ -33,14 +35,21 @@ __global__ __launch_bounds__(kHeurThreads) void diag_magnitude_kernel(int L, con
     __shared__ float part[kHeurThreads];
     const typename Tr::storage *row = values + size_t(blockIdx.x) * L;
     float s = 0.f;
-    for (int p = threadIdx.x; p < L; p += kHeurThreads) s += fabsf(Tr::load(row + p));
+    for (int first = threadIdx.x; first < L; first += 8 * kHeurThreads) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = first + u * kHeurThreads < L ? fabsf(Tr::load(row + first + u * kHeurThreads)) : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
     part[threadIdx.x] = s;
     __syncthreads();
-    for (int w = kHeurThreads / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) magnitudes[blockIdx.x] = part[0];
+    if (threadIdx.x >= 64) return;
+    s = (s + part[threadIdx.x + 128]) + (part[threadIdx.x + 64] + part[threadIdx.x + 192]);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);
+    if (threadIdx.x == 0) magnitudes[blockIdx.x] = s;
 }
 
 // The two selections one after the other, as above.  slot: table offset -> position in `offsets` (-1: not active), complete.
