@@ -60,7 +60,8 @@ template <int THREADS, int SLOTS>
 struct SelectScratch {
     static constexpr int kWaves = THREADS / 64, kPairs = SLOTS * kWaves;
     static constexpr int kCopies = SLOTS >= 3 ? 4 : 1, kCopyStride = 264;  // of the first pass's histogram: other banks, rows of 16 bytes
-    unsigned first[kCopies * kCopyStride], hist[3][256];
+    static constexpr int kCounters = kCopies * kCopyStride + 3 * 256;      // then those of the other passes
+    unsigned hist[kCounters];
     unsigned gt[kPairs], eq[kPairs];  // per (slot, wave): how many are larger than tau / equal to it; then those before
 };
 
@@ -78,12 +79,13 @@ __device__ __forceinline__ void select_block(int D, int K, const uint32_t (&key)
     constexpr int kWaves = Scratch::kWaves, kPairs = Scratch::kPairs;
     const int lane = tid & 63, wave = tid >> 6;
     constexpr int kCopies = Scratch::kCopies, kCopyStride = Scratch::kCopyStride;
-    for (int i = tid; i < kCopies * kCopyStride + 3 * 256; i += THREADS) s.first[i] = 0u;  // and hist behind it
+    for (int i = tid; i < Scratch::kCounters; i += THREADS) s.hist[i] = 0u;
     __syncthreads();
     unsigned prefix = 0u, mask = 0u, remaining = unsigned(K);
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 24 - 8 * pass;
+        unsigned *const hist = s.hist + (pass == 0 ? 0 : kCopies * kCopyStride + (pass - 1) * 256);
         unsigned lowest = 0u;
 #pragma unroll
         for (int j = 0; j < SLOTS; ++j) {
@@ -93,18 +95,18 @@ __device__ __forceinline__ void select_block(int D, int K, const uint32_t (&key)
                 lowest += unsigned(__popcll(low));
                 counts = counts && key[j] >> 24 != 0u;
             }
-            unsigned *to = pass == 0 ? s.first + (lane & (kCopies - 1)) * kCopyStride : s.hist[pass - 1];
-            if (counts) atomicAdd(to + ((key[j] >> shift) & 255u), 1u);
+            const int copy = pass == 0 ? (lane & (kCopies - 1)) * kCopyStride : 0;
+            if (counts) atomicAdd(&hist[copy + ((key[j] >> shift) & 255u)], 1u);
         }
-        if (MASKED_OUT && pass == 0 && lane == 0 && lowest) atomicAdd(&s.first[0], lowest);
+        if (MASKED_OUT && pass == 0 && lane == 0 && lowest) atomicAdd(&hist[0], lowest);
         __syncthreads();
         // lane l owns bins 255 - 4l ... 252 - 4l (descending); the bin where the running count of larger-or-equal keys
         // first reaches `remaining`
-        uint4 bins = *reinterpret_cast<const uint4 *>((pass == 0 ? s.first : s.hist[pass - 1]) + 252 - 4 * lane);
+        uint4 bins = *reinterpret_cast<const uint4 *>(&hist[252 - 4 * lane]);
         if (pass == 0) {
 #pragma unroll
             for (int c = 1; c < kCopies; ++c) {
-                const uint4 more = *reinterpret_cast<const uint4 *>(&s.first[c * kCopyStride + 252 - 4 * lane]);
+                const uint4 more = *reinterpret_cast<const uint4 *>(&hist[c * kCopyStride + 252 - 4 * lane]);
                 bins.x += more.x, bins.y += more.y, bins.z += more.z, bins.w += more.w;
             }
         }

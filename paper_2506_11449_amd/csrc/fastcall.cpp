@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <exception>
 #include <unordered_map>
 
 #include "../../include/dynadiag.h"
@@ -206,7 +207,12 @@ PyObject *answer(F body, R &...results)
         PyErr_Clear();
         Py_RETURN_NONE;
     }
-    return status == DD_OK ? result(results...) : PyObject_CallFunction(check, "i", status);
+    try {
+        return status == DD_OK ? result(results...) : PyObject_CallFunction(check, "i", status);
+    } catch (const std::exception &e) {  // a new output that cannot be wrapped
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
 }
 
 // product(transposed, src, offsets, values, dst, features of dst, algo, workspace, stream)
