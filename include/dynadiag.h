@@ -215,9 +215,9 @@ dd_status dd_bwd_weight(const dd_layer *layer, const void *X, const void *dY, co
  * LDS; a schedule that takes the tokens in runs small enough for dY to stay cached between the two was built and
  * measured slower than this one at every benchmark shape (more launches and partial sums than the cached read saves).
  *   X [tokens x M], dY [tokens x N] in;  dX [tokens x M] out;  dValues [K x L] fp32 out.
- * For a handful of diagonals (K <= 8, bf16, M <= N, multiples of 128) the two read dY at the same places and are one kernel,
- * bit for bit the two calls with DD_ALGO_VECTOR; DD_ALGO_AUTO weighs it against both products together, so that it may
- * take it where one of the two calls by itself would run on the matrix cores.  The vector kernels for few tokens share a launch.
+ * For a handful of diagonals (K <= 8, bf16, M <= N, multiples of 128) the two read dY at the same places and are one kernel
+ * where both calls would take the vector kernels.  The vector kernels for few tokens share a launch.  Either way the bits are those
+ * of the two calls, whatever the size of the scratch.
  *   layer->algo = DD_ALGO_PREPARED: `prepared` is the block dd_prepare filled (values is not read); any other
  *   algo: prepared is not read.  DD_ALGO_BLOCKS: DD_ERR_UNSUPPORTED.
  *   ws: dd_workspace_bytes(DD_OP_BWD, layer, 0).  Errors as for the two calls.

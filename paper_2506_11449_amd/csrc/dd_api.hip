@@ -96,16 +96,12 @@ bool fits_ragged(const Shape &s, const void *ws, size_t ws_bytes)
     return ws && reinterpret_cast<uintptr_t>(ws) % kWsAlign == 0 && ws_bytes >= dd::product_ragged_ws_bytes(s.D, s.L);
 }
 
-// Both gradients of an expanding layer with a handful of diagonals in one kernel (they read dY at the same shifted places).  It
-// is ahead of two such kernels wherever they run (1024^2, 4 diagonals, 25216 tokens 59 -> 41 us), and of the two products that
-// DD_ALGO_AUTO would take one by one up to 8 diagonals (us, one kernel and the two calls, 25216 tokens: 512^2, 8 diagonals 40 and
-// 47, 768^2, 6 43 and 58, 1024^2, 8 55 and 79; 3000 tokens: 512^2, 8 18 and 20) but on narrow layers with many tokens (256^2, 6
-// 29 and 26, 128^2, 4 33 and 18), where the sum over the workgroups weighs.
+// Both gradients of an expanding layer with a handful of diagonals in one kernel (they read dY at the same shifted places), where the
+// two calls by themselves would run such kernels: it is ahead of the two wherever they run (1024^2, 4 diagonals, 25216 tokens
+// 59 -> 41 us), gives their bits and needs their scratch.  Not where either call would run on the matrix cores, whose sums have another order.
 bool wants_lowk_bwd(const dd_layer *l, const Shape &s)
 {
-    if (!s.expanding || !dd::lowk_bwd_supported(l->tokens, s.D, s.L, l->K, l->dtype == DD_BF16)) return false;
-    if (wants_lowk(l, s, false) && wants_lowk_wgrad(l, s)) return true;
-    return l->algo == DD_ALGO_AUTO && (s.L >= 512 || l->tokens <= 4096);
+    return s.expanding && wants_lowk(l, s, false) && wants_lowk_wgrad(l, s) && dd::lowk_bwd_supported(l->tokens, s.D, s.L, l->K, l->dtype == DD_BF16);
 }
 
 // the block dd_prepare fills: the operand of the forward product, then the one of the backward-input product
@@ -409,8 +405,7 @@ dd_status dd_bwd(const dd_layer *layer, const void *X, const void *dY, const int
         const bool aligned_input = aligned16(dY) && aligned16(dX), aligned_weight = aligned16(X) && aligned16(dY);
         const dd::WeightGradArgs w = {layer->tokens, s.D, s.L, layer->K, layer->dtype == DD_BF16, s.expanding ? X : dY, s.expanding ? dY : X,
                                       offsets, dValues, ws};
-        if (aligned_input && aligned_weight && wants_lowk_bwd(layer, s) &&
-            ws_bytes >= dd::weight_grad_lowk_ws_bytes(layer->tokens, s.D, s.L, layer->K))
+        if (aligned_input && aligned_weight && wants_lowk_bwd(layer, s))
             return dd::launch_lowk_bwd(w, values, dX, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? DD_OK : DD_ERR_HIP;
         dd::ProductArgs p;
         p.T = layer->tokens;
