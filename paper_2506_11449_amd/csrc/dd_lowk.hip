@@ -16,6 +16,8 @@
 #include "dd_common.h"
 #include "dd_launch.h"
 
+#include <limits.h>
+
 namespace dd {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -320,6 +322,10 @@ __global__ __launch_bounds__(64 * (WITH_DX ? lowk_bwd_max_waves(NI, KC) : lowk_m
     if (tid < KC) s_off[tid] = tid < K ? canonical_offset(offsets[tid], D) : 0;
 
     const int ppr = wlds / 8, total = rows * ppr;
+    // Seven and eight diagonals leave no registers for the pieces' rows, which say what lies past the last token: there the pieces' places
+    // do, and of eight diagonals two are read at a time (28 bytes of scratch per lane without either; 768 -> 3072, 8 diagonals,
+    // 25216 tokens 78 -> 72 us, 256 -> 1024 59 -> 55, few tokens and square layers within 2 %).  Fewer diagonals are 2 % behind that way.
+    constexpr bool kByPlace = WITH_DX && NI == 1 && KC > 6;
     int g_at[kLkPieces], l_at[kLkPieces], row_of[kLkPieces];
 #pragma unroll
     for (int p = 0; p < kLkPieces; ++p) {
@@ -340,9 +346,10 @@ __global__ __launch_bounds__(64 * (WITH_DX ? lowk_bwd_max_waves(NI, KC) : lowk_m
     unsigned live = 0;
     auto fetch = [&](int64_t t0) {
         live = 0;
+        const unsigned left = kByPlace ? unsigned(min((T - t0) * D, int64_t(INT_MAX))) : 0u;  // elements of B from the tile on
 #pragma unroll
         for (int p = 0; p < kLkPieces; ++p) {
-            const bool there = g_at[p] >= 0 && t0 + row_of[p] < T;
+            const bool there = kByPlace ? unsigned(g_at[p]) < left : g_at[p] >= 0 && t0 + row_of[p] < T;
             live |= unsigned(there) << p;
             next[p] = *reinterpret_cast<const u32x4 *>(there ? B + t0 * D + g_at[p] : B);
         }
@@ -419,7 +426,7 @@ __global__ __launch_bounds__(64 * (WITH_DX ? lowk_bwd_max_waves(NI, KC) : lowk_m
                 Cols::unpack(cur_a[q][i], odd, a0[i], a1[i]);
                 d0[i] = d1[i] = 0.f;
             }
-            constexpr int kBatch = WITH_DX && KC > 6 ? 4 : 8, KB = kBatch / NI < KC ? kBatch / NI : KC;
+            constexpr int kBatch = WITH_DX && KC > 6 ? (kByPlace && KC > 7 ? 2 : 4) : 8, KB = kBatch / NI < KC ? kBatch / NI : KC;
 #pragma unroll
             for (int kb = 0; kb < KC; kb += KB) {
                 float xv[KB][NI][2];

@@ -1,5 +1,5 @@
-"""The products for a handful of diagonals keep their weights and sums in registers: none of their kernels may spill to
-scratch memory (a spill costs them a factor of four).  Compiled here for gfx950; needs hipcc, no GPU."""
+"""The products for a handful of diagonals keep their weights and sums in registers, and so does the kernel that takes both gradients:
+none of these may spill to scratch memory (a spill costs a product a factor of four).  Compiled here for gfx950; needs hipcc, no GPU."""
 import os
 import re
 import subprocess
@@ -22,7 +22,9 @@ def _scratch(source, tmp_path):
                                              out.stderr, flags=re.S)}
 
 
-def test_products_for_a_handful_of_diagonals_do_not_spill(tmp_path):
-    scratch = {n: b for n, b in _scratch("dd_lowk.hip", tmp_path).items() if "lowk_product_kernel" in n}
-    assert len(scratch) >= 40
-    assert {n: b for n, b in scratch.items() if b} == {}
+def test_kernels_for_a_handful_of_diagonals_do_not_spill(tmp_path):
+    scratch = _scratch("dd_lowk.hip", tmp_path)
+    products = {n: b for n, b in scratch.items() if "lowk_product_kernel" in n}
+    both_gradients = {n: b for n, b in scratch.items() if re.search(r"lowk_wgrad_kernelILi\d+ELi\d+ELb1E", n)}
+    assert len(products) >= 40 and len(both_gradients) == 24  # 1, 2, 4 column pairs a lane, 1 ... 8 diagonals
+    assert {n: b for n, b in {**products, **both_gradients}.items() if b} == {}
