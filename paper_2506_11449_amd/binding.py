@@ -8,6 +8,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import threading
 
 import torch  # imported before the library so that both share one HIP runtime
 
@@ -46,7 +47,7 @@ def _load_fastcall(lib):
     loader = importlib.machinery.ExtensionFileLoader(f"{__package__}._fastcall", FASTCALL_PATH)
     module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(loader.name, FASTCALL_PATH, loader=loader))
     loader.exec_module(module)
-    module.bind(_current_stream, _check, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _FAST_ENTRIES))
+    module.bind(_current_stream, _check, _default_block, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _FAST_ENTRIES))
     return module
 
 
@@ -163,7 +164,8 @@ def _dev(t, dtype, shape, name):
 
 
 class Workspace:
-    """A reusable block of device scratch, grown on demand by the caller's side of the ABI."""
+    """A reusable block of device scratch, grown on demand by the caller's side of the ABI.  Calls that may run at the same time (on
+    different streams, from different threads, replays of a graph) need a workspace each; calls with ws=None see to that themselves."""
 
     def __init__(self):
         self.buf = None
@@ -176,18 +178,73 @@ class Workspace:
         return self.buf, self.buf.numel()
 
 
-_default_ws = Workspace()
+class DefaultBlocks(threading.local):
+    """The scratch of calls that are given no workspace: a block for each thread, device and stream, so that no two calls that may run
+    at the same time share one.  Every block belongs to its stream (it is allocated there), which orders whatever takes its memory
+    next behind the calls that used it: it may be replaced by a larger one, or given up as the oldest of MOST, at any time.  A
+    thread's blocks go with it."""
+
+    MOST = 16
+
+    def __init__(self):
+        self.blocks = {}
+
+    def get(self, key, nbytes, allocate):
+        block = self.blocks.get(key)
+        if block is None or block.numel() < nbytes:
+            block = allocate(nbytes)
+            self.blocks.pop(key, None)
+            if len(self.blocks) >= self.MOST:
+                del self.blocks[next(iter(self.blocks))]
+            self.blocks[key] = block
+        return block
 
 
-def _ws_for(need, device, ws):
-    buf, n = (ws or _default_ws).get(need, device)
-    return _ptr(buf), n
+_default_blocks = DefaultBlocks()
+
+
+def _on(stream, device):
+    """Context in which `stream` (a torch stream, or any object with a handle) is the current one."""
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    return torch.cuda.stream(stream)
+
+
+def _default_block(nbytes, beside, stream):
+    """Scratch for a call on `stream` (None: the current one) with tensors on the device of `beside`.  A call that is being captured
+    gets a block of its own, which then belongs to the graph: a replay may meet calls of any stream."""
+    device = beside.device
+    if stream is not None:
+        with _on(stream, device):
+            return _default_block(nbytes, beside, None)
+    allocate = lambda n: torch.empty(n, dtype=torch.uint8, device=device)
+    if torch.cuda.is_current_stream_capturing():
+        return allocate(nbytes)
+    return _default_blocks.get((device, _current_stream()), nbytes, allocate)
+
+
+def _ws_for(need, beside, ws, stream):
+    """(address, bytes, the tensor itself: to be held until the call has been made) of the scratch for a call."""
+    if need == 0:
+        return None, 0, None
+    if ws is None:
+        buf = _default_block(need, beside, stream)
+        return _ptr(buf), buf.numel(), buf
+    old = getattr(ws, "buf", None)
+    if stream is None:
+        buf, n = ws.get(need, beside.device)
+    else:
+        with _on(stream, beside.device):  # memory that this stream may use at once
+            buf, n = ws.get(need, beside.device)
+            if old is not None and old is not buf:
+                old.record_stream(torch.cuda.current_stream())
+    return _ptr(buf), n, buf
 
 
 def _scratch(ws):
-    """The tensor behind a workspace, for _fast; an object that it refuses where only .get() can tell."""
+    """What _fast takes for a workspace: its tensor, ... for none, or an object that it refuses where only .get() can tell."""
     if ws is None:
-        return _default_ws.buf
+        return ...
     return ws.buf if type(ws) is Workspace else ()
 
 
@@ -338,7 +395,7 @@ def _product(fn, op, src, offsets, values, n_src, n_dst, M, N, dst, algo, ws, st
         _check(fn(ref, _ptr(src), _ptr(offsets) if algo == DD_ALGO_BLOCKS else None, None, _ptr(dst), wp, wn,
                   _stream(stream)))
     else:
-        wp, wn = _ws_for(need, src.device, ws)
+        wp, wn, held = _ws_for(need, src, ws, stream)
         _check(fn(ref, _ptr(src), _ptr(offsets), _ptr(values), _ptr(dst), wp, wn, _stream(stream)))
     return dst
 
@@ -385,7 +442,7 @@ def dd_bwd_weight(X, dY, offsets, dValues=None, algo=DD_ALGO_AUTO, ws=None, stre
     if dValues is None:
         dValues = torch.empty((K, min(M, N)), dtype=torch.float32, device=X.device)
     _dev(dValues, torch.float32, (K, min(M, N)), "dValues")
-    wp, wn = _ws_for(need, X.device, ws)
+    wp, wn, held = _ws_for(need, X, ws, stream)
     _check(_lib.dd_bwd_weight(ref, _ptr(X), _ptr(dY), _ptr(offsets), _ptr(dValues), wp, wn, _stream(stream)))
     return dValues
 
@@ -418,7 +475,7 @@ def dd_bwd(X, dY, offsets, values, dX=None, dValues=None, algo=DD_ALGO_AUTO, ws=
         dValues = torch.empty((K, min(M, N)), dtype=torch.float32, device=X.device)
     _dev(dX, X.dtype, (T, M), "dX")
     _dev(dValues, torch.float32, (K, min(M, N)), "dValues")
-    wp, wn = _ws_for(need, X.device, ws)
+    wp, wn, held = _ws_for(need, X, ws, stream)
     pp, pn = (None, 0) if prepared is None else (_ptr(prepared.buf), prepared.buf.numel())
     _check(load_library().dd_bwd(ref, _ptr(X), _ptr(dY), _ptr(offsets), _ptr(values), pp, pn, _ptr(dX), _ptr(dValues),
                                  wp, wn, _stream(stream)))
@@ -457,7 +514,7 @@ def dd_select_diagonals(scores, K, offsets_out=None, ws=None, stream=None):
         offsets_out = torch.empty((B, K), dtype=torch.int32, device=scores.device)
     _dev(offsets_out, torch.int32, (B, K), "offsets_out")
     _, _, need = _plan(DD_OP_SELECT, 0, D, D, int(K), DD_F32, DD_ALGO_AUTO, batch=B)
-    wp, wn = _ws_for(need, scores.device, ws)
+    wp, wn, held = _ws_for(need, scores, ws, stream)
     _check(_lib.dd_select_diagonals(B, D, int(K), _ptr(scores), _ptr(offsets_out), wp, wn, _stream(stream)))
     return offsets_out
 
@@ -511,7 +568,7 @@ def dd_bwd_weight_scaled(X, dY, offsets, alpha_tilde, V, dV=None, d_alpha_tilde=
         d_alpha_tilde = torch.empty((D,), dtype=torch.float32, device=X.device)
     _dev(dV, torch.float32, (K, L), "dV")
     _dev(d_alpha_tilde, torch.float32, (D,), "d_alpha_tilde")
-    wp, wn = _ws_for(need, X.device, ws)
+    wp, wn, held = _ws_for(need, X, ws, stream)
     _check(load_library().dd_bwd_weight_scaled(ref, _ptr(X), _ptr(dY), _ptr(offsets), _ptr(alpha_tilde), _ptr(V),
                                                _ptr(dV), _ptr(d_alpha_tilde), wp, wn, _stream(stream)))
     return dV, d_alpha_tilde
@@ -568,7 +625,7 @@ def dd_scale_values_bwd(offsets, alpha_tilde, V, dValues, ws=None, stream=None):
     dV = torch.empty((K, L), dtype=torch.float32, device=V.device)
     d_alpha = torch.empty((D,), dtype=torch.float32, device=V.device)
     _, _, need = _plan(DD_OP_SCALE_VALUES_BWD, 0, D, D, K, DD_F32, DD_ALGO_AUTO)
-    wp, wn = _ws_for(need, V.device, ws)
+    wp, wn, held = _ws_for(need, V, ws, stream)
     _check(load_library().dd_scale_values_bwd(K, L, D, _DTYPES[V.dtype], _ptr(offsets), _ptr(alpha_tilde), _ptr(V),
                                               _ptr(dValues), _ptr(dV), _ptr(d_alpha), wp, wn, _stream(stream)))
     return dV, d_alpha
@@ -607,7 +664,7 @@ def dd_diagheur_update(D, offsets, magnitudes, random, n_drop, new_offsets=None,
     _dev(new_offsets, torch.int32, (K,), "new_offsets")
     _dev(source, torch.int32, (K,), "source")
     _, _, need = _plan(DD_OP_DIAGHEUR, 0, D, D, K, DD_F32, DD_ALGO_AUTO)
-    wp, wn = _ws_for(need, offsets.device, ws)
+    wp, wn, held = _ws_for(need, offsets, ws, stream)
     _check(load_library().dd_diagheur_update(D, K, int(n_drop), _ptr(offsets), _ptr(magnitudes), _ptr(random),
                                              _ptr(new_offsets), _ptr(source), wp, wn, _stream(stream)))
     return new_offsets, source

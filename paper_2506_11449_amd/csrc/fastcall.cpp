@@ -123,13 +123,23 @@ bool sizes(dd_layer &l, int64_t T, int64_t M, int64_t N, int64_t K)
     return true;
 }
 
-// A block of bytes: the workspace, if it is as large as the call needs and lies on its device, or prepared operands.
+// A block of bytes: the workspace, if it is as large as the call needs and lies on its device (... for the block that binding.py keeps
+// for calls without one), or prepared operands.
 struct Block {
     void *p = nullptr;
     size_t n = 0;
+    PyObject *kept = nullptr;  // a block of binding.py, held for as long as the call is being made
+    ~Block() { Py_XDECREF(kept); }
 };
-bool workspace(PyObject *o, size_t need, const at::Tensor &beside, Block &b)
+PyObject *default_block = nullptr;
+bool workspace(PyObject *o, size_t need, PyObject *beside_object, const at::Tensor &beside, PyObject *stream, Block &b)
 {
+    if (o == Py_Ellipsis) {
+        if (need == 0) return true;
+        b.kept = PyObject_CallFunction(default_block, "nOO", Py_ssize_t(need), beside_object, stream);
+        o = b.kept;
+        if (!o) return false;
+    }
     const at::Tensor *t = o == Py_None ? nullptr : tensor(o, 1, at::kByte);
     if (o != Py_None && !t) return false;
     if (need == 0) return true;
@@ -232,7 +242,7 @@ PyObject *product(PyObject *, PyObject *const *a, Py_ssize_t n)
             const at::Tensor *values = matrix(a[3], src->scalar_type(), K, std::min(M, N));
             if (!values || !sizes(l, T, M, N, K)) return kLongWay;
             l.algo = int32_t(algo);
-            if (!workspace(a[7], scratch(back ? DD_OP_BWD_INPUT : DD_OP_FWD, l), *src, ws) || !dst.take(a[4], src->scalar_type(), {T, wide}, *src) ||
+            if (!workspace(a[7], scratch(back ? DD_OP_BWD_INPUT : DD_OP_FWD, l), a[1], *src, a[8], ws) || !dst.take(a[4], src->scalar_type(), {T, wide}, *src) ||
                 !handle(a[8], stream))
                 return kLongWay;
             return int(call(back ? lib.bwd_input : lib.fwd, &l, src->data_ptr(), offsets->data_ptr<int32_t>(), values->data_ptr(),
@@ -285,7 +295,7 @@ PyObject *bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
             const at::Tensor *values = a[3] == Py_None ? nullptr : matrix(a[3], type, l.K, L);
             if (!values && (a[3] != Py_None || a[4] == Py_None)) return kLongWay;
             l.algo = int32_t(algo);
-            if (!workspace(a[8], scratch(DD_OP_BWD, l), *X, ws) || !dX.take(a[5], type, {l.tokens, l.in_features}, *X) ||
+            if (!workspace(a[8], scratch(DD_OP_BWD, l), a[0], *X, a[9], ws) || !dX.take(a[5], type, {l.tokens, l.in_features}, *X) ||
                 !dV.take(a[6], at::kFloat, {l.K, L}, *X) || !handle(a[9], stream))
                 return kLongWay;
             return int(call(lib.bwd, &l, X->data_ptr(), dY->data_ptr(), offsets->data_ptr<int32_t>(), values ? values->data_ptr() : nullptr,
@@ -310,7 +320,7 @@ PyObject *bwd_weight(PyObject *, PyObject *const *a, Py_ssize_t n)
             const at::Tensor *dY = tensor(a[1], 2, X->scalar_type());
             if (!dY || dY->size(0) != X->size(0) || !sizes(l, X->size(0), X->size(1), dY->size(1), offsets->size(0))) return kLongWay;
             l.algo = int32_t(algo);
-            if (!workspace(a[5], scratch(DD_OP_BWD_WEIGHT, l), *X, ws) ||
+            if (!workspace(a[5], scratch(DD_OP_BWD_WEIGHT, l), a[0], *X, a[6], ws) ||
                 !dV.take(a[3], at::kFloat, {l.K, std::min(l.in_features, l.out_features)}, *X) || !handle(a[6], stream))
                 return kLongWay;
             return int(call(lib.bwd_weight, &l, X->data_ptr(), dY->data_ptr(), offsets->data_ptr<int32_t>(), dV.t.data_ptr<float>(), ws.p, ws.n, stream));
@@ -390,7 +400,7 @@ PyObject *diagheur_update(PyObject *, PyObject *const *a, Py_ssize_t n)
             const at::Tensor *magnitudes = vector(a[3], at::kFloat, l.K), *random = vector(a[4], at::kFloat, D);
             if (!magnitudes || !random) return kLongWay;
             l.dtype = DD_F32, l.algo = DD_ALGO_AUTO;
-            if (!workspace(a[7], scratch(DD_OP_DIAGHEUR, l), *offsets, ws) || !fresh.take(a[5], at::kInt, {l.K}, *offsets) ||
+            if (!workspace(a[7], scratch(DD_OP_DIAGHEUR, l), a[2], *offsets, a[8], ws) || !fresh.take(a[5], at::kInt, {l.K}, *offsets) ||
                 !source.take(a[6], at::kInt, {l.K}, *offsets) || !handle(a[8], stream))
                 return kLongWay;
             return int(call(lib.diagheur_update, int32_t(D), l.K, int32_t(drop), offsets->data_ptr<int32_t>(), magnitudes->data_ptr<float>(),
@@ -399,20 +409,22 @@ PyObject *diagheur_update(PyObject *, PyObject *const *a, Py_ssize_t n)
         fresh, source);
 }
 
-// bind(function that answers the current stream's handle, function that raises for a status, addresses of Entries in order)
+// bind(function that answers the current stream's handle, function that raises for a status, function that answers the scratch of
+// calls without a workspace, addresses of Entries in order)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     constexpr int kEntries = sizeof(Entries) / sizeof(void *);
-    if (n != 2 + kEntries) return PyErr_Format(PyExc_TypeError, "bind takes two functions and %d addresses", kEntries);
+    if (n != 3 + kEntries) return PyErr_Format(PyExc_TypeError, "bind takes three functions and %d addresses", kEntries);
     void *p[kEntries];
     for (int i = 0; i < kEntries; ++i) {
-        p[i] = PyLong_AsVoidPtr(a[2 + i]);
+        p[i] = PyLong_AsVoidPtr(a[3 + i]);
         if (PyErr_Occurred()) return nullptr;
     }
-    Py_INCREF(a[0]);
-    Py_INCREF(a[1]);
-    Py_XSETREF(current_stream, a[0]);
-    Py_XSETREF(check, a[1]);
+    PyObject **const functions[] = {&current_stream, &check, &default_block};
+    for (int i = 0; i < 3; ++i) {
+        Py_INCREF(a[i]);
+        Py_XSETREF(*functions[i], a[i]);
+    }
     memcpy(&lib, p, sizeof lib);
     Py_RETURN_NONE;
 }
