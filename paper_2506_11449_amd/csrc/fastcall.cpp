@@ -214,6 +214,7 @@ PyObject *answer(F body, R &...results)
     } catch (...) {
     }
     if (status == kLongWay) {
+        if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;  // an interrupt is not a refusal
         PyErr_Clear();
         Py_RETURN_NONE;
     }

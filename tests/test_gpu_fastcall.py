@@ -106,3 +106,21 @@ def test_wrapped_tensors_take_the_long_way():
     torch.func.vmap(f)(X[None])
     torch.func.grad(lambda x: f(x).sum())(X)
     assert seen == [None, None]
+
+
+def test_an_interrupt_is_not_lost():
+    X, dY, V, _ = _layer(16, 64, 64, 8, torch.float32)
+    off = torch.arange(8, dtype=torch.int32, device="cuda")
+
+    class Interrupted:
+        asked = 0
+
+        @property
+        def cuda_stream(self):
+            self.asked += 1
+            if self.asked == 1:
+                raise KeyboardInterrupt
+            return torch.cuda.current_stream().cuda_stream
+
+    with pytest.raises(KeyboardInterrupt):
+        dd.dd_fwd(X, off, V, 64, Y=torch.empty_like(dY), stream=Interrupted())
