@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kFusedThreads) void select_materialize_kernel(int D
 // ---------------------------------------------------------------------------------------------
 // What a product of a layer whose widths are multiples of eight only needs beside its padded operand (RaggedArgs of the kernels
 // below; the others ignore it).  The dense contraction multiplies every input by the zeros between the diagonals, which an input
-// that is not finite must not survive: a workgroup that meets one takes its tile diagonal by diagonal instead.
+// that is not finite must not survive: the tokens that hold one are taken diagonal by diagonal.
 struct RaggedArgs {
     const int *offsets;
     const uint16_t *values;
@@ -294,24 +294,155 @@ __device__ __forceinline__ void note_not_finite(unsigned &seen, u32x4 v)
     asm volatile("" : "+v"(seen));
 }
 
-// Result tile of tokens t0 ... t0 + BM - 1 and columns j0 ... j0 + BN - 1, from offsets and values: rare, and as slow as it looks.
-template <int BM, int BN>
-__device__ __forceinline__ void tile_by_diagonals(const RaggedArgs &r, const uint16_t *__restrict__ A, uint16_t *__restrict__ C, int T, int t0, int j0)
+// What a workgroup has met: each wave notes its share, after a barrier everyone knows.
+__device__ __forceinline__ void note_met(int *met, unsigned undefined)
 {
-    const int src_cols = r.masked ? r.L : r.D, dst_cols = r.masked ? r.D : r.L;
-    for (int e = threadIdx.x; e < BM * BN; e += blockDim.x) {
-        const int t = t0 + e / BN, j = j0 + e % BN;
-        if (t >= T || j >= dst_cols) continue;
-        const uint16_t *row = A + size_t(t) * src_cols;
-        float acc = 0.f;
-        for (int k = 0; k < r.K; ++k) {
-            const int o = canonical_offset(r.offsets[k], r.D);
-            int c = r.masked ? j - o : j + o;
-            c += c < 0 ? r.D : 0;
-            c -= c >= r.D ? r.D : 0;
-            if (c < src_cols) acc = fmaf(bf16_to_f32(row[c]), bf16_to_f32(r.values[size_t(k) * r.L + (r.masked ? c : j)]), acc);
+    const int found = __ballot(undefined & 0x80008000u) ? 1 : 0;
+    if ((threadIdx.x & 63) == 0) met[threadIdx.x >> 6] = found;
+}
+template <int WAVES>
+__device__ __forceinline__ int all_met(const int *met)
+{
+    int found = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) found |= met[w];
+    return __builtin_amdgcn_readfirstlane(found);
+}
+
+// Tokens of a tile whose results come diagonal by diagonal: those that hold a number which is not finite.
+template <int BM>
+struct RowsApart {
+    static_assert(BM <= 256, "a byte for each");
+    unsigned bits[(BM + 31) / 32];
+    int count;
+    unsigned char list[BM];
+    __device__ __forceinline__ bool has(int row) const { return bits[row >> 5] >> (row & 31) & 1u; }
+};
+
+template <int BM, int THREADS>
+__device__ __forceinline__ void find_rows_apart(RowsApart<BM> &rows, const uint16_t *__restrict__ A, int a_cols, int T, int t0)
+{
+    const int tid = threadIdx.x, present = min(BM, T - t0);
+    for (int i = tid; i < (BM + 31) / 32; i += THREADS)
+        rows.bits[i] = 0u;
+    __syncthreads();
+    {
+        const int per_row = a_cols / 8, pieces = present * per_row;
+        const u32x4 *src = reinterpret_cast<const u32x4 *>(A + size_t(t0) * a_cols);
+        for (int first = tid; first < pieces; first += 8 * THREADS) {
+            u32x4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[min(first + u * THREADS, pieces - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                unsigned seen = 0u;
+                note_not_finite(seen, v[u]);
+                const int row = min(first + u * THREADS, pieces - 1) / per_row;
+                if (seen & 0x80008000u) atomicOr(&rows.bits[row >> 5], 1u << (row & 31));
+            }
         }
-        C[size_t(t) * dst_cols + j] = f32_to_bf16(acc);
+        __syncthreads();
+    }
+    int before = 0, count = 0;
+#pragma unroll
+    for (int i = 0; i < (BM + 31) / 32; ++i) {
+        const unsigned word = rows.bits[i];
+        before += __popc(32 * i + 32 <= tid ? word : 32 * i < tid ? word & ((1u << (tid & 31)) - 1u) : 0u);
+        count += __popc(word);
+    }
+    if (tid < BM && rows.has(tid)) rows.list[before] = static_cast<unsigned char>(tid);
+    if (tid == 0) rows.count = count;
+    __syncthreads();
+}
+
+// The results of those tokens in columns j0 ... j0 + BN - 1.  R of them at a time lie in LDS (the workgroup's whole block, no longer in
+// use), column by column; a thread takes a result column and one of THREADS / BN parts of the diagonals, whose weights are requested
+// eight ahead.  Bound by the latency of the weights where few tokens are apart, by vector instructions where all are.  12608 tokens, us, all
+// numbers finite, one NaN, one in every 100 tokens, nothing but NaN, and the vector kernels whatever the numbers: 1496^2, 598 diagonals
+// 86, 133, 186, 1730, 658; 1000^2, 100 diagonals 46, 58, 73, 340, 95 (the whole tile diagonal by diagonal: 12000 and 24000; 1650 and 3280).
+template <int BM, int BN, int THREADS, int LDS_BYTES>
+__device__ __forceinline__ void rows_by_diagonals(const RaggedArgs &r, const RowsApart<BM> &rows, unsigned char *lds, const uint16_t *__restrict__ A,
+                                                  uint16_t *__restrict__ C, int t0, int j0)
+{
+    constexpr int R = LDS_BYTES >= 40000 ? 8 : 4, PARTS = THREADS / BN, AHEAD = 8;
+    static_assert(LDS_BYTES >= (kRaggedMaxD + 1) * 2 * R && LDS_BYTES >= (PARTS - 1) * BN * R * 4, "rows and sums fit");
+    typedef unsigned Words __attribute__((ext_vector_type(R / 2)));
+    __shared__ uint16_t offset[kRaggedMaxD];
+    const int tid = threadIdx.x, src_cols = r.masked ? r.L : r.D, dst_cols = r.masked ? r.D : r.L;
+    const int col = tid % BN, part = tid / BN, j = j0 + col;
+    const int k_lo = r.K * part / PARTS, k_hi = r.K * (part + 1) / PARTS;
+    uint16_t *x = reinterpret_cast<uint16_t *>(lds);  // [src_cols + 1][R], the last column zeros
+    float *sums = reinterpret_cast<float *>(lds);     // [PARTS - 1][R][BN]
+    for (int k = tid; k < r.K; k += THREADS) {  // the source column of result column 0, so to speak
+        const int o = canonical_offset(r.offsets[k], r.D);
+        offset[k] = uint16_t(r.masked && o > 0 ? r.D - o : o);
+    }
+    // diagonals k ... k + AHEAD - 1 of this thread: where in x its source columns lie (that of zeros where there is none), and the weights
+    const uint16_t *const weights = r.values + (r.masked ? 0 : min(j, dst_cols - 1));
+    auto request = [&](int k, int (&at)[AHEAD], uint16_t (&w)[AHEAD]) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int own = min(k + u, k_hi - 1);
+            int c = j + offset[own];
+            c -= c >= r.D ? r.D : 0;
+            const bool counts = k + u < k_hi && c < src_cols;
+            at[u] = counts ? c : src_cols;
+            w[u] = weights[size_t(own) * r.L + (r.masked ? min(c, r.L - 1) : 0)];
+        }
+    };
+    for (int first = 0; first < rows.count; first += R) {
+        const int n = min(R, rows.count - first);
+        __syncthreads();  // the block is free
+        for (int idx = tid; idx < R * (src_cols / 8); idx += THREADS) {
+            const int q = idx % R, ch = idx / R;
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (q < n) v = *reinterpret_cast<const u32x4 *>(A + size_t(t0 + rows.list[first + q]) * src_cols + ch * 8);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[(ch * 8 + i) * R + q] = uint16_t(v[i >> 1] >> (16 * (i & 1)));
+        }
+        if (tid < R) x[src_cols * R + tid] = 0;
+        __syncthreads();
+        float acc[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) acc[q] = 0.f;
+        auto multiply = [&](const int (&at)[AHEAD], const uint16_t (&w)[AHEAD]) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const Words words = *reinterpret_cast<const Words *>(x + at[u] * R);
+                const float weight = at[u] == src_cols ? 0.f : bf16_to_f32(w[u]);
+#pragma unroll
+                for (int h = 0; h < R / 2; ++h) {
+                    acc[2 * h] = fmaf(__uint_as_float(words[h] << 16), weight, acc[2 * h]);
+                    acc[2 * h + 1] = fmaf(__uint_as_float(words[h] & 0xffff0000u), weight, acc[2 * h + 1]);
+                }
+            }
+        };
+        if (j < dst_cols && k_lo < k_hi) {
+            int at0[AHEAD], at1[AHEAD];
+            uint16_t w0[AHEAD], w1[AHEAD];
+            request(k_lo, at0, w0);
+            for (int k = k_lo; k < k_hi; k += 2 * AHEAD) {
+                const bool second = k + AHEAD < k_hi;
+                if (second) request(k + AHEAD, at1, w1);
+                multiply(at0, w0);
+                if (k + 2 * AHEAD < k_hi) request(k + 2 * AHEAD, at0, w0);
+                if (second) multiply(at1, w1);
+            }
+        }
+        __syncthreads();  // the rows have been read
+        if (part > 0) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) sums[((part - 1) * R + q) * BN + col] = acc[q];
+        }
+        __syncthreads();
+        if (part == 0 && j < dst_cols) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                if (q >= n) break;
+                for (int s = 0; s < PARTS - 1; ++s) acc[q] += sums[(s * R + q) * BN + col];
+                C[size_t(t0 + rows.list[first + q]) * dst_cols + j] = f32_to_bf16(acc[q]);
+            }
+        }
     }
 }
 
@@ -366,8 +497,10 @@ __device__ __forceinline__ void store_tile(uint16_t *__restrict__ C, const unsig
 }
 
 // RAGGED: one product whose widths a_cols and c_cols are multiples of eight; KD and NC are those of the operand, padded with zeros.
+// (waves per SIMD: as many as the main loop's registers leave room for, so that the rare rows apart take no more)
+constexpr int ragged_waves(int BM, int NW) { return BM > 64 ? 2 : NW == 8 ? 4 : 3; }
 template <int BM, int BN, int NW, bool RAGGED = false>
-__global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int a_cols, int c_cols, int tiles_m,
+__global__ __launch_bounds__(64 * NW, RAGGED ? ragged_waves(BM, NW) : 1) void mm_kernel(int T, int NC, int KD, int a_cols, int c_cols, int tiles_m,
                                                         int tiles_n, int group_n, const uint16_t *__restrict__ A,
                                                         const uint16_t *__restrict__ Wf,
                                                         uint16_t *__restrict__ C, RaggedArgs ragged)
@@ -547,12 +680,8 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
         DD_SLICE(kt, wf0, wf1, xg0)
         DD_SLICE(kt + 1, wf1, wf0, xg1)
     }
-    if (!RAGGED) break;
-    if (pass == 0 && __syncthreads_or(undefined & 0x80008000u)) {
-        tile_by_diagonals<BM, BN>(ragged, A, C, T, tm * BM, tn * BN);
-        return;
-    }
-    if (!rests || pass == 1) break;
+    if (!RAGGED || !rests || pass == 1) break;
+    __syncthreads();  // the ring is free
 #pragma unroll
     for (int a = 0; a < Tl::FA; ++a) w_src[a] += ragged.rest_at;  // once more with what the rounding of the operand left
     x_off = 0;
@@ -585,14 +714,27 @@ __global__ __launch_bounds__(64 * NW) void mm_kernel(int T, int NC, int KD, int 
                 const int j_local = wave * Tl::WN + a * 32 + 8 * g + 4 * half;
                 *reinterpret_cast<bf16x4 *>(smem + t_local * Tl::C_STRIDE + j_local * 2) = h;
             }
+    __shared__ RowsApart<RAGGED ? BM : 1> apart;
+    __shared__ int met[NW];
+    if constexpr (RAGGED) note_met(met, undefined);
     __syncthreads();
     if constexpr (RAGGED) {
-        for (int idx = tid; idx < BM * (BN / 8); idx += kMmThreads) {
-            const int row = idx / (BN / 8), ch = idx % (BN / 8), t = tm * BM + row, col = tn * BN + ch * 8;
-            if (t < T && col < c_cols)
-                __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(smem + row * Tl::C_STRIDE + ch * 16),
-                                            reinterpret_cast<u32x4 *>(C + size_t(t) * c_cols + col));
+        const int found = all_met<NW>(met);
+        auto store = [&](auto counts) {
+            for (int idx = tid; idx < BM * (BN / 8); idx += kMmThreads) {
+                const int row = idx / (BN / 8), ch = idx % (BN / 8), t = tm * BM + row, col = tn * BN + ch * 8;
+                if (t < T && col < c_cols && counts(row))
+                    __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(smem + row * Tl::C_STRIDE + ch * 16),
+                                                reinterpret_cast<u32x4 *>(C + size_t(t) * c_cols + col));
+            }
+        };
+        if (!found) {
+            store([](int) { return true; });
+            return;
         }
+        find_rows_apart<BM, kMmThreads>(apart, A, a_cols, T, tm * BM);
+        store([&](int row) { return !apart.has(row); });
+        rows_by_diagonals<BM, BN, kMmThreads, Tl::LDS_BYTES>(ragged, apart, smem, A, C, tm * BM, tn * BN);
         return;
     }
     store_tile<BM, BN, kMmThreads>(C, smem, Tl::C_STRIDE, tm, tn, T, c_cols, tid);
@@ -952,7 +1094,7 @@ struct BlockArgs {
 };
 
 template <int FA, int FB, int KS, bool BLOCKS, bool RAGGED = false>
-__global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_cols, int c_cols, int tiles_m, int tiles_n,
+__global__ __launch_bounds__(64 * KS, RAGGED ? (FA * FB == 1 ? 3 : 2) : 1) void mm_small_kernel(int T, int KD, int a_cols, int c_cols, int tiles_m, int tiles_n,
                                                            const uint16_t *__restrict__ A,
                                                            const uint16_t *__restrict__ Wf, uint16_t *__restrict__ C, BlockArgs blocks,
                                                            RaggedArgs ragged)
@@ -1127,13 +1269,14 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
 #undef DD_SMALL_LOAD_W
 #undef DD_SMALL_LOAD_X
 #undef DD_SMALL_MASK
-    if constexpr (RAGGED) {
-        if (__syncthreads_or(undefined & 0x80008000u)) {
-            tile_by_diagonals<BM, BN>(ragged, A, C, T, tm * BM, tn * BN);
-            return;
-        }
-    }
+    __shared__ RowsApart<RAGGED ? BM : 1> apart;
+    __shared__ int met[KS];
+    if constexpr (RAGGED) note_met(met, undefined);
     __syncthreads();  // the sums take the place of the rows
+    const int found = RAGGED ? all_met<KS>(met) : 0;
+    const bool some = found != 0;
+    if constexpr (RAGGED)
+        if (some) find_rows_apart<BM, 64 * KS>(apart, A, a_cols, T, tm * BM);
 
     // Accumulator i of lane l is output column 8*(i/4) + 4*(l/32) + i%4 of token l%32 inside its 32x32 tile.
     float *sums = reinterpret_cast<float *>(smem);  // [KS][BM][STRIDE]
@@ -1157,7 +1300,11 @@ __global__ __launch_bounds__(64 * KS) void mm_small_kernel(int T, int KD, int a_
             lo += *reinterpret_cast<const f32x4 *>(src + k * BM * Tl::STRIDE);
             hi += *reinterpret_cast<const f32x4 *>(src + k * BM * Tl::STRIDE + 4);
         }
-        if (t < T && (!RAGGED || first_col + ch * 8 < c_cols)) *reinterpret_cast<u32x4 *>(C + (size_t(matrix) * T + t) * c_cols + first_col + ch * 8) = pack_bf16x8(lo, hi);
+        if (t < T && (!RAGGED || (first_col + ch * 8 < c_cols && !(some && apart.has(row)))))
+            *reinterpret_cast<u32x4 *>(C + (size_t(matrix) * T + t) * c_cols + first_col + ch * 8) = pack_bf16x8(lo, hi);
+    }
+    if constexpr (RAGGED) {
+        if (some) rows_by_diagonals<BM, BN, 64 * KS, Tl::LDS_BYTES>(ragged, apart, smem, A, C, tm * BM, tn * BN);
     }
 }
 
@@ -1204,7 +1351,7 @@ static hipError_t launch_mm(int T, int NC, int KD, int a_cols, int c_cols, const
     const int tiles_m = (T + BM - 1) / BM, tiles_n = (NC + BN - 1) / BN;
     const int per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds;
     hipLaunchKernelGGL((mm_kernel<BM, BN, NW, RAGGED>), dim3(per_xcd * kXcds), dim3(Tl::THREADS), Tl::LDS_BYTES, stream, T, NC, KD,
-                       a_cols, c_cols, tiles_m, tiles_n, tiles_n, A, Wf, C, ragged);  // every tile is resident at once: plain order
+                       a_cols, c_cols, tiles_m, tiles_n, tiles_n, A, Wf, C, ragged);  // few tiles for each CU: plain order
     return hipGetLastError();
 }
 

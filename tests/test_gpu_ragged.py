@@ -111,6 +111,28 @@ def test_nothing_finite(M, N, K, T):
     assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got[~got.isnan()], ref[~ref.isnan()])
 
 
+def _us(call):
+    call()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3)
+    return min(times)
+
+
+def test_a_number_that_is_not_finite_costs_its_token_only():
+    """One token in a thousand with such a number: the product stays well ahead of the vector kernels (115-125 and 650 us)."""
+    M, N, K, T = 1496, 1496, 598, 12608
+    _, (off, V, x, dy) = _case(M, N, K, T)
+    x[::1000, 3] = float("nan")
+    Y, ws = torch.empty_like(dy), dd.Workspace()
+    assert _us(lambda: dd.dd_fwd(x, off, V, N, Y=Y, ws=ws)) <= 0.5 * _us(lambda: dd.dd_fwd(x, off, V, N, Y=Y, ws=ws, algo=VECTOR))
+
+
 @pytest.mark.parametrize("M,N,K,T", [(392, 376, 392, 601), (264, 264, 105, 5005), (1000, 320, 400, 2000)])
 def test_repeated_offsets_cost_no_precision(M, N, K, T):
     """Half of the offsets given three times: against 64 bits the products are as exact as those of the vector kernels, which add the
