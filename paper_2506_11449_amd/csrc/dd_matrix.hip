@@ -96,9 +96,73 @@ constexpr int kMatRange = 256;
 constexpr int kMatChunk = 512;             // diagonals looked at per pass
 constexpr int kMatStride = kMatRange + 8;  // floats per row in LDS: the 32 rows of a fragment start 8 banks apart
 
+// The rows of materialize_kernel once more where an offset is given twice (rare): every thread adds to entries of its own, in the order
+// of the diagonals, the values of four of them on their way at once.  hit_k, hit_first: room for THREADS entries, wave_hits for one
+// per wave.  Ends with a barrier.  (Kept to 32 registers: with 46 two of these workgroups a CU took 2 us more, offsets unrepeated.
+// 520^2, 208 diagonals 8 us, 1496^2, 598 14 us.)
+template <int THREADS>
+__device__ __forceinline__ void add_in_order(int D, int L, int K, bool long_major, int r0, int i0, int extent, const int *__restrict__ offsets,
+                                             const uint16_t *__restrict__ values, float *rows, int *hit_k, int *hit_first, int *wave_hits)
+{
+    constexpr int kOwn = kMatRange * kMatRows / THREADS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rr = tid % kMatRows, own = tid / kMatRows;
+    const int window = i0 + wave * 2 * kOwn;  // first of the wave's contraction indices
+    for (int c = tid; c < kMatRows * kMatStride / 4; c += THREADS) reinterpret_cast<f32x4 *>(rows)[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < K; k0 += THREADS) {
+        // the diagonals that meet the block, listed in order
+        const int oc = canonical_offset(offsets[min(k0 + tid, K - 1)], D);
+        int first = long_major ? r0 - oc : r0 + oc;
+        first += first < 0 ? D : 0;
+        first -= first >= D ? D : 0;
+        int d = first - i0;
+        d += d < 0 ? D : 0;
+        const bool hit = k0 + tid < K && (d < extent || d + kMatRows > D);
+        const unsigned long long word = __ballot(hit);
+        if (lane == 0) wave_hits[wave] = __popcll(word);
+        __syncthreads();
+        int before = __builtin_amdgcn_mbcnt_hi(unsigned(word >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(word), 0u)), listed = 0;
+#pragma unroll 1
+        for (int w = 0; w < THREADS / 64; ++w) {
+            before += w < wave ? wave_hits[w] : 0;
+            listed += wave_hits[w];
+        }
+        if (hit) {
+            hit_k[before] = k0 + tid;
+            hit_first[before] = first;
+        }
+        __syncthreads();
+        for (int h0 = 0; h0 < listed; h0 += 64) {  // a lane looks at one of them: does it meet the wave's indices?
+            const int k_of = hit_k[min(h0 + lane, listed - 1)], first_of = hit_first[min(h0 + lane, listed - 1)];
+            int e = first_of - window;
+            e += e < 0 ? D : 0;
+            unsigned long long meets = __ballot(h0 + lane < listed && (e < 2 * kOwn || e + kMatRows > D));
+            while (meets) {
+                int at[4];
+                uint16_t v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int h = meets ? __ffsll(meets) - 1 : 0;
+                    int i = __builtin_amdgcn_readlane(first_of, h) + rr;
+                    i -= i >= D ? D : 0;
+                    const int p = long_major ? i : r0 + rr;
+                    const bool mine = meets && unsigned(i - i0) < unsigned(extent) && p < L && (i - i0) / kOwn == own;
+                    at[u] = mine ? i - i0 : -1;
+                    v[u] = values[mine ? size_t(__builtin_amdgcn_readlane(k_of, h)) * L + p : 0];
+                    meets &= meets - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (at[u] >= 0) rows[rr * kMatStride + at[u]] += bf16_to_f32(v[u]);
+            }
+        }
+        __syncthreads();  // the list may be overwritten; after the last pass: the rows are complete
+    }
+}
+
 // RAGGED: D and L are multiples of eight and the operand is padded with zeros to kd_total contraction indices and whole blocks of
-// rows.  One operand of one layer; where an offset is given twice the rounded sums leave a rest, which goes to a second operand
-// `rest_at` elements behind the first, and *repeated says whether there is one.
+// rows.  One operand of one layer.  Where an offset is given twice, the copies are added in the order of their diagonals and the
+// rounded sums leave a rest, which goes to a second operand `rest_at` elements behind the first; repeated[0] says whether there is one
+// and then repeated[1 + b] whether a sum of workgroup b came out infinite or undefined.
 template <bool RAGGED = false, int THREADS = 256>
 __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int K, int masked_blocks,
                                                           const int *__restrict__ offsets,
@@ -179,6 +243,8 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
         }
         __syncthreads();  // the list may be overwritten; after the last pass: the rows are complete
     }
+    if constexpr (RAGGED)
+        if (any_repeated) add_in_order<THREADS>(D, L, K, long_major, r0, i0, extent, offsets, values, rows, hit_k, hit_first, hit_offset);
     // fragments (r0 / 32, i0 / 16 ...) lie one after the other: piece `pc` is lane pc % 64 of fragment pc / 64
     u32x4 *out = reinterpret_cast<u32x4 *>(Wf + fragment_index(r0 + set * place.col_step, i0 + set * place.k_step,
                                                                 place.kd_total));
@@ -188,8 +254,9 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
         out[pc] = pack_bf16x8(*reinterpret_cast<const f32x4 *>(src), *reinterpret_cast<const f32x4 *>(src + 4));
     }
     if constexpr (RAGGED) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) *repeated = int(any_repeated);
+        if (blockIdx.x == 0 && threadIdx.x == 0) repeated[0] = int(any_repeated);
         if (!any_repeated) return;
+        bool beyond = false;
         u32x4 *rest = reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(out) + rest_at);
         for (int pc = threadIdx.x; pc < extent * 4; pc += THREADS) {
             const int lane = pc & 63;
@@ -199,9 +266,12 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
             for (int i = 0; i < 8; ++i) {
                 const float rounded = bf16_to_f32(f32_to_bf16(src[i])), left = src[i] - rounded;
                 v[i >> 2][i & 3] = fabsf(rounded) < INFINITY ? left : 0.f;
+                beyond |= !(fabsf(rounded) < INFINITY);
             }
             rest[pc] = pack_bf16x8(v[0], v[1]);
         }
+        const bool any_beyond = __syncthreads_or(beyond);
+        if (threadIdx.x == 0) repeated[1 + blockIdx.x] = any_beyond;
     }
 }
 
@@ -281,7 +351,8 @@ struct RaggedArgs {
     int D, L, K;
     bool masked;
     size_t rest_at;       // elements from the operand to the one of the rests ...
-    const int *repeated;  // ... which counts if this is set
+    const int *repeated;  // ... which counts if [0] is set; then, by block of 32 operand rows and `ranges`: is a sum not finite?
+    int ranges;
 };
 __device__ __align__(16) const unsigned int mm_zero_piece[4] = {0u, 0u, 0u, 0u};
 
@@ -294,10 +365,22 @@ __device__ __forceinline__ void note_not_finite(unsigned &seen, u32x4 v)
     asm volatile("" : "+v"(seen));
 }
 
-// What a workgroup has met: each wave notes its share, after a barrier everyone knows.
-__device__ __forceinline__ void note_met(int *met, unsigned undefined)
+// Is a sum of weights that the columns j0 ... j0 + BN - 1 use not finite, though its terms may be?
+template <int BN>
+__device__ __forceinline__ bool sums_beyond(const RaggedArgs &r, int j0)
 {
-    const int found = __ballot(undefined & 0x80008000u) ? 1 : 0;
+    bool found = false;
+    for (int i = threadIdx.x; i < BN / 32 * r.ranges; i += blockDim.x) found |= r.repeated[1 + j0 / 32 * r.ranges + i] != 0;
+    return found;
+}
+
+// What a workgroup has met: each wave notes its share, after a barrier everyone knows.
+enum { kNotFinite = 1, kBeyond = 2 };
+template <int BN>
+__device__ __forceinline__ void note_met(int *met, unsigned undefined, bool rests, const RaggedArgs &r, int j0)
+{
+    const bool beyond = rests && sums_beyond<BN>(r, j0);
+    const int found = (__ballot(undefined & 0x80008000u) ? kNotFinite : 0) | (__ballot(beyond) ? kBeyond : 0);
     if ((threadIdx.x & 63) == 0) met[threadIdx.x >> 6] = found;
 }
 template <int WAVES>
@@ -309,7 +392,7 @@ __device__ __forceinline__ int all_met(const int *met)
     return __builtin_amdgcn_readfirstlane(found);
 }
 
-// Tokens of a tile whose results come diagonal by diagonal: those that hold a number which is not finite.
+// Tokens of a tile whose results come diagonal by diagonal: those that hold a number which is not finite, or all of them.
 template <int BM>
 struct RowsApart {
     static_assert(BM <= 256, "a byte for each");
@@ -320,13 +403,13 @@ struct RowsApart {
 };
 
 template <int BM, int THREADS>
-__device__ __forceinline__ void find_rows_apart(RowsApart<BM> &rows, const uint16_t *__restrict__ A, int a_cols, int T, int t0)
+__device__ __forceinline__ void find_rows_apart(RowsApart<BM> &rows, const uint16_t *__restrict__ A, int a_cols, int T, int t0, bool all)
 {
     const int tid = threadIdx.x, present = min(BM, T - t0);
     for (int i = tid; i < (BM + 31) / 32; i += THREADS)
-        rows.bits[i] = 0u;
+        rows.bits[i] = !all ? 0u : present >= 32 * i + 32 ? ~0u : present > 32 * i ? (1u << (present - 32 * i)) - 1u : 0u;
     __syncthreads();
-    {
+    if (!all) {
         const int per_row = a_cols / 8, pieces = present * per_row;
         const u32x4 *src = reinterpret_cast<const u32x4 *>(A + size_t(t0) * a_cols);
         for (int first = tid; first < pieces; first += 8 * THREADS) {
@@ -716,7 +799,7 @@ __global__ __launch_bounds__(64 * NW, RAGGED ? ragged_waves(BM, NW) : 1) void mm
             }
     __shared__ RowsApart<RAGGED ? BM : 1> apart;
     __shared__ int met[NW];
-    if constexpr (RAGGED) note_met(met, undefined);
+    if constexpr (RAGGED) note_met<BN>(met, undefined, rests, ragged, tn * BN);
     __syncthreads();
     if constexpr (RAGGED) {
         const int found = all_met<NW>(met);
@@ -732,7 +815,7 @@ __global__ __launch_bounds__(64 * NW, RAGGED ? ragged_waves(BM, NW) : 1) void mm
             store([](int) { return true; });
             return;
         }
-        find_rows_apart<BM, kMmThreads>(apart, A, a_cols, T, tm * BM);
+        find_rows_apart<BM, kMmThreads>(apart, A, a_cols, T, tm * BM, found & kBeyond);
         store([&](int row) { return !apart.has(row); });
         rows_by_diagonals<BM, BN, kMmThreads, Tl::LDS_BYTES>(ragged, apart, smem, A, C, tm * BM, tn * BN);
         return;
@@ -1271,12 +1354,12 @@ __global__ __launch_bounds__(64 * KS, RAGGED ? (FA * FB == 1 ? 3 : 2) : 1) void 
 #undef DD_SMALL_MASK
     __shared__ RowsApart<RAGGED ? BM : 1> apart;
     __shared__ int met[KS];
-    if constexpr (RAGGED) note_met(met, undefined);
+    if constexpr (RAGGED) note_met<BN>(met, undefined, rests, ragged, tn * BN);
     __syncthreads();  // the sums take the place of the rows
     const int found = RAGGED ? all_met<KS>(met) : 0;
     const bool some = found != 0;
     if constexpr (RAGGED)
-        if (some) find_rows_apart<BM, 64 * KS>(apart, A, a_cols, T, tm * BM);
+        if (some) find_rows_apart<BM, 64 * KS>(apart, A, a_cols, T, tm * BM, found & kBeyond);
 
     // Accumulator i of lane l is output column 8*(i/4) + 4*(l/32) + i%4 of token l%32 inside its 32x32 tile.
     float *sums = reinterpret_cast<float *>(smem);  // [KS][BM][STRIDE]
@@ -1600,8 +1683,8 @@ bool product_ragged_pays(int64_t T, int D, int L, int K, bool masked)
     return us < 0.9 * product_vector_us(T, D, L, K, masked);
 }
 
-// the operand and the one of the rests, padded, and the flag
-size_t product_ragged_ws_bytes(int D, int L) { return 2 * size_t(padded256(D)) * size_t(padded256(L)) * 2 + 256; }
+// the operand and the one of the rests, padded, and the flags (up to 64 blocks of rows, eight ranges each)
+size_t product_ragged_ws_bytes(int D, int L) { return 2 * size_t(padded256(D)) * size_t(padded256(L)) * 2 + 2304; }
 
 hipError_t launch_product_ragged(const ProductArgs &a, hipStream_t stream)
 {
@@ -1613,11 +1696,12 @@ hipError_t launch_product_ragged(const ProductArgs &a, hipStream_t stream)
     const uint16_t *A = static_cast<const uint16_t *>(a.src), *values = static_cast<const uint16_t *>(a.values);
     uint16_t *C = static_cast<uint16_t *>(a.dst);
     const OperandPlace place = {KD, 0, 0, 0};
-    const int blocks = NC / kMatRows * ((KD + kMatRange - 1) / kMatRange);
+    const int ranges = (KD + kMatRange - 1) / kMatRange, blocks = NC / kMatRows * ranges;
+    static_assert((1 + (kRaggedMaxD / kMatRows) * (kRaggedMaxD / kMatRange)) * sizeof(int) <= 2304, "a flag for each workgroup");
     hipLaunchKernelGGL((materialize_kernel<true, 1024>), dim3(blocks), dim3(1024), 0, stream, a.D, a.L, a.K, a.masked ? NC / kMatRows : 0, a.offsets,
                        values, Wf, Wf, place, place, static_cast<const float *>(nullptr), operand, repeated);
     if (hipError_t e = hipGetLastError()) return e;
-    const RaggedArgs r = {a.offsets, values, a.D, a.L, a.K, a.masked, operand, repeated};
+    const RaggedArgs r = {a.offsets, values, a.D, a.L, a.K, a.masked, operand, repeated, ranges};
     double us;
     switch (pick_ragged(a.T, c_cols, a_cols, us)) {
     case 3232: return launch_mm_small<1, 1, 4, false, true>(T, c_cols, KD, a_cols, c_cols, A, Wf, C, stream, {}, r);

@@ -146,6 +146,41 @@ def test_repeated_offsets_cost_no_precision(M, N, K, T):
         assert (got.double() - ref).norm() <= 1.01 * (vector.double() - ref).norm()
 
 
+@pytest.mark.parametrize("M,N,K,T,runs", [(392, 376, 392, 601, "b"), (264, 264, 105, 5005, "fb"), (1000, 320, 400, 2000, "fbg"), (1496, 1496, 1496, 3000, "fbg")])
+def test_copies_of_an_offset_add_in_order(M, N, K, T, runs):
+    """Weights of 1e30, -1e30 and about one on one offset: added in the order of the diagonals their sum is the last, exactly; in another
+    order nothing is left of it.  (1496 diagonals are looked at in two passes.)"""
+    assert _families(M, N, K, T) == runs
+    _, (off, V, x, dy) = _case(M, N, K, T)
+    n = K // 6  # triples from positions far apart
+    off[n:2 * n] = off[:n]
+    off[K - n:] = off[:n]
+    V[:n], V[n:2 * n] = 1e30, -1e30
+    small = V.clone()
+    small[:2 * n] = 0
+    exact = _exact(x, dy, off, small, M, N)
+    Y, dX = dd.dd_fwd(x, off, V, N), dd.dd_bwd_input(dy, off, V, M)
+    if "f" in runs:
+        assert rel_err(to_host(Y), exact[0].cpu().numpy()) <= TOL["bf16"]
+    if "b" in runs:
+        assert rel_err(to_host(dX), exact[1].cpu().numpy()) <= TOL["bf16"]
+    for _ in range(3):
+        assert torch.equal(Y, dd.dd_fwd(x, off, V, N)) and torch.equal(dX, dd.dd_bwd_input(dy, off, V, M))
+
+
+@pytest.mark.parametrize("M,N,K,T,runs", [(264, 264, 105, 5005, "fb"), (1000, 320, 400, 2000, "fbg"), (392, 376, 392, 601, "b")])
+def test_copies_whose_sum_leaves_the_range(M, N, K, T, runs):
+    """Two weights of 2e38 on one offset, inputs so small that their products are finite: so are the results."""
+    assert _families(M, N, K, T) == runs
+    _, (off, V, x, dy) = _case(M, N, K, T)
+    off[K - 1] = off[0]
+    V[0] = V[K - 1] = 2e38
+    x, dy = (x * 1e-3).bfloat16(), (dy * 1e-3).bfloat16()
+    exact = _exact(x, dy, off, V, M, N)
+    for got, ref in ((dd.dd_fwd(x, off, V, N), exact[0]), (dd.dd_bwd_input(dy, off, V, M), exact[1])):
+        assert torch.isfinite(got).all() and rel_err(to_host(got), ref.cpu().numpy()) <= TOL["bf16"]
+
+
 def test_without_scratch_the_vector_kernels_serve():
     M, N, K, T = 264, 264, 105, 5005
     _, (off, V, x, dy) = _case(M, N, K, T)
