@@ -22,3 +22,35 @@ def test_both_gradients(M, N, K, T, dtype):
     assert rel_err(to_host(dX), orc.bwd_input(dY, offsets, values, M)) <= TOL[dtype]
     assert rel_err(to_host(dV), orc.bwd_weight(X, dY, offsets)) <= TOL_DV
     assert torch.equal(dX, dd.dd_bwd_input(dy, off, V, M)) and torch.equal(dV, dd.dd_bwd_weight(x, dy, off))
+
+
+def _us(call, repeats=20):
+    call()
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(repeats):
+                call()
+    times = []
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / repeats)
+    return min(times)
+
+
+# layers on which one launch took 1.2 to 1.5 times as long as two: much work, long sides, many entries
+@pytest.mark.parametrize("M,N,K,T", [(519, 519, 300, 192), (6000, 1000, 20, 192), (7293, 7293, 1316, 1)])
+def test_one_launch_is_not_taken_where_two_are_ahead(M, N, K, T):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K + T)
+    r = lambda *s: torch.randn(s, device="cuda", generator=g)
+    x, dy, V, off = r(T, M), r(T, N), r(K, min(M, N)), torch.randperm(max(M, N), device="cuda", generator=g)[:K].to(torch.int32)
+    dX, dV, ws = torch.empty_like(x), torch.empty_like(V), dd.Workspace()
+    ws.get(1 << 26, x.device)
+    one = _us(lambda: dd.dd_bwd(x, dy, off, V, dX=dX, dValues=dV, ws=ws))
+    two = _us(lambda: (dd.dd_bwd_input(dy, off, V, M, dX=dX, ws=ws), dd.dd_bwd_weight(x, dy, off, dValues=dV, ws=ws)))
+    assert one <= 1.12 * two
