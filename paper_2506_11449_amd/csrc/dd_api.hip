@@ -80,16 +80,15 @@ bool wants_lowk_wgrad(const dd_layer *l, const Shape &s)
 
 // Widths that are multiples of eight but not of 128: the matrix cores on an operand padded with zeros, where that is ahead of the
 // vector kernels and the caller's scratch has room for the operand (it may be the smaller scratch of the vector kernels).  Scratch
-// is asked for wherever it might be of use at that many tokens or more.
-constexpr int64_t kRaggedTokens = 256;  // the fewest for which the two launches were ever ahead (1496^2, 40 % of the diagonals)
+// is asked for wherever it is of use at that many tokens or at fewer, and only there: a larger block changes nothing.
 bool may_be_ragged(const dd_layer *l, const Shape &s)
 {
-    return l->algo == DD_ALGO_AUTO && l->tokens >= kRaggedTokens && !wants_matrix(l, s) &&
-           dd::product_ragged_supported(l->tokens, s.D, s.L, l->dtype == DD_BF16);
+    return l->algo == DD_ALGO_AUTO && !wants_matrix(l, s) && dd::product_ragged_supported(l->tokens, s.D, s.L, l->dtype == DD_BF16);
 }
 bool wants_ragged(const dd_layer *l, const Shape &s, bool masked)
 {
-    return may_be_ragged(l, s) && dd::product_ragged_pays(l->tokens, s.D, s.L, l->K, masked);
+    return may_be_ragged(l, s) && dd::product_ragged_pays(l->tokens, s.D, s.L, l->K, masked) &&
+           dd::product_ragged_ever_pays(l->tokens, s.D, s.L, l->K, masked);
 }
 bool fits_ragged(const Shape &s, const void *ws, size_t ws_bytes)
 {
@@ -223,7 +222,8 @@ size_t dd_workspace_bytes(int op, const dd_layer *layer, int32_t batch)
     switch (op) {
     case DD_OP_FWD:
     case DD_OP_BWD_INPUT:
-        if (may_be_ragged(layer, s)) return dd::product_ragged_ws_bytes(s.D, s.L);
+        if (may_be_ragged(layer, s) && dd::product_ragged_ever_pays(layer->tokens, s.D, s.L, layer->K, (op == DD_OP_BWD_INPUT) != s.expanding))
+            return dd::product_ragged_ws_bytes(s.D, s.L);
         return product_ws_bytes(layer, s);
     case DD_OP_PREPARE:
         return dd::product_matrix_supported(1, s.D, s.L, layer->dtype == DD_BF16) ? prepared_bytes(s) : 0;

@@ -82,6 +82,7 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream);
 // repeated offsets cost no precision.
 bool product_ragged_supported(int64_t T, int D, int L, bool bf16);
 bool product_ragged_pays(int64_t T, int D, int L, int K, bool masked);
+bool product_ragged_ever_pays(int64_t T, int D, int L, int K, bool masked);  // at that many tokens or at fewer
 size_t product_ragged_ws_bytes(int D, int L);
 double product_vector_us(int64_t T, int D, int L, int K, bool masked);  // what it is weighed against
 hipError_t launch_product_ragged(const ProductArgs &a, hipStream_t stream);

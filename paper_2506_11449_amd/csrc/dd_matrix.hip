@@ -1623,9 +1623,11 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
 static int padded256(int n) { return (n + 255) / 256 * 256; }
 static int padded(int n) { return (n + 127) / 128 * 128; }
 
+constexpr int64_t kRaggedTokens = 256;  // the fewest for which the two launches were ever ahead (1496^2, 40 % of the diagonals)
+
 bool product_ragged_supported(int64_t T, int D, int L, bool bf16)
 {
-    return bf16 && T > 0 && T < (int64_t(1) << 31) && D % 8 == 0 && L % 8 == 0 && D >= 256 && D <= kRaggedMaxD;
+    return bf16 && T >= kRaggedTokens && T < (int64_t(1) << 31) && D % 8 == 0 && L % 8 == 0 && D >= 256 && D <= kRaggedMaxD;
 }
 
 // Tile of the product, and the time it should take in us.  The kernels for few tokens as pick_small has them; mm_kernel: every round of
@@ -1681,6 +1683,20 @@ bool product_ragged_pays(int64_t T, int D, int L, int K, bool masked)
     pick_ragged(T, masked ? D : L, masked ? L : D, us);
     us = 4.5 + 1.2 * us + 10.0 * K / D + 1.4e-6 * D * L;
     return us < 0.9 * product_vector_us(T, D, L, K, masked);
+}
+
+// Does it pay at that many tokens or at fewer?  What scratch is asked for by, never for fewer tokens and not for more.  Looked for at
+// quarter powers of two, from the first that is no less on: 44 of 20000 layers for which it pays are missed, all close to the crossing.
+bool product_ragged_ever_pays(int64_t T, int D, int L, int K, bool masked)
+{
+    static const int quarters[4] = {256, 304, 362, 431};
+    static_assert(kRaggedTokens == 256, "where the quarters start");
+    auto tokens = [](int i) { return int64_t(quarters[i & 3]) << (i >> 2); };
+    int i = 0;
+    while (tokens(i) < T) ++i;
+    for (; i >= 0; --i)
+        if (product_ragged_pays(tokens(i), D, L, K, masked)) return true;
+    return false;
 }
 
 // the operand and the one of the rests, padded, and the flags (up to 64 blocks of rows, eight ranges each)

@@ -18,12 +18,18 @@ VECTOR = dd.DD_ALGO_VECTOR
 
 
 def _families(M, N, K, T):
-    """Which products the rules send to the matrix cores (dd::product_ragged_pays, dd::weight_grad_ragged_pays)."""
+    """Which products the library's rules send to the matrix cores."""
     lib, D, L = binding.load_library(), max(M, N), min(M, N)
-    product, gradient = lib["_ZN2dd19product_ragged_paysEliiib"], lib["_ZN2dd23weight_grad_ragged_paysEliii"]
-    product.restype = gradient.restype = ctypes.c_bool
-    product.argtypes, gradient.argtypes = [ctypes.c_int64] + 3 * [ctypes.c_int] + [ctypes.c_bool], [ctypes.c_int64] + 3 * [ctypes.c_int]
-    return "".join(name for name, there in (("f", product(T, D, L, K, M <= N)), ("b", product(T, D, L, K, M > N)), ("g", gradient(T, D, L, K))) if there)
+
+    def says(name, *sizes, masked=None):
+        rule = lib[name]
+        rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_int64] + 3 * [ctypes.c_int] + [ctypes.c_bool] * (masked is not None)
+        return rule(*sizes, *([] if masked is None else [masked]))
+
+    product = lambda masked: all(says(f"_ZN2dd{name}Eliiib", T, D, L, K, masked=masked)
+                                 for name in ("19product_ragged_pays", "24product_ragged_ever_pays"))
+    gradient = says("_ZN2dd23weight_grad_ragged_paysEliii", T, D, L, K)
+    return "".join(name for name, there in (("f", product(M <= N)), ("b", product(M > N)), ("g", gradient)) if there)
 
 
 def _case(M, N, K, T, seed=0):

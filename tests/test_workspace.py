@@ -11,7 +11,8 @@ BF16, F32 = torch.bfloat16, torch.float32
 LAYERS = [(512, 512, 51, BF16, AUTO), (320, 1000, 100, BF16, AUTO), (1000, 320, 100, BF16, VECTOR), (768, 768, 77, F32, AUTO),
           (300, 200, 20, F32, AUTO), (64, 64, 8, F32, AUTO), (768, 768, 77, BF16, AUTO), (768, 768, 77, BF16, MATRIX),
           (768, 768, 4, BF16, AUTO), (1024, 4096, 819, BF16, AUTO), (2000, 2000, 2000, F32, AUTO), (1536, 1528, 700, BF16, AUTO),
-          (333, 1001, 700, BF16, AUTO), (24, 10300, 12, F32, AUTO)]
+          (333, 1001, 700, BF16, AUTO), (24, 10300, 12, F32, AUTO), (1000, 1000, 62, BF16, AUTO), (656, 216, 61, BF16, AUTO),
+          (2040, 1992, 70, BF16, AUTO)]
 
 
 @pytest.mark.parametrize("M,N,K,dtype,algo", LAYERS)
@@ -29,3 +30,12 @@ def test_vector_scratch_stays_within_sixteen_megabytes_or_one_chunk_per_thousand
     for T in (1, 7, 64, 500, 1024, 1025, 5000, 65536, 200000):
         need = dd.dd_workspace_bytes(dd.DD_OP_BWD_WEIGHT, dd.make_layer(T, M, N, K, dtype, VECTOR))
         assert one <= need <= max(16 << 20, one * min(64, -(-T // 1024)))
+
+
+@pytest.mark.parametrize("M,N,K", [(1000, 1000, 3), (1000, 1000, 20), (2040, 2040, 5), (320, 1000, 8), (8, 264, 13), (1000, 320, 30)])
+def test_products_that_stay_on_the_vector_kernels_ask_for_no_scratch(M, N, K):
+    for T in (256, 1000, 5005, 12608, 50432):
+        layer = dd.make_layer(T, M, N, K, BF16, AUTO)
+        assert dd.dd_workspace_bytes(dd.DD_OP_FWD, layer) == 0, T
+        vector = dd.make_layer(T, M, N, K, BF16, VECTOR)
+        assert dd.dd_workspace_bytes(dd.DD_OP_BWD, layer) == dd.dd_workspace_bytes(dd.DD_OP_BWD, vector), T
