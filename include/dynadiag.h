@@ -26,7 +26,8 @@
  *     stream's device must be the current device of the calling thread.
  *   - Errors are reported by the return value; nothing is thrown and nothing aborts.
  *     DD_ERR_INVALID_ARG: null pointer, tokens < 0, features < 1, K < 1, K > D, unknown
- *     dtype or algo.  DD_ERR_WORKSPACE: ws_bytes below dd_workspace_bytes or ws misaligned.
+ *     dtype or algo.  DD_ERR_WORKSPACE: ws_bytes below dd_workspace_bytes or ws misaligned (but where that scratch is
+ *     optional, below).
  *     DD_ERR_UNSUPPORTED: a size the kernels do not cover (stated per function); for the three
  *     products: max(M, N) > 65535, or DD_ALGO_MATRIX / DD_ALGO_PREPARED forced where the matrix-core
  *     kernels do not apply.  They cover bf16 storage, 16-byte aligned matrices and M, N both multiples
@@ -36,14 +37,17 @@
  *     regime of >= 99 % sparsity) it takes vector kernels built for that case, whose time follows K down to
  *     the cost of reading the input and writing the output once -- and the vector kernels everywhere else, except that
  *     from 256 tokens on bf16 layers with M and N multiples of 8 (256 <= max(M, N) <= 2048) go to the matrix cores where
- *     that is faster: with the same results, inputs that are not finite and repeated offsets included.  The products need
- *     scratch for it (dd_workspace_bytes); without it they take the vector kernels.  Those serve
+ *     that is faster: an input that is not finite reaches the results of its own diagonals only, the copies of a repeated offset are
+ *     added in order, and a sum of weights beyond bf16's range spoils nothing, as with the vector kernels.  The products ask for
+ *     scratch for it (dd_workspace_bytes), which is optional: without it they take the vector kernels.  Those serve
  *     also for a matrix that is not 16-byte aligned (a view that starts at an odd element): such a call is legal under DD_ALGO_AUTO
  *     and several times slower; DD_ALGO_MATRIX / DD_ALGO_PREPARED report it as DD_ERR_UNSUPPORTED instead.
  *     DD_ERR_HIP: the launch itself failed.
  *   - tokens == 0 is legal: fwd / bwd_input return DD_OK without a launch; bwd_weight
  *     writes zeros.
- *   - Two calls with the same arguments give the same bits.  Calls of other sizes may take other kernels, whose fp32 sums
+ *   - Two calls with the same arguments give the same bits, with scratch of any size from dd_workspace_bytes on.  (Exception: an offset
+ *     given three times or more on the matrix cores, M and N multiples of 128, and in dd_bwd_weight_scaled's d_alpha_tilde: the copies are added in no
+ *     particular order.)  Calls of other sizes may take other kernels, whose fp32 sums
  *     run in another order: a token's row may differ in rounding between batches of few and of many tokens, and a
  *     layer's result between dd_fwd and dd_fwd_shared.  Scratch sizes never fall as tokens grow, so scratch sized for
  *     the largest batch serves every smaller one.

@@ -72,11 +72,12 @@ __global__ __launch_bounds__(kProdThreads) void masked_gather_kernel(
 // last column lies one of zeros: what a slot without a diagonal reads, so that an infinite or undefined input reaches the
 // results of its own diagonals only.
 //
-// What bounds it: the reads out of LDS, one element per multiply-add, on the busiest CU.  A wave of 16 fp32 tokens makes four
-// 16-byte reads per lane and diagonal, 32 clk of its CU's LDS at 128 bytes a clock: 12.3 us for 768 x 768, 77 diagonals, 3152
-// tokens, whose 197 tiles leave a quarter of the CUs idle.  Beside them it issues 38 (gather) or 42 (masked) vector instructions,
-// 16 of which are multiply-adds; with scalar addresses and no bounds, 23 of them, that layer took 24.1 / 20.2 us against 21.6 /
-// 20.1, and larger ones 9-11 % more.  bf16 multiply-adds are taken in pairs of diagonals by
+// What bounds it: the vector instructions of the busy CUs.  A wave of 16 fp32 tokens spends 38 (gather) or 42 (masked) of them per
+// diagonal, 16 of which are multiply-adds; the rest are the wrap, the bounds and the byte address of every lane's column, and the
+// staging.  On 768 x 768, 77 diagonals, 3152 tokens, whose 197 tiles leave a quarter of the CUs idle, they keep the SIMDs busy 96 % of
+// the time, the reads out of LDS (one element per multiply-add) the LDS 40-44 %.  The waits that they cover are as long: with
+// scalar addresses and no bounds, 23 vector instructions, that layer took 24.1 / 20.2 us against 21.6 / 20.1, and larger ones 9-11 %
+// more.  bf16 multiply-adds are taken in pairs of diagonals by
 // v_dot2_f32_bf16 (one v_perm per pair of tokens to bring two diagonals' elements together): one vector instruction per
 // multiply-add.  Measured, that layer in fp32: 21 / 20 us (forward / backward-input; 5.6 us for the multiply-adds at the 67
 // TFLOP/s of plain fp32), with four waves per workgroup, which left the reads' latency open, 43 / 44 us; 307 diagonals 61 /
