@@ -12,10 +12,11 @@ the 256 MB Infinity Cache.  The metric is the effective (sparse) rate, sum over 
 Prints ONE JSON line.  Besides the contract fields it carries
   roofline      the kernel with the largest summed time against the ceiling that bounds the method's arithmetic,
   cpu_baseline  the CPU oracle timed on this host's cores on a slice of the workload (a baseline, not a target),
-  breakdown     per-entry-point and per-shape times of the step, the dense bf16 GEMMs of the same shapes (hipBLASLt /
-                rocBLAS through torch, with the fastest solution per GEMM where a tuning file is present), speedups,
-                and one sub-line per layer of the smaller configurations (ViT-B attention projection, ViT-B MLP pair,
-                the nine ViT-L layer x sparsity cases, Tiny).
+  breakdown     per-entry-point times of the step, the dense bf16 GEMMs of the same shapes (hipBLASLt / rocBLAS through torch,
+                with the fastest solution per GEMM where a tuning file is present) and the speedups over them.
+With --details the breakdown also holds the times per shape, the GEMM solutions, and one sub-line per layer of the smaller
+configurations (ViT-B attention projection, ViT-B MLP pair, the nine ViT-L layer x sparsity cases, Tiny): 24 KB, more than what
+keeps only the end of a program's output gets to see of the line.
 
 Other modes:  --workload NAME times a step over that workload's layers instead (select + prepare + three products
 per layer); --tune-dense writes the tuning file of the dense baseline; --table prints the per-layer table as
@@ -54,7 +55,8 @@ def parse():
     ap.add_argument("--algo", default="auto", choices=["auto", "vector", "matrix"])
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-dense", action="store_true")
-    ap.add_argument("--no-configs", action="store_true", help="leave out the sub-lines of the smaller configurations")
+    ap.add_argument("--details", action="store_true", help="the breakdown per shape and the sub-lines of the smaller configurations")
+    ap.add_argument("--no-configs", action="store_true", help="with --details: leave out the sub-lines of the smaller configurations")
     ap.add_argument("--offset-bands", type=int, default=0,
                     help="0: seeded uniform offsets (the benchmark); n > 0: the K diagonals in n runs of adjacent ones")
     ap.add_argument("--per-layer", action="store_true",
@@ -719,6 +721,15 @@ def markdown_table(lines_by_config):
     return "\n".join(out)
 
 
+def headline(out):
+    """The line without what --details adds: a few kilobytes."""
+    out = json.loads(json.dumps(out))
+    for key in ("stack_shapes", "configs"):
+        out["breakdown"].pop(key, None)
+    out["breakdown"].get("dense_stack_ms", {}).pop("solutions", None)
+    return out
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -756,11 +767,13 @@ def main():
 
     if args.workload == "vitb_stack" and not args.per_layer and args.offset_bands == 0:
         out = run_stack(args, torch, dd, synth, dense)
-        if not args.no_configs:
+        if (args.details or args.table) and not args.no_configs:
             out["breakdown"]["configs"] = config_sublines(args, torch, dd, synth, dense)
         if args.table:
             print(markdown_table(out["breakdown"].get("configs", {})))
             return 0
+        if not args.details:
+            out = headline(out)
     else:
         out, lines = run_layers(args, torch, dd, synth, dense, args.workload)
         if args.table:
