@@ -124,6 +124,9 @@ __global__ __launch_bounds__(kScaleThreads) void scatter_alpha_grad_kernel(int D
                                         : (slots_) <= 8  ? kernel_<kSelectThreadsFew, 8>                \
                                                          : kernel_<kSelectThreadsFew, 16>)              \
                                      : ((slots_) <= 4  ? kernel_<kSelectThreads, 4>                   \
+                                        : (slots_) <= 6  ? kernel_<kSelectThreads, 6>                   \
+                                        : (slots_) <= 8  ? kernel_<kSelectThreads, 8>                   \
+                                        : (slots_) <= 12 ? kernel_<kSelectThreads, 12>                  \
                                         : (slots_) <= 16 ? kernel_<kSelectThreads, 16>                  \
                                                          : kernel_<kSelectThreads, 0>))
 

@@ -110,7 +110,8 @@ __device__ __forceinline__ float exponentials_held(int D, float inv_temp, const 
 // Candidates that a thread holds at most; longer vectors (from 16385 candidates on) are read again by each pass.  Held, the scores are
 // read and their exponentials taken once, us before and now: selection and weights of 1 x 768 5.7 -> 4.4 (with 256 threads, which had been
 // behind 1024 while each pass read memory), 1 x 4096 9.1 -> 7.1, 1000 x 4096 24.8 -> 17.9; weights of 1 x 768 3.2 -> 2.7, their derivative 4.0 ->
-// 3.0, of 1000 x 4096 29 -> 9.7.
+// 3.0, of 1000 x 4096 29 -> 9.7.  No more are held than a thread has, in steps of a third or so: with room for 16384, 300 x 4467 took 8.7 and
+// 13.3 us, behind the 7.3 and 10.4 of passes over memory; 5.9 and 7.1 with room for 6144.
 constexpr int kSoftHeldSlots = 16;
 // scores of a thread's candidates, the last one once more past the end
 template <int THREADS, int SLOTS>

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-5  # fp32 exponentials and sums against the fp64 oracle, as max|gpu - ref| / max|ref|
 
 
-@pytest.mark.parametrize("D", [1, 255, 256, 257, 513, 1024, 1025, 2048, 2049, 4096, 4097, 16384, 16385])
+@pytest.mark.parametrize("D", [1, 255, 256, 257, 513, 1024, 1025, 2048, 2049, 4096, 4097, 5120, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 16385])
 def test_weights_and_derivative(D):
     K = max(1, D // 10)
     scores, g = synth.draw_scores(1, D, seed=D), np.random.default_rng(D).standard_normal((1, D)).astype(np.float32)

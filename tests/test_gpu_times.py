@@ -69,3 +69,13 @@ def test_many_score_vectors(entry, batch, D, limit):
              "soft": lambda: dd.dd_select_soft(scores, K, 0.5, offsets_out=offsets, alpha_tilde=alpha),
              "weights": lambda: dd.dd_soft_topk(scores, K, 0.5, alpha_tilde=alpha)}
     assert _microseconds(calls[entry]) < limit
+
+
+# measured 5.9 and 7.1 us; with scores held for 16384 candidates 8.7 and 13.3 us
+@pytest.mark.parametrize("entry,limit", [("weights", 7.3), ("derivative", 9.5)])
+def test_score_vectors_between_the_powers_of_two(entry, limit):
+    scores, g = torch.randn((300, 4467), device="cuda"), torch.randn((300, 4467), device="cuda")
+    out = torch.empty_like(scores)
+    calls = {"weights": lambda: dd.dd_soft_topk(scores, 446, 0.5, alpha_tilde=out),
+             "derivative": lambda: dd.dd_soft_topk_bwd(scores, 446, 0.5, g, d_scores=out)}
+    assert _microseconds(calls[entry]) < limit
