@@ -120,7 +120,7 @@ def test_nothing_finite(M, N, K, T):
 def _us(call):
     call()
     times = []
-    for _ in range(5):
+    for _ in range(15):
         a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         a.record()
         call()
