@@ -125,7 +125,11 @@ hipError_t launch_weight_grad_matrix(const WeightGradArgs &a, hipStream_t stream
 // The same where the feature counts are multiples of eight only (dValues 16-byte aligned), in the scratch of the vector kernels.
 bool weight_grad_ragged_supported(int64_t T, int D, int L, bool bf16);
 bool weight_grad_ragged_pays(int64_t T, int D, int L, int K);
-double weight_grad_vector_us(int64_t T, int D, int L, int K, int &chunks, int &most);
+struct WgYardstick {  // what the matrix cores are weighed against there: us (0: no tile) and chunks of tokens
+    double us;
+    int chunks;
+};
+WgYardstick weight_grad_yardstick(int64_t T, int D, int L, int K, int &most);
 hipError_t launch_weight_grad_ragged(const WeightGradArgs &a, hipStream_t stream);
 // The same with the adjoint of the scaling by the importance weights (Sec. 3.2 Eq. 4) as the epilogue of the ordered
 // sum over the token chunks: dV[k][p] = alpha[o_k] * dValues[k][p] (to a.dValues) and dalpha[i] = sum over the

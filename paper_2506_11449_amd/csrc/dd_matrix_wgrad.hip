@@ -706,8 +706,9 @@ static WgradPlan plan_wgrad_ragged(int64_t T, int D, int L, int K, double &us, d
     pl.slices = int(slices);
     pl.skew = 0;
     pl.splits = 0;
-    int vector_chunks;
-    vector_us = weight_grad_vector_us(T, D, L, K, vector_chunks, pl.most);
+    const WgYardstick yardstick = weight_grad_yardstick(T, D, L, K, pl.most);
+    const int vector_chunks = yardstick.chunks;
+    vector_us = yardstick.us;
     if (pl.most > slices) pl.most = int(slices);
     const double exact = 0.147 * T / vector_chunks + 0.055 * vector_chunks;
     us = 1e300;

@@ -4,6 +4,8 @@
 #include "dd_common.h"
 #include "dd_launch.h"
 
+#include <type_traits>
+
 namespace dd {
 
 constexpr int kProdThreads = 256;
@@ -589,6 +591,57 @@ __device__ __forceinline__ float multiply_group(u32x4v a, u32x4v b, float acc)
     return acc;
 }
 
+// A wave's share of a tile on its way from memory to LDS: one group of G rows of 64 * V neighbouring columns at a time, V columns a
+// lane.  Which group that is, its rows and its matrix are the same for all lanes of the wave, so the addresses of its loads are a
+// lane's column, which never changes, and scalars: no vector instruction goes into them.
+template <class S, int V>
+struct Share {
+    static constexpr int G = Group<S>::kTokens;
+    using E = typename S::storage;
+    using row = std::conditional_t<V == 2, unsigned, E>;  // what a lane loads of a row
+    static_assert(V == 1 || sizeof(E) == 2, "two columns of bf16 make one word");
+    row v[G];
+    // rows first ... first + G - 1 of the matrix at `base`; past `end` the last row once more.  (In 32 bits: 64-bit comparisons
+    // would go through vector registers, behind waits for loads on their way.)
+    __device__ __forceinline__ void load(const E *base, unsigned pitch, int first, int end, unsigned in_row)
+    {
+        const int row0 = min(first, end - 1), last = end - 1 - row0;
+        const __amdgpu_buffer_rsrc_t at = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(reinterpret_cast<const char *>(base) + uint64_t(unsigned(row0)) * pitch), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const unsigned down = unsigned(min(i, last)) * pitch;
+            if constexpr (sizeof(row) == 4) v[i] = __builtin_bit_cast(row, __builtin_amdgcn_raw_buffer_load_b32(at, in_row, down, 0));
+            else v[i] = __builtin_amdgcn_raw_buffer_load_b16(at, in_row, down, 0);
+        }
+    }
+    // to LDS, column by column; of the G rows the first `rows` count, zeros in place of the others
+    __device__ __forceinline__ void store(unsigned char *to, int stride, int rows)
+    {
+        if (rows < G) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) v[i] = i < rows ? v[i] : row(0);
+        }
+        if constexpr (V == 2) {
+            u32x4v lo, hi;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                lo[i] = __builtin_amdgcn_perm(v[2 * i + 1], v[2 * i], 0x05040100u);
+                hi[i] = __builtin_amdgcn_perm(v[2 * i + 1], v[2 * i], 0x07060302u);
+            }
+            *reinterpret_cast<u32x4v *>(to) = lo;
+            *reinterpret_cast<u32x4v *>(to + stride) = hi;
+        } else if constexpr (sizeof(E) == 4) {
+            *reinterpret_cast<f32x4v *>(to) = f32x4v{v[0], v[1], v[2], v[3]};
+        } else {
+            u32x4v r;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = unsigned(v[2 * i]) | (unsigned(v[2 * i + 1]) << 16);
+            *reinterpret_cast<u32x4v *>(to) = r;
+        }
+    }
+};
+
 // The same with a tile of tokens in LDS, laid out as in product_tiled_kernel: all D columns of the long side and, behind
 // them, the short-side columns of this workgroup's positions.  A wave owns 64 positions and a block of KN diagonals: one
 // accumulator and one LDS address per lane and diagonal, fixed for the whole kernel, and one 16-byte read per diagonal and
@@ -596,12 +649,14 @@ __device__ __forceinline__ float multiply_group(u32x4v a, u32x4v b, float acc)
 // one workgroup per CU, with the next tile on its way into registers while the current one is multiplied and two tiles in
 // LDS.  A workgroup takes one chunk of the tokens; the chunks are added afterwards in order, or, if there is only one,
 // `partial` is the result.
-// Bound by neither unit alone: vector instructions take 49 % of the waves' life in fp32 and 66 % in bf16 (v_dot2_f32_bf16 takes
-// two tokens), LDS reads 25 %; the rest is the staging of the next tile and the barrier between tiles.
-// Measured: 768 x 768, 77 diagonals, fp32, 3152 tokens 30 us (one thread per gradient entry, straight from memory: 212 us),
-// 307 diagonals 69 us; 320 -> 1000, 100 diagonals, bf16, 5005 tokens 23 us (four waves per workgroup on a tile of their
-// own: 38 us).
-template <class S, int NT, int KN>
+// V: columns a lane stages at a time; 2 needs bf16 and rows that start on 4-byte boundaries.
+// What bounds it: the multiply-adds and the reads of a tile (768 x 768, 77 diagonals, fp32, 3152 tokens: 9 us of 22), and as long again the
+// next tile's way to LDS, whose loads are on their way meanwhile but whose stores and barrier are not; 6 us are launch, first tile and
+// partial sums.  Measured, that layer with the sum over the chunks 35.0 -> 26.5 us, 307 diagonals 67.6 -> 60.6; 320 -> 1000, 100
+// diagonals, bf16, 5005 tokens 31.2 -> 20.0; 1400 -> 200, 140, bf16, 3000 tokens 24.0 -> 16.2.  What it was before: every lane worked out
+// the address of each load (215 vector instructions a tile beside 128 multiply-adds), the offsets came one scalar load after the other,
+// each LDS read was waited for.
+template <class S, int NT, int KN, int V>
 __global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
     int64_t T, int D, int L, int K, int chunks, int per_chunk, int waves_k, int groups_k, int k_blocks,
     const typename S::storage *__restrict__ A, const typename S::storage *__restrict__ B,
@@ -621,8 +676,8 @@ __global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
         chunk = blockIdx.x / per_chunk;
         sub = blockIdx.x % per_chunk;
     }
-    const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int waves_p = (threads >> 6) / waves_k;
+    const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves_p = waves / waves_k;
     const int p_first = sub / groups_k * waves_p * 64;  // first position of the workgroup
     const int p_cols = min(waves_p * 64, L - p_first);
     const int p_local = wave / waves_k * 64 + lane, p = p_first + p_local;
@@ -633,85 +688,106 @@ __global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
     // tokens are dealt in whole groups
     const int64_t groups = (T + G - 1) / G;
     const int64_t t_begin = groups * chunk / chunks * G, t_end = min(groups * (chunk + 1) / chunks * G, T);
+    const int n_rows = int(t_end - t_begin);  // a chunk of 2^31 tokens would not fit memory
 
     int at[KN];
     float acc[KN];
+    // lane u has the offset of diagonal u: one load, one wait
+    const int o_lane = nk > 0 ? canonical_offset(offsets[k_lo + min(lane, nk - 1)], D) : 0;
 #pragma unroll
     for (int u = 0; u < KN; ++u) {
         acc[u] = 0.f;
-        int q = 0;
-        if (works && u < nk) {
-            q = min(p, L - 1) + canonical_offset(offsets[k_lo + u], D);
-            q -= q >= D ? D : 0;
-        }
-        at[u] = q * STRIDE;
+        int q = min(p, L - 1) + __builtin_amdgcn_readlane(o_lane, u);
+        q -= q >= D ? D : 0;
+        at[u] = (works && u < nk ? q : 0) * STRIDE;
     }
     const int a_at = (D + min(p_local, p_cols - 1)) * STRIDE;
     const int buffer = (D + waves_p * 64) * STRIDE;
-    // A thread's share of a tile: groups tid, tid + threads, ... of the long side, kAheadB of them on their way into
-    // registers while the tile before is multiplied (wider layers: the rest afterwards), and kAheadA of the short side.
-    constexpr int kAheadB = kLoadAhead * 4 / G, kAheadA = kLoadAhead * 2 / G;
-    const unsigned n_b = unsigned(D) * NT, n_a = unsigned(p_cols) * NT;
-    unsigned name_b[kAheadB], name_a[kAheadA];  // past the end: the last group once more
+    // Unit u of a tile: a group of tokens of 64 * V columns, first those of the long side, block by block and group by group, then those
+    // of the short side.  Wave w has units w, w + waves, ...; kAhead of them on their way into registers while the tile before is
+    // multiplied (wider layers: the rest afterwards).
+    constexpr int kAhead = 24 / G;
+    const int blocks_b = (D + 64 * V - 1) / (64 * V), blocks_a = (p_cols + 64 * V - 1) / (64 * V);
+    const int units_b = NT * blocks_b, units = units_b + NT * blocks_a;
+    struct Unit {
+        const E *base;
+        unsigned pitch, in_row;  // bytes; in_row: of the lane's column(s)
+        int row, at;             // first row in the tile; where the lane's first column lies in LDS
+    };
+    auto unit = [&](int u) {
+        const bool is_a = u >= units_b;
+        const int blocks = is_a ? blocks_a : blocks_b;
+        int q = 0, block = is_a ? u - units_b : u;
 #pragma unroll
-    for (int i = 0; i < kAheadB; ++i) name_b[i] = group_name(min(unsigned(tid + i * threads), n_b - 1), unsigned(D));
+        for (int i = 1; i < NT; ++i)
+            if (block >= blocks) {
+                block -= blocks;
+                ++q;
+            }
+        const int col = min(block * (64 * V) + lane * V, (is_a ? p_cols : D) - V);  // past the end: the last ones once more
+        return Unit{is_a ? A + t_begin * L + p_first : B + t_begin * D, unsigned(is_a ? L : D) * unsigned(sizeof(E)), unsigned(col) * unsigned(sizeof(E)), q * G,
+                    ((is_a ? D : 0) + col) * STRIDE + q * 16};
+    };
+    Unit mine[kAhead];
 #pragma unroll
-    for (int i = 0; i < kAheadA; ++i) name_a[i] = group_name(min(unsigned(tid + i * threads), n_a - 1), unsigned(p_cols));
-    Loaded<E> gb[kAheadB], ga[kAheadA];
-    auto request = [&](int64_t t0) {
-        const int rows = int(min(t_end - t0, int64_t(TT)));
+    for (int i = 0; i < kAhead; ++i) mine[i] = unit(min(wave + i * waves, units - 1));
+    Share<S, V> share[kAhead];
+    auto request = [&](int t0) {
 #pragma unroll
-        for (int i = 0; i < kAheadB; ++i) {
-            if (unsigned(i * threads) >= n_b) break;
-            asm volatile("" : "+v"(name_b[i]));  // what follows from it is worked out anew: registers are short
-            load_group(gb[i], B + t0 * D, name_b[i], rows, D);
-        }
+        for (int i = 0; i < kAhead; ++i)
+            if (wave + i * waves < units) share[i].load(mine[i].base, mine[i].pitch, t0 + mine[i].row, n_rows, mine[i].in_row);
+    };
+    auto place = [&](int t0, unsigned char *to) {
+        const int rows = n_rows - t0;
 #pragma unroll
-        for (int i = 0; i < kAheadA; ++i) {
-            if (unsigned(i * threads) >= n_a) break;
-            asm volatile("" : "+v"(name_a[i]));
-            load_group(ga[i], A + t0 * L + p_first, name_a[i], rows, L);
+        for (int i = 0; i < kAhead; ++i)
+            if (wave + i * waves < units) share[i].store(to + mine[i].at, STRIDE, rows - mine[i].row);
+        for (int u = wave + kAhead * waves; u < units; u += waves) {  // wide layers: the rest of the tile
+            const Unit one = unit(u);
+            Share<S, V> s;
+            s.load(one.base, one.pitch, t0 + one.row, n_rows, one.in_row);
+            s.store(to + one.at, STRIDE, rows - one.row);
         }
     };
-    auto place = [&](int64_t t0, unsigned char *to) {
-        const int rows = int(min(t_end - t0, int64_t(TT)));
-#pragma unroll
-        for (int i = 0; i < kAheadB; ++i) {
-            if (unsigned(i * threads) >= n_b) break;
-            asm volatile("" : "+v"(name_b[i]));
-            *reinterpret_cast<u32x4v *>(to + group_place(name_b[i], STRIDE)) = pack_group<TT>(gb[i], name_b[i], rows);
-        }
-#pragma unroll
-        for (int i = 0; i < kAheadA; ++i) {
-            if (unsigned(i * threads) >= n_a) break;
-            asm volatile("" : "+v"(name_a[i]));
-            *reinterpret_cast<u32x4v *>(to + D * STRIDE + group_place(name_a[i], STRIDE)) = pack_group<TT>(ga[i], name_a[i], rows);
-        }
-        for (unsigned e = tid + kAheadB * threads; e < n_b; e += threads) {  // wide layers: the rest of the tile
-            const unsigned name = group_name(e, unsigned(D));
-            Loaded<E> g;
-            load_group(g, B + t0 * D, name, rows, D);
-            *reinterpret_cast<u32x4v *>(to + group_place(name, STRIDE)) = pack_group<TT>(g, name, rows);
-        }
-    };
-    if (t_begin < t_end) {
-        request(t_begin);
-        place(t_begin, tile);
+    if (n_rows > 0) {
+        request(0);
+        place(0, tile);
     }
     __syncthreads();
     int cur = 0;
-    for (int64_t t0 = t_begin; t0 < t_end; t0 += TT) {
-        const bool more = t0 + TT < t_end;
+    for (int t0 = 0; t0 < n_rows; t0 += TT) {
+        const bool more = t0 + TT < n_rows;
         if (more) request(t0 + TT);  // in flight while this tile is multiplied
         if (works) {
+            // STEP diagonals at a time, the reads of the next ones on their way; a sum of its own for every two groups, so that an
+            // accumulator goes through one addition a tile
             const unsigned char *base = tile + cur;
+            constexpr int STEP = NT < 4 ? 4 / NT : 1, STEPS = KN / STEP;
+            static_assert(KN % STEP == 0, "whole steps");
+            regs x[2][STEP][NT], a[NT];
+            auto fetch = [&](int step) {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) {
-                const regs a = *reinterpret_cast<const regs *>(base + a_at + q * 16);
+                for (int i = 0; i < STEP; ++i)
 #pragma unroll
-                for (int u = 0; u < KN; ++u) {  // slots without a diagonal read column 0 and are dropped
-                    acc[u] = multiply_group(a, *reinterpret_cast<const regs *>(base + at[u] + q * 16), acc[u]);
-                    if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // else more reads are hoisted than there are registers
+                    for (int q = 0; q < NT; ++q) x[step & 1][i][q] = *reinterpret_cast<const regs *>(base + at[step * STEP + i] + q * 16);
+            };
+#pragma unroll
+            for (int q = 0; q < NT; ++q) a[q] = *reinterpret_cast<const regs *>(base + a_at + q * 16);
+            fetch(0);
+#pragma unroll
+            for (int step = 0; step < STEPS; ++step) {  // slots without a diagonal read column 0 and are dropped
+                __builtin_amdgcn_sched_barrier(0);
+                if (step + 1 < STEPS) fetch(step + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < STEP; ++i) {
+                    float sum = 0.f, second = 0.f;
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) {
+                        float &to = q < 2 ? sum : second;
+                        to = multiply_group(a[q], x[step & 1][i][q], to);
+                    }
+                    acc[step * STEP + i] += NT > 2 ? sum + second : sum;
                 }
             }
         }
@@ -727,39 +803,51 @@ __global__ __launch_bounds__(64 * kWgMaxWaves) void weight_grad_tiled_kernel(
     }
 }
 
-// dV[i] = sum over the chunks of partial[chunk][i]: the chunks are cut into four runs that four waves add up side by side,
-// each in a fixed order with eight loads in flight; the four sums are then added in order.
-__global__ __launch_bounds__(256) void weight_grad_reduce_kernel(size_t n, int splits, const float *__restrict__ partial,
+// dV[i] = sum over the chunks of partial[chunk][i], W entries a thread: the chunks are cut into runs of about eight (four, eight or sixteen
+// runs) that neighbouring groups of threads add up side by side, each in a fixed order with eight loads in flight; the runs' sums are then
+// added in pairs.
+constexpr int sum_runs(int splits) { return splits > 64 ? 16 : splits > 24 ? 8 : 4; }
+template <int W>
+__global__ __launch_bounds__(256) void weight_grad_reduce_kernel(size_t n, int splits, int runs, const float *__restrict__ partial,
                                                                 float *__restrict__ dV)
 {
-    __shared__ float run_s[3][64];
-    const int run = threadIdx.x >> 6, g = threadIdx.x & 63;
-    const size_t i = (size_t(blockIdx.y) * gridDim.x + blockIdx.x) * 64 + g;
-    const int per_run = (splits + 3) / 4;
+    typedef float vec __attribute__((ext_vector_type(W)));
+    __shared__ vec run_s[256];
+    const int lanes = 256 / runs, run = threadIdx.x / lanes, g = threadIdx.x % lanes;
+    const size_t i = ((size_t(blockIdx.y) * gridDim.x + blockIdx.x) * lanes + g) * W;
+    const int per_run = (splits + runs - 1) / runs;
     const int s_begin = min(run * per_run, splits), s_end = min(s_begin + per_run, splits);
-    float acc = 0.f;
+    vec acc = 0.f;
     if (i < n) {
         const float *src = partial + size_t(s_begin) * n + i;
         int s = s_begin;
         for (; s + 8 <= s_end; s += 8, src += 8 * n) {
-            float v[8];
+            vec v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = src[u * n];
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const vec *>(src + u * n);
             // in pairs: added one after the other, 256 chunks cost more precision than the chains that they cut short
             acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
-        for (; s < s_end; ++s, src += n) acc += *src;
+        if (s < s_end) {  // the last few, zeros in place of those that are not there
+            vec v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = s + u < s_end ? *reinterpret_cast<const vec *>(src + u * n) : vec(0.f);
+            acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        }
     }
-    if (run > 0) run_s[run - 1][g] = acc;
-    __syncthreads();
-    if (run == 0 && i < n) dV[i] = ((acc + run_s[0][g]) + run_s[1][g]) + run_s[2][g];
+    run_s[threadIdx.x] = acc;
+    for (int step = 1; step < runs; step *= 2) {
+        __syncthreads();
+        if (run % (2 * step) == 0) run_s[threadIdx.x] = acc = acc + run_s[threadIdx.x + step * lanes];
+    }
+    if (run == 0 && i < n) *reinterpret_cast<vec *>(dV + i) = acc;
 }
 
 struct WgTiledPlan {
     int nt, kn;              // nt = 0: no tile fits LDS
     int waves_p, waves_k, groups_k, k_blocks, per_chunk, chunks;
     size_t lds;
-    double clocks;  // of a CU, as estimated
+    double us;  // with the sum over the chunks, as estimated
 };
 
 // The fewest chunks a plan may take, so that no sum is a longer chain of additions than the kernels before these made it: at
@@ -785,54 +873,54 @@ static int wg_most_chunks(int64_t T, int D, int L, int K, bool bf16)
     return int(most > fewest ? most : fewest);
 }
 
-// Block of diagonals, tile and chunks by the time they should take, as in make_tiled_plan.
+// Block of diagonals, tile and chunks by the time they should take.  Constants fitted to 9900 measured plans of 450 layers, 48 ... 1536
+// features, 200 ... 12608 tokens, 5 ... 40 % of the diagonals (nine tenths of the predictions within a tenth; the plan taken is at
+// most 13 % behind the best one measured, 2 % in the mean).
 static WgTiledPlan make_wg_tiled_plan(int64_t T, int D, int L, int K, bool bf16)
 {
     WgTiledPlan best = {};
-    const int p_blocks = (L + 63) / 64, group = bf16 ? 8 : 4;
-    const size_t one = size_t(K) * L * sizeof(float);
+    const int p_blocks = (L + 63) / 64, group = bf16 ? 8 : 4, ahead = bf16 ? 3 : 6, load = bf16 && D % 2 == 0 && L % 2 == 0 ? 128 : 64;
     const int fewest = wg_fewest_chunks(T, D, L, bf16), most = wg_most_chunks(T, D, L, K, bf16);
-    double best_cost = 1e300;
-    static const int kns[] = {8, 16, 24}, nts[] = {1, 2, 4};
+    best.us = 1e300;
+    static const int kns[] = {8, 12, 16, 20}, nts[] = {1, 2, 4};
     for (int kn : kns) {
         const int k_blocks = (K + kn - 1) / kn;
         const int groups_k = (k_blocks + kWgMaxWaves - 1) / kWgMaxWaves, waves_k = (k_blocks + groups_k - 1) / groups_k;
         for (int waves_p = 1; waves_p * waves_k <= kWgMaxWaves && waves_p <= p_blocks; ++waves_p) {
-            const int waves = waves_p * waves_k, threads = waves * 64;
+            const int waves = waves_p * waves_k, p_cols = waves_p * 64 < L ? waves_p * 64 : L;
             const int per_chunk = (p_blocks + waves_p - 1) / waves_p * groups_k;
-            const int64_t cols = D + waves_p * 64;
             for (int nt : nts) {
-                const int tt = nt * group;
-                const size_t lds = 2 * size_t(cols) * tile_stride(nt);
-                if (lds > kLdsPerCu || nt > (bf16 ? 1 : 2) * waves_k) continue;
-                const int64_t tiles = (T + tt - 1) / tt;
-                int64_t chunks = kWgCus / per_chunk;  // one workgroup per CU: more cost more staging than they hide
-                if (chunks > tiles) chunks = tiles;
-                if (chunks > most) chunks = most;
-                if (chunks < fewest) chunks = fewest;
-                // per tile: LDS reads of all waves, or one wave's chain of instructions; the barrier and the next tile
-                const double lds_clk = waves * nt * (kn + 4) * 8, issue = nt * (kn * 16 + 8) * 1.3 * ((waves + 3) / 4);
-                const double staging = 1500 + 150.0 * cols * nt / threads + (cols * nt > (bf16 ? 2 : 4) * threads ? 2000 : 0);
-                for (;;) {  // that many chunks, or as few as may be (one: no sum over them)
-                    const double rounds = double((chunks * per_chunk + 255) / 256);
-                    const double steps = double((tiles + chunks - 1) / chunks);
-                    const double cost = rounds * (steps * ((lds_clk > issue ? lds_clk : issue) + staging) + 3000) +
-                                        (chunks > 1 ? 8000 + 2.0 * chunks * one / 2000 : 0);
-                    if (cost < best_cost) {
-                        best_cost = cost;
-                        best.nt = nt;
-                        best.kn = kn;
-                        best.waves_p = waves_p;
-                        best.waves_k = waves_k;
-                        best.groups_k = groups_k;
-                        best.k_blocks = k_blocks;
-                        best.per_chunk = per_chunk;
-                        best.chunks = int(chunks);
-                        best.lds = lds;
-                        best.clocks = cost;
-                    }
+                const size_t lds = 2 * size_t(D + waves_p * 64) * tile_stride(nt);
+                if (lds > kLdsPerCu) continue;
+                const int64_t tiles = (T + nt * group - 1) / (nt * group);
+                int resident = int(kLdsPerCu / lds);
+                if (resident * waves > kWgMaxWaves) resident = kWgMaxWaves / waves;
+                const int units = nt * ((D + load - 1) / load + (p_cols + load - 1) / load), slots = (units + waves - 1) / waves;
+                for (int fill = 2; fill >= 0; --fill) {  // as many chunks as fill the CUs twice, once, or as few as may be
+                    int64_t chunks = kWgCus * fill / per_chunk;
+                    if (chunks > tiles) chunks = tiles;
+                    if (chunks > most) chunks = most;
+                    if (chunks < fewest) chunks = fewest;
+                    const int64_t wgs = chunks * per_chunk;
+                    const double rounds = double((wgs + kWgCus * resident - 1) / (kWgCus * resident));
+                    const int side_by_side = int(wgs + kWgCus - 1) / kWgCus < resident ? int(wgs + kWgCus - 1) / kWgCus : resident;
+                    // of a tile, in ns: the busiest SIMD's multiply-adds, the LDS reads of all waves or one wave's chain; the next tile's
+                    // loads and stores, dearer one by one and beyond those on their way at once; the barrier
+                    const int w = waves * side_by_side;
+                    const double valu = (w + 3) / 4 * nt * (bf16 ? 12.4 * kn : 8.7 * kn + 28), reads = w * nt * (kn + 1) * (bf16 ? 2.7 : 2.6);
+                    const double chain = nt * kn * (bf16 ? 16.6 : 15.4);
+                    double multiply = valu > reads ? valu : reads;
+                    if (chain > multiply) multiply = chain;
+                    if (multiply < 100) multiply = 100;
+                    const int late = slots > ahead ? slots - ahead : 0;
+                    double stage = units * side_by_side * (bf16 ? 11.8 : 4.5) + (slots - late) * (bf16 ? 103 : 64) + late * (bf16 ? 110 : 126);
+                    if (bf16 && load == 64) stage *= 1.6;
+                    const double step = multiply + stage + (bf16 ? 173 : 119);
+                    double us = 3.1 + rounds * (double((tiles + chunks - 1) / chunks) * step + (bf16 ? 785 : 1916) + late * 120) / 1000 +
+                                      (chunks > 1 ? 2.6 + 3.0e-6 * chunks * K * L : 0.0);
+                    if (kn == 20) us *= bf16 ? 1.03 : 1.015;  // registers are short
+                    if (us < best.us) best = {nt, kn, waves_p, waves_k, groups_k, k_blocks, per_chunk, int(chunks), lds, us};
                     if (chunks == fewest) break;
-                    chunks = fewest;
                 }
             }
         }
@@ -859,41 +947,106 @@ size_t weight_grad_vector_ws_bytes(int64_t T, int D, int L, int K, bool bf16)
     return size_t(wg_most_chunks(T, D, L, K, bf16)) * size_t(K) * size_t(L) * sizeof(float);
 }
 
-// What the tiled kernels for bf16 should take, in us (estimates of the plans against measured times, 56 ... 1500 features, 50 ... 12608
-// tokens, 2 ... 40 % of the diagonals: nine tenths of them within a fifth), or 0 where no tile is taken; and into how many chunks the
-// weight gradient cuts the tokens, of how many it may.
+// What the tiled product kernels for bf16 should take, in us (estimates of the plans against measured times, 56 ... 1500 features, 50 ...
+// 12608 tokens, 2 ... 40 % of the diagonals: nine tenths of them within a fifth), or 0 where no tile is taken.
 double product_vector_us(int64_t T, int D, int L, int K, bool masked)
 {
     const TiledPlan pl = plan_tiled(T, D, L, K, true, masked);
     return pl.nt ? 5.0 + pl.clocks / 2400 * (masked ? 1.23 : 1.13) : 0.0;
 }
 
-double weight_grad_vector_us(int64_t T, int D, int L, int K, int &chunks, int &most)
+// What the matrix cores are held to where they take the weight gradient of widths that are multiples of eight only: a tiled plan with blocks
+// of 8, 16 or 24 diagonals whose accumulators take one addition for every two tokens.  Its chunks say how exact an entry's sum has to be,
+// its time where the matrix cores are worth their padding.  (The tiled kernel itself adds tile by tile and is some 15 % faster: between
+// the two lie layers of 20-30 us for which either would do.)
+static WgYardstick make_wg_yardstick(int64_t T, int D, int L, int K)
 {
-    const WgTiledPlan pl = plan_wg_tiled(T, D, L, K, true);
-    most = wg_most_chunks(T, D, L, K, true);
-    chunks = pl.nt ? pl.chunks : weight_grad_splits(T);
-    return pl.nt ? 2.6 + 1.35 * pl.clocks / 2400 : 0.0;
+    const int p_blocks = (L + 63) / 64, fewest = wg_fewest_chunks(T, D, L, true), most = wg_most_chunks(T, D, L, K, true);
+    const size_t one = size_t(K) * L * sizeof(float);
+    WgYardstick best = {0.0, weight_grad_splits(T)};
+    double best_clocks = 1e300;
+    static const int kns[] = {8, 16, 24}, nts[] = {1, 2, 4};
+    for (int kn : kns) {
+        const int k_blocks = (K + kn - 1) / kn;
+        const int groups_k = (k_blocks + kWgMaxWaves - 1) / kWgMaxWaves, waves_k = (k_blocks + groups_k - 1) / groups_k;
+        for (int waves_p = 1; waves_p * waves_k <= kWgMaxWaves && waves_p <= p_blocks; ++waves_p) {
+            const int waves = waves_p * waves_k, threads = waves * 64, per_chunk = (p_blocks + waves_p - 1) / waves_p * groups_k;
+            const int64_t cols = D + waves_p * 64;
+            for (int nt : nts) {
+                if (2 * size_t(cols) * tile_stride(nt) > kLdsPerCu || nt > waves_k) continue;
+                const int64_t tiles = (T + nt * 8 - 1) / (nt * 8);
+                int64_t chunks = kWgCus / per_chunk;
+                if (chunks > tiles) chunks = tiles;
+                if (chunks > most) chunks = most;
+                if (chunks < fewest) chunks = fewest;
+                const double reads = waves * nt * (kn + 4) * 8, issue = nt * (kn * 16 + 8) * 1.3 * ((waves + 3) / 4);
+                const double staging = 1500 + 150.0 * cols * nt / threads + (cols * nt > 2 * threads ? 2000 : 0);
+                for (;;) {
+                    const double rounds = double((chunks * per_chunk + 255) / 256), steps = double((tiles + chunks - 1) / chunks);
+                    const double clocks = rounds * (steps * ((reads > issue ? reads : issue) + staging) + 3000) +
+                                          (chunks > 1 ? 8000 + 2.0 * chunks * one / 2000 : 0);
+                    if (clocks < best_clocks) {
+                        best_clocks = clocks;
+                        best = {2.6 + 1.35 * clocks / 2400, int(chunks)};
+                    }
+                    if (chunks == fewest) break;
+                    chunks = fewest;
+                }
+            }
+        }
+    }
+    return best;
 }
 
-template <class S, int NT, int KN>
+WgYardstick weight_grad_yardstick(int64_t T, int D, int L, int K, int &most)
+{
+    most = wg_most_chunks(T, D, L, K, true);
+    if (wg_few_tokens(T, L, K)) return {0.0, weight_grad_splits(T)};
+    static thread_local PlanMemo<WgYardstick> memo;
+    return memo.get(T, D, L, K, 0, [&] { return make_wg_yardstick(T, D, L, K); });
+}
+
+template <class S, int NT, int KN, int V>
 static hipError_t launch_wg_tiled(const WeightGradArgs &a, const WgTiledPlan &pl, float *partial, hipStream_t stream)
 {
     using st = typename S::storage;
     static std::atomic<uint64_t> lds_allowed{0};  // one bit per device
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&weight_grad_tiled_kernel<S, NT, KN>), int(kLdsPerCu), lds_allowed)) return e;
-    hipLaunchKernelGGL((weight_grad_tiled_kernel<S, NT, KN>), dim3(pl.chunks * pl.per_chunk), dim3(64 * pl.waves_p * pl.waves_k),
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&weight_grad_tiled_kernel<S, NT, KN, V>), int(kLdsPerCu), lds_allowed)) return e;
+    hipLaunchKernelGGL((weight_grad_tiled_kernel<S, NT, KN, V>), dim3(pl.chunks * pl.per_chunk), dim3(64 * pl.waves_p * pl.waves_k),
                        pl.lds, stream, a.T, a.D, a.L, a.K, pl.chunks, pl.per_chunk, pl.waves_k, pl.groups_k, pl.k_blocks,
                        static_cast<const st *>(a.A), static_cast<const st *>(a.B), a.offsets, partial);
     return hipGetLastError();
 }
 
+template <class S, int NT, int KN>
+static hipError_t launch_wg_tiled(const WeightGradArgs &a, const WgTiledPlan &pl, float *partial, hipStream_t stream)
+{
+    if constexpr (sizeof(typename S::storage) == 2) {
+        // two columns to a load: rows and matrices on 4-byte boundaries
+        const bool words = a.D % 2 == 0 && a.L % 2 == 0 && (reinterpret_cast<uintptr_t>(a.A) | reinterpret_cast<uintptr_t>(a.B)) % 4 == 0;
+        if (words) return launch_wg_tiled<S, NT, KN, 2>(a, pl, partial, stream);
+    }
+    return launch_wg_tiled<S, NT, KN, 1>(a, pl, partial, stream);
+}
+
 template <class S, int NT>
 static hipError_t launch_wg_tiled(const WeightGradArgs &a, const WgTiledPlan &pl, float *partial, hipStream_t stream)
 {
-    return pl.kn == 24   ? launch_wg_tiled<S, NT, 24>(a, pl, partial, stream)
+    return pl.kn == 20   ? launch_wg_tiled<S, NT, 20>(a, pl, partial, stream)
            : pl.kn == 16 ? launch_wg_tiled<S, NT, 16>(a, pl, partial, stream)
+           : pl.kn == 12 ? launch_wg_tiled<S, NT, 12>(a, pl, partial, stream)
                          : launch_wg_tiled<S, NT, 8>(a, pl, partial, stream);
+}
+
+template <int W>
+static hipError_t launch_sum(size_t n, int splits, const float *partial, float *dV, hipStream_t stream)
+{
+    // two dimensions: one holds 2^32 threads, a gradient up to 2^32 entries with up to sixteen threads each
+    const int runs = sum_runs(splits);
+    const size_t each = 256 / runs * W, blocks = (n + each - 1) / each, across = blocks < (size_t(1) << 20) ? blocks : size_t(1) << 20;
+    hipLaunchKernelGGL(weight_grad_reduce_kernel<W>, dim3(unsigned(across), unsigned((blocks + across - 1) / across)), dim3(256), 0,
+                       stream, n, splits, runs, partial, dV);
+    return hipGetLastError();
 }
 
 template <class S>
@@ -920,11 +1073,8 @@ static hipError_t launch_weight_grad_t(const WeightGradArgs &a, hipStream_t stre
         e = hipGetLastError();
     }
     if (e != hipSuccess || splits == 1) return e;
-    // two dimensions: one holds 2^32 threads, a gradient up to 2^32 entries with four threads each
-    const size_t blocks = (n + 63) / 64, across = blocks < (size_t(1) << 20) ? blocks : size_t(1) << 20;
-    hipLaunchKernelGGL(weight_grad_reduce_kernel, dim3(unsigned(across), unsigned((blocks + across - 1) / across)), dim3(256), 0,
-                       stream, n, splits, partial, a.dValues);
-    return hipGetLastError();
+    return n % 4 == 0 && reinterpret_cast<uintptr_t>(a.dValues) % 16 == 0 ? launch_sum<4>(n, splits, partial, a.dValues, stream)
+                                                                         : launch_sum<1>(n, splits, partial, a.dValues, stream);
 }
 
 hipError_t launch_weight_grad_vector(const WeightGradArgs &a, hipStream_t stream)
