@@ -70,26 +70,29 @@ __global__ __launch_bounds__(kProdThreads) void masked_gather_kernel(
 // Layout: a tile holds NT 16-byte groups of tokens per source column (a group: four fp32 or eight bf16 tokens), columns
 // one after the other STRIDE bytes apart.  A lane owns one destination column and all tokens of the tile: per diagonal it
 // works out its source column once and fetches its tokens with NT 16-byte reads.  STRIDE is an odd multiple of 16 bytes,
-// so that the lanes of a read, which sit on neighbouring columns whatever the offset, fall on different banks.  Behind the
-// last column lies one of zeros: what a slot without a diagonal reads, so that an infinite or undefined input reaches the
-// results of its own diagonals only.
+// so that the lanes of a read, which sit on neighbouring columns whatever the offset, fall on different banks.  The 64 lanes of a wave
+// read 64 neighbouring columns, so a diagonal is one scalar, the column of lane 0: behind the last column the first ones follow once
+// more, and where the source has no column there are zeros.  A diagonal's weights are read as a buffer of L entries, past whose ends
+// there are zeros too, so that an infinite or undefined input reaches the results of its own diagonals only.
 //
-// What bounds it: the vector instructions of the busy CUs.  A wave of 16 fp32 tokens spends 38 (gather) or 42 (masked) of them per
-// diagonal, 16 of which are multiply-adds; the rest are the wrap, the bounds and the byte address of every lane's column, and the
-// staging.  On 768 x 768, 77 diagonals, 3152 tokens, whose 197 tiles leave a quarter of the CUs idle, they keep the SIMDs busy 96 % of
-// the time, the reads out of LDS (one element per multiply-add) the LDS 40-44 %.  The waits that they cover are as long: with
-// scalar addresses and no bounds, 23 vector instructions, that layer took 24.1 / 20.2 us against 21.6 / 20.1, and larger ones 9-11 %
-// more.  bf16 multiply-adds are taken in pairs of diagonals by
-// v_dot2_f32_bf16 (one v_perm per pair of tokens to bring two diagonals' elements together): one vector instruction per
-// multiply-add.  Measured, that layer in fp32: 21 / 20 us (forward / backward-input; 5.6 us for the multiply-adds at the 67
-// TFLOP/s of plain fp32), with four waves per workgroup, which left the reads' latency open, 43 / 44 us; 307 diagonals 61 /
-// 57 us; 320 -> 1000, 100 diagonals, bf16, 5005 tokens 23 / 23 us, converted to fp32 in LDS 70 / 44 us.
+// What bounds it: the vector instructions of the busy CUs and, as long as a workgroup is alone on its CU, the tile's way from memory.
+// A wave of 16 fp32 tokens spends 20 (gather) or 22 (masked) instructions per diagonal, 16 of which are multiply-adds.  On 768 x 768, 77
+// diagonals, 3152 tokens, whose 197 tiles leave a quarter of the CUs idle, a workgroup takes 17.3 us: 4.1 until its tile is laid out, 12.5
+// for the diagonals (9 at one instruction a clock; the oldest wave of a SIMD is through after 9, the youngest after 12.5), 0.7 for the
+// stores.  Without the reads of every second diagonal, without the weights or without the tile that layer takes 1.8 to 2 us less each.
+// bf16 multiply-adds are taken in pairs of diagonals by v_dot2_f32_bf16 (one v_perm per pair of tokens to bring two diagonals' elements
+// together): one vector instruction per multiply-add.  Measured (forward / backward-input), before -> now: that layer in fp32
+// 20.9 / 18.8 -> 17.9 / 16.6 us, 307 diagonals 56.0 / 51.5 -> 47.5 / 44.6; 320 -> 1000, 100 diagonals, bf16, 5005 tokens
+// 22.5 / 23.0 -> 17.2 / 18.5; 1000^2, 100, bf16, 12608 tokens 92.7 / 87.6 -> 75.6 / 71.6; the smallest, 64^2, 8, fp32, 16 tokens
+// 3.4 / 3.2 -> 3.0 / 3.0; over 31 layers 1.12x.  (104^2, 16, bf16, 12608 tokens, where the 64 columns that are laid out once more weigh
+// most, 6.6 -> 7.0.)  Before, every lane worked out and checked its own column and the address of its weight (38 and 42 instructions),
+// each pair of reads was waited for, the tile's loads spent an address a lane, and offsets, tile and first weights came one
+// after the other.  Scalar addresses alone had been no faster: the waits behind the instructions were as long.
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2p __attribute__((ext_vector_type(2)));
 
 constexpr int kMaxWaves = 16;     // waves per workgroup of the product kernel
-constexpr int kLoadAhead = 4;     // groups of a tile a thread has on their way at once
 constexpr int kWideSource = 4500; // columns beyond which a tile may not pay
 constexpr int kListLen = 256;     // diagonals looked at per pass; their list is private to a wave
 constexpr size_t kLdsPerCu = 160 * 1024;
@@ -108,69 +111,137 @@ template <> struct Group<BF16> {
 
 constexpr int tile_stride(int nt) { return nt == 1 ? 16 : nt * 16 + 16; }  // nt is 1 or even
 
-// A group of a tile is named by (group of rows << 16 | column).  Its rows as they come from memory, and as the 16 bytes of
-// the group.  `base`: the tile's first row in a row-major matrix with `ld` columns (uniform over the wave: a lane only adds
-// an offset).  Of the tile's TT rows the first `rows` exist; the others are read from the last of these and replaced by
-// zeros in the group.
-template <class E> struct Loaded { E v[16 / sizeof(E)]; };
-template <class E>
-__device__ __forceinline__ void load_group(Loaded<E> &g, const E *base, unsigned name, int rows, int ld)
-{
-    constexpr unsigned G = 16 / sizeof(E), kSize = sizeof(E);
-    const unsigned pitch = unsigned(ld) * kSize, in_row = (name & 0xffffu) * kSize;
-    const unsigned first = (name >> 16) * G * pitch + in_row, last = unsigned(rows - 1) * pitch + in_row;
+// A wave's share of a tile on its way from memory to LDS: one group of G rows of 64 * V neighbouring columns at a time, V columns a
+// lane.  Which group that is, its rows and its matrix are the same for all lanes of the wave, so the addresses of its loads are a
+// lane's column, which never changes, and scalars: no vector instruction goes into them.
+template <class S, int V>
+struct Share {
+    static constexpr int G = Group<S>::kTokens;
+    using E = typename S::storage;
+    using row = std::conditional_t<V == 2, unsigned, E>;  // what a lane loads of a row
+    static_assert(V == 1 || sizeof(E) == 2, "two columns of bf16 make one word");
+    row v[G];
+    // rows first ... first + G - 1 of the matrix at `base`; past `end` the last row once more.  (In 32 bits: 64-bit comparisons
+    // would go through vector registers, behind waits for loads on their way.)
+    __device__ __forceinline__ void load(const E *base, unsigned pitch, int first, int end, unsigned in_row)
+    {
+        const int row0 = min(first, end - 1), last = end - 1 - row0;
+        const __amdgpu_buffer_rsrc_t at = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(reinterpret_cast<const char *>(base) + uint64_t(unsigned(row0)) * pitch), 0, 0x7fffffff, 0x00020000);
 #pragma unroll
-    for (unsigned i = 0; i < G; ++i)
-        g.v[i] = *reinterpret_cast<const E *>(reinterpret_cast<const char *>(base) + min(first + i * pitch, last));
-}
-__device__ __forceinline__ unsigned group_name(unsigned e, unsigned cols)  // the e-th group, column by column
-{
-    const unsigned q = e / cols;
-    return q << 16 | (e - q * cols);
-}
-__device__ __forceinline__ unsigned group_place(unsigned name, int stride) { return (name & 0xffffu) * unsigned(stride) + (name >> 16) * 16u; }
-template <int TT>
-__device__ __forceinline__ u32x4v pack_group(const Loaded<float> &g, unsigned name, int rows)
-{
-    const int row0 = int(name >> 16) * 4;
-    u32x4v r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = rows == TT || row0 + i < rows ? __float_as_uint(g.v[i]) : 0u;
-    return r;
-}
-template <int TT>
-__device__ __forceinline__ u32x4v pack_group(const Loaded<uint16_t> &g, unsigned name, int rows)
-{
-    const int row0 = int(name >> 16) * 8;
-    u32x4v r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        r[i] = unsigned(g.v[2 * i]) | (unsigned(g.v[2 * i + 1]) << 16);
-        if (rows != TT) r[i] = row0 + 2 * i + 1 < rows ? r[i] : (row0 + 2 * i < rows ? r[i] & 0xffffu : 0u);
+        for (int i = 0; i < G; ++i) {
+            const unsigned down = unsigned(min(i, last)) * pitch;
+            if constexpr (sizeof(row) == 4) v[i] = __builtin_bit_cast(row, __builtin_amdgcn_raw_buffer_load_b32(at, in_row, down, 0));
+            else v[i] = __builtin_amdgcn_raw_buffer_load_b16(at, in_row, down, 0);
+        }
     }
-    return r;
-}
+    // to LDS, column by column; of the G rows the first `rows` count, zeros in place of the others
+    __device__ __forceinline__ void store(unsigned char *to, int stride, int rows)
+    {
+        if (rows < G) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) v[i] = i < rows ? v[i] : row(0);
+        }
+        if constexpr (V == 2) {
+            u32x4v lo, hi;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                lo[i] = __builtin_amdgcn_perm(v[2 * i + 1], v[2 * i], 0x05040100u);
+                hi[i] = __builtin_amdgcn_perm(v[2 * i + 1], v[2 * i], 0x07060302u);
+            }
+            *reinterpret_cast<u32x4v *>(to) = lo;
+            *reinterpret_cast<u32x4v *>(to + stride) = hi;
+        } else if constexpr (sizeof(E) == 4) {
+            *reinterpret_cast<f32x4v *>(to) = f32x4v{v[0], v[1], v[2], v[3]};
+        } else {
+            u32x4v r;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = unsigned(v[2 * i]) | (unsigned(v[2 * i + 1]) << 16);
+            *reinterpret_cast<u32x4v *>(to) = r;
+        }
+    }
+};
 
 __device__ __forceinline__ float dot2(unsigned a, unsigned b, float c)
 {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2p, a), __builtin_bit_cast(bf16x2p, b), c, false);
 }
 
-// Diagonals two at a time: acc[t] += x0[t] * w0 + x1[t] * w1 for the tokens of group q of the columns at p0 and p1.
-__device__ __forceinline__ void multiply_pair(float *acc, const unsigned char *p0, const unsigned char *p1, float w0, float w1)
+// Diagonals two at a time: acc[t] += x0[t] * w0 + x1[t] * w1 for the tokens of a group.
+__device__ __forceinline__ void multiply_pair(float *acc, f32x4v x0, f32x4v x1, float w0, float w1)
 {
-    const f32x4v x0 = *reinterpret_cast<const f32x4v *>(p0), x1 = *reinterpret_cast<const f32x4v *>(p1);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = fmaf(x1[i], w1, fmaf(x0[i], w0, acc[i]));
 }
-__device__ __forceinline__ void multiply_pair(float *acc, const unsigned char *p0, const unsigned char *p1, unsigned w0, unsigned w1)
+__device__ __forceinline__ void multiply_pair(float *acc, u32x4v x0, u32x4v x1, unsigned w0, unsigned w1)
 {
-    const u32x4v x0 = *reinterpret_cast<const u32x4v *>(p0), x1 = *reinterpret_cast<const u32x4v *>(p1);
     const unsigned w = w0 | (w1 << 16);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         acc[2 * i] = dot2(__builtin_amdgcn_perm(x1[i], x0[i], 0x05040100u), w, acc[2 * i]);
         acc[2 * i + 1] = dot2(__builtin_amdgcn_perm(x1[i], x0[i], 0x07060302u), w, acc[2 * i + 1]);
+    }
+}
+// The last one of an odd number.
+__device__ __forceinline__ void multiply_one(float *acc, f32x4v x, float w)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = fmaf(x[i], w, acc[i]);
+}
+__device__ __forceinline__ void multiply_one(float *acc, u32x4v x, unsigned w) { multiply_pair(acc, x, u32x4v{0u, 0u, 0u, 0u}, w, 0u); }
+
+// Columns of a tile: the source's, the first ones once more behind them (what a read of 64 neighbouring columns wraps into), and for a
+// source narrower than the destination zeros wherever there is no source column, also in front.
+constexpr int kWrapCols = 64;
+__host__ __device__ constexpr int tile_front(int D, int L, bool masked) { return masked && D > L ? kWrapCols : 0; }
+__host__ __device__ constexpr int tile_cols(int D, int L, bool masked) { return tile_front(D, L, masked) + (masked ? L : D) + kWrapCols; }
+
+// The tile's tokens, V columns a lane and load (V = 2: even widths, rows on 4-byte boundaries).  meanwhile(): what a wave does while
+// its first loads are on their way.
+template <class S, int NT, bool MASKED, int V, class F>
+__device__ __forceinline__ void stage_tile(unsigned char *tile, const typename S::storage *base, int rows, int D, int L, F meanwhile)
+{
+    constexpr int STRIDE = tile_stride(NT), kAhead = 4;
+    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int src_cols = MASKED ? L : D, front = tile_front(D, L, MASKED), cols = tile_cols(D, L, MASKED);
+    const int blocks = (cols + 64 * V - 1) / (64 * V), units = NT * blocks;
+    Share<S, V> g[kAhead];
+    int at[kAhead];
+    auto request = [&](int u0) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const int u = u0 + i * waves;
+            if (u >= units) continue;
+            int q = 0, block = u;
+#pragma unroll
+            for (int j = 1; j < NT; ++j) {
+                const bool next = block >= blocks;
+                block -= next ? blocks : 0;
+                q += next ? 1 : 0;
+            }
+            const int e = min(block * (64 * V) + lane * V, cols - V);  // past the end: the last ones once more
+            int c = e - front;
+            if (D < kWrapCols) c %= D;
+            c += c < 0 ? D : 0;
+            c -= c >= D ? D : 0;
+            g[i].load(base, unsigned(src_cols) * unsigned(sizeof(typename S::storage)), q * Group<S>::kTokens, rows,
+                      c < src_cols ? unsigned(c) * unsigned(sizeof(typename S::storage)) : 0x80000000u);  // beyond the buffer: zero
+            at[i] = e * STRIDE + q * 16;
+        }
+    };
+    auto place = [&](int u0) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if (u0 + i * waves < units) g[i].store(tile + at[i], STRIDE, Group<S>::kTokens);
+    };
+    request(wave);
+    __builtin_amdgcn_sched_barrier(0);
+    meanwhile();
+    __builtin_amdgcn_sched_barrier(0);
+    place(wave);
+    for (int u0 = wave + kAhead * waves; u0 < units; u0 += kAhead * waves) {
+        request(u0);
+        place(u0);
     }
 }
 
@@ -179,7 +250,7 @@ __device__ __forceinline__ void multiply_pair(float *acc, const unsigned char *p
 // sums are added through LDS in order -- for calls with so few tokens that the chip would otherwise stand idle.  Every
 // wave lists the diagonals of its part that meet its columns (all of them for the plain gather; for the masked gather
 // onto a longer side most miss a given block), and walks the list eight at a time, the weights of the next eight on
-// their way while the current eight are multiplied.
+// their way while the current eight are multiplied, the reads of the next pair on theirs while a pair is.
 template <class S, int NT, bool MASKED>
 __device__ __forceinline__ void product_tiled(unsigned char *tile, unsigned tile_x, int tile_y, int64_t T, int D, int L, int K, int k_parts,
                                               const typename S::storage *__restrict__ src, const int *__restrict__ offsets,
@@ -187,96 +258,150 @@ __device__ __forceinline__ void product_tiled(unsigned char *tile, unsigned tile
 {
     constexpr int G = Group<S>::kTokens, TT = NT * G, STRIDE = tile_stride(NT), KB = 8;
     using weight = typename Group<S>::weight;
-    const int src_cols = MASKED ? L : D, dst_cols = MASKED ? D : L;
-    const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    unsigned *list = reinterpret_cast<unsigned *>(tile + size_t(src_cols + 1) * STRIDE) + wave * kListLen;
+    using regs = typename Group<S>::regs;
+    using E = typename S::storage;
+    const int src_cols = MASKED ? L : D, dst_cols = MASKED ? D : L, front = tile_front(D, L, MASKED);
+    const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned *list = reinterpret_cast<unsigned *>(tile + size_t(tile_cols(D, L, MASKED)) * STRIDE) + wave * kListLen;
     const int64_t t0 = int64_t(tile_x) * TT;
-
-    const int rows = int(min(T - t0, int64_t(TT)));  // tokens past the last one repeat it; their results are not stored
-    const unsigned n_groups = unsigned(src_cols) * NT;
-    for (unsigned e0 = tid; e0 < n_groups; e0 += kLoadAhead * threads) {
-        Loaded<typename S::storage> g[kLoadAhead];
-        unsigned at[kLoadAhead];
-#pragma unroll
-        for (int i = 0; i < kLoadAhead; ++i) {  // the last round repeats its first piece
-            const unsigned name = group_name(e0 + i * threads < n_groups ? e0 + i * threads : e0, unsigned(src_cols));
-            load_group(g[i], src + t0 * src_cols, name, rows, src_cols);
-            at[i] = group_place(name, STRIDE);
-        }
-#pragma unroll
-        for (int i = 0; i < kLoadAhead; ++i)
-            *reinterpret_cast<u32x4v *>(tile + at[i]) = pack_group<TT>(g[i], 0, TT);
-    }
-    if (tid < NT) *reinterpret_cast<u32x4v *>(tile + size_t(src_cols) * STRIDE + tid * 16) = u32x4v{0u, 0u, 0u, 0u};
-    __syncthreads();
-
     const int blocks_per_group = (threads >> 6) / k_parts;
     const int part = wave % k_parts, local_block = wave / k_parts;
     const int k_lo = int(int64_t(part) * K / k_parts), k_hi = int(int64_t(part + 1) * K / k_parts);
     const int j0 = (tile_y * blocks_per_group + local_block) * 64, j = j0 + lane;
-    const bool active = j < dst_cols;
-    float acc[TT];
+    const bool active = j < dst_cols, works = j0 < dst_cols;
+
+    // A pass looks at kListLen diagonals from k0 on and lists those that meet the wave's columns: (diagonal - k0) << 16 | column of the
+    // tile that lane 0 reads.
+    constexpr int kLooks = kListLen / 64;
+    int o[kLooks], n = 0;
+    auto look = [&](int k0) {
 #pragma unroll
-    for (int t = 0; t < TT; ++t) acc[t] = 0.f;
-    for (int k0 = k_lo; k0 < k_hi && j0 < dst_cols; k0 += kListLen) {
-        int n = 0;
+        for (int r = 0; r < kLooks; ++r) o[r] = offsets[min(k0 + r * 64 + lane, K - 1)];
+    };
+    auto make_list = [&](int k0) {
+        n = 0;
 #pragma unroll
-        for (int r = 0; r < kListLen / 64; ++r) {
-            const int k = k0 + r * 64 + lane;
-            bool meets = k < k_hi;
-            int o = 0;
-            if (meets) o = canonical_offset(offsets[k], D);
+        for (int r = 0; r < kLooks; ++r) {
+            if (r > 0 && k0 + r * 64 >= k_hi) break;
+            const int oc = canonical_offset(o[r], D);
+            bool meets = k0 + r * 64 + lane < k_hi;
+            int first;
             if (MASKED) {  // source columns j0 - o ... j0 - o + 63 (mod D): does one of them exist?
-                int a = j0 - o;
-                a += a < 0 ? D : 0;
-                meets = meets && (a < L || a + 63 >= D);
+                first = j0 - oc;
+                first += first < 0 ? D : 0;
+                meets = meets && (first < L || first + 63 >= D);
+                first -= first >= L ? D : 0;
+            } else {
+                first = j0 + oc;
+                first -= first >= D ? D : 0;
             }
             const unsigned long long b = __ballot(meets);
             const int rank = __builtin_amdgcn_mbcnt_hi(unsigned(b >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(b), 0u));
-            if (meets) list[n + rank] = (unsigned(r * 64 + lane) << 16) | unsigned(o);
+            if (meets) list[n + rank] = (unsigned(r * 64 + lane) << 16) | unsigned(first + front);
             n += __popcll(b);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        weight w_cur[KB], w_nxt[KB];
-        int c_cur[KB], c_nxt[KB];
-        auto fetch = [&](int i0, weight (&w)[KB], int (&at)[KB]) {
-            const unsigned entries = list[min(i0 + (lane & (KB - 1)), n - 1)];  // lane u: entry i0 + u
+    };
+    // Eight listed diagonals: their weights requested, their columns in bytes (the same for all lanes).
+    weight w_cur[KB], w_nxt[KB];
+    int c_cur[KB], c_nxt[KB];
+    unsigned entries = 0;
+    const unsigned lane_bytes = unsigned(lane) * unsigned(sizeof(E)), D_bytes = unsigned(D) * unsigned(sizeof(E));
+    const unsigned row_bytes = unsigned(L) * unsigned(sizeof(E)), j_bytes = unsigned(j) * unsigned(sizeof(E));
+    auto fetch = [&](int k0, int i0, weight (&w)[KB], int (&at)[KB]) {
+        if (i0 % 64 == 0) entries = list[min(i0 + lane, n - 1)];
+        const E *rows_k0 = values + size_t(k0) * L;
 #pragma unroll
-            for (int u = 0; u < KB; ++u) {
-                const unsigned e = unsigned(__builtin_amdgcn_readlane(int(entries), u));
-                const int o = int(e & 0xffffu);
-                const bool there = i0 + u < n;
-                const typename S::storage *row = values + size_t(unsigned(k0) + (e >> 16)) * L;
-                if (MASKED) {
-                    const unsigned d = unsigned(j - o), c = min(d, d + unsigned(D));
-                    const bool valid = c < (there ? unsigned(L) : 0u);
-                    const weight v = row[min(c, unsigned(L - 1))];
-                    w[u] = valid ? v : weight(0);
-                    at[u] = int(valid ? c : unsigned(L)) * STRIDE;
-                } else {
-                    const unsigned jj = unsigned(min(j, L - 1)), s = jj + unsigned(o), c = min(s, s - unsigned(D));
-                    const weight v = row[jj];
-                    w[u] = there ? v : weight(0);
-                    at[u] = int(there ? c : unsigned(D)) * STRIDE;
+        for (int u = 0; u < KB; ++u) {
+            const unsigned e = unsigned(__builtin_amdgcn_readlane(int(entries), (i0 + u) % 64));
+            const int col = int(e & 0xffffu);
+            // a diagonal's values as a buffer: past its ends there are zeros
+            const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(const_cast<E *>(rows_k0 + size_t(e >> 16) * L), 0, int(row_bytes), 0x00020000);
+            unsigned at_w = j_bytes;
+            if (MASKED) {
+                at_w = lane_bytes + unsigned(col - front) * unsigned(sizeof(E));
+                at_w = min(at_w, at_w - D_bytes);
+            }
+            if constexpr (sizeof(E) == 4) w[u] = __builtin_bit_cast(weight, __builtin_amdgcn_raw_buffer_load_b32(row, at_w, 0, 0));
+            else w[u] = __builtin_amdgcn_raw_buffer_load_b16(row, at_w, 0, 0);
+            at[u] = col * STRIDE;
+        }
+    };
+
+    look(k_lo);
+    {
+        const int rows = int(min(T - t0, int64_t(TT)));  // tokens past the last one repeat it; their results are not stored
+        const E *base = src + t0 * src_cols;
+        auto meanwhile = [&] { if (works) make_list(k_lo); };
+        bool staged = false;
+        if constexpr (sizeof(E) == 2) {
+            if (D % 2 == 0 && L % 2 == 0 && reinterpret_cast<uintptr_t>(src) % 4 == 0) {
+                stage_tile<S, NT, MASKED, 2>(tile, base, rows, D, L, meanwhile);
+                staged = true;
+            }
+        }
+        if (!staged) stage_tile<S, NT, MASKED, 1>(tile, base, rows, D, L, meanwhile);
+    }
+    if (n > 0) fetch(k_lo, 0, w_cur, c_cur);
+    __syncthreads();
+
+    float acc[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[t] = 0.f;
+    const unsigned char *own = tile + lane * STRIDE;
+    for (int k0 = k_lo; works && k0 < k_hi;) {
+        if (n > 0) {
+            // a step: QN groups of two diagonals
+            constexpr int QN = TT == 32 ? NT / 2 : NT, PER_PAIR = NT / QN, STEPS = KB / 2 * PER_PAIR;
+            regs x[2][2][QN];
+            auto read = [&](int step, int c0, int c1) {
+#pragma unroll
+                for (int q = 0; q < QN; ++q) x[step & 1][0][q] = *reinterpret_cast<const regs *>(own + c0 + (step % PER_PAIR * QN + q) * 16);
+#pragma unroll
+                for (int q = 0; q < QN; ++q) x[step & 1][1][q] = *reinterpret_cast<const regs *>(own + c1 + (step % PER_PAIR * QN + q) * 16);
+            };
+            read(0, c_cur[0], c_cur[1]);
+            int i0 = 0;
+            for (; i0 + KB < n; i0 += KB) {
+                fetch(k0, i0 + KB, w_nxt, c_nxt);
+#pragma unroll
+                for (int step = 0; step < STEPS; ++step) {
+                    const int u = step / PER_PAIR * 2, v = (step + 1) / PER_PAIR * 2;
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (v < KB) read(step + 1, c_cur[v % KB], c_cur[(v + 1) % KB]);
+                    else read(step + 1, c_nxt[0], c_nxt[1]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int q = 0; q < QN; ++q)
+                        multiply_pair(acc + (step % PER_PAIR * QN + q) * G, x[step & 1][0][q], x[step & 1][1][q], w_cur[u], w_cur[u + 1]);
+                }
+#pragma unroll
+                for (int u = 0; u < KB; ++u) { w_cur[u] = w_nxt[u]; c_cur[u] = c_nxt[u]; }
+            }
+#pragma unroll
+            for (int step = 0; step < STEPS; ++step) {  // the last ones, one to eight
+                const int u = step / PER_PAIR * 2, v = (step + 1) / PER_PAIR * 2;
+                if (i0 + u >= n) break;
+                __builtin_amdgcn_sched_barrier(0);
+                if (v < KB) read(step + 1, c_cur[v % KB], c_cur[(v + 1) % KB]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < QN; ++q) {
+                    float *to = acc + (step % PER_PAIR * QN + q) * G;
+                    if (i0 + u + 1 < n) multiply_pair(to, x[step & 1][0][q], x[step & 1][1][q], w_cur[u], w_cur[u + 1]);
+                    else multiply_one(to, x[step & 1][0][q], w_cur[u]);
                 }
             }
-        };
-        if (n > 0) fetch(0, w_cur, c_cur);
-        for (int i0 = 0; i0 < n; i0 += KB) {
-            if (i0 + KB < n) fetch(i0 + KB, w_nxt, c_nxt);
-#pragma unroll
-            for (int u = 0; u < KB; u += 2) {
-#pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    multiply_pair(acc + q * G, tile + c_cur[u] + q * 16, tile + c_cur[u + 1] + q * 16, w_cur[u], w_cur[u + 1]);
-                if (TT == 32) __builtin_amdgcn_sched_barrier(0);  // else more reads are hoisted than there are registers
-            }
-#pragma unroll
-            for (int u = 0; u < KB; ++u) { w_cur[u] = w_nxt[u]; c_cur[u] = c_nxt[u]; }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        k0 += kListLen;
+        if (k0 < k_hi) {
+            look(k0);
+            make_list(k0);
+            if (n > 0) fetch(k0, 0, w_cur, c_cur);
+        }
     }
     if (k_parts > 1) {  // the tile is not needed any more
         __syncthreads();
@@ -294,12 +419,12 @@ __device__ __forceinline__ void product_tiled(unsigned char *tile, unsigned tile
     if (active) {
         if (t0 + TT <= T) {
 #pragma unroll
-            for (int t = 0; t < TT; ++t, out += dst_cols) S::store(out + j, acc[t]);
+            for (int t = 0; t < TT; ++t, out += dst_cols) S::stream(out + j, acc[t]);
         } else {
             const int rows = int(T - t0);
 #pragma unroll
             for (int t = 0; t < TT; ++t, out += dst_cols)
-                if (t < rows) S::store(out + j, acc[t]);
+                if (t < rows) S::stream(out + j, acc[t]);
         }
     }
 }
@@ -370,7 +495,7 @@ static TiledPlan make_tiled_plan(int64_t T, int D, int L, int K, bool bf16, bool
                 if (per_group > 1 && per_group / 2 >= n_blocks) break;
                 const int w = per_group > n_blocks ? n_blocks * parts : waves;
                 const int groups = (n_blocks + w / parts - 1) / (w / parts);
-                size_t lds = size_t(src_cols + 1) * tile_stride(nt) + size_t(w) * kListLen * 4;
+                size_t lds = size_t(tile_cols(D, L, masked)) * tile_stride(nt) + size_t(w) * kListLen * 4;
                 const size_t sums = size_t(w) * tt * 256;
                 if (parts > 1 && sums > lds) lds = sums;
                 if (lds > kLdsPerCu || groups > 65535) continue;
@@ -590,57 +715,6 @@ __device__ __forceinline__ float multiply_group(u32x4v a, u32x4v b, float acc)
     for (int i = 0; i < 4; ++i) acc = dot2(a[i], b[i], acc);
     return acc;
 }
-
-// A wave's share of a tile on its way from memory to LDS: one group of G rows of 64 * V neighbouring columns at a time, V columns a
-// lane.  Which group that is, its rows and its matrix are the same for all lanes of the wave, so the addresses of its loads are a
-// lane's column, which never changes, and scalars: no vector instruction goes into them.
-template <class S, int V>
-struct Share {
-    static constexpr int G = Group<S>::kTokens;
-    using E = typename S::storage;
-    using row = std::conditional_t<V == 2, unsigned, E>;  // what a lane loads of a row
-    static_assert(V == 1 || sizeof(E) == 2, "two columns of bf16 make one word");
-    row v[G];
-    // rows first ... first + G - 1 of the matrix at `base`; past `end` the last row once more.  (In 32 bits: 64-bit comparisons
-    // would go through vector registers, behind waits for loads on their way.)
-    __device__ __forceinline__ void load(const E *base, unsigned pitch, int first, int end, unsigned in_row)
-    {
-        const int row0 = min(first, end - 1), last = end - 1 - row0;
-        const __amdgpu_buffer_rsrc_t at = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char *>(reinterpret_cast<const char *>(base) + uint64_t(unsigned(row0)) * pitch), 0, 0x7fffffff, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-            const unsigned down = unsigned(min(i, last)) * pitch;
-            if constexpr (sizeof(row) == 4) v[i] = __builtin_bit_cast(row, __builtin_amdgcn_raw_buffer_load_b32(at, in_row, down, 0));
-            else v[i] = __builtin_amdgcn_raw_buffer_load_b16(at, in_row, down, 0);
-        }
-    }
-    // to LDS, column by column; of the G rows the first `rows` count, zeros in place of the others
-    __device__ __forceinline__ void store(unsigned char *to, int stride, int rows)
-    {
-        if (rows < G) {
-#pragma unroll
-            for (int i = 0; i < G; ++i) v[i] = i < rows ? v[i] : row(0);
-        }
-        if constexpr (V == 2) {
-            u32x4v lo, hi;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                lo[i] = __builtin_amdgcn_perm(v[2 * i + 1], v[2 * i], 0x05040100u);
-                hi[i] = __builtin_amdgcn_perm(v[2 * i + 1], v[2 * i], 0x07060302u);
-            }
-            *reinterpret_cast<u32x4v *>(to) = lo;
-            *reinterpret_cast<u32x4v *>(to + stride) = hi;
-        } else if constexpr (sizeof(E) == 4) {
-            *reinterpret_cast<f32x4v *>(to) = f32x4v{v[0], v[1], v[2], v[3]};
-        } else {
-            u32x4v r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = unsigned(v[2 * i]) | (unsigned(v[2 * i + 1]) << 16);
-            *reinterpret_cast<u32x4v *>(to) = r;
-        }
-    }
-};
 
 // The same with a tile of tokens in LDS, laid out as in product_tiled_kernel: all D columns of the long side and, behind
 // them, the short-side columns of this workgroup's positions.  A wave owns 64 positions and a block of KN diagonals: one
