@@ -80,7 +80,7 @@ struct OperandPlace {
 // (a workgroup per row would write its 16-byte pieces 512 bytes apart, every one a partial line).
 // blockIdx.x numbers the (block of 32 rows, range of contraction indices) pairs, ranges innermost: first those of
 // the `masked_blocks` blocks of the masked-gather operand, then those of the gather operand (either count may be
-// zero).  Entries are summed in fp32 in LDS (repeated offsets add,
+// zero).  Entries are stored as fp32 in LDS (repeated offsets add,
 // Eq. 3) and rounded to bf16 once.  alpha (or null): importance weights of the D candidates (Sec. 3.2 Eq. 4);
 // diagonal k then enters as alpha[o_k] * values[k], rounded to bf16 first -- exactly the values dd_scale_values
 // would have stored.
@@ -89,6 +89,10 @@ struct OperandPlace {
 // to the right (the sets' outputs side by side) or s*k_step contraction indices down (their results summed),
 // inside a matrix of kd_total contraction indices; or, for layers that merely share a launch, set s has a whole
 // operand of its own block_step elements further on.  D, L, col_step and k_step are multiples of 32.
+// What bounds it: three trips to memory one after the other (offsets, values, the operand's way out) with a barrier behind each, and
+// from some 4096 columns on the operand's bytes.  Both operands, us: 768^2, 77 diagonals 4.9 -> 3.6, 307 10.1 -> 5.0; 768 -> 3072, 307
+// 8.4 -> 5.5; 1024 -> 4096, 819 15.9 -> 8.3; 4096^2, 1638 94 -> 33.5 (45 with 256 threads, 39 with 1024: with 512, four workgroups still
+// share a CU and a list is dealt out in half the turns).  Before, every entry was an atomic addition in LDS, by 256 threads.
 // ---------------------------------------------------------------------------------------------
 constexpr int kRaggedMaxD = 2048;          // long side of layers whose widths are multiples of eight only (scratch: 16.8 MB at most)
 constexpr int kMatRows = 32;
@@ -163,7 +167,7 @@ __device__ __forceinline__ void add_in_order(int D, int L, int K, bool long_majo
 // rows.  One operand of one layer.  Where an offset is given twice, the copies are added in the order of their diagonals and the
 // rounded sums leave a rest, which goes to a second operand `rest_at` elements behind the first; repeated[0] says whether there is one
 // and then repeated[1 + b] whether a sum of workgroup b came out infinite or undefined.
-template <bool RAGGED = false, int THREADS = 256>
+template <bool RAGGED, int THREADS>
 __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int K, int masked_blocks,
                                                           const int *__restrict__ offsets,
                                                           const uint16_t *__restrict__ values,
@@ -177,7 +181,7 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
     constexpr int kMatPer = kMatChunk / THREADS > 0 ? kMatChunk / THREADS : 1;  // offsets a thread looks at per pass
     static_assert(kMatPer * THREADS <= kMatList, "the list holds what a pass finds");
     __shared__ int hit_k[kMatList], hit_first[kMatList], hit_offset[kMatList], n_hits;
-    __shared__ unsigned seen[RAGGED ? kRaggedMaxD / 32 : 1], any_repeated;
+    __shared__ unsigned seen[RAGGED ? kRaggedMaxD / 32 : (kMatRange + kMatRows) / 32], any_repeated;  // offsets (not ragged: places of hits)
     const int ranges_masked = RAGGED ? (place_masked.kd_total + kMatRange - 1) / kMatRange : (L + kMatRange - 1) / kMatRange;
     const int ranges_gather = RAGGED ? (place_gather.kd_total + kMatRange - 1) / kMatRange : (D + kMatRange - 1) / kMatRange;
     const bool long_major = int(blockIdx.x) < masked_blocks * ranges_masked;
@@ -194,10 +198,8 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
     uint16_t *Wf = (long_major ? Wf_masked : Wf_gather) + size_t(set) * place.block_step;
     for (int c = threadIdx.x; c < kMatRows * kMatStride / 4; c += THREADS)
         reinterpret_cast<f32x4 *>(rows)[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (RAGGED) {
-        for (int i = threadIdx.x; i < (D + 31) / 32; i += THREADS) seen[i] = 0u;
-        if (threadIdx.x == 0) any_repeated = 0u;
-    }
+    for (int i = threadIdx.x; i < (RAGGED ? D + 31 : kMatRange + kMatRows) / 32; i += THREADS) seen[i] = 0u;
+    if (threadIdx.x == 0) any_repeated = 0u;
     // A diagonal meets the block where the contraction indices of the 32 rows -- consecutive modulo D from `first`
     // on -- fall into this workgroup's range; most diagonals miss.  Up to kMatChunk diagonals at a time: every thread
     // looks at its share of the offsets (all loads first: one trip to memory) and lists the ones that meet the block;
@@ -225,6 +227,10 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
             int d = first - i0;
             d += d < 0 ? D : 0;
             if (d >= extent && d + kMatRows <= D) continue;  // neither the first row inside nor a wrap into the range
+            if constexpr (!RAGGED) {  // the same place twice: the same offset
+                const int at = d < extent ? d : kMatRange + kMatRows - (D - d);
+                if (atomicOr(&seen[at >> 5], 1u << (at & 31)) >> (at & 31) & 1u) any_repeated = 1u;
+            }
             const int slot = atomicAdd(&n_hits, 1);
             hit_k[slot] = k;
             hit_first[slot] = first;
@@ -232,6 +238,7 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
         }
         __syncthreads();
         const int items = n_hits * kMatRows;
+        const bool add = any_repeated != 0u;
         for (int item = threadIdx.x; item < items; item += THREADS) {
             const int h = item / kMatRows, rr = item % kMatRows;
             const int i = hit_first[h] + rr >= D ? hit_first[h] + rr - D : hit_first[h] + rr;
@@ -239,7 +246,11 @@ __global__ __launch_bounds__(THREADS) void materialize_kernel(int D, int L, int 
             if (unsigned(i - i0) >= unsigned(extent) || p >= L) continue;
             float v = bf16_to_f32(values[size_t(hit_k[h]) * L + p]);
             if (alpha) v = bf16_to_f32(f32_to_bf16(alpha[hit_offset[h]] * v));
-            atomicAdd(&rows[rr * kMatStride + i - i0], v);
+            // Offsets that differ meet in no entry: a store (atomic additions took half of the kernel's time).  Once an offset was met
+            // again the entries are added to; the ragged kernel takes the rows anew.
+            float *entry = &rows[rr * kMatStride + i - i0];
+            if (!RAGGED && add) atomicAdd(entry, v);
+            else *entry = v + 0.f;
         }
         __syncthreads();  // the list may be overwritten; after the last pass: the rows are complete
     }
@@ -1454,7 +1465,7 @@ hipError_t launch_prepare_matrix(int D, int L, int K, int sets, bool expanding, 
     // of each other (the sets' contributions to the one input gradient add up in the contraction).
     const OperandPlace side_by_side = {expanding ? L : D, expanding ? D : L, 0, 0};
     const OperandPlace stacked = {sets * (expanding ? D : L), 0, expanding ? D : L, 0};
-    hipLaunchKernelGGL(materialize_kernel<false>, materialize_grid(D, L, D, L, sets), dim3(256), 0, stream, D, L, K, D / kMatRows,
+    hipLaunchKernelGGL((materialize_kernel<false, 512>), materialize_grid(D, L, D, L, sets), dim3(512), 0, stream, D, L, K, D / kMatRows,
                        offsets, static_cast<const uint16_t *>(values),
                        static_cast<uint16_t *>(expanding ? forward_operand : backward_operand),
                        static_cast<uint16_t *>(expanding ? backward_operand : forward_operand),
@@ -1470,7 +1481,7 @@ hipError_t launch_prepare_matrix_batched(int D, int L, int K, int layers, bool e
     const size_t operand = size_t(D) * L;
     const OperandPlace masked = {L, 0, 0, 2 * operand}, gather = {D, 0, 0, 2 * operand};
     uint16_t *first = static_cast<uint16_t *>(prepared);
-    hipLaunchKernelGGL(materialize_kernel<false>, materialize_grid(D, L, D, L, layers), dim3(256), 0, stream, D, L, K, D / kMatRows,
+    hipLaunchKernelGGL((materialize_kernel<false, 512>), materialize_grid(D, L, D, L, layers), dim3(512), 0, stream, D, L, K, D / kMatRows,
                        offsets, static_cast<const uint16_t *>(values), expanding ? first : first + operand,
                        expanding ? first + operand : first, masked, gather, static_cast<const float *>(nullptr), size_t(0), static_cast<int *>(nullptr));
     return hipGetLastError();
@@ -1589,7 +1600,7 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
     if (!a.prepared) {
         if (a.src_sets != 1 || a.dst_sets != 1) return hipErrorInvalidValue;  // groups come prepared
         const OperandPlace place = {KD, 0, 0, 0};
-        hipLaunchKernelGGL(materialize_kernel<false>, materialize_grid(a.D, a.L, a.masked ? NC : 0, a.masked ? 0 : NC, 1), dim3(256), 0, stream, a.D, a.L, a.K,
+        hipLaunchKernelGGL((materialize_kernel<false, 512>), materialize_grid(a.D, a.L, a.masked ? NC : 0, a.masked ? 0 : NC, 1), dim3(512), 0, stream, a.D, a.L, a.K,
                            a.masked ? NC / kMatRows : 0, a.offsets, static_cast<const uint16_t *>(a.values), Wf, Wf, place, place,
                            static_cast<const float *>(nullptr), size_t(0), static_cast<int *>(nullptr));
         hipError_t e = hipGetLastError();
