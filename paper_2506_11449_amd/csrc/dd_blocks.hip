@@ -16,7 +16,10 @@
 // from global memory straight into a three-deep ring of LDS stages; slices without a crossed block are not visited.
 // With most blocks skipped a slice is multiplied in a few hundred clocks and a tile is a handful of slices: what
 // bounds the kernel is latency (list, pipeline fill, copy-out), which the three workgroups of a CU hide for each other.
-// Which blocks are crossed is worked out by every workgroup from the offsets (a bitmap of the D candidates in LDS).
+// Which blocks are crossed is worked out by every workgroup from the offsets (a bitmap of the D candidates in LDS), four offsets a
+// thread at once, a thread to both blocks of a column block and slice; by one wave, block by block, that took a fifth of a
+// workgroup's life (768 -> 3072, 5 runs of 307, 25216 tokens: 4100 of 19100 clocks beside 10600 for the slices), now 1200.  That layer
+// 72.4 -> 70.7 us, back 52.9 -> 51.9; 768^2, one run of 77, 12608 tokens 11.9 / 11.6 -> 11.3 / 10.9; over eleven layers 1.04x.
 #include "dd_common.h"
 #include "dd_launch.h"
 #include "dd_blocks.h"
@@ -53,7 +56,7 @@ struct BlkTile {
     static constexpr int Rounds = XRounds + WRounds;
     static constexpr int CStride = kBlkBN * 2 + 16;           // bytes per token row of the result on its way out
     static constexpr int RingBytes = kBlkRing * StageBytes;
-    static constexpr int LdsBytes = RingBytes + (kBlkMaxD / 32 + kBlkMaxSlices + 4) * 4;
+    static constexpr int LdsBytes = RingBytes + (kBlkMaxD / 32 + kBlkMaxSlices) * 4 + kBlkMaxSlices;
     static_assert(XBytes % (1024 * NW) == 0 && kBlkWBytes % (1024 * NW) == 0, "a stage is moved in whole rounds of the workgroup");
     static_assert(32 * FB * CStride * NW <= RingBytes, "the result tile fits the ring on its way out");
     static_assert(3 * LdsBytes <= 160 * 1024, "three workgroups share a CU");
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(64 * NW, 3) void mm_blocks_kernel(int T, int NC, in
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned *bits = reinterpret_cast<unsigned *>(smem + Tl::RingBytes);  // [D / 32]
     unsigned *slice_list = bits + kBlkMaxD / 32;                           // [KD / 32]: slice | mask << 16
-    int *n_list_p = reinterpret_cast<int *>(slice_list + kBlkMaxSlices);
+    unsigned char *slice_mask = reinterpret_cast<unsigned char *>(slice_list + kBlkMaxSlices);  // [KD / 32]
 
     // Workgroups are dealt round-robin to the eight XCDs; every XCD gets one contiguous run of tiles, column tiles
     // innermost, so that the column tiles of a token block run on one L2 at about the same time.
@@ -93,39 +96,51 @@ __global__ __launch_bounds__(64 * NW, 3) void mm_blocks_kernel(int T, int NC, in
     const int n_slices = KD / kBlkSlice;
 
     // ---- which blocks of this column tile are crossed ----
+    constexpr int kLooks = 4;  // offsets a thread has on their way at once
+    int o[kLooks];
+#pragma unroll
+    for (int i = 0; i < kLooks; ++i) o[i] = offsets[min(i * Tl::THREADS + tid, K - 1)];
     for (int i = tid; i < D / 32; i += Tl::THREADS) bits[i] = 0u;
     __syncthreads();
-    for (int k = tid; k < K; k += Tl::THREADS) {
-        const int o = canonical_offset(offsets[k], D);
-        atomicOr(&bits[o >> 5], 1u << (o & 31));
+    for (int k0 = 0;;) {  // the last offset may be marked several times
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) {
+            const int oc = canonical_offset(o[i], D);
+            if (k0 + i * Tl::THREADS < K) atomicOr(&bits[oc >> 5], 1u << (oc & 31));
+        }
+        k0 += kLooks * Tl::THREADS;
+        if (k0 >= K) break;
+#pragma unroll
+        for (int i = 0; i < kLooks; ++i) o[i] = offsets[min(k0 + i * Tl::THREADS + tid, K - 1)];
     }
     __syncthreads();
     // slice g, block (a, ks): output columns j0 = 128 tn + 32 a .. +31, contraction indices i0 = 32 g + 16 ks .. +15;
     // long - short index runs over [j0 - i0 - 15, j0 - i0 + 31] (long columns) or [i0 - j0 - 31, i0 - j0 + 15].
-    // Wave 0 ranks the slices that hold a crossed block, in order.
-    if (wave == 0) {
-        int base = 0;
-        for (int g0 = 0; g0 < n_slices; g0 += 64) {
-            const int g = g0 + lane;
-            unsigned mask = 0;
-            if (g < n_slices) {
-#pragma unroll
-                for (int a = 0; a < kBlkFA; ++a)
-#pragma unroll
-                    for (int ks = 0; ks < kBlkSteps; ++ks) {
-                        const int j0 = tn * kBlkBN + a * 32, i0 = g * kBlkSlice + ks * 16;
-                        if (blk_crossed(bits, D, blk_first_offset(j0, i0, long_cols))) mask |= 1u << (a * kBlkSteps + ks);
-                    }
-            }
-            const unsigned long long any = __ballot(mask != 0);
-            const int rank = __builtin_amdgcn_mbcnt_hi(unsigned(any >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(any), 0u));
-            if (mask) slice_list[base + rank] = unsigned(g) | (mask << 16);
-            base += __popcll(any);
-        }
-        if (lane == 0) *n_list_p = base;
+    // A lane looks at both blocks of one column block of a slice, the two windows of which lie in 63 neighbouring offsets.
+    static_assert(kBlkSteps == 2 && kBlkFA == 4, "a slice's column blocks are looked at by four neighbouring lanes");
+    for (int i = tid; i < (n_slices * kBlkFA + 63) / 64 * 64; i += Tl::THREADS) {
+        const int g = min(i / kBlkFA, n_slices - 1), a = i % kBlkFA;
+        const int j0 = tn * kBlkBN + a * 32, i0 = g * kBlkSlice;
+        const unsigned long long window = blk_window(bits, D, blk_first_offset(j0, long_cols ? i0 + 16 : i0, long_cols));
+        const unsigned low = (window & ((1ull << 47) - 1)) != 0, high = ((window >> 16) & ((1ull << 47) - 1)) != 0;
+        unsigned mask = (long_cols ? high | low << 1 : low | high << 1) << (a * kBlkSteps);
+        mask |= unsigned(__builtin_amdgcn_mov_dpp(int(mask), 0xb1, 0xf, 0xf, true));  // lane ^ 1
+        mask |= unsigned(__builtin_amdgcn_mov_dpp(int(mask), 0x4e, 0xf, 0xf, true));  // lane ^ 2
+        if (a == 0 && i / kBlkFA < n_slices) slice_mask[g] = (unsigned char)mask;
     }
     __syncthreads();
-    const int n_list = __builtin_amdgcn_readfirstlane(*n_list_p);
+    // every wave ranks the slices that hold a crossed block, in order, and writes the same list
+    int n_list = 0;
+    for (int g0 = 0; g0 < n_slices; g0 += 64) {
+        const int g = g0 + lane;
+        const unsigned mask = g < n_slices ? slice_mask[g] : 0u;
+        const unsigned long long any = __ballot(mask != 0);
+        const int rank = __builtin_amdgcn_mbcnt_hi(unsigned(any >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(any), 0u));
+        if (mask) slice_list[n_list + rank] = unsigned(g) | (mask << 16);
+        n_list += __popcll(any);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 
     // ---- transfers: memory -> LDS, 1 KB per wave and round ----
     // token rows: round i of wave w moves rows 16 (i NW + w) .. +15 of the tile; lane l lands at row 16j + l/4, 16-byte
