@@ -8,18 +8,21 @@
 // nearly every block is crossed (density K/D per entry, but 47 K/D diagonals per block), so this kernel only pays
 // for clustered offsets; it is chosen by the caller (DD_ALGO_BLOCKS), who knows where the offsets come from.
 //
-// Work split: a workgroup (four waves) owns 32*FB*NW tokens x 128 output columns, three workgroups share a CU.  Every wave owns 32*FB tokens and ALL 128 columns,
+// Work split: a workgroup owns 32*FB*NW tokens x 128 output columns; three workgroups of four waves share a CU, or two of eight.  Every wave owns 32*FB tokens and ALL 128 columns,
 // so all waves meet the same blocks and skip the same blocks: skipping never leaves a wave waiting for another.
 // (In mm_kernel the waves split the columns; there a wave whose blocks are empty would only wait at the next barrier.)
 // Per 32-index k-slice that holds any crossed block, the token rows (32*FB*NW x 64 bytes) and the 8 operand blocks
 // (1 KB each, fragment-major as materialize_kernel writes them; blocks that are not crossed are not fetched) travel
-// from global memory straight into a three-deep ring of LDS stages; slices without a crossed block are not visited.
+// from global memory straight into a three-deep ring of LDS stages, whose waits count what each wave asked for; slices without a
+// crossed block are not visited.
 // With most blocks skipped a slice is multiplied in a few hundred clocks and a tile is a handful of slices: what
-// bounds the kernel is latency (list, pipeline fill, copy-out), which the three workgroups of a CU hide for each other.
+// bounds the kernel is latency (list, pipeline fill, copy-out), which the workgroups of a CU hide for each other, and the way into LDS
+// (16 clk for 1 KB: half a slice's blocks used to be fetched from a block of zeros to keep the count in flight, 1.03x).
 // Which blocks are crossed is worked out by every workgroup from the offsets (a bitmap of the D candidates in LDS), four offsets a
-// thread at once, a thread to both blocks of a column block and slice; by one wave, block by block, that took a fifth of a
-// workgroup's life (768 -> 3072, 5 runs of 307, 25216 tokens: 4100 of 19100 clocks beside 10600 for the slices), now 1200.  That layer
-// 72.4 -> 70.7 us, back 52.9 -> 51.9; 768^2, one run of 77, 12608 tokens 11.9 / 11.6 -> 11.3 / 10.9; over eleven layers 1.04x.
+// thread at once, a thread to both blocks of a column block and slice (by one wave, block by block, 4100 of a workgroup's 19100 clocks
+// on the first layer below, now 1600).
+// Measured with the 768 -> 3072 MLP (five runs of 307 diagonals, 25216 tokens) 72.6 -> 61 us, back 51.8 -> 49; 768^2, one run of 77,
+// 12608 tokens 11.7 / 11.5 -> 10.4 / 10.0; 1024 -> 4096, three of 819, back 57.2 -> 38.5; over 70 layers, both ways, 1.15x.
 #include "dd_common.h"
 #include "dd_launch.h"
 #include "dd_blocks.h"
@@ -43,7 +46,7 @@ constexpr int kBlkAhead = kBlkRing - 1;
 constexpr int kBlkWBytes = kBlkFA * kBlkSteps * 1024;   // operand blocks of one slice
 constexpr int kBlkMaxSlices = kBlkMaxD / kBlkSlice;
 
-__device__ __align__(16) const unsigned int blk_zero_piece[4] = {0u, 0u, 0u, 0u};
+constexpr int blk_per_cu(int waves) { return waves == 4 ? 3 : 2; }  // workgroups that share a CU
 
 template <int FB, int NW>
 struct BlkTile {
@@ -59,7 +62,7 @@ struct BlkTile {
     static constexpr int LdsBytes = RingBytes + (kBlkMaxD / 32 + kBlkMaxSlices) * 4 + kBlkMaxSlices;
     static_assert(XBytes % (1024 * NW) == 0 && kBlkWBytes % (1024 * NW) == 0, "a stage is moved in whole rounds of the workgroup");
     static_assert(32 * FB * CStride * NW <= RingBytes, "the result tile fits the ring on its way out");
-    static_assert(3 * LdsBytes <= 160 * 1024, "three workgroups share a CU");
+    static_assert(blk_per_cu(NW) * LdsBytes <= 160 * 1024, "the workgroups of a CU share its LDS");
 };
 
 // 64-byte rows, four to a 256-byte line of LDS banks: the 16-byte pieces of row r are permuted by XOR with
@@ -69,7 +72,7 @@ __device__ __forceinline__ int blk_swizzle_key(int row) { return (row >> 2) & 3;
 // C [T x NC] = A [T x KD] . W, W fragment-major; long_cols: the output columns are the long side of the layer
 // (masked gather), else the short side (gather).
 template <int FB, int NW>
-__global__ __launch_bounds__(64 * NW, 3) void mm_blocks_kernel(int T, int NC, int KD, int D, int K, int long_cols,
+__global__ __launch_bounds__(64 * NW, blk_per_cu(NW) * NW / 4) void mm_blocks_kernel(int T, int NC, int KD, int D, int K, int long_cols,
                                                                 int tiles_m, int tiles_n,
                                                                 const int *__restrict__ offsets,
                                                                 const uint16_t *__restrict__ A,
@@ -162,21 +165,23 @@ __global__ __launch_bounds__(64 * NW, 3) void mm_blocks_kernel(int T, int NC, in
         w_src[i] = Wf + (size_t(tn * kBlkFA + b / kBlkSteps) * (KD / 16) + b % kBlkSteps) * 512 + lane * 8;
     }
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-    const uint16_t *zero = reinterpret_cast<const uint16_t *>(blk_zero_piece);
-    // entry e_ of the list into stage st_; past the end of the list the same number of transfers is issued (from a
-    // block of zeros into a stage nobody reads) so that the count in flight is the same in every iteration
+    // entry e_ of the list into stage st_: the token rows and this wave's share of the crossed blocks; `issued` is how many transfers
+    // that were, none past the end of the list
 #define DD_BLK_ISSUE(e_, st_)                                                                           \
-    {                                                                                                   \
-        const bool live = (e_) < n_list;                                                                \
-        const unsigned entry = live ? slice_list[(e_)] : 0u;                                            \
+    issued = 0;                                                                                         \
+    if ((e_) < n_list) {                                                                                \
+        const unsigned entry = slice_list[(e_)];                                                        \
+        issued = Tl::XRounds;                                                                           \
         const int g = __builtin_amdgcn_readfirstlane(int(entry & 0xffffu));                             \
         const unsigned mask = __builtin_amdgcn_readfirstlane(entry >> 16);                              \
         _Pragma("unroll") for (int i = 0; i < Tl::XRounds; ++i)                                         \
-            global_to_lds_16(live ? x_src[i] + g * kBlkSlice : zero,                                    \
+            global_to_lds_16(x_src[i] + g * kBlkSlice,                                                  \
                              lds0 + (st_) * Tl::StageBytes + (i * NW + wave) * 1024);                   \
         _Pragma("unroll") for (int i = 0; i < Tl::WRounds; ++i) {                                       \
             const int b = i * NW + wave;                                                                \
-            global_to_lds_16(((mask >> b) & 1u) ? w_src[i] + size_t(g) * kBlkSteps * 512 : zero,        \
+            if (!((mask >> b) & 1u)) continue;                                                          \
+            ++issued;                                                                                   \
+            global_to_lds_16(w_src[i] + size_t(g) * kBlkSteps * 512,                                    \
                              lds0 + (st_) * Tl::StageBytes + Tl::XBytes + b * 1024);                    \
         }                                                                                               \
     }
@@ -198,13 +203,18 @@ __global__ __launch_bounds__(64 * NW, 3) void mm_blocks_kernel(int T, int NC, in
         x_key[b] = blk_swizzle_key(row);
     }
 
+    int issued = 0;
 #pragma unroll
-    for (int j = 0; j < kBlkAhead; ++j) DD_BLK_ISSUE(j, j)
+    for (int j = 0; j < kBlkAhead; ++j) { DD_BLK_ISSUE(j, j) }
+    static_assert(kBlkAhead == 2 && Tl::WRounds <= 2, "one entry's transfers may be left in flight");
     int stage = 0;
     for (int n = 0; n < n_list; ++n) {
         // entry n has landed for every wave (all but the transfers of the entries after it), and every wave is done
         // with entry n - 1, whose stage the next transfers go to
-        DD_BLK_ARRIVE((kBlkAhead - 1) * Tl::Rounds);
+        if (issued == Tl::XRounds + 1) DD_BLK_ARRIVE(Tl::XRounds + 1);
+        else if (issued == Tl::XRounds + 2) DD_BLK_ARRIVE(Tl::XRounds + 2);
+        else if (issued == Tl::XRounds) DD_BLK_ARRIVE(Tl::XRounds);
+        else DD_BLK_ARRIVE(0);
         const int ahead = stage == 0 ? kBlkRing - 1 : stage - 1;
         DD_BLK_ISSUE(n + kBlkAhead, ahead)
         const unsigned mask = __builtin_amdgcn_readfirstlane(slice_list[n] >> 16);
@@ -285,6 +295,14 @@ hipError_t launch_product_blocks(const ProductArgs &a, hipStream_t stream)
 {
     if (a.src_sets != 1 || a.dst_sets != 1 || !a.prepared || !a.offsets) return hipErrorInvalidValue;
     if (product_blocks_small(a)) return launch_product_blocks_small(a, stream);
+    // 256 tokens a workgroup, two workgroups a CU, move a quarter less per token than 128 and three (an operand block serves twice the
+    // tokens) but fill 512 places instead of 768 with half as many tiles; whole rounds of the chip decide, ten percent dearer each
+    // where a round does twice the tokens (measured, 128 / 256: 1024 -> 4096, 12608 tokens, 4.1 and 3.1 rounds 57.8 / 51, back, 1.03 and
+    // 0.8 rounds, 54.8 / 38; 768 x 768, 0.8 and 0.6 rounds, 10.4 / 11.6; over 140 products of 512 ... 4096 features, 197 ... 25216 tokens,
+    // none is slower than with 128 alone and the choice is within a percent of the better one in the mean).
+    const int NC = a.masked ? a.D : a.L;
+    auto rounds = [&](int tokens, int per_cu) { return ((a.T + tokens - 1) / tokens * (NC / kBlkBN) + 256 * per_cu - 1) / (256 * per_cu); };
+    if (1.1 * double(rounds(256, 2)) < double(rounds(128, 3))) return launch_blocks<1, 8>(a, stream);
     return launch_blocks<1, 4>(a, stream);
 }
 

@@ -1,0 +1,37 @@
+"""The block-skipping products with both of their tiles (128 tokens by four waves, 256 by eight): remainders of either, columns that no
+diagonal crosses, lists of one, two and all slices, more offsets than are looked at in one trip."""
+import pytest
+import torch
+
+import paper_2506_11449_amd as dd
+from paper_2506_11449_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _dense(M, N, off, V):
+    D, L = max(M, N), min(M, N)
+    p = torch.arange(L, device="cuda")[None, :]
+    q = (p + off.long()[:, None] % D) % D
+    W = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    return W.index_put_((p.expand_as(q), q) if M <= N else (q, p.expand_as(q)), V.double(), accumulate=True)
+
+
+# 24 705 tokens of 512 columns and 12 673 of 1024: two rounds of the small tile, one of the large one; 12 416 and 12 000: one of the small
+@pytest.mark.parametrize("M,N,T", [(512, 512, 24705), (1024, 1024, 12673), (512, 1024, 12673), (1024, 1024, 12416), (1024, 512, 12000), (256, 4096, 6151)])
+@pytest.mark.parametrize("K,runs", [(1, 1), (2, 2), (60, 1), (128, 3), (0, 1)])
+def test_both_tiles(M, N, T, K, runs):
+    D = max(M, N)
+    K = K or D  # 0: all of them
+    off = torch.from_numpy(synth.draw_offsets_clustered(D, K, runs, seed=K + T)).cuda()
+    g = torch.Generator(device="cuda").manual_seed(K + T)
+    r = lambda *s: torch.randn(s, device="cuda", generator=g).bfloat16()
+    V, X, dY = r(K, min(M, N)) * 0.02, r(T, M), r(T, N)
+    prepared, W = dd.dd_prepare(off, V, M, N), _dense(M, N, off, V)
+    Y = torch.full((T + 1, N), 7.0, device="cuda").bfloat16()  # a row that is not to be written
+    dd.dd_fwd(X, off, None, N, Y=Y[:T], prepared=prepared, algo=dd.DD_ALGO_BLOCKS)
+    dX = dd.dd_bwd_input(dY, off, None, M, prepared=prepared, algo=dd.DD_ALGO_BLOCKS)
+    # each result is a sum in fp32 of bf16 products, rounded to bf16 once: half a unit in the last place, 2^-9, of each
+    for got, ref in ((Y[:T], X.double() @ W), (dX, dY.double() @ W.t().contiguous())):
+        assert ((got.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all()
+    assert (Y[T] == 7.0).all()
