@@ -1588,6 +1588,53 @@ static int pick_small(int64_t T, int NC, int KD, int a_cols)
     return best;
 }
 
+// More tiles of 160 x 256 than CUs: how many tokens the persistent kernel takes, and the tile that mm_kernel takes the rest in (0: none
+// left).  The persistent kernel keeps its pipeline running but works in whole rounds of 256 tiles of one height, and its last round may
+// be nearly empty: 1.1 rounds take 2.  Against it stand mm_kernel on all tokens, whose taller or shorter tiles may fit the chip better, and
+// the persistent kernel on one or all of its full rounds with the rest behind it in a tile that fills the chip once.  (A group's
+// matrices lie T rows apart and are not cut.)
+// Times in us, fitted to 2000 measured products of 1.0 ... 9 rounds, 256 ... 4096 features (nine tenths of them within a twelfth); to
+// leave the persistent kernel 6 % have to be predicted, with which the slowest of 300 choices was 2 % behind it.  Measured, persistent ->
+// chosen: 768^2, 15360 tokens 26.0 -> 18.9 us, 1408 -> 1536, 7144 42.1 -> 28.6, 2688 -> 4096, 2824 75.6 -> 50.4 (all with 192 rows),
+// 1024^2, 12608 35.7 -> 30.0, 4096 -> 1024, 25216 175 -> 167 (two full rounds, the rest in 64 and 96 rows); over those products 1.06x.
+struct MmPlan {
+    int first, rest_tile;
+};
+static MmPlan plan_mm(int T, int NC, int KD, bool may_cut)
+{
+    const double slices = KD / 64.0;
+    const int cols = NC / 256;
+    auto fill = [&](int tokens, int bm) { return double((int64_t(tokens) + bm - 1) / bm * cols) / 256; };
+    auto rounds = [](double fill, double light) {  // a last round that is not full leaves its CUs more of clock and memory
+        const double full = double(int64_t(fill));
+        return full + (fill > full ? 1 - light * (1 - (fill - full)) : 0);
+    };
+    auto persistent = [&](int tokens) { return 2.34 + rounds(fill(tokens, 160), 0.133) * (1.55 + 0.942 * slices); };
+    static const struct {
+        int bm;
+        double slice;
+    } tiles[] = {{192, 1.142}, {160, 0.958}, {128, 0.759}, {96, 0.532}, {64, 0.368}};
+    MmPlan best = {T, 0};
+    double best_us = 0.94 * persistent(T);
+    auto weigh = [&](int first, double us) {
+        for (const auto &t : tiles) {
+            if (first == 0 && t.bm < 128) continue;
+            const double both = us + 4.2 + rounds(fill(T - first, t.bm), 0.194) * (2.15 + t.slice * slices);
+            if (both < best_us) {
+                best_us = both;
+                best = {first, t.bm};
+            }
+        }
+    };
+    const double all = fill(T, 160);
+    if (all < 4) weigh(0, 0.0);
+    for (int full = int(all) > 1 ? int(all) - 1 : 1; may_cut && full <= int(all) && full < 64; ++full) {
+        const int first = full * 256 / cols * 160;
+        if (first > 0 && first < T) weigh(first, persistent(first));
+    }
+    return best;
+}
+
 hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
 {
     // masked gather: dst has D columns, contraction over the L columns of src  -> operand rows are long-side
@@ -1618,13 +1665,20 @@ hipError_t launch_product_matrix(const ProductArgs &a, hipStream_t stream)
     const int64_t tiles160 = ((a.T + 159) / 160) * ((NC + 255) / 256);
     if (NC % 256 == 0) {
         // more tiles than CUs: one workgroup per CU walks its tiles with the pipeline kept running
-        if (tiles160 > 256) return launch_mm_persistent<160, 256, kMmWaves>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
-        switch (pick_tile(a.T, NC)) {
-        case 192: return launch_mm<192, 256, kMmWaves>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
-        case 160: return launch_mm<160, 256, kMmWaves>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
-        case 128: return launch_mm<128, 256, kMmWaves>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
-        case 96: return launch_mm<96, 256, kMmWaves>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
-        default: return launch_mm<64, 256, kMmWaves>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+        const MmPlan plan = tiles160 > 256 ? plan_mm(T, NC, KD, a.src_sets == 1 && a.dst_sets == 1) : MmPlan{0, pick_tile(a.T, NC)};
+        if (plan.first > 0) {
+            if (hipError_t e = launch_mm_persistent<160, 256, kMmWaves>(plan.first, NC, KD, a_cols, c_cols, A, Wf, C, stream)) return e;
+            if (plan.first == T) return hipSuccess;
+            A += size_t(plan.first) * a_cols;
+            C += size_t(plan.first) * c_cols;
+        }
+        const int rest = T - plan.first;
+        switch (plan.rest_tile) {
+        case 192: return launch_mm<192, 256, kMmWaves>(rest, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+        case 160: return launch_mm<160, 256, kMmWaves>(rest, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+        case 128: return launch_mm<128, 256, kMmWaves>(rest, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+        case 96: return launch_mm<96, 256, kMmWaves>(rest, NC, KD, a_cols, c_cols, A, Wf, C, stream);
+        default: return launch_mm<64, 256, kMmWaves>(rest, NC, KD, a_cols, c_cols, A, Wf, C, stream);
         }
     }
     return launch_mm<128, 128, 4>(T, NC, KD, a_cols, c_cols, A, Wf, C, stream);

@@ -1,0 +1,56 @@
+"""Products of somewhat more tiles than the chip holds: all tokens in taller or shorter tiles, or full rounds by the persistent kernel
+and the rest behind it.  Against 64 bits, and bit for bit against the same tokens in two calls."""
+import pytest
+import torch
+
+import paper_2506_11449_amd as dd
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(M, N, K, T):
+    g = torch.Generator(device="cuda").manual_seed(M + N + T)
+    r = lambda *s: torch.randn(s, device="cuda", generator=g).bfloat16()
+    off = torch.randperm(max(M, N), device="cuda", generator=g)[:K].to(torch.int32)
+    return off, r(K, min(M, N)) * 0.02, r(T, M), r(T, N)
+
+
+def _dense(M, N, off, V):
+    D, L = max(M, N), min(M, N)
+    p = torch.arange(L, device="cuda")[None, :]
+    q = (p + off.long()[:, None]) % D
+    W = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    return W.index_put_((p.expand_as(q), q) if M <= N else (q, p.expand_as(q)), V.double(), accumulate=True)
+
+
+# rounds of 160 rows: 1.004 and 1.12 (192 rows), 1.23 (one round and 64 rows, both ways), 2.1 and 2.5 (cut, or not), 3.3 (192 rows), just below
+# and above one round, columns that do not divide the chip, one column tile, and 9 rounds, which stay whole
+@pytest.mark.parametrize("M,N,T", [(512, 1024, 10241), (768, 768, 15360), (1024, 1024, 12608), (512, 1280, 17281), (1024, 512, 50432),
+                                   (1536, 1280, 26723), (768, 768, 13600), (768, 768, 13761), (896, 1792, 6001), (640, 256, 50432), (256, 2304, 42000)])
+def test_rounds(M, N, T):
+    K = max(M, N) // 10
+    off, V, X, dY = _layer(M, N, K, T)
+    prepared, W = dd.dd_prepare(off, V, M, N), _dense(M, N, off, V)
+    out = torch.full((T + 1, max(M, N)), 7.0, device="cuda").bfloat16()
+    Y = out.view(-1)[:(T + 1) * N].view(T + 1, N)
+    dd.dd_fwd(X, None, None, N, Y=Y[:T], prepared=prepared)
+    dX = dd.dd_bwd_input(dY, None, None, M, prepared=prepared)
+    # sums in fp32 of bf16 products, rounded to bf16 once: half a unit in the last place, 2^-9, of each
+    for got, ref in ((Y[:T], X.double() @ W), (dX, dY.double() @ W.t().contiguous())):
+        assert ((got.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all()
+    assert (Y[T] == 7.0).all()
+    half = T // 2 + 3
+    assert torch.equal(Y[:T], torch.cat([dd.dd_fwd(x.contiguous(), None, None, N, prepared=prepared) for x in (X[:half], X[half:])]))
+
+
+def test_groups_are_not_cut():
+    M, N, S, T = 512, 512, 3, 12608  # 1.85 rounds forward (the sets' columns side by side), 0.6 back
+    layers = [_layer(M, N, 51, T) for _ in range(S)]
+    X = layers[0][2]
+    dY = torch.stack([l[3] * (i + 1) for i, l in enumerate(layers)])
+    off, V = torch.stack([l[0] for l in layers]), torch.stack([l[1] * (i + 1) for i, l in enumerate(layers)])
+    prepared = dd.dd_prepare_shared(off, V, M, N)
+    Y, dX = dd.dd_fwd_shared(X, prepared), dd.dd_bwd_input_shared(dY, prepared)
+    W = [_dense(M, N, off[i], V[i]) for i in range(S)]
+    for got, ref in ((Y, torch.stack([X.double() @ w for w in W])), (dX, sum(dY[i].double() @ W[i].t().contiguous() for i in range(S)))):
+        assert ((got.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all()
